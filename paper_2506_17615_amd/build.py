@@ -24,6 +24,9 @@ HIPCC_FLAGS = [
     # honours it (tests/test_build_flags.py looks at the device assembly); hipcc hands -Xclang options to its
     # x86 host pass as well, which answers each with a harmless "not a recognized feature for this target".
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the leading kernel arguments arrive in scalar registers with the wave (gfx950's kernarg preload, 14 dwords at
+    # most) instead of through a scalar load that every kernel would begin by waiting for
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-shared", "-fPIC",
     "-I", INCLUDE, "-I", CSRC,
 ]

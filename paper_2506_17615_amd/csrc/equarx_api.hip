@@ -77,17 +77,17 @@ void launch_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, int8_t
     const int64_t nb = blocks_of(n, B);
     const int64_t shard_elems = (nb + P - 1) / P * B;       // ceil(nb / P) blocks per shard, as the single launch
     const unsigned gx = grid_for(shard_elems, kTilesHop), gy = (unsigned)P;
-    ctx.launch2d(quantize_ring_kernel<B, kTilesHop>, gx, gy, kThreads, tab, P, n, shard_elems, c[0], s[0]);
+    ctx.launch2d(quantize_ring_kernel<B, kTilesHop>, gx, gy, kThreads, P, n, shard_elems, c[0], s[0], tab);
     for (int i = 1; i + 1 < P; ++i) {
-        ctx.launch2d(hop_ring_kernel<B, kTilesHop>, gx, gy, kThreads, c[(i - 1) & 1], s[(i - 1) & 1], tab, P, i, n, shard_elems,
-                 c[i & 1], s[i & 1]);
+        ctx.launch2d(hop_ring_kernel<B, kTilesHop>, gx, gy, kThreads, c[(i - 1) & 1], s[(i - 1) & 1], P, i, n, shard_elems,
+                 c[i & 1], s[i & 1], tab);
     }
     if (ag) {
-        ctx.launch2d(tail_ring_kernel<B, kTilesHop, true>, gx, gy, kThreads, c[(P - 2) & 1], s[(P - 2) & 1], tab, P, P - 1, n,
-                 shard_elems, out);
+        ctx.launch2d(tail_ring_kernel<B, kTilesHop, true>, gx, gy, kThreads, c[(P - 2) & 1], s[(P - 2) & 1], P, P - 1, n,
+                 shard_elems, out, tab);
     } else {
-        ctx.launch2d(tail_ring_kernel<B, kTilesHop, false>, gx, gy, kThreads, c[(P - 2) & 1], s[(P - 2) & 1], tab, P, P - 1, n,
-                 shard_elems, out);
+        ctx.launch2d(tail_ring_kernel<B, kTilesHop, false>, gx, gy, kThreads, c[(P - 2) & 1], s[(P - 2) & 1], P, P - 1, n,
+                 shard_elems, out, tab);
     }
 }
 
@@ -142,8 +142,8 @@ void launch_chain_k(const PartialTable &tab, int P, int64_t n, bool rs, bool ag,
 {
     const ChainGrid g = chain_grid(n, B, P, ring, K);
 #define EQUARX_CHAIN(RS, AG, WIRE)                                                                        \
-    ctx.launch2d(chain_kernel<B, K, RS, AG, WIRE>, g.x, g.y, kThreads, tab, P, n, g.shard_elems, out, wire_codes,   \
-             wire_scales, c_step, s_step)
+    ctx.launch2d(chain_kernel<B, K, RS, AG, WIRE>, g.x, g.y, kThreads, P, n, g.shard_elems, out, wire_codes,        \
+                 wire_scales, c_step, s_step, tab)
     if (rs && ag) {
         if (wire_codes) {
             EQUARX_CHAIN(true, true, true);
@@ -166,9 +166,9 @@ void launch_chain(const PartialTable &tab, int P, int64_t n, bool rs, bool ag, b
     if (rs && ag && !ring && tiles <= kChainSmallTiles) {
         const unsigned grid = grid_for(n, 1);
         if (wire_codes) {
-            ctx.launch(chain_small_kernel<B, true>, grid, kThreads, tab, P, n, out, wire_codes, wire_scales, c_step, s_step);
+            ctx.launch(chain_small_kernel<B, true>, grid, kThreads, P, n, out, wire_codes, wire_scales, c_step, s_step, tab);
         } else {
-            ctx.launch(chain_small_kernel<B, false>, grid, kThreads, tab, P, n, out, wire_codes, wire_scales, c_step, s_step);
+            ctx.launch(chain_small_kernel<B, false>, grid, kThreads, P, n, out, wire_codes, wire_scales, c_step, s_step, tab);
         }
     } else if (tiles <= kChainMediumTiles) {
         launch_chain_k<B, 1>(tab, P, n, rs, ag, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
@@ -187,9 +187,9 @@ void launch_semi(const PartialTable &tab, int P, int64_t n, bool ag, bool ring, 
 {
     const ChainGrid g = chain_grid(n, B, P, ring, kTilesSemi);
     if (ag) {
-        ctx.launch2d(semi_kernel<B, kTilesSemi, true>, g.x, g.y, kThreads, tab, P, n, g.shard_elems, out);
+        ctx.launch2d(semi_kernel<B, kTilesSemi, true>, g.x, g.y, kThreads, P, n, g.shard_elems, out, tab);
     } else {
-        ctx.launch2d(semi_kernel<B, kTilesSemi, false>, g.x, g.y, kThreads, tab, P, n, g.shard_elems, out);
+        ctx.launch2d(semi_kernel<B, kTilesSemi, false>, g.x, g.y, kThreads, P, n, g.shard_elems, out, tab);
     }
 }
 
@@ -205,13 +205,13 @@ void launch_flat_as(const uint16_t *local, const WireTable &tab, int R, int64_t 
     const unsigned grid = grid_for(n, kTilesFlat);
     const int64_t nb = blocks_of(n, B);
     if (!ag) {      // bf16 output of the unquantized sum; callers pass out and no wire
-        ctx.launch(flat_kernel<B, kTilesFlat, true, false, false, kStream>, grid, kThreads, local, tab, R, n, out, codes_out, scales_out, nb);
+        ctx.launch(flat_kernel<B, kTilesFlat, true, false, false, kStream>, grid, kThreads, local, R, n, out, codes_out, scales_out, nb, tab);
     } else if (out && codes_out) {
-        ctx.launch(flat_kernel<B, kTilesFlat, true, true, true, kStream>, grid, kThreads, local, tab, R, n, out, codes_out, scales_out, nb);
+        ctx.launch(flat_kernel<B, kTilesFlat, true, true, true, kStream>, grid, kThreads, local, R, n, out, codes_out, scales_out, nb, tab);
     } else if (out) {
-        ctx.launch(flat_kernel<B, kTilesFlat, true, false, true, kStream>, grid, kThreads, local, tab, R, n, out, codes_out, scales_out, nb);
+        ctx.launch(flat_kernel<B, kTilesFlat, true, false, true, kStream>, grid, kThreads, local, R, n, out, codes_out, scales_out, nb, tab);
     } else {
-        ctx.launch(flat_kernel<B, kTilesFlat, false, true, true, kStream>, grid, kThreads, local, tab, R, n, out, codes_out, scales_out, nb);
+        ctx.launch(flat_kernel<B, kTilesFlat, false, true, true, kStream>, grid, kThreads, local, R, n, out, codes_out, scales_out, nb, tab);
     }
 }
 
@@ -300,7 +300,7 @@ void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, c
             to.codes[d] = w.c[2 * d + (t & 1)];
             to.scales[d] = w.s[2 * d + (t & 1)];
         }
-        ctx.launch3d(semi_ring_step_kernel<B, kTilesHop>, gx, gy, 2u, kThreads, tab, P, t, n, shard_elems, in, to);
+        ctx.launch3d(semi_ring_step_kernel<B, kTilesHop>, gx, gy, 2u, kThreads, P, t, n, shard_elems, in, to, tab);
     }
     WireTable wires;
     for (int r = 0; r < kMaxPartials; ++r) {
@@ -315,11 +315,11 @@ void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, c
         ++received;
     }
     if (ag) {
-        ctx.launch2d(semi_ring_owner_kernel<B, kTilesFlat, true>, grid_for(shard_elems, kTilesFlat), gy, kThreads, tab, P, n, shard_elems,
-                     wires, received, out);
+        ctx.launch2d(semi_ring_owner_kernel<B, kTilesFlat, true>, grid_for(shard_elems, kTilesFlat), gy, kThreads, P, n, shard_elems,
+                     received, out, wires, tab);
     } else {
-        ctx.launch2d(semi_ring_owner_kernel<B, kTilesFlat, false>, grid_for(shard_elems, kTilesFlat), gy, kThreads, tab, P, n,
-                     shard_elems, wires, received, out);
+        ctx.launch2d(semi_ring_owner_kernel<B, kTilesFlat, false>, grid_for(shard_elems, kTilesFlat), gy, kThreads, P, n,
+                     shard_elems, received, out, wires, tab);
     }
 }
 
@@ -372,7 +372,7 @@ inline StridedSource chain_source(const PartialTable &tab, int P, int per_shard,
 
 void do_quantize_strided(const StridedSource &src, int64_t n, int32_t chunks, int8_t *codes, float *scales, LaunchCtx &ctx)
 {
-#define CALL(RR) ctx.launch(quantize_strided_kernel<RR>, strided_grid(n, chunks), kThreads, src, codes, scales)
+#define CALL(RR) ctx.launch(quantize_strided_kernel<RR>, strided_grid(n, chunks), kThreads, codes, scales, src)
     EQUARX_DISPATCH_CHUNKS(chunks, CALL)
 #undef CALL
 }
@@ -380,7 +380,7 @@ void do_quantize_strided(const StridedSource &src, int64_t n, int32_t chunks, in
 void do_hop_strided(const int8_t *cin, const float *sin, const StridedSource &src, int64_t n, int32_t chunks, int8_t *cout,
                     float *sout, LaunchCtx &ctx)
 {
-#define CALL(RR) ctx.launch(hop_strided_kernel<RR>, strided_grid(n, chunks), kThreads, cin, sin, src, cout, sout)
+#define CALL(RR) ctx.launch(hop_strided_kernel<RR>, strided_grid(n, chunks), kThreads, cin, sin, cout, sout, src)
     EQUARX_DISPATCH_CHUNKS(chunks, CALL)
 #undef CALL
 }
@@ -390,8 +390,8 @@ void do_owner_strided(const StridedSource &own, const StridedWires &wires, int r
 {
 #define CALL(RR)                                                                                                           \
     do {                                                                                                                   \
-        if (ag) ctx.launch(owner_strided_kernel<RR, true>, strided_grid(n, chunks), kThreads, own, wires, received, out);  \
-        else ctx.launch(owner_strided_kernel<RR, false>, strided_grid(n, chunks), kThreads, own, wires, received, out);    \
+        if (ag) ctx.launch(owner_strided_kernel<RR, true>, strided_grid(n, chunks), kThreads, received, out, wires, own);  \
+        else ctx.launch(owner_strided_kernel<RR, false>, strided_grid(n, chunks), kThreads, received, out, wires, own);    \
     } while (0)
     EQUARX_DISPATCH_CHUNKS(chunks, CALL)
 #undef CALL
@@ -402,11 +402,11 @@ template <int R, int W>
 void launch_chain_strided_as(const PartialTable &tab, int P, unsigned grid, int per_shard, bool semi, bool rs, bool ag,
                              uint16_t *out, LaunchCtx &ctx)
 {
-    if (semi && ag) ctx.launch(chain_strided_kernel<R, W, true, true, true>, grid, kThreads, tab, P, per_shard, out);
-    else if (semi) ctx.launch(chain_strided_kernel<R, W, true, true, false>, grid, kThreads, tab, P, per_shard, out);
-    else if (rs && ag) ctx.launch(chain_strided_kernel<R, W, false, true, true>, grid, kThreads, tab, P, per_shard, out);
-    else if (rs) ctx.launch(chain_strided_kernel<R, W, false, true, false>, grid, kThreads, tab, P, per_shard, out);
-    else ctx.launch(chain_strided_kernel<R, W, false, false, true>, grid, kThreads, tab, P, per_shard, out);
+    if (semi && ag) ctx.launch(chain_strided_kernel<R, W, true, true, true>, grid, kThreads, P, per_shard, out, tab);
+    else if (semi) ctx.launch(chain_strided_kernel<R, W, true, true, false>, grid, kThreads, P, per_shard, out, tab);
+    else if (rs && ag) ctx.launch(chain_strided_kernel<R, W, false, true, true>, grid, kThreads, P, per_shard, out, tab);
+    else if (rs) ctx.launch(chain_strided_kernel<R, W, false, true, false>, grid, kThreads, P, per_shard, out, tab);
+    else ctx.launch(chain_strided_kernel<R, W, false, false, true>, grid, kThreads, P, per_shard, out, tab);
 }
 
 // ring: shards of ceil(minishards / P) whole minishards, shard k in the order a ring gives it.
@@ -522,7 +522,7 @@ int equarx_quantize_batch(const void *const *x_bf16, int8_t *const *codes, float
     if (int st = mem.check()) return st;      // two tensors sharing an output, or an output inside an input
 #define CALL(BB)                                                                                                  \
     ctx.launch2d(quantize_batch_kernel<BB, kTilesQuantize, kWireLeavesTheDevice>, grid_for(n, kTilesQuantize), (unsigned)count, \
-                 kThreads, tab, n, blocks_of(n, BB))
+                 kThreads, n, blocks_of(n, BB), tab)
     EQUARX_DISPATCH_BLOCK(block, CALL)
 #undef CALL
     return ctx.status();
@@ -1073,7 +1073,7 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
         dirs.d[0] = {h + 1 + t, t ? c[0] : nullptr, t ? s[0] : nullptr, c[0], s[0]};
         dirs.d[1] = {h - t, t ? c[1] : nullptr, t ? s[1] : nullptr, c[1], s[1]};
         if (t < na) {
-#define CALL(RR) ctx.launch2d(semi_step_strided_kernel<RR>, strided_grid(n, chunks), 2u, kThreads, tab, (int)P, per_shard, dirs)
+#define CALL(RR) ctx.launch2d(semi_step_strided_kernel<RR>, strided_grid(n, chunks), 2u, kThreads, (int)P, per_shard, dirs, tab)
             EQUARX_DISPATCH_CHUNKS(chunks, CALL)
 #undef CALL
         } else if (t == 0) {

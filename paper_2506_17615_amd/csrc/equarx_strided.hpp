@@ -153,9 +153,9 @@ __device__ __forceinline__ void quantize_strided_body(const uint16_t *__restrict
 }
 
 template <int R>
-__global__ __launch_bounds__(kThreads) void quantize_strided_kernel(const StridedSource src,
-                                                                    int8_t *__restrict__ codes,
-                                                                    float *__restrict__ scales)
+__global__ __launch_bounds__(kThreads) void quantize_strided_kernel(int8_t *__restrict__ codes,
+                                                                    float *__restrict__ scales,
+                                                                    const StridedSource src)
 {
     __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
     const StridedSpot sp = strided_spot(R * kChunkGroups);
@@ -222,7 +222,7 @@ __device__ __forceinline__ void hop_strided_body(const int8_t *cin, const float 
 
 template <int R>
 __global__ __launch_bounds__(kThreads) void hop_strided_kernel(const int8_t *cin, const float *sin,
-                                                               const StridedSource src, int8_t *cout, float *sout)
+                                                               int8_t *cout, float *sout, const StridedSource src)
 {
     __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
     const StridedSpot sp = strided_spot(R * kChunkGroups);
@@ -246,8 +246,8 @@ struct StridedDirections {
 };
 
 template <int R>
-__global__ __launch_bounds__(kThreads) void semi_step_strided_kernel(const PartialTable tab, int P, int per_shard,
-                                                                     const StridedDirections dirs)
+__global__ __launch_bounds__(kThreads) void semi_step_strided_kernel(int P, int per_shard, const StridedDirections dirs,
+                                                                     const PartialTable tab)
 {
     __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
     const StridedSpot sp = strided_spot(R * kChunkGroups);
@@ -272,8 +272,8 @@ struct StridedWires {
 };
 
 template <int R, bool kAG>
-__global__ __launch_bounds__(kThreads) void owner_strided_kernel(const StridedSource src, const StridedWires wires,
-                                                                 int received, uint16_t *out)
+__global__ __launch_bounds__(kThreads) void owner_strided_kernel(int received, uint16_t *out,
+                                                                 const StridedWires wires, const StridedSource src)
 {
     __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
     constexpr int chunks = R * kChunkGroups;
@@ -505,7 +505,7 @@ constexpr int strided_chain_waves(bool semi, bool rs) { return (!semi && rs) ? 2
 // as its owner and the devices k+1, k+2, ... around it.  per_shard == 0: array order everywhere.
 template <int R, int W, bool kSemi, bool kRS, bool kAG>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, strided_chain_waves(kSemi, kRS))))
-void chain_strided_kernel(const PartialTable tab, int P, int per_shard, uint16_t *out)
+void chain_strided_kernel(int P, int per_shard, uint16_t *out, const PartialTable tab)
 {
     static_assert(kRS || !kSemi, "the semi-loop is a quantized reduce-scatter");
     __shared__ __align__(16) uint32_t red[W > 1 ? 2 : 1][kThreads / 64][64];

@@ -41,3 +41,11 @@ def test_kernels_are_there_and_use_what_the_sources_say(device_asm):
     assert "v_permlane32_swap" in asm and "v_permlane16_swap" in asm and "row_mirror" in asm
     assert "v_cvt_pk_bf16_f32" in asm
     assert "v_perm_b32" in asm
+
+
+def test_leading_kernel_arguments_are_preloaded(device_asm):
+    asm = device_asm["equarx_api.hip"]
+    for kernel, dwords in (("hop_kernelILi256E", 14), ("quantize_kernelILi256E", 10), ("dequantize_kernelILi256E", 10),
+                           ("chain_kernelILi256E", 14), ("flat_kernelILi256E", 14)):
+        found = re.findall(r"^\s*\.amdhsa_kernel _ZN6equarx\d+" + kernel + r".*?preload_length (\d+)", asm, flags=re.M | re.S)
+        assert found and all(int(f) == dwords for f in found), (kernel, found)
