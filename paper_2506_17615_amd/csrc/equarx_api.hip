@@ -42,21 +42,29 @@ int static_scratch(unsigned char **ptr)
     return EQUARX_OK;
 }
 
+using FlatShape = Shape<256, 4>;        // the flat reduce and the semi-loop owners' launch
+
 template <int B>
 void launch_head(const uint16_t *x0, const uint16_t *x1, int64_t n, int8_t *cout, float *sout, LaunchCtx &ctx)
 {
-    ctx.launch(head_kernel<B, kTilesHead>, grid_for(n, kTilesHead), kThreads, x0, x1, n, cout, sout, blocks_of(n, B));
+    with_pass_shape(n, [&](auto shape) {
+        using S = decltype(shape);
+        ctx.launch(head_kernel<B, S::K>, grid_for<S>(n), S::T, x0, x1, n, cout, sout, blocks_of(n, B));
+    });
 }
 
 template <int B>
 void launch_tail(const int8_t *cin, const float *sin, const uint16_t *x, int64_t n, uint16_t *out, LaunchCtx &ctx,
                  bool ag = true)
 {
-    if (ag) {
-        ctx.launch(tail_kernel<B, kTilesTail, true>, grid_for(n, kTilesTail), kThreads, cin, sin, x, n, out, blocks_of(n, B));
-    } else {
-        ctx.launch(tail_kernel<B, kTilesTail, false>, grid_for(n, kTilesTail), kThreads, cin, sin, x, n, out, blocks_of(n, B));
-    }
+    with_pass_shape(n, [&](auto shape) {
+        using S = decltype(shape);
+        if (ag) {
+            ctx.launch(tail_kernel<B, S::K, true>, grid_for<S>(n), S::T, cin, sin, x, n, out, blocks_of(n, B));
+        } else {
+            ctx.launch(tail_kernel<B, S::K, false>, grid_for<S>(n), S::T, cin, sin, x, n, out, blocks_of(n, B));
+        }
+    });
 }
 
 // P >= 3: [Q_B(x_0) + hop 1], hops 2 .. P-2, [hop P-1 + quantize/dequantize pair]; c_i lives in wire buffer i & 1.
@@ -76,27 +84,29 @@ void launch_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, int8_t
 {
     const int64_t nb = blocks_of(n, B);
     const int64_t shard_elems = (nb + P - 1) / P * B;       // ceil(nb / P) blocks per shard, as the single launch
-    const unsigned gx = grid_for(shard_elems, kTilesHop), gy = (unsigned)P;
-    ctx.launch2d(quantize_ring_kernel<B, kTilesHop>, gx, gy, kThreads, P, n, shard_elems, c[0], s[0], tab);
-    for (int i = 1; i + 1 < P; ++i) {
-        ctx.launch2d(hop_ring_kernel<B, kTilesHop>, gx, gy, kThreads, c[(i - 1) & 1], s[(i - 1) & 1], P, i, n, shard_elems,
-                 c[i & 1], s[i & 1], tab);
-    }
-    if (ag) {
-        ctx.launch2d(tail_ring_kernel<B, kTilesHop, true>, gx, gy, kThreads, c[(P - 2) & 1], s[(P - 2) & 1], P, P - 1, n,
-                 shard_elems, out, tab);
-    } else {
-        ctx.launch2d(tail_ring_kernel<B, kTilesHop, false>, gx, gy, kThreads, c[(P - 2) & 1], s[(P - 2) & 1], P, P - 1, n,
-                 shard_elems, out, tab);
-    }
+    const unsigned gy = (unsigned)P;
+    with_pass_shape(n, [&](auto shape) {
+        using S = decltype(shape);
+        const unsigned gx = grid_for<S>(shard_elems);
+        ctx.launch2d(quantize_ring_kernel<B, S::K>, gx, gy, S::T, P, n, shard_elems, c[0], s[0], tab);
+        for (int i = 1; i + 1 < P; ++i) {
+            ctx.launch2d(hop_ring_kernel<B, S::K>, gx, gy, S::T, c[(i - 1) & 1], s[(i - 1) & 1], P, i, n,
+                         shard_elems, c[i & 1], s[i & 1], tab);
+        }
+        if (ag) {
+            ctx.launch2d(tail_ring_kernel<B, S::K, true>, gx, gy, S::T, c[(P - 2) & 1], s[(P - 2) & 1], P, P - 1,
+                         n, shard_elems, out, tab);
+        } else {
+            ctx.launch2d(tail_ring_kernel<B, S::K, false>, gx, gy, S::T, c[(P - 2) & 1], s[(P - 2) & 1], P,
+                         P - 1, n, shard_elems, out, tab);
+        }
+    });
 }
 
 // Single-launch chain, measured on MI355X (27B-shaped size): 4 tiles per thread is fastest (63 us; 1, 2, 6, 8
 // tiles and 512- or 1024-thread groups are 1-8 % slower).
-#ifndef EQUARX_TILES_CHAIN
-#define EQUARX_TILES_CHAIN 4
-#endif
-constexpr int kTilesChain = EQUARX_TILES_CHAIN;
+using ChainShape = Shape<256, 4>;
+using ChainMediumShape = Shape<256, 1>;
 static_assert(kMaxPartials == EQUARX_MAX_PARTIALS && kMaxBatch == EQUARX_MAX_PARTIALS, "header and device limits differ");
 
 // Shape of a chain launch: the whole tensor in array order, or (ring layout) one grid row per shard.
@@ -105,17 +115,18 @@ struct ChainGrid {
     int64_t shard_elems;
 };
 
-inline ChainGrid chain_grid(int64_t n, int32_t block, int32_t P, bool ring, int tiles)
+template <typename S>
+inline ChainGrid chain_grid(int64_t n, int32_t block, int32_t P, bool ring)
 {
     ChainGrid g;
     if (ring) {
         const int64_t nb = blocks_of(n, block);
         g.shard_elems = (nb + P - 1) / P * block;           // ceil(nb / P) blocks per shard
-        g.x = grid_for(g.shard_elems, tiles);
+        g.x = grid_for<S>(g.shard_elems);
         g.y = (unsigned)P;
     } else {
         g.shard_elems = 0;
-        g.x = grid_for(n, tiles);
+        g.x = grid_for<S>(n);
         g.y = 1;
     }
     return g;
@@ -126,7 +137,7 @@ inline ChainGrid chain_grid(int64_t n, int32_t block, int32_t P, bool ring, int 
 //                              at 344 k elements;
 //   up to kChainMediumTiles    the bandwidth kernel with one tile per thread, so that every compute unit gets
 //                              work: 8.4 us vs 9.8 us at 2 M elements;
-//   above                      kTilesChain tiles per thread.
+//   above                      four tiles per thread.
 #ifndef EQUARX_CHAIN_SMALL_MAX_TILES
 #define EQUARX_CHAIN_SMALL_MAX_TILES 512
 #endif
@@ -136,13 +147,13 @@ inline ChainGrid chain_grid(int64_t n, int32_t block, int32_t P, bool ring, int 
 constexpr int64_t kChainSmallTiles = EQUARX_CHAIN_SMALL_MAX_TILES;
 constexpr int64_t kChainMediumTiles = EQUARX_CHAIN_MEDIUM_MAX_TILES;
 
-template <int B, int K>
-void launch_chain_k(const PartialTable &tab, int P, int64_t n, bool rs, bool ag, bool ring, uint16_t *out,
+template <int B, typename S>
+void launch_chain_as(const PartialTable &tab, int P, int64_t n, bool rs, bool ag, bool ring, uint16_t *out,
                     int8_t *wire_codes, float *wire_scales, int64_t c_step, int64_t s_step, LaunchCtx &ctx)
 {
-    const ChainGrid g = chain_grid(n, B, P, ring, K);
+    const ChainGrid g = chain_grid<S>(n, B, P, ring);
 #define EQUARX_CHAIN(RS, AG, WIRE)                                                                        \
-    ctx.launch2d(chain_kernel<B, K, RS, AG, WIRE>, g.x, g.y, kThreads, P, n, g.shard_elems, out, wire_codes,        \
+    ctx.launch2d(chain_kernel<B, S::T, S::K, RS, AG, WIRE>, g.x, g.y, S::T, P, n, g.shard_elems, out, wire_codes,        \
                  wire_scales, c_step, s_step, tab)
     if (rs && ag) {
         if (wire_codes) {
@@ -162,56 +173,50 @@ template <int B>
 void launch_chain(const PartialTable &tab, int P, int64_t n, bool rs, bool ag, bool ring, uint16_t *out,
                   int8_t *wire_codes, float *wire_scales, int64_t c_step, int64_t s_step, LaunchCtx &ctx)
 {
-    const int64_t tiles = (n + kTileElems - 1) / kTileElems;
+    const int64_t tiles = (n + tile_elems<kThreads> - 1) / tile_elems<kThreads>;
     if (rs && ag && !ring && tiles <= kChainSmallTiles) {
-        const unsigned grid = grid_for(n, 1);
+        const unsigned grid = grid_for<Shape<kThreads, 1>>(n);
         if (wire_codes) {
             ctx.launch(chain_small_kernel<B, true>, grid, kThreads, P, n, out, wire_codes, wire_scales, c_step, s_step, tab);
         } else {
             ctx.launch(chain_small_kernel<B, false>, grid, kThreads, P, n, out, wire_codes, wire_scales, c_step, s_step, tab);
         }
     } else if (tiles <= kChainMediumTiles) {
-        launch_chain_k<B, 1>(tab, P, n, rs, ag, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
+        launch_chain_as<B, ChainMediumShape>(tab, P, n, rs, ag, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
     } else {
-        launch_chain_k<B, kTilesChain>(tab, P, n, rs, ag, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
+        launch_chain_as<B, ChainShape>(tab, P, n, rs, ag, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
     }
 }
 
-#ifndef EQUARX_TILES_SEMI
-#define EQUARX_TILES_SEMI 2       // measured at the 27B shape: 66 us against 67.5 us with 4 (two running sums per tile)
-#endif
-constexpr int kTilesSemi = EQUARX_TILES_SEMI;
+using SemiShape = Shape<256, 2>;        // measured at the 27B shape: 66 us against 67.5 us with 4 (two running sums per tile)
 
 template <int B>
 void launch_semi(const PartialTable &tab, int P, int64_t n, bool ag, bool ring, uint16_t *out, LaunchCtx &ctx)
 {
-    const ChainGrid g = chain_grid(n, B, P, ring, kTilesSemi);
+    using S = SemiShape;
+    const ChainGrid g = chain_grid<S>(n, B, P, ring);
     if (ag) {
-        ctx.launch2d(semi_kernel<B, kTilesSemi, true>, g.x, g.y, kThreads, P, n, g.shard_elems, out, tab);
+        ctx.launch2d(semi_kernel<B, S::T, S::K, true>, g.x, g.y, S::T, P, n, g.shard_elems, out, tab);
     } else {
-        ctx.launch2d(semi_kernel<B, kTilesSemi, false>, g.x, g.y, kThreads, P, n, g.shard_elems, out, tab);
+        ctx.launch2d(semi_kernel<B, S::T, S::K, false>, g.x, g.y, S::T, P, n, g.shard_elems, out, tab);
     }
 }
-
-#ifndef EQUARX_TILES_FLAT
-#define EQUARX_TILES_FLAT 4
-#endif
-constexpr int kTilesFlat = EQUARX_TILES_FLAT;
 
 template <int B, bool kStream>
 void launch_flat_as(const uint16_t *local, const WireTable &tab, int R, int64_t n, uint16_t *out, int8_t *codes_out,
                     float *scales_out, LaunchCtx &ctx, bool ag)
 {
-    const unsigned grid = grid_for(n, kTilesFlat);
+    using S = FlatShape;
+    const unsigned grid = grid_for<S>(n);
     const int64_t nb = blocks_of(n, B);
     if (!ag) {      // bf16 output of the unquantized sum; callers pass out and no wire
-        ctx.launch(flat_kernel<B, kTilesFlat, true, false, false, kStream>, grid, kThreads, local, R, n, out, codes_out, scales_out, nb, tab);
+        ctx.launch(flat_kernel<B, S::T, S::K, true, false, false, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
     } else if (out && codes_out) {
-        ctx.launch(flat_kernel<B, kTilesFlat, true, true, true, kStream>, grid, kThreads, local, R, n, out, codes_out, scales_out, nb, tab);
+        ctx.launch(flat_kernel<B, S::T, S::K, true, true, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
     } else if (out) {
-        ctx.launch(flat_kernel<B, kTilesFlat, true, false, true, kStream>, grid, kThreads, local, R, n, out, codes_out, scales_out, nb, tab);
+        ctx.launch(flat_kernel<B, S::T, S::K, true, false, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
     } else {
-        ctx.launch(flat_kernel<B, kTilesFlat, false, true, true, kStream>, grid, kThreads, local, R, n, out, codes_out, scales_out, nb, tab);
+        ctx.launch(flat_kernel<B, S::T, S::K, false, true, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
     }
 }
 
@@ -290,7 +295,7 @@ void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, c
 {
     const int64_t nb = blocks_of(n, B);
     const int64_t shard_elems = (nb + P - 1) / P * B;       // ceil(nb / P) blocks per shard, as the single launch
-    const unsigned gx = grid_for(shard_elems, kTilesHop), gy = (unsigned)P;
+    const unsigned gy = (unsigned)P;
     const int h = P / 2, count[2] = {P - 1 - h, h};
     for (int t = 0; t < h; ++t) {
         WirePair in, to;
@@ -300,7 +305,11 @@ void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, c
             to.codes[d] = w.c[2 * d + (t & 1)];
             to.scales[d] = w.s[2 * d + (t & 1)];
         }
-        ctx.launch3d(semi_ring_step_kernel<B, kTilesHop>, gx, gy, 2u, kThreads, P, t, n, shard_elems, in, to, tab);
+        with_pass_shape(2 * n, [&](auto shape) {        // two shards' worth of work per shard: one per direction
+            using S = decltype(shape);
+            ctx.launch3d(semi_ring_step_kernel<B, S::K>, grid_for<S>(shard_elems), gy, 2u, S::T, P, t, n, shard_elems,
+                         in, to, tab);
+        });
     }
     WireTable wires;
     for (int r = 0; r < kMaxPartials; ++r) {
@@ -314,12 +323,13 @@ void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, c
         wires.scales[received] = w.s[2 * d + ((count[d] - 1) & 1)];
         ++received;
     }
+    using S = FlatShape;
     if (ag) {
-        ctx.launch2d(semi_ring_owner_kernel<B, kTilesFlat, true>, grid_for(shard_elems, kTilesFlat), gy, kThreads, P, n, shard_elems,
+        ctx.launch2d(semi_ring_owner_kernel<B, S::T, S::K, true>, grid_for<S>(shard_elems), gy, S::T, P, n, shard_elems,
                      received, out, wires, tab);
     } else {
-        ctx.launch2d(semi_ring_owner_kernel<B, kTilesFlat, false>, grid_for(shard_elems, kTilesFlat), gy, kThreads, P, n,
-                     shard_elems, received, out, wires, tab);
+        ctx.launch2d(semi_ring_owner_kernel<B, S::T, S::K, false>, grid_for<S>(shard_elems), gy, S::T, P, n, shard_elems,
+                     received, out, wires, tab);
     }
 }
 
@@ -427,8 +437,11 @@ void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chu
 void do_dequantize_strided(const int8_t *codes, const float *scales, int64_t n, int32_t chunks, void *out,
                            LaunchCtx &ctx)
 {
-    ctx.launch(dequantize_strided_kernel<kTilesDequantize>, grid_for(n, kTilesDequantize), kThreads, codes, scales, n, (int)chunks,
-           static_cast<uint16_t *>(out));
+    with_pass_shape(n, [&](auto shape) {
+        using S = decltype(shape);
+        ctx.launch(dequantize_strided_kernel<S::K>, grid_for<S>(n), S::T, codes, scales, n, (int)chunks,
+                   static_cast<uint16_t *>(out));
+    });
 }
 
 }  // namespace
@@ -521,8 +534,11 @@ int equarx_quantize_batch(const void *const *x_bf16, int8_t *const *codes, float
     }
     if (int st = mem.check()) return st;      // two tensors sharing an output, or an output inside an input
 #define CALL(BB)                                                                                                  \
-    ctx.launch2d(quantize_batch_kernel<BB, kTilesQuantize, kWireLeavesTheDevice>, grid_for(n, kTilesQuantize), (unsigned)count, \
-                 kThreads, n, blocks_of(n, BB), tab)
+    with_pass_shape(count * n, [&](auto shape) {                                                                  \
+        using S = decltype(shape);                                                                                \
+        ctx.launch2d(quantize_batch_kernel<BB, S::K, kWireLeavesTheDevice>, grid_for<S>(n), (unsigned)count,    \
+                     S::T, n, blocks_of(n, BB), tab);                                                             \
+    })
     EQUARX_DISPATCH_BLOCK(block, CALL)
 #undef CALL
     return ctx.status();

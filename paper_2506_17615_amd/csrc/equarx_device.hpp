@@ -9,10 +9,10 @@
 //            (G = 4 .. 64, always inside one wavefront), reduced with DPP row
 //            operations and the gfx950 row-swap permutes;
 //   wave   : 512 consecutive elements per tile;
-//   block of 256 threads : 2048 consecutive elements per tile, K tiles per
-//            thread in flight, tile k of a workgroup starting 2048*k further.
-// Every load instruction of a workgroup therefore reads one contiguous 4 KiB
-// (bf16) or 2 KiB (codes) span.  Elements past n read as zero -- a zero never
+//   workgroup of T threads : 8*T consecutive elements per tile, K tiles per
+//            thread in flight, tile k of a workgroup starting 8*T*k further.
+// Every load instruction of a workgroup therefore reads one contiguous 16*T
+// (bf16) or 8*T byte (codes) span.  Elements past n read as zero -- a zero never
 // changes a block's max-abs, so a ragged last block needs no special
 // arithmetic -- and are not stored.
 //
@@ -35,9 +35,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // one 16-byte acc
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));   // one 8-byte access
 
 // Build-time tuning knobs (defaults are what the library ships with).
-#ifndef EQUARX_THREADS
-#define EQUARX_THREADS 256          // threads per workgroup
-#endif
 #ifndef EQUARX_NT_LOAD_BF16
 #define EQUARX_NT_LOAD_BF16 1       // bf16 inputs are read once: non-temporal loads
 #endif
@@ -51,40 +48,62 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));   // one 8-byte acce
 #define EQUARX_SCHED_BARRIER 1      // keep every load of a thread ahead of its arithmetic
 #endif
 constexpr int kLaneElems = 8;
-constexpr int kThreads = EQUARX_THREADS;
-constexpr int kTileElems = kThreads * kLaneElems;   // 2048 elements per workgroup tile
+constexpr int kThreads = 256;       // workgroups of kernels without a shape of their own
 
-// Tiles a thread keeps in flight (K): 2048*K elements per workgroup.
-// Measured on MI355X at the 27B-shaped size: 3 beats 1, 2 and 4 by 2-5 %.
-#ifndef EQUARX_TILES_QUANTIZE
-#define EQUARX_TILES_QUANTIZE 3
-#endif
-#ifndef EQUARX_TILES_HOP
-#define EQUARX_TILES_HOP 3
-#endif
-#ifndef EQUARX_TILES_DEQUANTIZE
-#define EQUARX_TILES_DEQUANTIZE 3
-#endif
-// First and last launch of the ends-fused schedule: 2, 3 and 4 tiles are within 1 % of each other, 1 is 7 % slower.
-#ifndef EQUARX_TILES_HEAD
-#define EQUARX_TILES_HEAD 3
-#endif
-#ifndef EQUARX_TILES_TAIL
-#define EQUARX_TILES_TAIL 3
-#endif
-constexpr int kTilesHead = EQUARX_TILES_HEAD;
-constexpr int kTilesTail = EQUARX_TILES_TAIL;
-constexpr int kTilesQuantize = EQUARX_TILES_QUANTIZE;
-constexpr int kTilesHop = EQUARX_TILES_HOP;
-constexpr int kTilesDequantize = EQUARX_TILES_DEQUANTIZE;
+// Shape of a launch: T threads per workgroup, K tiles per thread in flight, so
+// T*K*8 consecutive elements per workgroup.
+template <int T_, int K_>
+struct Shape {
+    static constexpr int T = T_, K = K_;
+    static constexpr int64_t kElems = (int64_t)T_ * K_ * kLaneElems;
+};
 
-// Workgroups of a launch whose workgroups take `tiles` tiles each.
-inline unsigned grid_for(int64_t n, int tiles)
+// Elements of one tile of a workgroup of T threads.
+template <int T>
+constexpr int tile_elems = T * kLaneElems;
+
+// Workgroups of a launch of that shape over n elements.
+template <typename S>
+inline unsigned grid_for(int64_t n)
 {
-    const int64_t per_wg = (int64_t)kTileElems * tiles;
-    return (unsigned)((n + per_wg - 1) / per_wg);
+    return (unsigned)((n + S::kElems - 1) / S::kElems);
 }
 
+// The two shapes of the kernels that make one pass over a message: quantize, hop, dequantize, the ends-fused
+// chain's head and tail, the ring steps.
+//
+// NarrowPass, one tile per thread: a launch is over when its slowest wave is, and with everything resident at once
+// a wave's time is one memory round trip plus its own arithmetic; a second and third tile per thread only make that
+// chain longer.  WidePass once the message no longer fits the chip in one round of workgroups (256 CUs x 8
+// workgroups x 2048 elements = 4 Mi): from there what counts is few workgroups to dispatch and two loads per lane
+// in flight.  Measured on MI355X, us per hop-by-hop chain (P = 6, block 256), against 256 threads x 3 tiles for
+// every size:
+//     elements      256 x 3    256 x 1    512 x 2    256 x 2
+//     40 k            20.6       14.5       17.0       16.6
+//     640 k           23.9       15.8       19.2       18.7
+//     2.75 M          28.2       23.3       24.6       27.5
+//     4.0 M           35.2       27.7       30.6       28.7
+//     5.5 M           39.8       35.1       34.7       33.9
+//     12 M            59.1       57.2       54.9       55.1
+//     22 M            94.0      101.6       93.9       95.5
+//     33.5 M         140.1      145.0      137.5      137.6
+constexpr int pass_threads(int K) { return K == 1 ? 256 : 512; }
+template <int K>
+using PassShape = Shape<pass_threads(K), K>;
+using NarrowPass = PassShape<1>;
+using WidePass = PassShape<2>;
+constexpr int64_t kOneRound = (int64_t)2048 * NarrowPass::kElems;
+
+// f(shape) with the shape for a pass over n elements.
+template <typename F>
+inline void with_pass_shape(int64_t n, F f)
+{
+    if (n <= kOneRound) {
+        f(NarrowPass{});
+    } else {
+        f(WidePass{});
+    }
+}
 
 // Smallest max-abs that still gets a non-zero scale: 127 * 2^-126, so that
 // scale = absmax/127 stays a normal number and 127/absmax stays finite.
@@ -383,20 +402,20 @@ __device__ __forceinline__ u32x2 quantize_lane(const float (&t)[8], float &scale
 // The K scales a group leader holds, stored after all K tiles are computed: one
 // conditional region at the end instead of one per tile, so the tiles'
 // arithmetic stays in a single basic block.
-template <int B, int K, bool kFull>
+template <int B, int T, int K, bool kFull>
 __device__ __forceinline__ void store_group_scales(float *scales, const float (&scale)[K], int64_t wg_at, int64_t nb)
 {
     constexpr int G = B / kLaneElems;
     if ((threadIdx.x % G) == 0) {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const int64_t blk = (wg_at + k * kTileElems + threadIdx.x * kLaneElems) / B;
+            const int64_t blk = (wg_at + k * tile_elems<T> + threadIdx.x * kLaneElems) / B;
             if (kFull || blk < nb) scales[blk] = scale[k];
         }
     }
 }
 
-template <int B, int K, bool kFull, bool kStream = false>
+template <int B, int T, int K, bool kFull, bool kStream = false>
 __device__ __forceinline__ void quantize_body(const uint16_t *__restrict__ x, int64_t n, int8_t *__restrict__ codes,
                                               float *__restrict__ scales, int64_t nb, int64_t wg_at)
 {
@@ -405,32 +424,33 @@ __device__ __forceinline__ void quantize_body(const uint16_t *__restrict__ x, in
 
     u32x4 xv[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) xv[k] = load_bf16x8(x, wg_at + k * kTileElems + lane_at, n, kFull);
+    for (int k = 0; k < K; ++k) xv[k] = load_bf16x8(x, wg_at + k * tile_elems<T> + lane_at, n, kFull);
     loads_first();
 
     float scale[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * kTileElems + lane_at;
+        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
         float t[8];
         widen_bf16x8(xv[k], t);
         const u32x2 w = quantize_lane<G>(t, scale[k]);
         store_i8x8<kStream>(codes, at, n, kFull, w);
     }
-    store_group_scales<B, K, kFull>(scales, scale, wg_at, nb);
+    store_group_scales<B, T, K, kFull>(scales, scale, wg_at, nb);
 }
 
 // Pass 0 of the chain: quantize a bf16 tensor.
 template <int B, int K, bool kStream = false>
-__global__ __launch_bounds__(kThreads) void quantize_kernel(const uint16_t *__restrict__ x, int64_t n,
+__global__ __launch_bounds__(pass_threads(K)) void quantize_kernel(const uint16_t *__restrict__ x, int64_t n,
                                                             int8_t *__restrict__ codes, float *__restrict__ scales,
                                                             int64_t nb)
 {
-    const int64_t wg_at = (int64_t)blockIdx.x * (kTileElems * K);
-    if (wg_at + kTileElems * K <= n) {
-        quantize_body<B, K, true, kStream>(x, n, codes, scales, nb, wg_at);
+    constexpr int T = pass_threads(K);
+    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
+    if (wg_at + tile_elems<T> * K <= n) {
+        quantize_body<B, T, K, true, kStream>(x, n, codes, scales, nb, wg_at);
     } else {
-        quantize_body<B, K, false, kStream>(x, n, codes, scales, nb, wg_at);
+        quantize_body<B, T, K, false, kStream>(x, n, codes, scales, nb, wg_at);
     }
 }
 
@@ -446,20 +466,21 @@ struct QuantizeBatch {
 };
 
 template <int B, int K, bool kStream = false>
-__global__ __launch_bounds__(kThreads) void quantize_batch_kernel(int64_t n, int64_t nb, const QuantizeBatch tab)
+__global__ __launch_bounds__(pass_threads(K)) void quantize_batch_kernel(int64_t n, int64_t nb, const QuantizeBatch tab)
 {
+    constexpr int T = pass_threads(K);
     const uint16_t *x = tab.x[blockIdx.y];
     int8_t *codes = tab.codes[blockIdx.y];
     float *scales = tab.scales[blockIdx.y];
-    const int64_t wg_at = (int64_t)blockIdx.x * (kTileElems * K);
-    if (wg_at + kTileElems * K <= n) {
-        quantize_body<B, K, true, kStream>(x, n, codes, scales, nb, wg_at);
+    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
+    if (wg_at + tile_elems<T> * K <= n) {
+        quantize_body<B, T, K, true, kStream>(x, n, codes, scales, nb, wg_at);
     } else {
-        quantize_body<B, K, false, kStream>(x, n, codes, scales, nb, wg_at);
+        quantize_body<B, T, K, false, kStream>(x, n, codes, scales, nb, wg_at);
     }
 }
 
-template <int B, int K, bool kFull, bool kStream = false>
+template <int B, int T, int K, bool kFull, bool kStream = false>
 __device__ __forceinline__ void hop_body(const int8_t *cin, const float *sin, const uint16_t *__restrict__ x,
                                          int64_t n, int8_t *cout, float *sout, int64_t nb, int64_t wg_at)
 {
@@ -471,7 +492,7 @@ __device__ __forceinline__ void hop_body(const int8_t *cin, const float *sin, co
     float sv[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * kTileElems + lane_at;
+        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
         xv[k] = load_bf16x8(x, at, n, kFull);
         cv[k] = load_i8x8<kStream>(cin, at, n, kFull);
         const int64_t blk = at / B;
@@ -482,7 +503,7 @@ __device__ __forceinline__ void hop_body(const int8_t *cin, const float *sin, co
     float scale[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * kTileElems + lane_at;
+        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
         float xf[8], qf[8], t[8];
         widen_bf16x8(xv[k], xf);
         widen_i8x8(cv[k], qf);
@@ -491,7 +512,7 @@ __device__ __forceinline__ void hop_body(const int8_t *cin, const float *sin, co
         const u32x2 w = quantize_lane<G>(t, scale[k]);
         store_i8x8<kStream>(cout, at, n, kFull, w);
     }
-    store_group_scales<B, K, kFull>(sout, scale, wg_at, nb);
+    store_group_scales<B, T, K, kFull>(sout, scale, wg_at, nb);
 }
 
 // One hop: dequantize the incoming wire, add the local bf16 shard in fp32
@@ -499,19 +520,20 @@ __device__ __forceinline__ void hop_body(const int8_t *cin, const float *sin, co
 // wire may be the input wire: a thread reads its own elements, and a group its
 // own scale, before either is written.
 template <int B, int K, bool kStream = false>
-__global__ __launch_bounds__(kThreads) void hop_kernel(const int8_t *cin, const float *sin,
+__global__ __launch_bounds__(pass_threads(K)) void hop_kernel(const int8_t *cin, const float *sin,
                                                        const uint16_t *__restrict__ x, int64_t n,
                                                        int8_t *cout, float *sout, int64_t nb)
 {
-    const int64_t wg_at = (int64_t)blockIdx.x * (kTileElems * K);
-    if (wg_at + kTileElems * K <= n) {
-        hop_body<B, K, true, kStream>(cin, sin, x, n, cout, sout, nb, wg_at);
+    constexpr int T = pass_threads(K);
+    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
+    if (wg_at + tile_elems<T> * K <= n) {
+        hop_body<B, T, K, true, kStream>(cin, sin, x, n, cout, sout, nb, wg_at);
     } else {
-        hop_body<B, K, false, kStream>(cin, sin, x, n, cout, sout, nb, wg_at);
+        hop_body<B, T, K, false, kStream>(cin, sin, x, n, cout, sout, nb, wg_at);
     }
 }
 
-template <int B, int K, bool kFull, bool kStream = false>
+template <int B, int T, int K, bool kFull, bool kStream = false>
 __device__ __forceinline__ void dequantize_body(const int8_t *__restrict__ codes, const float *__restrict__ scales,
                                                 int64_t n, uint16_t *__restrict__ out, int64_t nb, int64_t wg_at)
 {
@@ -521,7 +543,7 @@ __device__ __forceinline__ void dequantize_body(const int8_t *__restrict__ codes
     float sv[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * kTileElems + lane_at;
+        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
         cv[k] = load_i8x8<kStream>(codes, at, n, kFull);
         const int64_t blk = at / B;
         sv[k] = (kFull || blk < nb) ? scales[blk] : 0.0f;
@@ -529,7 +551,7 @@ __device__ __forceinline__ void dequantize_body(const int8_t *__restrict__ codes
 
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * kTileElems + lane_at;
+        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
         float qf[8];
         widen_i8x8(cv[k], qf);
         u32x4 w;
@@ -543,15 +565,16 @@ __device__ __forceinline__ void dequantize_body(const int8_t *__restrict__ codes
 
 // Last pass: dequantize the wire to bf16.
 template <int B, int K, bool kStream = false>
-__global__ __launch_bounds__(kThreads) void dequantize_kernel(const int8_t *__restrict__ codes,
+__global__ __launch_bounds__(pass_threads(K)) void dequantize_kernel(const int8_t *__restrict__ codes,
                                                               const float *__restrict__ scales, int64_t n,
                                                               uint16_t *__restrict__ out, int64_t nb)
 {
-    const int64_t wg_at = (int64_t)blockIdx.x * (kTileElems * K);
-    if (wg_at + kTileElems * K <= n) {
-        dequantize_body<B, K, true, kStream>(codes, scales, n, out, nb, wg_at);
+    constexpr int T = pass_threads(K);
+    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
+    if (wg_at + tile_elems<T> * K <= n) {
+        dequantize_body<B, T, K, true, kStream>(codes, scales, n, out, nb, wg_at);
     } else {
-        dequantize_body<B, K, false, kStream>(codes, scales, n, out, nb, wg_at);
+        dequantize_body<B, T, K, false, kStream>(codes, scales, n, out, nb, wg_at);
     }
 }
 
@@ -577,12 +600,12 @@ struct PartialTable {
     const uint16_t *x[kMaxPartials];
 };
 
-template <int K, bool kFull>
+template <int T, int K, bool kFull>
 __device__ __forceinline__ void load_tiles(const uint16_t *p, int64_t wg_at, int64_t n, u32x4 (&v)[K])
 {
     const int lane_at = threadIdx.x * kLaneElems;
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = load_bf16x8(p, wg_at + k * kTileElems + lane_at, n, kFull);
+    for (int k = 0; k < K; ++k) v[k] = load_bf16x8(p, wg_at + k * tile_elems<T> + lane_at, n, kFull);
 }
 
 // Writes what the wire carries after a quantization of one tile (8 codes per
@@ -640,7 +663,7 @@ __device__ __forceinline__ void finish_tile(const float (&t)[8], uint16_t *out,
 // the same order, so the same bits.
 
 // (c_1, s_1) = Q_B( fma(codes_0, s_0, x_1) ),  (codes_0, s_0) = Q_B(x_0) kept in registers.
-template <int B, int K, bool kFull>
+template <int B, int T, int K, bool kFull>
 __device__ __forceinline__ void head_body(const uint16_t *__restrict__ x0, const uint16_t *__restrict__ x1, int64_t n,
                                           int8_t *__restrict__ cout, float *__restrict__ sout, int64_t nb,
                                           int64_t wg_at)
@@ -648,13 +671,13 @@ __device__ __forceinline__ void head_body(const uint16_t *__restrict__ x0, const
     constexpr int G = B / kLaneElems;
     const int lane_at = threadIdx.x * kLaneElems;
     u32x4 av[K], bv[K];
-    load_tiles<K, kFull>(x0, wg_at, n, av);
-    load_tiles<K, kFull>(x1, wg_at, n, bv);
+    load_tiles<T, K, kFull>(x0, wg_at, n, av);
+    load_tiles<T, K, kFull>(x1, wg_at, n, bv);
     loads_first();
     float scale[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * kTileElems + lane_at;
+        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
         float t[8], r[8], xf[8], s0;
         widen_bf16x8(av[k], t);
         quantize_lane_f<G, false>(t, r, s0);        // a -0.0 code only flips the sign of a zero sum, which Q_B ignores
@@ -664,26 +687,27 @@ __device__ __forceinline__ void head_body(const uint16_t *__restrict__ x0, const
         const u32x2 w = quantize_lane<G>(t, scale[k]);
         store_i8x8(cout, at, n, kFull, w);
     }
-    store_group_scales<B, K, kFull>(sout, scale, wg_at, nb);
+    store_group_scales<B, T, K, kFull>(sout, scale, wg_at, nb);
 }
 
 template <int B, int K>
-__global__ __launch_bounds__(kThreads) void head_kernel(const uint16_t *__restrict__ x0,
+__global__ __launch_bounds__(pass_threads(K)) void head_kernel(const uint16_t *__restrict__ x0,
                                                         const uint16_t *__restrict__ x1, int64_t n,
                                                         int8_t *__restrict__ cout, float *__restrict__ sout,
                                                         int64_t nb)
 {
-    const int64_t wg_at = (int64_t)blockIdx.x * (kTileElems * K);
-    if (wg_at + kTileElems * K <= n) {
-        head_body<B, K, true>(x0, x1, n, cout, sout, nb, wg_at);
+    constexpr int T = pass_threads(K);
+    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
+    if (wg_at + tile_elems<T> * K <= n) {
+        head_body<B, T, K, true>(x0, x1, n, cout, sout, nb, wg_at);
     } else {
-        head_body<B, K, false>(x0, x1, n, cout, sout, nb, wg_at);
+        head_body<B, T, K, false>(x0, x1, n, cout, sout, nb, wg_at);
     }
 }
 
 // out = bf16( DQ( Q_B( fma(codes_in, s_in, x) ) ) ): the last hop and the quantized all-gather's pair (Sec. 3.4);
 // kAG = false: out = bf16( fma(codes_in, s_in, x) ), the all-gather left unquantized.
-template <int B, int K, bool kAG, bool kFull>
+template <int B, int T, int K, bool kAG, bool kFull>
 __device__ __forceinline__ void tail_body(const int8_t *__restrict__ cin, const float *__restrict__ sin,
                                           const uint16_t *x, int64_t n, uint16_t *out,
                                           int64_t nb, int64_t wg_at)
@@ -694,7 +718,7 @@ __device__ __forceinline__ void tail_body(const int8_t *__restrict__ cin, const 
     float sv[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * kTileElems + lane_at;
+        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
         xv[k] = load_bf16x8(x, at, n, kFull);
         cv[k] = load_i8x8(cin, at, n, kFull);
         const int64_t blk = at / B;
@@ -708,20 +732,21 @@ __device__ __forceinline__ void tail_body(const int8_t *__restrict__ cin, const 
         widen_i8x8(cv[k], qf);
 #pragma unroll
         for (int j = 0; j < 8; ++j) t[j] = __builtin_fmaf(qf[j], sv[k], xf[j]);
-        finish_tile<B, kAG, false, kFull>(t, out, nullptr, nullptr, 0, 0, 0, wg_at + k * kTileElems + lane_at, n);
+        finish_tile<B, kAG, false, kFull>(t, out, nullptr, nullptr, 0, 0, 0, wg_at + k * tile_elems<T> + lane_at, n);
     }
 }
 
 template <int B, int K, bool kAG>
-__global__ __launch_bounds__(kThreads) void tail_kernel(const int8_t *__restrict__ cin, const float *__restrict__ sin,
+__global__ __launch_bounds__(pass_threads(K)) void tail_kernel(const int8_t *__restrict__ cin, const float *__restrict__ sin,
                                                         const uint16_t *x, int64_t n,      // out may be x (in place)
                                                         uint16_t *out, int64_t nb)
 {
-    const int64_t wg_at = (int64_t)blockIdx.x * (kTileElems * K);
-    if (wg_at + kTileElems * K <= n) {
-        tail_body<B, K, kAG, true>(cin, sin, x, n, out, nb, wg_at);
+    constexpr int T = pass_threads(K);
+    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
+    if (wg_at + tile_elems<T> * K <= n) {
+        tail_body<B, T, K, kAG, true>(cin, sin, x, n, out, nb, wg_at);
     } else {
-        tail_body<B, K, kAG, false>(cin, sin, x, n, out, nb, wg_at);
+        tail_body<B, T, K, kAG, false>(cin, sin, x, n, out, nb, wg_at);
     }
 }
 
@@ -739,7 +764,7 @@ __device__ __forceinline__ int ring_prev(int j, int P) { return j == 0 ? P - 1 :
 // quantized all-gather a -0.0 code can only flip the sign of zero sums along
 // the chain, which no max-abs, scale or integer code sees, and the last
 // quantization hands out +0.0 codes.
-template <int B, int K, bool kRS, bool kWire, bool kPositiveZero, bool kFull>
+template <int B, int T, int K, bool kRS, bool kWire, bool kPositiveZero, bool kFull>
 __device__ __forceinline__ void hop_tiles(float (&t)[K][8], const u32x4 (&x)[K], int8_t *__restrict__ wire_codes,
                                           float *__restrict__ wire_scales, int64_t c_step, int64_t s_step, int row,
                                           int64_t wg_at, int64_t n)
@@ -753,7 +778,7 @@ __device__ __forceinline__ void hop_tiles(float (&t)[K][8], const u32x4 (&x)[K],
             quantize_lane_f<G, kPositiveZero>(t[k], r, s);
             if (kWire) {
                 store_wire_tile<B, kFull>(wire_codes, wire_scales, c_step, s_step, row,
-                                          wg_at + k * kTileElems + lane_at, n, r, s);
+                                          wg_at + k * tile_elems<T> + lane_at, n, r, s);
             }
             float xf[8];
             widen_bf16x8(x[k], xf);
@@ -776,7 +801,7 @@ __device__ __forceinline__ void hop_tiles(float (&t)[K][8], const u32x4 (&x)[K],
 // at the 27B-shaped size): with three waves per SIMD and four 16-byte loads
 // per lane in flight the memory system is already saturated, and more
 // outstanding requests only lengthen its queues.
-template <int B, int K, bool kRS, bool kAG, bool kWire, bool kFull>
+template <int B, int T, int K, bool kRS, bool kAG, bool kWire, bool kFull>
 __device__ __forceinline__ void chain_body(const PartialTable &tab, int P, int rot, int64_t n,
                                            uint16_t *out, int8_t *__restrict__ wire_codes,
                                            float *__restrict__ wire_scales, int64_t c_step, int64_t s_step,
@@ -787,19 +812,19 @@ __device__ __forceinline__ void chain_body(const PartialTable &tab, int P, int r
     u32x4 x0[K], xv[K];     // separate registers: partial 1 may be requested before partial 0 has arrived
 
     int j = rot >= P ? rot - P : rot;               // rot < 2P
-    load_tiles<K, kFull>(tab.x[j], wg_at, n, x0);
+    load_tiles<T, K, kFull>(tab.x[j], wg_at, n, x0);
 #pragma unroll
     for (int k = 0; k < K; ++k) widen_bf16x8(x0[k], t[k]);
     for (int i = 1; i < P; ++i) {
         j = ring_next(j, P);
-        load_tiles<K, kFull>(tab.x[j], wg_at, n, xv);
-        hop_tiles<B, K, kRS, kWire, !kAG, kFull>(t, xv, wire_codes, wire_scales, c_step, s_step, i - 1, wg_at, n);
+        load_tiles<T, K, kFull>(tab.x[j], wg_at, n, xv);
+        hop_tiles<B, T, K, kRS, kWire, !kAG, kFull>(t, xv, wire_codes, wire_scales, c_step, s_step, i - 1, wg_at, n);
     }
 
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         finish_tile<B, kAG, kWire, kFull>(t[k], out, wire_codes, wire_scales, c_step, s_step, P - 1,
-                                          wg_at + k * kTileElems + lane_at, n);
+                                          wg_at + k * tile_elems<T> + lane_at, n);
     }
 }
 
@@ -812,12 +837,12 @@ __device__ __forceinline__ void chain_body(const PartialTable &tab, int P, int r
 // access still covers whole 128-byte lines: the lanes of a block read B/2
 // consecutive elements, B bytes, per load.  Same operations per element in the
 // same order: same bits.  Full tiles only; the kept-wire form stays on chain_body.
-template <int B, int K2, bool kRS, bool kAG>
+template <int B, int T, int K2, bool kRS, bool kAG>
 __device__ __forceinline__ void chain_body_paired(const PartialTable &tab, int P, int rot,
                                                   uint16_t *out, int64_t wg_at)
 {
     constexpr int Gh = B / 16;                      // lanes per block
-    constexpr int kPairElems = 2 * kTileElems;      // 4096 elements per pair of pieces
+    constexpr int kPairElems = 2 * tile_elems<T>;      // 4096 elements per pair of pieces
     const int64_t lane_at = wg_at + (int64_t)(threadIdx.x / Gh) * B + (threadIdx.x % Gh) * kLaneElems;
     float t[K2][2][8];
     u32x4 x0[K2][2], xv[K2][2];
@@ -911,7 +936,7 @@ struct Span {
     bool any;
 };
 
-template <int K>
+template <int T, int K>
 __device__ __forceinline__ Span workgroup_span(int64_t n, int64_t shard_elems, int rot_bias)
 {
     Span sp;
@@ -923,28 +948,28 @@ __device__ __forceinline__ Span workgroup_span(int64_t n, int64_t shard_elems, i
         sp.hi = lo + shard_elems < n ? lo + shard_elems : n;
         sp.rot = (int)blockIdx.y + rot_bias;
     }
-    sp.wg_at = lo + (int64_t)blockIdx.x * (kTileElems * K);
+    sp.wg_at = lo + (int64_t)blockIdx.x * (tile_elems<T> * K);
     sp.any = sp.wg_at < sp.hi;
     return sp;
 }
 
-template <int B, int K, bool kRS, bool kAG, bool kWire>
-__global__ __launch_bounds__(kThreads) void chain_kernel(int P, int64_t n, int64_t shard_elems, uint16_t *out,
+template <int B, int T, int K, bool kRS, bool kAG, bool kWire>
+__global__ __launch_bounds__(T) void chain_kernel(int P, int64_t n, int64_t shard_elems, uint16_t *out,
                                                          int8_t *__restrict__ wire_codes,
                                                          float *__restrict__ wire_scales, int64_t c_step,
                                                          int64_t s_step, const PartialTable tab)
 {
-    const Span sp = workgroup_span<K>(n, shard_elems, 1);     // shard k: devices k+1, k+2, ..., k
+    const Span sp = workgroup_span<T, K>(n, shard_elems, 1);     // shard k: devices k+1, k+2, ..., k
     if (!sp.any) return;                                      // uniform over the workgroup
-    if (sp.wg_at + kTileElems * K <= sp.hi) {
+    if (sp.wg_at + tile_elems<T> * K <= sp.hi) {
         if (EQUARX_CHAIN_PAIRED && B >= 128 && K % 2 == 0 && !kWire) {
-            chain_body_paired<(B >= 128 ? B : 128), (K >= 2 ? K / 2 : 1), kRS, kAG>(tab, P, sp.rot, out, sp.wg_at);
+            chain_body_paired<(B >= 128 ? B : 128), T, (K >= 2 ? K / 2 : 1), kRS, kAG>(tab, P, sp.rot, out, sp.wg_at);
         } else {
-            chain_body<B, K, kRS, kAG, kWire, true>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step,
+            chain_body<B, T, K, kRS, kAG, kWire, true>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step,
                                                     s_step, sp.wg_at);
         }
     } else {
-        chain_body<B, K, kRS, kAG, kWire, false>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step, s_step,
+        chain_body<B, T, K, kRS, kAG, kWire, false>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step, s_step,
                                                  sp.wg_at);
     }
 }
@@ -957,51 +982,54 @@ __global__ __launch_bounds__(kThreads) void chain_kernel(int P, int64_t n, int64
 // kernels; only the partial, and the end of the range, depend on the grid row.
 
 template <int B, int K>
-__global__ __launch_bounds__(kThreads) void quantize_ring_kernel(int P, int64_t n, int64_t shard_elems,
+__global__ __launch_bounds__(pass_threads(K)) void quantize_ring_kernel(int P, int64_t n, int64_t shard_elems,
                                                                  int8_t *__restrict__ codes,
                                                                  float *__restrict__ scales, const PartialTable tab)
 {
-    const Span sp = workgroup_span<K>(n, shard_elems, 1);
+    constexpr int T = pass_threads(K);
+    const Span sp = workgroup_span<T, K>(n, shard_elems, 1);
     if (!sp.any) return;
     const uint16_t *x = tab.x[sp.rot >= P ? sp.rot - P : sp.rot];
     const int64_t nb = (sp.hi + B - 1) / B;
-    if (sp.wg_at + kTileElems * K <= sp.hi) {
-        quantize_body<B, K, true>(x, sp.hi, codes, scales, nb, sp.wg_at);
+    if (sp.wg_at + tile_elems<T> * K <= sp.hi) {
+        quantize_body<B, T, K, true>(x, sp.hi, codes, scales, nb, sp.wg_at);
     } else {
-        quantize_body<B, K, false>(x, sp.hi, codes, scales, nb, sp.wg_at);
+        quantize_body<B, T, K, false>(x, sp.hi, codes, scales, nb, sp.wg_at);
     }
 }
 
 template <int B, int K>
-__global__ __launch_bounds__(kThreads) void hop_ring_kernel(const int8_t *cin, const float *sin, int P, int step,
+__global__ __launch_bounds__(pass_threads(K)) void hop_ring_kernel(const int8_t *cin, const float *sin, int P, int step,
                                                             int64_t n, int64_t shard_elems, int8_t *cout, float *sout,
                                                             const PartialTable tab)
 {
-    const Span sp = workgroup_span<K>(n, shard_elems, 1 + step);    // row + 1 + step < 2P
+    constexpr int T = pass_threads(K);
+    const Span sp = workgroup_span<T, K>(n, shard_elems, 1 + step);    // row + 1 + step < 2P
     if (!sp.any) return;
     const uint16_t *x = tab.x[sp.rot >= P ? sp.rot - P : sp.rot];
     const int64_t nb = (sp.hi + B - 1) / B;
-    if (sp.wg_at + kTileElems * K <= sp.hi) {
-        hop_body<B, K, true>(cin, sin, x, sp.hi, cout, sout, nb, sp.wg_at);
+    if (sp.wg_at + tile_elems<T> * K <= sp.hi) {
+        hop_body<B, T, K, true>(cin, sin, x, sp.hi, cout, sout, nb, sp.wg_at);
     } else {
-        hop_body<B, K, false>(cin, sin, x, sp.hi, cout, sout, nb, sp.wg_at);
+        hop_body<B, T, K, false>(cin, sin, x, sp.hi, cout, sout, nb, sp.wg_at);
     }
 }
 
 template <int B, int K, bool kAG>
-__global__ __launch_bounds__(kThreads) void tail_ring_kernel(const int8_t *__restrict__ cin,
+__global__ __launch_bounds__(pass_threads(K)) void tail_ring_kernel(const int8_t *__restrict__ cin,
                                                              const float *__restrict__ sin, int P, int step, int64_t n,
                                                              int64_t shard_elems, uint16_t *out,
                                                              const PartialTable tab)
 {
-    const Span sp = workgroup_span<K>(n, shard_elems, 1 + step);
+    constexpr int T = pass_threads(K);
+    const Span sp = workgroup_span<T, K>(n, shard_elems, 1 + step);
     if (!sp.any) return;
     const uint16_t *x = tab.x[sp.rot >= P ? sp.rot - P : sp.rot];
     const int64_t nb = (sp.hi + B - 1) / B;
-    if (sp.wg_at + kTileElems * K <= sp.hi) {
-        tail_body<B, K, kAG, true>(cin, sin, x, sp.hi, out, nb, sp.wg_at);
+    if (sp.wg_at + tile_elems<T> * K <= sp.hi) {
+        tail_body<B, T, K, kAG, true>(cin, sin, x, sp.hi, out, nb, sp.wg_at);
     } else {
-        tail_body<B, K, kAG, false>(cin, sin, x, sp.hi, out, nb, sp.wg_at);
+        tail_body<B, T, K, kAG, false>(cin, sin, x, sp.hi, out, nb, sp.wg_at);
     }
 }
 
@@ -1028,13 +1056,13 @@ __device__ __forceinline__ void chain_small_body(const PartialTable &tab, int P,
     u32x4 a[D][1], b[D][1];
 
 #pragma unroll
-    for (int d = 0; d < D; ++d) load_tiles<1, kFull>(tab.x[d < P ? d : P - 1], wg_at, n, a[d]);
+    for (int d = 0; d < D; ++d) load_tiles<kThreads, 1, kFull>(tab.x[d < P ? d : P - 1], wg_at, n, a[d]);
 
     for (int base = 0; base < P; base += 2 * D) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const int i = base + D + d;
-            load_tiles<1, kFull>(tab.x[i < P ? i : P - 1], wg_at, n, b[d]);
+            load_tiles<kThreads, 1, kFull>(tab.x[i < P ? i : P - 1], wg_at, n, b[d]);
         }
 #pragma unroll
         for (int d = 0; d < D; ++d) {
@@ -1042,20 +1070,20 @@ __device__ __forceinline__ void chain_small_body(const PartialTable &tab, int P,
             if (i == 0) {
                 widen_bf16x8(a[0][0], t[0]);
             } else if (i < P) {
-                hop_tiles<B, 1, true, kWire, false, kFull>(t, a[d], wire_codes, wire_scales, c_step, s_step, i - 1,
+                hop_tiles<B, kThreads, 1, true, kWire, false, kFull>(t, a[d], wire_codes, wire_scales, c_step, s_step, i - 1,
                                                            wg_at, n);
             }
         }
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const int i = base + 2 * D + d;
-            load_tiles<1, kFull>(tab.x[i < P ? i : P - 1], wg_at, n, a[d]);
+            load_tiles<kThreads, 1, kFull>(tab.x[i < P ? i : P - 1], wg_at, n, a[d]);
         }
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const int i = base + D + d;
             if (i < P) {
-                hop_tiles<B, 1, true, kWire, false, kFull>(t, b[d], wire_codes, wire_scales, c_step, s_step, i - 1,
+                hop_tiles<B, kThreads, 1, true, kWire, false, kFull>(t, b[d], wire_codes, wire_scales, c_step, s_step, i - 1,
                                                            wg_at, n);
             }
         }
@@ -1069,8 +1097,8 @@ __global__ __launch_bounds__(kThreads) void chain_small_kernel(int P, int64_t n,
                                                                float *__restrict__ wire_scales, int64_t c_step,
                                                                int64_t s_step, const PartialTable tab)
 {
-    const int64_t wg_at = (int64_t)blockIdx.x * kTileElems;
-    if (wg_at + kTileElems <= n) {
+    const int64_t wg_at = (int64_t)blockIdx.x * tile_elems<kThreads>;
+    if (wg_at + tile_elems<kThreads> <= n) {
         chain_small_body<B, kWire, true>(tab, P, n, out, wire_codes, wire_scales, c_step, s_step, wg_at);
     } else {
         chain_small_body<B, kWire, false>(tab, P, n, out, wire_codes, wire_scales, c_step, s_step, wg_at);
@@ -1082,7 +1110,7 @@ __global__ __launch_bounds__(kThreads) void chain_small_kernel(int P, int64_t n,
 // chain h+1, h+2, ..., P-1 and the clockwise chain h, h-1, ..., 1 each end in a
 // quantized send to the owner, which adds them to its own fp32 shard, the
 // shorter counter-clockwise chain first.
-template <int B, int K, bool kAG, bool kFull>
+template <int B, int T, int K, bool kAG, bool kFull>
 __device__ __forceinline__ void semi_body(const PartialTable &tab, int P, int rot, int64_t n,
                                           uint16_t *out, int64_t wg_at)
 {
@@ -1092,7 +1120,7 @@ __device__ __forceinline__ void semi_body(const PartialTable &tab, int P, int ro
     u32x4 xv[K];
 
     const int owner = rot >= P ? rot - P : rot;     // rot < 2P
-    load_tiles<K, kFull>(tab.x[owner], wg_at, n, xv);
+    load_tiles<T, K, kFull>(tab.x[owner], wg_at, n, xv);
 #pragma unroll
     for (int k = 0; k < K; ++k) widen_bf16x8(xv[k], own[k]);
 
@@ -1103,13 +1131,13 @@ __device__ __forceinline__ void semi_body(const PartialTable &tab, int P, int ro
         if (count <= 0) continue;
         int j = owner + (dir == 0 ? h + 1 : h);     // < 2P
         if (j >= P) j -= P;
-        load_tiles<K, kFull>(tab.x[j], wg_at, n, xv);
+        load_tiles<T, K, kFull>(tab.x[j], wg_at, n, xv);
 #pragma unroll
         for (int k = 0; k < K; ++k) widen_bf16x8(xv[k], t[k]);
         for (int c = 1; c < count; ++c) {
             j = dir == 0 ? ring_next(j, P) : ring_prev(j, P);
-            load_tiles<K, kFull>(tab.x[j], wg_at, n, xv);
-            hop_tiles<B, K, true, false, !kAG, kFull>(t, xv, nullptr, nullptr, 0, 0, 0, wg_at, n);
+            load_tiles<T, K, kFull>(tab.x[j], wg_at, n, xv);
+            hop_tiles<B, T, K, true, false, !kAG, kFull>(t, xv, nullptr, nullptr, 0, 0, 0, wg_at, n);
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -1123,20 +1151,20 @@ __device__ __forceinline__ void semi_body(const PartialTable &tab, int P, int ro
 
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        finish_tile<B, kAG, false, kFull>(own[k], out, nullptr, nullptr, 0, 0, 0, wg_at + k * kTileElems + lane_at, n);
+        finish_tile<B, kAG, false, kFull>(own[k], out, nullptr, nullptr, 0, 0, 0, wg_at + k * tile_elems<T> + lane_at, n);
     }
 }
 
-template <int B, int K, bool kAG>
-__global__ __launch_bounds__(kThreads) void semi_kernel(int P, int64_t n, int64_t shard_elems, uint16_t *out,
+template <int B, int T, int K, bool kAG>
+__global__ __launch_bounds__(T) void semi_kernel(int P, int64_t n, int64_t shard_elems, uint16_t *out,
                                                         const PartialTable tab)
 {
-    const Span sp = workgroup_span<K>(n, shard_elems, 0);     // shard k: owner is device k
+    const Span sp = workgroup_span<T, K>(n, shard_elems, 0);     // shard k: owner is device k
     if (!sp.any) return;
-    if (sp.wg_at + kTileElems * K <= sp.hi) {
-        semi_body<B, K, kAG, true>(tab, P, sp.rot, sp.hi, out, sp.wg_at);
+    if (sp.wg_at + tile_elems<T> * K <= sp.hi) {
+        semi_body<B, T, K, kAG, true>(tab, P, sp.rot, sp.hi, out, sp.wg_at);
     } else {
-        semi_body<B, K, kAG, false>(tab, P, sp.rot, sp.hi, out, sp.wg_at);
+        semi_body<B, T, K, kAG, false>(tab, P, sp.rot, sp.hi, out, sp.wg_at);
     }
 }
 
@@ -1153,7 +1181,7 @@ struct WireTable {
     const float *scales[kMaxPartials];
 };
 
-template <int B, int K, bool kOutBf16, bool kOutWire, bool kAG, bool kFull, bool kStream = false>
+template <int B, int T, int K, bool kOutBf16, bool kOutWire, bool kAG, bool kFull, bool kStream = false>
 __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable &tab, int R, int64_t n,
                                           uint16_t *out, int8_t *__restrict__ codes_out,
                                           float *__restrict__ scales_out, int64_t nb, int64_t wg_at)
@@ -1162,7 +1190,7 @@ __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable
     const int lane_at = threadIdx.x * kLaneElems;
     float acc[K][8];
     u32x4 xv[K];
-    load_tiles<K, kFull>(local, wg_at, n, xv);
+    load_tiles<T, K, kFull>(local, wg_at, n, xv);
 #pragma unroll
     for (int k = 0; k < K; ++k) widen_bf16x8(xv[k], acc[k]);
 
@@ -1173,7 +1201,7 @@ __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable
         float sv[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const int64_t at = wg_at + k * kTileElems + lane_at;
+            const int64_t at = wg_at + k * tile_elems<T> + lane_at;
             cv[k] = load_i8x8<kStream>(c, at, n, kFull);
             const int64_t blk = at / B;
             sv[k] = (kFull || blk < nb) ? sc[blk] : 0.0f;
@@ -1189,7 +1217,7 @@ __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable
 
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * kTileElems + lane_at;
+        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
         if (!kAG) {                 // all-gather left unquantized (the semi-loop's owner, Sec. 3.3/3.4): no wire out
             store_narrowed_tile<kFull>(out, at, n, acc[k]);
             continue;
@@ -1209,16 +1237,16 @@ __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable
     }
 }
 
-template <int B, int K, bool kOutBf16, bool kOutWire, bool kAG = true, bool kStream = false>
-__global__ __launch_bounds__(kThreads) void flat_kernel(const uint16_t *local, int R, int64_t n, uint16_t *out,
+template <int B, int T, int K, bool kOutBf16, bool kOutWire, bool kAG = true, bool kStream = false>
+__global__ __launch_bounds__(T) void flat_kernel(const uint16_t *local, int R, int64_t n, uint16_t *out,
                                                         int8_t *__restrict__ codes_out, float *__restrict__ scales_out,
                                                         int64_t nb, const WireTable tab)
 {
-    const int64_t wg_at = (int64_t)blockIdx.x * (kTileElems * K);
-    if (wg_at + kTileElems * K <= n) {
-        flat_body<B, K, kOutBf16, kOutWire, kAG, true, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
+    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
+    if (wg_at + tile_elems<T> * K <= n) {
+        flat_body<B, T, K, kOutBf16, kOutWire, kAG, true, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
     } else {
-        flat_body<B, K, kOutBf16, kOutWire, kAG, false, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
+        flat_body<B, T, K, kOutBf16, kOutWire, kAG, false, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
     }
 }
 
@@ -1236,11 +1264,12 @@ struct WirePair {           // one wire buffer per direction
 };
 
 template <int B, int K>
-__global__ __launch_bounds__(kThreads) void semi_ring_step_kernel(int P, int t, int64_t n, int64_t shard_elems,
+__global__ __launch_bounds__(pass_threads(K)) void semi_ring_step_kernel(int P, int t, int64_t n, int64_t shard_elems,
                                                                   const WirePair in, const WirePair out,
                                                                   const PartialTable tab)
 {
-    const Span sp = workgroup_span<K>(n, shard_elems, 0);       // rot = the owner's device number
+    constexpr int T = pass_threads(K);
+    const Span sp = workgroup_span<T, K>(n, shard_elems, 0);       // rot = the owner's device number
     if (!sp.any) return;
     const int dir = blockIdx.z, h = P / 2;
     const int count = dir == 0 ? P - 1 - h : h;                 // devices in this direction's chain
@@ -1249,35 +1278,35 @@ __global__ __launch_bounds__(kThreads) void semi_ring_step_kernel(int P, int t, 
     if (dev >= P) dev -= P;
     const uint16_t *x = tab.x[dev];
     const int64_t nb = (sp.hi + B - 1) / B;
-    const bool full = sp.wg_at + kTileElems * K <= sp.hi;
+    const bool full = sp.wg_at + tile_elems<T> * K <= sp.hi;
     if (t == 0) {
         if (full) {
-            quantize_body<B, K, true>(x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
+            quantize_body<B, T, K, true>(x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
         } else {
-            quantize_body<B, K, false>(x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
+            quantize_body<B, T, K, false>(x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
         }
     } else if (full) {
-        hop_body<B, K, true>(in.codes[dir], in.scales[dir], x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
+        hop_body<B, T, K, true>(in.codes[dir], in.scales[dir], x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
     } else {
-        hop_body<B, K, false>(in.codes[dir], in.scales[dir], x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
+        hop_body<B, T, K, false>(in.codes[dir], in.scales[dir], x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
     }
 }
 
 // The owner's last step: its own shard plus the wires that arrived (counter-clockwise first), then the all-gather's
 // quantize/dequantize pair or the plain narrowing.
-template <int B, int K, bool kAG>
-__global__ __launch_bounds__(kThreads) void semi_ring_owner_kernel(int P, int64_t n, int64_t shard_elems,
+template <int B, int T, int K, bool kAG>
+__global__ __launch_bounds__(T) void semi_ring_owner_kernel(int P, int64_t n, int64_t shard_elems,
                                                                    int received, uint16_t *out, const WireTable wires,
                                                                    const PartialTable tab)
 {
-    const Span sp = workgroup_span<K>(n, shard_elems, 0);
+    const Span sp = workgroup_span<T, K>(n, shard_elems, 0);
     if (!sp.any) return;
     const uint16_t *own = tab.x[sp.rot >= P ? sp.rot - P : sp.rot];
     const int64_t nb = (sp.hi + B - 1) / B;
-    if (sp.wg_at + kTileElems * K <= sp.hi) {
-        flat_body<B, K, true, false, kAG, true>(own, wires, received, sp.hi, out, nullptr, nullptr, nb, sp.wg_at);
+    if (sp.wg_at + tile_elems<T> * K <= sp.hi) {
+        flat_body<B, T, K, true, false, kAG, true>(own, wires, received, sp.hi, out, nullptr, nullptr, nb, sp.wg_at);
     } else {
-        flat_body<B, K, true, false, kAG, false>(own, wires, received, sp.hi, out, nullptr, nullptr, nb, sp.wg_at);
+        flat_body<B, T, K, true, false, kAG, false>(own, wires, received, sp.hi, out, nullptr, nullptr, nb, sp.wg_at);
     }
 }
 

@@ -71,9 +71,12 @@ int equarx_calib_hop_traffic(const void *const *partials_bf16, int32_t P, int64_
 #define CALL(BB)                                                                                                   \
     case BB:                                                                                                       \
         for (int32_t i = 1; i < P; ++i) {                                                                          \
-            ctx.launch(hop_traffic_kernel<BB, kTilesHop>, grid_for(n, kTilesHop), kThreads,                        \
-                       reinterpret_cast<const u32x4 *>(partials_bf16[i]), c[(i - 1) & 1], s[(i - 1) & 1], lanes,   \
-                       c[i & 1], s[i & 1]);                                                                        \
+            with_pass_shape(n, [&](auto shape) {                                                                   \
+                using S = decltype(shape);                                                                         \
+                ctx.launch(hop_traffic_kernel<BB, S::K>, grid_for<S>(n), S::T,                               \
+                           reinterpret_cast<const u32x4 *>(partials_bf16[i]), c[(i - 1) & 1], s[(i - 1) & 1],      \
+                           lanes, c[i & 1], s[i & 1]);                                                             \
+            });                                                                                                    \
         }                                                                                                          \
         break;
     switch (block) {

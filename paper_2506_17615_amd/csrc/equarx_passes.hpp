@@ -13,36 +13,42 @@ namespace host {
 template <int B>
 void launch_quantize(const uint16_t *x, int64_t n, int8_t *codes, float *scales, LaunchCtx &ctx, bool streaming = false)
 {
-    const unsigned grid = grid_for(n, kTilesQuantize);
-    if (streaming) {
-        ctx.launch(quantize_kernel<B, kTilesQuantize, true>, grid, kThreads, x, n, codes, scales, blocks_of(n, B));
-    } else {
-        ctx.launch(quantize_kernel<B, kTilesQuantize, false>, grid, kThreads, x, n, codes, scales, blocks_of(n, B));
-    }
+    with_pass_shape(n, [&](auto shape) {
+        using S = decltype(shape);
+        if (streaming) {
+            ctx.launch(quantize_kernel<B, S::K, true>, grid_for<S>(n), S::T, x, n, codes, scales, blocks_of(n, B));
+        } else {
+            ctx.launch(quantize_kernel<B, S::K, false>, grid_for<S>(n), S::T, x, n, codes, scales, blocks_of(n, B));
+        }
+    });
 }
 
 template <int B>
 void launch_hop(const int8_t *cin, const float *sin, const uint16_t *x, int64_t n, int8_t *cout, float *sout,
                 LaunchCtx &ctx, bool streaming = false)
 {
-    const unsigned grid = grid_for(n, kTilesHop);
-    if (streaming) {
-        ctx.launch(hop_kernel<B, kTilesHop, true>, grid, kThreads, cin, sin, x, n, cout, sout, blocks_of(n, B));
-    } else {
-        ctx.launch(hop_kernel<B, kTilesHop, false>, grid, kThreads, cin, sin, x, n, cout, sout, blocks_of(n, B));
-    }
+    with_pass_shape(n, [&](auto shape) {
+        using S = decltype(shape);
+        if (streaming) {
+            ctx.launch(hop_kernel<B, S::K, true>, grid_for<S>(n), S::T, cin, sin, x, n, cout, sout, blocks_of(n, B));
+        } else {
+            ctx.launch(hop_kernel<B, S::K, false>, grid_for<S>(n), S::T, cin, sin, x, n, cout, sout, blocks_of(n, B));
+        }
+    });
 }
 
 template <int B>
 void launch_dequantize(const int8_t *codes, const float *scales, int64_t n, uint16_t *out, LaunchCtx &ctx,
                        bool streaming = false)
 {
-    const unsigned grid = grid_for(n, kTilesDequantize);
-    if (streaming) {
-        ctx.launch(dequantize_kernel<B, kTilesDequantize, true>, grid, kThreads, codes, scales, n, out, blocks_of(n, B));
-    } else {
-        ctx.launch(dequantize_kernel<B, kTilesDequantize, false>, grid, kThreads, codes, scales, n, out, blocks_of(n, B));
-    }
+    with_pass_shape(n, [&](auto shape) {
+        using S = decltype(shape);
+        if (streaming) {
+            ctx.launch(dequantize_kernel<B, S::K, true>, grid_for<S>(n), S::T, codes, scales, n, out, blocks_of(n, B));
+        } else {
+            ctx.launch(dequantize_kernel<B, S::K, false>, grid_for<S>(n), S::T, codes, scales, n, out, blocks_of(n, B));
+        }
+    });
 }
 
 #define EQUARX_DISPATCH_BLOCK(block, CALL)      \

@@ -578,18 +578,19 @@ void chain_strided_kernel(int P, int per_shard, uint16_t *out, const PartialTabl
 }
 
 // Dequantize in the strided geometry: element e uses scale (e / (1024*chunks)) * 1024 + e % 1024, so the 8
-// elements of a lane use 8 consecutive scales.  n is a multiple of 1024, hence of the 2048-element tile.
+// elements of a lane use 8 consecutive scales.  n is a multiple of 1024: 8 elements are inside or outside as a whole.
 template <int K>
-__global__ __launch_bounds__(kThreads) void dequantize_strided_kernel(const int8_t *__restrict__ codes,
+__global__ __launch_bounds__(pass_threads(K)) void dequantize_strided_kernel(const int8_t *__restrict__ codes,
                                                                       const float *__restrict__ scales, int64_t n,
                                                                       int chunks, uint16_t *__restrict__ out)
 {
-    const int64_t wg_at = (int64_t)blockIdx.x * (kTileElems * K);
+    constexpr int T = pass_threads(K);
+    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
     const int lane_at = threadIdx.x * kLaneElems;
     const int64_t minishard = (int64_t)kChunk * chunks;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * kTileElems + lane_at;
+        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
         if (at >= n) continue;                       // n % 8 == 0: a lane is inside or outside as a whole
         const u32x2 cv = *reinterpret_cast<const u32x2 *>(codes + at);
         const float *s = scales + (at / minishard) * kChunk + at % kChunk;

@@ -1,0 +1,67 @@
+"""Sizes on both sides of every line at which a call changes its launch shape, against the oracle, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_17615_amd import binding as eq
+from test_parity_gpu import _oracle_variant, gpu  # noqa: F401  (the fixture that loads the library)
+
+pytestmark = pytest.mark.gpu
+
+ONE_ROUND = 2048 * 2048         # elements: up to here one tile of 256 threads per workgroup, above 512 threads x 2 tiles
+
+
+@pytest.fixture(scope="module")
+def values(gpu):  # noqa: F811
+    """Partials of the longest length used here; shorter ones are slices of them."""
+    rng = np.random.default_rng(77)
+    n = ONE_ROUND + (1 << 17)
+    return [gpu.bf16_of(rng.standard_normal(n, dtype=np.float32) * np.exp2(rng.integers(-3, 4, n)).astype(np.float32))
+            for _ in range(4)]
+
+
+@pytest.fixture(autouse=True)
+def threads(oracle):
+    oracle.set_threads(8)
+    yield
+    oracle.set_threads(1)
+
+
+def _bits(t):
+    return t.cpu().numpy().view(np.uint32)
+
+
+@pytest.mark.parametrize("n", (ONE_ROUND - 5, ONE_ROUND, ONE_ROUND + 1, ONE_ROUND + 8192 + 4096 + 24))
+@pytest.mark.parametrize("B", (32, 512))
+def test_passes_around_one_round_of_workgroups(gpu, oracle, values, n, B):  # noqa: F811
+    x = [v[:n] for v in values[:3]]
+    want, wc, ws = oracle.reduce_chain(x, B, keep_wire=True)
+    got, c, s = gpu.gpu_chain_per_step(x, B)
+    assert (got == want).all() and (c == wc).all() and (s.view(np.uint32) == ws.view(np.uint32)).all()
+    assert (gpu.gpu_chain(x, B, keep_wire=False) == want).all()
+    assert (gpu.gpu_chain_fused_ends(x, B) == want).all()
+    for flags in (eq.AG_UNQUANTIZED, eq.RING_ORDER, eq.SEMI_LOOP, eq.SEMI_LOOP | eq.RING_ORDER):
+        out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+        eq.equarx_reduce_variant_hops([gpu.dev_bf16(p) for p in x], B, flags, out,
+                                      eq.alloc_variant_workspace(flags, 3, n, B))
+        assert (gpu.host_u16(out) == _oracle_variant(oracle, x, B, flags)).all(), flags
+
+
+@pytest.mark.parametrize("n", (ONE_ROUND // 2 - 3, ONE_ROUND // 2 + 1))
+def test_two_directions_around_one_round_of_workgroups(gpu, oracle, values, n):  # noqa: F811
+    x, flags = [v[:n] for v in values], eq.SEMI_LOOP | eq.RING_ORDER
+    out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    eq.equarx_reduce_variant_hops([gpu.dev_bf16(p) for p in x], 64, flags, out,
+                                  eq.alloc_variant_workspace(flags, 4, n, 64))
+    assert (gpu.host_u16(out) == _oracle_variant(oracle, x, 64, flags)).all()
+
+
+@pytest.mark.parametrize("n", (ONE_ROUND // 2, ONE_ROUND // 2 + 3))
+def test_batch_around_one_round_of_workgroups(gpu, oracle, values, n):  # noqa: F811
+    x, nb = [v[:n] for v in values[:2]], eq.num_blocks(n, 128)
+    codes = [torch.empty(n, dtype=torch.int8, device="cuda") for _ in x]
+    scales = [torch.empty(nb, dtype=torch.float32, device="cuda") for _ in x]
+    eq.equarx_quantize_batch([gpu.dev_bf16(p) for p in x], 128, codes, scales)
+    for p, c, s in zip(x, codes, scales):
+        wc, ws = oracle.quantize_bf16(p, 128)
+        assert (c.cpu().numpy() == wc).all() and (_bits(s) == ws.view(np.uint32)).all()
