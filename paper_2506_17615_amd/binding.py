@@ -1,5 +1,8 @@
 """Thin Python binding of libequarx.so: argument marshalling only.
 
+The ordinary call -- plain contiguous GPU tensors, nothing to refuse -- is marshalled by the extension `_marshal`
+(csrc/marshal.cpp); whatever that one hands back goes through the checks written out here.
+
 Every function has the name and meaning of the C entry point declared in
 ``include/equarx.h``; tensors are torch CUDA tensors used purely as device
 memory, and work is enqueued on torch's current stream.  There is no CPU
@@ -15,6 +18,17 @@ import torch
 from . import build as _build
 
 _lib = None
+
+
+class _Unloaded:
+    """Stands in for the extension until the first call needs the library."""
+
+    def __getattr__(self, name):
+        load()
+        return getattr(_native, name)
+
+
+_native = _Unloaded()
 
 STATUS_OK = 0
 STATUS_NULL_POINTER = 1
@@ -85,7 +99,7 @@ def lib_path() -> str:
 
 def load() -> ctypes.CDLL:
     """Open libequarx.so (built in-tree by ``build.build()``); raises if it is not there."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         path = lib_path()
         if not os.path.exists(path):
@@ -97,7 +111,9 @@ def load() -> ctypes.CDLL:
             fn = getattr(lib, name)
             fn.restype = res
             fn.argtypes = args
-        _lib = lib
+        from . import _marshal
+        _marshal.bind({name: ctypes.cast(getattr(lib, name), _vp).value for name in SIGNATURES})
+        _lib, _native = lib, _marshal
     return _lib
 
 
@@ -144,6 +160,9 @@ def wire_row_scales(n: int, block: int) -> int:
 
 def equarx_quantize(x_bf16: torch.Tensor, block: int, codes: torch.Tensor, scales: torch.Tensor) -> None:
     """codes[n] int8, scales[nb] fp32 <- Q_B(x_bf16[n])."""
+    status = _native.equarx_quantize(x_bf16, block, codes, scales)
+    if status >= 0:
+        return _check(status, "equarx_quantize")
     n = x_bf16.numel()
     _need(x_bf16, torch.bfloat16, n, "x_bf16")
     _need(codes, torch.int8, n, "codes")
@@ -154,6 +173,9 @@ def equarx_quantize(x_bf16: torch.Tensor, block: int, codes: torch.Tensor, scale
 
 def equarx_quantize_batch(xs, block: int, codes_list, scales_list) -> None:
     """equarx_quantize on several bf16 tensors of equal length in one launch."""
+    status = _native.equarx_quantize_batch(xs, block, codes_list, scales_list)
+    if status >= 0:
+        return _check(status, "equarx_quantize_batch")
     count = len(xs)
     if len(codes_list) != count or len(scales_list) != count:
         raise ValueError("xs, codes_list and scales_list differ in length")
@@ -172,6 +194,9 @@ def equarx_quantize_batch(xs, block: int, codes_list, scales_list) -> None:
 
 def equarx_dequantize(codes: torch.Tensor, scales: torch.Tensor, block: int, out_bf16: torch.Tensor) -> None:
     """out_bf16[n] <- bf16(codes * scales[block])."""
+    status = _native.equarx_dequantize(codes, scales, block, out_bf16)
+    if status >= 0:
+        return _check(status, "equarx_dequantize")
     n = codes.numel()
     _need(codes, torch.int8, n, "codes")
     _need(scales, torch.float32, num_blocks(n, block), "scales")
@@ -182,6 +207,9 @@ def equarx_dequantize(codes: torch.Tensor, scales: torch.Tensor, block: int, out
 
 def equarx_reduce_stage(codes_in, scales_in, local_bf16, block: int, codes_out, scales_out) -> None:
     """One hop: (codes_out, scales_out) <- Q_B(fma(codes_in, scales_in, local_bf16))."""
+    status = _native.equarx_reduce_stage(codes_in, scales_in, local_bf16, block, codes_out, scales_out)
+    if status >= 0:
+        return _check(status, "equarx_reduce_stage")
     n = local_bf16.numel()
     nb = num_blocks(n, block)
     _need(local_bf16, torch.bfloat16, n, "local_bf16")
@@ -195,6 +223,9 @@ def equarx_reduce_stage(codes_in, scales_in, local_bf16, block: int, codes_out, 
 
 def equarx_reduce_quantized(partials, block: int, out_bf16, workspace=None, wire_codes=None, wire_scales=None) -> None:
     """The whole chain over the partials (sequence of bf16 tensors of equal length, chain order)."""
+    status = _native.equarx_reduce_quantized(partials, block, out_bf16, workspace, wire_codes, wire_scales)
+    if status >= 0:
+        return _check(status, "equarx_reduce_quantized")
     P = len(partials)
     n = partials[0].numel() if P else 0
     for p in partials:
@@ -218,6 +249,9 @@ STATIC_WORKSPACE_BYTES = 80 << 20
 
 def equarx_reduce_quantized_static(partials, block: int, out_bf16) -> None:
     """equarx_reduce_quantized with the wire buffers in the library's static device array (allocates nothing)."""
+    status = _native.equarx_reduce_quantized_static(partials, block, out_bf16)
+    if status >= 0:
+        return _check(status, "equarx_reduce_quantized_static")
     P = len(partials)
     n = partials[0].numel() if P else 0
     for p in partials:
@@ -232,6 +266,9 @@ def equarx_reduce_quantized_static(partials, block: int, out_bf16) -> None:
 
 def equarx_reduce_quantized_fused_ends(partials, block: int, out_bf16, workspace=None) -> None:
     """The hop-by-hop chain with its first two and last two passes fused (P-1 launches, same bits)."""
+    status = _native.equarx_reduce_quantized_fused_ends(partials, block, out_bf16, workspace)
+    if status >= 0:
+        return _check(status, "equarx_reduce_quantized_fused_ends")
     P = len(partials)
     n = partials[0].numel() if P else 0
     for p in partials:
@@ -249,6 +286,9 @@ def equarx_reduce_quantized_fused_ends(partials, block: int, out_bf16, workspace
 
 def equarx_reduce_fused(partials, block: int, out_bf16, wire_codes=None, wire_scales=None) -> None:
     """The whole chain in one launch (same bits as equarx_reduce_quantized, no workspace)."""
+    status = _native.equarx_reduce_fused(partials, block, out_bf16, wire_codes, wire_scales)
+    if status >= 0:
+        return _check(status, "equarx_reduce_fused")
     P = len(partials)
     n = partials[0].numel() if P else 0
     for p in partials:
@@ -266,6 +306,9 @@ def equarx_reduce_fused(partials, block: int, out_bf16, wire_codes=None, wire_sc
 
 def equarx_reduce_variant(partials, block: int, flags: int, out_bf16) -> None:
     """A variant of the chain in one launch; flags: SEMI_LOOP | RS_UNQUANTIZED | AG_UNQUANTIZED | RING_ORDER."""
+    status = _native.equarx_reduce_variant(partials, block, flags, out_bf16)
+    if status >= 0:
+        return _check(status, "equarx_reduce_variant")
     P = len(partials)
     n = partials[0].numel() if P else 0
     for p in partials:
@@ -284,6 +327,9 @@ def alloc_variant_workspace(flags: int, P: int, n: int, block: int) -> torch.Ten
 
 def equarx_reduce_variant_hops(partials, block: int, flags: int, out_bf16, workspace) -> None:
     """equarx_reduce_variant's full-loop / semi-loop forms hop by hop (one launch per hop, same bits)."""
+    status = _native.equarx_reduce_variant_hops(partials, block, flags, out_bf16, workspace)
+    if status >= 0:
+        return _check(status, "equarx_reduce_variant_hops")
     P = len(partials)
     n = partials[0].numel() if P else 0
     for p in partials:
@@ -302,6 +348,9 @@ def equarx_reduce_variant_hops(partials, block: int, flags: int, out_bf16, works
 def equarx_reduce_flat(local_bf16, codes_list, scales_list, block: int, out_bf16=None, codes_out=None,
                        scales_out=None) -> None:
     """Flat one-shot reduce of a local bf16 shard and R received (codes, scales) pairs."""
+    status = _native.equarx_reduce_flat(local_bf16, codes_list, scales_list, block, out_bf16, codes_out, scales_out)
+    if status >= 0:
+        return _check(status, "equarx_reduce_flat")
     n = local_bf16.numel()
     nb = num_blocks(n, block)
     R = len(codes_list)
@@ -331,6 +380,9 @@ def _strided_scales(n: int, chunks: int) -> int:
 
 def equarx_quantize_strided(x_bf16, chunks: int, codes, scales) -> None:
     """Q with the strided block geometry: scale m*1024+j covers position j of every chunk of minishard m."""
+    status = _native.equarx_quantize_strided(x_bf16, chunks, codes, scales)
+    if status >= 0:
+        return _check(status, "equarx_quantize_strided")
     n = x_bf16.numel()
     _need(x_bf16, torch.bfloat16, n, "x_bf16")
     _need(codes, torch.int8, n, "codes")
@@ -340,6 +392,9 @@ def equarx_quantize_strided(x_bf16, chunks: int, codes, scales) -> None:
 
 
 def equarx_dequantize_strided(codes, scales, chunks: int, out_bf16) -> None:
+    status = _native.equarx_dequantize_strided(codes, scales, chunks, out_bf16)
+    if status >= 0:
+        return _check(status, "equarx_dequantize_strided")
     n = codes.numel()
     _need(codes, torch.int8, n, "codes")
     _need(scales, torch.float32, _strided_scales(n, chunks), "scales")
@@ -349,6 +404,9 @@ def equarx_dequantize_strided(codes, scales, chunks: int, out_bf16) -> None:
 
 
 def equarx_reduce_stage_strided(codes_in, scales_in, local_bf16, chunks: int, codes_out, scales_out) -> None:
+    status = _native.equarx_reduce_stage_strided(codes_in, scales_in, local_bf16, chunks, codes_out, scales_out)
+    if status >= 0:
+        return _check(status, "equarx_reduce_stage_strided")
     n = local_bf16.numel()
     ns = _strided_scales(n, chunks)
     _need(local_bf16, torch.bfloat16, n, "local_bf16")
@@ -361,6 +419,9 @@ def equarx_reduce_stage_strided(codes_in, scales_in, local_bf16, chunks: int, co
 
 
 def equarx_reduce_quantized_strided(partials, chunks: int, out_bf16, workspace) -> None:
+    status = _native.equarx_reduce_quantized_strided(partials, chunks, out_bf16, workspace)
+    if status >= 0:
+        return _check(status, "equarx_reduce_quantized_strided")
     P = len(partials)
     n = partials[0].numel() if P else 0
     for p in partials:
@@ -378,6 +439,9 @@ def equarx_reduce_quantized_strided(partials, chunks: int, out_bf16, workspace) 
 
 def equarx_reduce_fused_strided(partials, chunks: int, out_bf16) -> None:
     """The strided chain in one launch (same bits as equarx_reduce_quantized_strided)."""
+    status = _native.equarx_reduce_fused_strided(partials, chunks, out_bf16)
+    if status >= 0:
+        return _check(status, "equarx_reduce_fused_strided")
     P = len(partials)
     n = partials[0].numel() if P else 0
     for p in partials:
@@ -392,6 +456,9 @@ def equarx_reduce_fused_strided(partials, chunks: int, out_bf16) -> None:
 
 def equarx_reduce_variant_strided(partials, chunks: int, flags: int, out_bf16) -> None:
     """Semi-loop / stage-knob flavours of the chain in the strided geometry, one launch."""
+    status = _native.equarx_reduce_variant_strided(partials, chunks, flags, out_bf16)
+    if status >= 0:
+        return _check(status, "equarx_reduce_variant_strided")
     P = len(partials)
     n = partials[0].numel() if P else 0
     for p in partials:
@@ -406,6 +473,9 @@ def equarx_reduce_variant_strided(partials, chunks: int, flags: int, out_bf16) -
 
 def equarx_reduce_variant_hops_strided(partials, chunks: int, flags: int, out_bf16, workspace) -> None:
     """Full loop or semi-loop, all-gather quantized or not, hop by hop in the strided geometry."""
+    status = _native.equarx_reduce_variant_hops_strided(partials, chunks, flags, out_bf16, workspace)
+    if status >= 0:
+        return _check(status, "equarx_reduce_variant_hops_strided")
     P = len(partials)
     n = partials[0].numel() if P else 0
     for p in partials:

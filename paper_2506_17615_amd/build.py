@@ -1,4 +1,4 @@
-"""Builds libequarx.so (the C-ABI HIP library) for gfx950 with hipcc, in-tree."""
+"""Builds libequarx.so (the C-ABI HIP library) for gfx950 with hipcc and the binding's _marshal.so with g++, in-tree."""
 from __future__ import annotations
 
 import os
@@ -31,8 +31,14 @@ HIPCC_FLAGS = [
     "-I", INCLUDE, "-I", CSRC,
 ]
 
+# the binding's native half: a Python extension against torch's headers, host code only
+MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
+MARSHAL_PATH = os.path.join(_PKG, "_marshal.so")
+MARSHAL_FLAGS = ["-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM"]
+
 
 STAMP_PATH = LIB_PATH + ".stamp"
+MARSHAL_STAMP_PATH = MARSHAL_PATH + ".stamp"
 
 
 def source_digest() -> str:
@@ -46,18 +52,48 @@ def source_digest() -> str:
     return h.hexdigest()
 
 
+def _marshal_digest() -> str:
+    import hashlib
+    import torch
+    h = hashlib.sha256(" ".join(MARSHAL_FLAGS + [torch.__version__]).encode())
+    for path in (MARSHAL_SOURCE, os.path.join(INCLUDE, "equarx.h")):
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
+
+
+def _differs(path: str, stamp: str, digest: str) -> bool:
+    if not os.path.exists(path) or not os.path.exists(stamp):
+        return True
+    with open(stamp) as f:
+        return f.read().strip() != digest
+
+
 def is_stale() -> bool:
-    """True if there is no library, or the one there was not built from the sources as they are now.  Decided
+    """True if a library is not there, or was not built from the sources as they are now.  Decided
     by content (a digest written next to the library at build time), not by file times, which a copy of the tree
     to another machine does not keep."""
-    if not os.path.exists(LIB_PATH) or not os.path.exists(STAMP_PATH):
-        return True
-    with open(STAMP_PATH) as f:
-        return f.read().strip() != source_digest()
+    return _differs(LIB_PATH, STAMP_PATH, source_digest()) or _differs(MARSHAL_PATH, MARSHAL_STAMP_PATH, _marshal_digest())
+
+
+def _build_marshal() -> None:
+    import sysconfig
+    import torch
+    home = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), *MARSHAL_FLAGS, f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(home, "include"), "-isystem",
+           os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), "-I", INCLUDE, MARSHAL_SOURCE, "-o", MARSHAL_PATH,
+           "-L", os.path.join(home, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    digest = _marshal_digest()
+    proc = subprocess.run(cmd, capture_output=True, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("the binding's extension does not compile:\n" + proc.stdout + proc.stderr)
+    with open(MARSHAL_STAMP_PATH, "w") as f:
+        f.write(digest + "\n")
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile the library; returns its path.  Raises if hipcc fails."""
+    """Compile the library and the binding's extension; returns the library's path.  Raises if a compiler fails."""
     if not force and not is_stale():
         return LIB_PATH
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -70,6 +106,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + proc.stdout + proc.stderr)
     with open(STAMP_PATH, "w") as f:
         f.write(digest + "\n")
+    _build_marshal()
     return LIB_PATH
 
 
