@@ -103,10 +103,6 @@ void launch_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, int8_t
     });
 }
 
-// Single-launch chain, measured on MI355X (27B-shaped size): 4 tiles per thread is fastest (63 us; 1, 2, 6, 8
-// tiles and 512- or 1024-thread groups are 1-8 % slower).
-using ChainShape = Shape<256, 4>;
-using ChainMediumShape = Shape<256, 1>;
 static_assert(kMaxPartials == EQUARX_MAX_PARTIALS && kMaxBatch == EQUARX_MAX_PARTIALS, "header and device limits differ");
 
 // Shape of a chain launch: the whole tensor in array order, or (ring layout) one grid row per shard.
@@ -132,20 +128,59 @@ inline ChainGrid chain_grid(int64_t n, int32_t block, int32_t P, bool ring)
     return g;
 }
 
-// Which chain kernel a message gets, by its size in 2048-element tiles (measured on MI355X, P = 8 and 16):
-//   up to kChainSmallTiles     the latency-shaped kernel (one tile per workgroup, batched loads): 4.8 us vs 7.6 us
-//                              at 344 k elements;
-//   up to kChainMediumTiles    the bandwidth kernel with one tile per thread, so that every compute unit gets
-//                              work: 8.4 us vs 9.8 us at 2 M elements;
-//   above                      four tiles per thread.
-#ifndef EQUARX_CHAIN_SMALL_MAX_TILES
-#define EQUARX_CHAIN_SMALL_MAX_TILES 512
-#endif
-#ifndef EQUARX_CHAIN_MEDIUM_MAX_TILES
-#define EQUARX_CHAIN_MEDIUM_MAX_TILES 2048
-#endif
-constexpr int64_t kChainSmallTiles = EQUARX_CHAIN_SMALL_MAX_TILES;
-constexpr int64_t kChainMediumTiles = EQUARX_CHAIN_MEDIUM_MAX_TILES;
+// The latency-shaped chain kernel (one tile per workgroup, batched loads) takes messages up to this size: 4.8 us vs
+// 7.6 us at 344 k elements.
+constexpr int64_t kChainSmallElems = (int64_t)512 * NarrowPass::kElems;
+
+// Launch shapes of the bandwidth kernels of the single-launch calls.  What a message of a few million elements pays
+// for is the last round of workgroups, so each shape is used where its rounds come out even:
+//   256 x 1   while that is one round on the chip (2048 workgroups, 4.2 M elements);
+//   512 x 2   while that is one round (768 workgroups, 6.3 M elements; their registers allow three per CU).  Not for a
+//             chain that writes its wire out: every hop stores there, 29.7 us with 256 x 4, 31.0 with 512 x 2, 28.2
+//             with 1024 x 1 at 6 M elements;
+//   1024 x 1  above: sixteen waves walk one 16 KiB piece of every partial together, each with a single load in flight;
+//   256 x 4   for the chain from 21 M elements on, where two pieces of a block per lane (chain_body_paired) save
+//             arithmetic that 1024 x 1 has to spend; the semi-loop, with its two sums per element, stays at 1024 x 1.
+// Measured on MI355X, us, P = 8, block 256 (semi-loop: P = 7, block 64):
+//     elements      256 x 4   512 x 2   1024 x 1     semi-loop: 256 x 2   512 x 2   1024 x 1
+//     5.0 M           18.1      15.5      17.9                     14.3      14.2      16.1
+//     6.0 M           18.6      17.1      18.8                     16.5      15.9      17.2
+//     6.7 M           21.8      22.0      20.3                     18.7      19.3      18.7
+//     7.9 M           22.8      23.9      22.1                     21.7      20.8      20.2
+//     8.4 M           31.9      28.2      26.8                     24.4      24.8      23.9
+//     12.5 M          36.4      36.4      35.2                     33.2      32.5      31.6
+//     16 M            45.4      45.1      44.1                     42.3      40.4      39.9
+//     20 M            58.4      56.7      54.9                     52.0      50.1      49.3
+//     22 M            60.7      61.4      61.2                     58.0      54.8      55.3
+//     33.5 M          91.6      93.9      92.2                     85.2      83.1      81.9
+constexpr int64_t kOneWideRound = (int64_t)768 * Shape<512, 2>::kElems;
+constexpr int64_t kPairedFrom = (int64_t)2560 * Shape<1024, 1>::kElems;
+
+template <typename F>
+void with_chain_shape(int64_t n, bool keeps_wire, F f)
+{
+    if (n <= kOneRound) {
+        f(Shape<256, 1>{});
+    } else if (n <= kOneWideRound && !keeps_wire) {
+        f(Shape<512, 2>{});
+    } else if (n <= kPairedFrom) {
+        f(Shape<1024, 1>{});
+    } else {
+        f(Shape<256, 4>{});
+    }
+}
+
+template <typename F>
+void with_semi_shape(int64_t n, F f)
+{
+    if (n <= kOneRound) {
+        f(Shape<256, 1>{});
+    } else if (n <= kOneWideRound) {
+        f(Shape<512, 2>{});
+    } else {
+        f(Shape<1024, 1>{});
+    }
+}
 
 template <int B, typename S>
 void launch_chain_as(const PartialTable &tab, int P, int64_t n, bool rs, bool ag, bool ring, uint16_t *out,
@@ -173,33 +208,32 @@ template <int B>
 void launch_chain(const PartialTable &tab, int P, int64_t n, bool rs, bool ag, bool ring, uint16_t *out,
                   int8_t *wire_codes, float *wire_scales, int64_t c_step, int64_t s_step, LaunchCtx &ctx)
 {
-    const int64_t tiles = (n + tile_elems<kThreads> - 1) / tile_elems<kThreads>;
-    if (rs && ag && !ring && tiles <= kChainSmallTiles) {
+    if (rs && ag && !ring && n <= kChainSmallElems) {
         const unsigned grid = grid_for<Shape<kThreads, 1>>(n);
         if (wire_codes) {
             ctx.launch(chain_small_kernel<B, true>, grid, kThreads, P, n, out, wire_codes, wire_scales, c_step, s_step, tab);
         } else {
             ctx.launch(chain_small_kernel<B, false>, grid, kThreads, P, n, out, wire_codes, wire_scales, c_step, s_step, tab);
         }
-    } else if (tiles <= kChainMediumTiles) {
-        launch_chain_as<B, ChainMediumShape>(tab, P, n, rs, ag, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
     } else {
-        launch_chain_as<B, ChainShape>(tab, P, n, rs, ag, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
+        with_chain_shape(n, wire_codes != nullptr, [&](auto shape) {
+            launch_chain_as<B, decltype(shape)>(tab, P, n, rs, ag, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
+        });
     }
 }
-
-using SemiShape = Shape<256, 2>;        // measured at the 27B shape: 66 us against 67.5 us with 4 (two running sums per tile)
 
 template <int B>
 void launch_semi(const PartialTable &tab, int P, int64_t n, bool ag, bool ring, uint16_t *out, LaunchCtx &ctx)
 {
-    using S = SemiShape;
-    const ChainGrid g = chain_grid<S>(n, B, P, ring);
-    if (ag) {
-        ctx.launch2d(semi_kernel<B, S::T, S::K, true>, g.x, g.y, S::T, P, n, g.shard_elems, out, tab);
-    } else {
-        ctx.launch2d(semi_kernel<B, S::T, S::K, false>, g.x, g.y, S::T, P, n, g.shard_elems, out, tab);
-    }
+    with_semi_shape(n, [&](auto shape) {
+        using S = decltype(shape);
+        const ChainGrid g = chain_grid<S>(n, B, P, ring);
+        if (ag) {
+            ctx.launch2d(semi_kernel<B, S::T, S::K, true>, g.x, g.y, S::T, P, n, g.shard_elems, out, tab);
+        } else {
+            ctx.launch2d(semi_kernel<B, S::T, S::K, false>, g.x, g.y, S::T, P, n, g.shard_elems, out, tab);
+        }
+    });
 }
 
 template <int B, bool kStream>

@@ -253,6 +253,27 @@ __device__ __forceinline__ void store_bf16x8(uint16_t *p, int64_t at, int64_t n,
     }
 }
 
+// The output of the single-launch kernels is either streamed (non-temporal, straight to memory) or cached: written
+// through L2 (sc0 sc1) so that it stays in the 256 MB Infinity Cache, where the next kernel that reads it, or the next call
+// that writes the same buffer, finds it; worth it while the output is a modest part of that cache.  Measured on
+// MI355X, P = 8, us streamed -> cached: three output buffers in turn 23.0 -> 22.6 (7.9 M elements), 61.8 -> 60.1
+// (22 M), 96.4 -> 92.3 (33.5 M), 131.4 -> 125.8 (44 M), 176.9 -> 182.4 (60 M); nine in turn, so that none is found
+// again, 23.4 -> 23.0, 62.5 -> 62.5, 97.0 -> 96.2, 132.0 -> 132.3, 179.0 -> 181.4.
+constexpr int64_t kCachedOutElems = (int64_t)32 << 20;      // 64 MiB of bf16, a quarter of the cache
+
+__device__ __forceinline__ bool out_stays_cached(int64_t n) { return n <= kCachedOutElems; }
+
+// 8 bf16 values at out[base + off]; `base` is the same in every lane of the workgroup, the 8 lie inside the output.
+__device__ __forceinline__ void store_out_bf16x8(uint16_t *out, int64_t base, int off, bool cached, const u32x4 &w)
+{
+    if (cached) {
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(out + base, 0, 0x7fffffff, 0x00027000);
+        __builtin_amdgcn_raw_buffer_store_b128(w, rsrc, off * (int)sizeof(uint16_t), 0, 1 | 16);    // sc0 sc1
+    } else {
+        __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(out + base + off));
+    }
+}
+
 // With all K tiles of a thread in one basic block the instruction scheduler
 // would sink some loads between the arithmetic of earlier tiles to save
 // registers; the kernels want every request in flight before the first wait.
@@ -622,15 +643,19 @@ __device__ __forceinline__ void store_wire_tile(int8_t *__restrict__ wire_codes,
 
 // out = bf16(v) for the 8 fp32 values of one lane.
 template <bool kFull>
-__device__ __forceinline__ void store_narrowed_tile(uint16_t *out, int64_t at, int64_t n,
-                                                    const float (&v)[8])
+__device__ __forceinline__ void store_narrowed_tile(uint16_t *out, int64_t base, int off, int64_t n,
+                                                    const float (&v)[8], bool cached = false)
 {
     u32x4 w;
     w.x = narrow_bf16x2(v[0], v[1]);
     w.y = narrow_bf16x2(v[2], v[3]);
     w.z = narrow_bf16x2(v[4], v[5]);
     w.w = narrow_bf16x2(v[6], v[7]);
-    store_bf16x8(out, at, n, kFull, w);
+    if (kFull) {
+        store_out_bf16x8(out, base, off, cached, w);
+    } else {
+        store_bf16x8(out, base + off, n, false, w);
+    }
 }
 
 // The last step of a chain for one tile: quantize the finished fp32 sum once
@@ -638,19 +663,20 @@ __device__ __forceinline__ void store_narrowed_tile(uint16_t *out, int64_t at, i
 template <int B, bool kAG, bool kWire, bool kFull>
 __device__ __forceinline__ void finish_tile(const float (&t)[8], uint16_t *out,
                                             int8_t *__restrict__ wire_codes, float *__restrict__ wire_scales,
-                                            int64_t c_step, int64_t s_step, int row, int64_t at, int64_t n)
+                                            int64_t c_step, int64_t s_step, int row, int64_t base, int off, int64_t n,
+                                            bool cached = false)
 {
     constexpr int G = B / kLaneElems;
     if (kAG) {
         float r[8], s;
         quantize_lane_f<G, true>(t, r, s);      // +0.0 codes: the product below shows the sign of a zero
-        if (kWire) store_wire_tile<B, kFull>(wire_codes, wire_scales, c_step, s_step, row, at, n, r, s);
+        if (kWire) store_wire_tile<B, kFull>(wire_codes, wire_scales, c_step, s_step, row, base + off, n, r, s);
         float d[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) d[j] = r[j] * s;
-        store_narrowed_tile<kFull>(out, at, n, d);
+        store_narrowed_tile<kFull>(out, base, off, n, d, cached);
     } else {
-        store_narrowed_tile<kFull>(out, at, n, t);
+        store_narrowed_tile<kFull>(out, base, off, n, t, cached);
     }
 }
 
@@ -732,7 +758,7 @@ __device__ __forceinline__ void tail_body(const int8_t *__restrict__ cin, const 
         widen_i8x8(cv[k], qf);
 #pragma unroll
         for (int j = 0; j < 8; ++j) t[j] = __builtin_fmaf(qf[j], sv[k], xf[j]);
-        finish_tile<B, kAG, false, kFull>(t, out, nullptr, nullptr, 0, 0, 0, wg_at + k * tile_elems<T> + lane_at, n);
+        finish_tile<B, kAG, false, kFull>(t, out, nullptr, nullptr, 0, 0, 0, wg_at, k * tile_elems<T> + lane_at, n);
     }
 }
 
@@ -805,7 +831,7 @@ template <int B, int T, int K, bool kRS, bool kAG, bool kWire, bool kFull>
 __device__ __forceinline__ void chain_body(const PartialTable &tab, int P, int rot, int64_t n,
                                            uint16_t *out, int8_t *__restrict__ wire_codes,
                                            float *__restrict__ wire_scales, int64_t c_step, int64_t s_step,
-                                           int64_t wg_at)
+                                           int64_t wg_at, bool cached)
 {
     const int lane_at = threadIdx.x * kLaneElems;
     float t[K][8];      // running fp32 sum
@@ -824,7 +850,7 @@ __device__ __forceinline__ void chain_body(const PartialTable &tab, int P, int r
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         finish_tile<B, kAG, kWire, kFull>(t[k], out, wire_codes, wire_scales, c_step, s_step, P - 1,
-                                          wg_at + k * tile_elems<T> + lane_at, n);
+                                          wg_at, k * tile_elems<T> + lane_at, n, cached);
     }
 }
 
@@ -839,11 +865,12 @@ __device__ __forceinline__ void chain_body(const PartialTable &tab, int P, int r
 // same order: same bits.  Full tiles only; the kept-wire form stays on chain_body.
 template <int B, int T, int K2, bool kRS, bool kAG>
 __device__ __forceinline__ void chain_body_paired(const PartialTable &tab, int P, int rot,
-                                                  uint16_t *out, int64_t wg_at)
+                                                  uint16_t *out, int64_t wg_at, bool cached)
 {
     constexpr int Gh = B / 16;                      // lanes per block
     constexpr int kPairElems = 2 * tile_elems<T>;      // 4096 elements per pair of pieces
-    const int64_t lane_at = wg_at + (int64_t)(threadIdx.x / Gh) * B + (threadIdx.x % Gh) * kLaneElems;
+    const int lane_off = (threadIdx.x / Gh) * B + (threadIdx.x % Gh) * kLaneElems;
+    const int64_t lane_at = wg_at + lane_off;
     float t[K2][2][8];
     u32x4 x0[K2][2], xv[K2][2];
 
@@ -920,11 +947,13 @@ __device__ __forceinline__ void chain_body_paired(const PartialTable &tab, int P
                 float d[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) d[e] = (__builtin_rintf(t[k][h][e] * inv) + 0.0f) * s;
-                store_narrowed_tile<true>(out, lane_at + k * kPairElems + h * (B / 2), 0, d);
+                store_narrowed_tile<true>(out, wg_at, lane_off + k * kPairElems + h * (B / 2), 0, d, cached);
             }
         } else {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) store_narrowed_tile<true>(out, lane_at + k * kPairElems + h * (B / 2), 0, t[k][h]);
+            for (int h = 0; h < 2; ++h) {
+                store_narrowed_tile<true>(out, wg_at, lane_off + k * kPairElems + h * (B / 2), 0, t[k][h], cached);
+            }
         }
     }
 }
@@ -963,14 +992,15 @@ __global__ __launch_bounds__(T) void chain_kernel(int P, int64_t n, int64_t shar
     if (!sp.any) return;                                      // uniform over the workgroup
     if (sp.wg_at + tile_elems<T> * K <= sp.hi) {
         if (EQUARX_CHAIN_PAIRED && B >= 128 && K % 2 == 0 && !kWire) {
-            chain_body_paired<(B >= 128 ? B : 128), T, (K >= 2 ? K / 2 : 1), kRS, kAG>(tab, P, sp.rot, out, sp.wg_at);
+            chain_body_paired<(B >= 128 ? B : 128), T, (K >= 2 ? K / 2 : 1), kRS, kAG>(tab, P, sp.rot, out, sp.wg_at,
+                                                                                            out_stays_cached(n));
         } else {
             chain_body<B, T, K, kRS, kAG, kWire, true>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step,
-                                                    s_step, sp.wg_at);
+                                                    s_step, sp.wg_at, out_stays_cached(n));
         }
     } else {
         chain_body<B, T, K, kRS, kAG, kWire, false>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step, s_step,
-                                                 sp.wg_at);
+                                                 sp.wg_at, out_stays_cached(n));
     }
 }
 
@@ -1088,7 +1118,7 @@ __device__ __forceinline__ void chain_small_body(const PartialTable &tab, int P,
             }
         }
     }
-    finish_tile<B, true, kWire, kFull>(t[0], out, wire_codes, wire_scales, c_step, s_step, P - 1, wg_at + lane_at, n);
+    finish_tile<B, true, kWire, kFull>(t[0], out, wire_codes, wire_scales, c_step, s_step, P - 1, wg_at, lane_at, n);
 }
 
 template <int B, bool kWire>
@@ -1112,7 +1142,7 @@ __global__ __launch_bounds__(kThreads) void chain_small_kernel(int P, int64_t n,
 // shorter counter-clockwise chain first.
 template <int B, int T, int K, bool kAG, bool kFull>
 __device__ __forceinline__ void semi_body(const PartialTable &tab, int P, int rot, int64_t n,
-                                          uint16_t *out, int64_t wg_at)
+                                          uint16_t *out, int64_t wg_at, bool cached)
 {
     const int lane_at = threadIdx.x * kLaneElems;
     const int h = P / 2;
@@ -1151,7 +1181,8 @@ __device__ __forceinline__ void semi_body(const PartialTable &tab, int P, int ro
 
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        finish_tile<B, kAG, false, kFull>(own[k], out, nullptr, nullptr, 0, 0, 0, wg_at + k * tile_elems<T> + lane_at, n);
+        finish_tile<B, kAG, false, kFull>(own[k], out, nullptr, nullptr, 0, 0, 0, wg_at, k * tile_elems<T> + lane_at, n,
+                                          cached);
     }
 }
 
@@ -1162,9 +1193,9 @@ __global__ __launch_bounds__(T) void semi_kernel(int P, int64_t n, int64_t shard
     const Span sp = workgroup_span<T, K>(n, shard_elems, 0);     // shard k: owner is device k
     if (!sp.any) return;
     if (sp.wg_at + tile_elems<T> * K <= sp.hi) {
-        semi_body<B, T, K, kAG, true>(tab, P, sp.rot, sp.hi, out, sp.wg_at);
+        semi_body<B, T, K, kAG, true>(tab, P, sp.rot, sp.hi, out, sp.wg_at, out_stays_cached(n));
     } else {
-        semi_body<B, T, K, kAG, false>(tab, P, sp.rot, sp.hi, out, sp.wg_at);
+        semi_body<B, T, K, kAG, false>(tab, P, sp.rot, sp.hi, out, sp.wg_at, out_stays_cached(n));
     }
 }
 
@@ -1219,7 +1250,7 @@ __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable
     for (int k = 0; k < K; ++k) {
         const int64_t at = wg_at + k * tile_elems<T> + lane_at;
         if (!kAG) {                 // all-gather left unquantized (the semi-loop's owner, Sec. 3.3/3.4): no wire out
-            store_narrowed_tile<kFull>(out, at, n, acc[k]);
+            store_narrowed_tile<kFull>(out, wg_at, k * tile_elems<T> + lane_at, n, acc[k]);
             continue;
         }
         float q[8], s;
@@ -1232,7 +1263,7 @@ __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable
             float d[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) d[j] = q[j] * s;
-            store_narrowed_tile<kFull>(out, at, n, d);
+            store_narrowed_tile<kFull>(out, wg_at, k * tile_elems<T> + lane_at, n, d);
         }
     }
 }

@@ -8,6 +8,9 @@ from test_parity_gpu import _oracle_variant, gpu  # noqa: F401  (the fixture tha
 
 pytestmark = pytest.mark.gpu
 
+WIDE_ROUND = 768 * 8192         # single-launch calls: up to here 512 threads x 2 tiles, above 1024 x 1
+PAIRED_FROM = 2560 * 8192       # single-launch chain: above, 256 threads x 4 tiles
+CACHED_OUT = 32 << 20           # single-launch calls: up to here the output stays in the Infinity Cache
 ONE_ROUND = 2048 * 2048         # elements: up to here one tile of 256 threads per workgroup, above 512 threads x 2 tiles
 
 
@@ -65,3 +68,33 @@ def test_batch_around_one_round_of_workgroups(gpu, oracle, values, n):  # noqa: 
     for p, c, s in zip(x, codes, scales):
         wc, ws = oracle.quantize_bf16(p, 128)
         assert (c.cpu().numpy() == wc).all() and (_bits(s) == ws.view(np.uint32)).all()
+
+
+SINGLE = (0, eq.RING_ORDER, eq.AG_UNQUANTIZED, eq.RS_UNQUANTIZED | eq.RING_ORDER, eq.SEMI_LOOP,
+          eq.SEMI_LOOP | eq.RING_ORDER | eq.AG_UNQUANTIZED)
+
+
+@pytest.mark.parametrize("n,flags", [(n, f) for n in (ONE_ROUND - 11, ONE_ROUND + 3, WIDE_ROUND, WIDE_ROUND + 8 * 1024 + 17)
+                                     for f in SINGLE] + [(PAIRED_FROM, 0), (PAIRED_FROM + 5, 0)])
+def test_single_launch_around_its_shapes(gpu, oracle, n, flags):  # noqa: F811
+    rng = np.random.default_rng(n % 1000 + flags)
+    x = [gpu.bf16_of(rng.standard_normal(n, dtype=np.float32)) for _ in range(3)]
+    B = 64 if flags & eq.RING_ORDER else 256
+    assert (gpu.gpu_variant(x, B, flags) == _oracle_variant(oracle, x, B, flags)).all()
+
+
+@pytest.mark.parametrize("n", (ONE_ROUND + 24, WIDE_ROUND + 3))
+def test_kept_wire_above_one_round(gpu, oracle, n):  # noqa: F811
+    rng = np.random.default_rng(n % 1000)
+    x = [gpu.bf16_of(rng.standard_normal(n, dtype=np.float32)) for _ in range(2)]
+    want, wc, ws = oracle.reduce_chain(x, 128, keep_wire=True)
+    got, c, s = gpu.gpu_chain_fused(x, 128)
+    assert (got == want).all() and (c == wc).all() and (s.view(np.uint32) == ws.view(np.uint32)).all()
+
+
+@pytest.mark.parametrize("n", (CACHED_OUT, CACHED_OUT + 1))
+@pytest.mark.parametrize("flags", (0, eq.SEMI_LOOP))
+def test_output_around_the_cache_rule(gpu, oracle, n, flags):  # noqa: F811
+    rng = np.random.default_rng(n % 1000)
+    one = gpu.bf16_of(rng.standard_normal(n, dtype=np.float32))
+    assert (gpu.gpu_variant([one, one], 32, flags) == _oracle_variant(oracle, [one, one], 32, flags)).all()
