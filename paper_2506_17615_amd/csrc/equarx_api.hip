@@ -3,6 +3,7 @@
 #include "equarx.h"
 
 #include <atomic>
+#include <type_traits>
 
 #include "equarx_device.hpp"
 #include "equarx_launch.hpp"
@@ -41,8 +42,6 @@ int static_scratch(unsigned char **ptr)
     *ptr = p;
     return EQUARX_OK;
 }
-
-using FlatShape = Shape<256, 4>;        // the flat reduce and the semi-loop owners' launch
 
 template <int B>
 void launch_head(const uint16_t *x0, const uint16_t *x1, int64_t n, int8_t *cout, float *sout, LaunchCtx &ctx)
@@ -236,34 +235,39 @@ void launch_semi(const PartialTable &tab, int P, int64_t n, bool ag, bool ring, 
     });
 }
 
-template <int B, bool kStream>
-void launch_flat_as(const uint16_t *local, const WireTable &tab, int R, int64_t n, uint16_t *out, int8_t *codes_out,
-                    float *scales_out, LaunchCtx &ctx, bool ag)
+// f(shape, how many received wires to request at a time) for a flat reduce of R wires over n elements: see flat_body.
+template <typename F>
+void with_flat_shape(int64_t n, int R, F f)
 {
-    using S = FlatShape;
-    const unsigned grid = grid_for<S>(n);
-    const int64_t nb = blocks_of(n, B);
-    if (!ag) {      // bf16 output of the unquantized sum; callers pass out and no wire
-        ctx.launch(flat_kernel<B, S::T, S::K, true, false, false, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
-    } else if (out && codes_out) {
-        ctx.launch(flat_kernel<B, S::T, S::K, true, true, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
-    } else if (out) {
-        ctx.launch(flat_kernel<B, S::T, S::K, true, false, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
+    using std::integral_constant;
+    if (n > kOneRound) {
+        f(WidePass{}, integral_constant<int, 1>{});
+    } else if (R <= 2) {
+        f(NarrowPass{}, integral_constant<int, 2>{});
+    } else if (R <= 4) {
+        f(NarrowPass{}, integral_constant<int, 4>{});
     } else {
-        ctx.launch(flat_kernel<B, S::T, S::K, false, true, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
+        f(NarrowPass{}, integral_constant<int, 8>{});
     }
 }
 
-// streaming: the received wires are read, and the outgoing wire is written, with non-temporal hints.
+// The owner's launch of a semi-loop: at most two wires, from this device, kept cacheable.
 template <int B>
-void launch_flat(const uint16_t *local, const WireTable &tab, int R, int64_t n, uint16_t *out, int8_t *codes_out,
-                 float *scales_out, LaunchCtx &ctx, bool ag = true, bool streaming = false)
+void launch_flat_owner(const uint16_t *local, const WireTable &tab, int R, int64_t n, uint16_t *out, LaunchCtx &ctx, bool ag)
 {
-    if (streaming) {
-        launch_flat_as<B, true>(local, tab, R, n, out, codes_out, scales_out, ctx, ag);
-    } else {
-        launch_flat_as<B, false>(local, tab, R, n, out, codes_out, scales_out, ctx, ag);
-    }
+    with_flat_shape(n, 2, [&](auto shape, auto batch) {
+        using S = decltype(shape);
+        constexpr int U = decltype(batch)::value;
+        if constexpr (U <= 2) {
+            if (ag) {
+                ctx.launch(flat_kernel<B, S::K, U, true, false, true, false>, grid_for<S>(n), S::T, local, R, n, out,
+                           nullptr, nullptr, blocks_of(n, B), tab);
+            } else {
+                ctx.launch(flat_kernel<B, S::K, U, true, false, false, false>, grid_for<S>(n), S::T, local, R, n, out,
+                           nullptr, nullptr, blocks_of(n, B), tab);
+            }
+        }
+    });
 }
 
 // The per-step entry points are what a device calls once per step of a collective: equarx_quantize,
@@ -272,6 +276,26 @@ void launch_flat(const uint16_t *local, const WireTable &tab, int R, int64_t n, 
 // with non-temporal hints.  The chain entry points, which run every step on this device, know that the next launch
 // reads what this one wrote and keep the wire cacheable.
 constexpr bool kWireLeavesTheDevice = true;
+
+template <int B>
+void launch_flat(const uint16_t *local, const WireTable &tab, int R, int64_t n, uint16_t *out, int8_t *codes_out,
+                 float *scales_out, LaunchCtx &ctx)
+{
+    const int64_t nb = blocks_of(n, B);
+    with_flat_shape(n, R, [&](auto shape, auto batch) {
+        using S = decltype(shape);
+        constexpr int U = decltype(batch)::value;
+        constexpr bool kStream = kWireLeavesTheDevice;
+        const unsigned grid = grid_for<S>(n);
+        if (out && codes_out) {
+            ctx.launch(flat_kernel<B, S::K, U, true, true, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
+        } else if (out) {
+            ctx.launch(flat_kernel<B, S::K, U, true, false, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
+        } else {
+            ctx.launch(flat_kernel<B, S::K, U, false, true, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
+        }
+    });
+}
 
 // The output of a chain may BE one of the partials (in-place reduction: every
 // kernel reads an element of every partial before the thread that owns the
@@ -357,14 +381,18 @@ void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, c
         wires.scales[received] = w.s[2 * d + ((count[d] - 1) & 1)];
         ++received;
     }
-    using S = FlatShape;
-    if (ag) {
-        ctx.launch2d(semi_ring_owner_kernel<B, S::T, S::K, true>, grid_for<S>(shard_elems), gy, S::T, P, n, shard_elems,
-                     received, out, wires, tab);
-    } else {
-        ctx.launch2d(semi_ring_owner_kernel<B, S::T, S::K, false>, grid_for<S>(shard_elems), gy, S::T, P, n, shard_elems,
-                     received, out, wires, tab);
-    }
+    with_flat_shape(n, 2, [&](auto shape, auto batch) {
+        using S = decltype(shape);
+        constexpr int U = decltype(batch)::value;
+        const unsigned gx = grid_for<S>(shard_elems);
+        if constexpr (U <= 2) {
+            if (ag) {
+                ctx.launch2d(semi_ring_owner_kernel<B, S::K, U, true>, gx, gy, S::T, P, n, shard_elems, received, out, wires, tab);
+            } else {
+                ctx.launch2d(semi_ring_owner_kernel<B, S::K, U, false>, gx, gy, S::T, P, n, shard_elems, received, out, wires, tab);
+            }
+        }
+    });
 }
 
 
@@ -894,7 +922,7 @@ int equarx_reduce_variant_hops(const void *const *partials_bf16, int32_t P, int6
         wires.scales[received] = s[u[(nbk - 1) & 1]];
         ++received;
     }
-#define CALL(BB) launch_flat<BB>(tab.x[0], wires, received, n, out, nullptr, nullptr, ctx, ag)
+#define CALL(BB) launch_flat_owner<BB>(tab.x[0], wires, received, n, out, ctx, ag)
     EQUARX_DISPATCH_BLOCK(block, CALL)
 #undef CALL
     return ctx.status();
@@ -935,7 +963,7 @@ int equarx_reduce_flat(const void *local_bf16, const int8_t *const *codes, const
     if (int st = mem.check()) return st;          // outputs must not share memory with inputs or one another
 #define CALL(BB)                                                                                                  \
     launch_flat<BB>(static_cast<const uint16_t *>(local_bf16), tab, R, n, static_cast<uint16_t *>(out_bf16), codes_out, \
-                    scales_out, ctx, true, kWireLeavesTheDevice)
+                    scales_out, ctx)
     EQUARX_DISPATCH_BLOCK(block, CALL)
 #undef CALL
     return ctx.status();

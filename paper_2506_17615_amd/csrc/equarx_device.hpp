@@ -1212,12 +1212,19 @@ struct WireTable {
     const float *scales[kMaxPartials];
 };
 
-template <int B, int T, int K, bool kOutBf16, bool kOutWire, bool kAG, bool kFull, bool kStream = false>
+// U received wires are requested at a time.  A wide launch has enough waves to cover the wait for one (U = 1: 36.1 us
+// for seven wires of 22 M elements on MI355X, 42.0 with U = 2, whose requests only queue); a narrow one has a wave or
+// two per SIMD, and asking for the next wire only when the last one has been added leaves it waiting R times over:
+// seven wires of 50 k elements 9.4 us with 256 threads x 4 tiles and U = 1, 4.1 with 256 x 1 and U = 8; of 2.75 M
+// 8.9 -> 7.7.  U = 2 for up to two wires (one wire of 50 k: 2.4 us, 2.9 with U = 4, 3.9 with U = 8), 4 for up to
+// four (three of 1.5 M: 4.4 us, 5.2 with U = 8).  Requests past the last wire repeat it and are ignored, so that no
+// load is behind a condition.
+template <int B, int K, int U, bool kOutBf16, bool kOutWire, bool kAG, bool kFull, bool kStream = false>
 __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable &tab, int R, int64_t n,
                                           uint16_t *out, int8_t *__restrict__ codes_out,
                                           float *__restrict__ scales_out, int64_t nb, int64_t wg_at)
 {
-    constexpr int G = B / kLaneElems;
+    constexpr int G = B / kLaneElems, T = pass_threads(K);
     const int lane_at = threadIdx.x * kLaneElems;
     float acc[K][8];
     u32x4 xv[K];
@@ -1225,24 +1232,32 @@ __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable
 #pragma unroll
     for (int k = 0; k < K; ++k) widen_bf16x8(xv[k], acc[k]);
 
-    for (int r = 0; r < R; ++r) {
-        const int8_t *c = tab.codes[r];
-        const float *sc = tab.scales[r];
-        u32x2 cv[K];
-        float sv[K];
+    for (int r0 = 0; r0 < R; r0 += U) {
+        u32x2 cv[U][K];
+        float sv[U][K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int64_t at = wg_at + k * tile_elems<T> + lane_at;
-            cv[k] = load_i8x8<kStream>(c, at, n, kFull);
-            const int64_t blk = at / B;
-            sv[k] = (kFull || blk < nb) ? sc[blk] : 0.0f;
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + u < R ? r0 + u : R - 1;
+            const int8_t *c = tab.codes[r];
+            const float *sc = tab.scales[r];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int64_t at = wg_at + k * tile_elems<T> + lane_at;
+                cv[u][k] = load_i8x8<kStream>(c, at, n, kFull);
+                const int64_t blk = at / B;
+                sv[u][k] = (kFull || blk < nb) ? sc[blk] : 0.0f;
+            }
         }
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            float qf[8];
-            widen_i8x8(cv[k], qf);
+        for (int u = 0; u < U; ++u) {
+            if (r0 + u >= R) break;             // uniform
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[k][j] = __builtin_fmaf(qf[j], sv[k], acc[k][j]);
+            for (int k = 0; k < K; ++k) {
+                float qf[8];
+                widen_i8x8(cv[u][k], qf);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[k][j] = __builtin_fmaf(qf[j], sv[u][k], acc[k][j]);
+            }
         }
     }
 
@@ -1268,16 +1283,16 @@ __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable
     }
 }
 
-template <int B, int T, int K, bool kOutBf16, bool kOutWire, bool kAG = true, bool kStream = false>
-__global__ __launch_bounds__(T) void flat_kernel(const uint16_t *local, int R, int64_t n, uint16_t *out,
+template <int B, int K, int U, bool kOutBf16, bool kOutWire, bool kAG = true, bool kStream = false>
+__global__ __launch_bounds__(pass_threads(K)) void flat_kernel(const uint16_t *local, int R, int64_t n, uint16_t *out,
                                                         int8_t *__restrict__ codes_out, float *__restrict__ scales_out,
                                                         int64_t nb, const WireTable tab)
 {
-    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
-    if (wg_at + tile_elems<T> * K <= n) {
-        flat_body<B, T, K, kOutBf16, kOutWire, kAG, true, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
+    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<pass_threads(K)> * K);
+    if (wg_at + tile_elems<pass_threads(K)> * K <= n) {
+        flat_body<B, K, U, kOutBf16, kOutWire, kAG, true, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
     } else {
-        flat_body<B, T, K, kOutBf16, kOutWire, kAG, false, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
+        flat_body<B, K, U, kOutBf16, kOutWire, kAG, false, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
     }
 }
 
@@ -1325,19 +1340,20 @@ __global__ __launch_bounds__(pass_threads(K)) void semi_ring_step_kernel(int P, 
 
 // The owner's last step: its own shard plus the wires that arrived (counter-clockwise first), then the all-gather's
 // quantize/dequantize pair or the plain narrowing.
-template <int B, int T, int K, bool kAG>
-__global__ __launch_bounds__(T) void semi_ring_owner_kernel(int P, int64_t n, int64_t shard_elems,
+template <int B, int K, int U, bool kAG>
+__global__ __launch_bounds__(pass_threads(K)) void semi_ring_owner_kernel(int P, int64_t n, int64_t shard_elems,
                                                                    int received, uint16_t *out, const WireTable wires,
                                                                    const PartialTable tab)
 {
+    constexpr int T = pass_threads(K);
     const Span sp = workgroup_span<T, K>(n, shard_elems, 0);
     if (!sp.any) return;
     const uint16_t *own = tab.x[sp.rot >= P ? sp.rot - P : sp.rot];
     const int64_t nb = (sp.hi + B - 1) / B;
     if (sp.wg_at + tile_elems<T> * K <= sp.hi) {
-        flat_body<B, T, K, true, false, kAG, true>(own, wires, received, sp.hi, out, nullptr, nullptr, nb, sp.wg_at);
+        flat_body<B, K, U, true, false, kAG, true>(own, wires, received, sp.hi, out, nullptr, nullptr, nb, sp.wg_at);
     } else {
-        flat_body<B, T, K, true, false, kAG, false>(own, wires, received, sp.hi, out, nullptr, nullptr, nb, sp.wg_at);
+        flat_body<B, K, U, true, false, kAG, false>(own, wires, received, sp.hi, out, nullptr, nullptr, nb, sp.wg_at);
     }
 }
 

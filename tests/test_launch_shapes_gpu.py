@@ -98,3 +98,19 @@ def test_output_around_the_cache_rule(gpu, oracle, n, flags):  # noqa: F811
     rng = np.random.default_rng(n % 1000)
     one = gpu.bf16_of(rng.standard_normal(n, dtype=np.float32))
     assert (gpu.gpu_variant([one, one], 32, flags) == _oracle_variant(oracle, [one, one], 32, flags)).all()
+
+
+@pytest.mark.parametrize("R", (0, 1, 2, 3, 4, 5, 8, 9, 16, 17))
+@pytest.mark.parametrize("n", (2048 * 3 + 40, ONE_ROUND + 8192 + 11))
+def test_flat_batches_of_received_wires(gpu, oracle, values, n, R):  # noqa: F811
+    if n > ONE_ROUND and R > 3:
+        n = ONE_ROUND + 3
+    B, local = 64, values[0][:n]
+    q = [oracle.quantize_bf16(values[1 + r % 3][:n], B) for r in range(min(R, 3))]
+    codes, scales = [q[r % 3][0] for r in range(R)], [q[r % 3][1] * np.float32(1 + r // 3) for r in range(R)]
+    out, wc, ws = oracle.reduce_flat(local, codes, scales, B)
+    dev = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in codes + scales]
+    got = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    c, s = torch.empty(n, dtype=torch.int8, device="cuda"), torch.empty(eq.num_blocks(n, B), device="cuda")
+    eq.equarx_reduce_flat(gpu.dev_bf16(local), dev[:R], dev[R:], B, got, c, s)
+    assert (gpu.host_u16(got) == out).all() and (c.cpu().numpy() == wc).all() and (_bits(s) == ws.view(np.uint32)).all()
