@@ -127,9 +127,21 @@ inline ChainGrid chain_grid(int64_t n, int32_t block, int32_t P, bool ring)
     return g;
 }
 
-// The latency-shaped chain kernel (one tile per workgroup, batched loads) takes messages up to this size: 4.8 us vs
-// 7.6 us at 344 k elements.
-constexpr int64_t kChainSmallElems = (int64_t)512 * NarrowPass::kElems;
+// Which single-launch calls the latency-shaped small_kernel takes: messages of up to three workgroups per CU, with
+// enough partials that requesting them together pays, and, for the semi-loop, whose code is twice as long, enough
+// tiles to repay fetching it.  Measured on MI355X, us with the bandwidth kernel -> with small_kernel:
+//     full loop, P =      2             4             8             16      semi-loop, P = 5       8            16 (ring)
+//     20 k            2.1 -> 2.2    2.4 -> 2.4    3.1 -> 2.9    4.6 -> 4.3     2.9 -> 3.2    3.5 -> 3.7     5.4 -> 6.6
+//     160 k           2.2 -> 2.3    2.5 -> 2.5    3.8 -> 3.2    7.8 -> 4.6     3.7 -> 3.6    4.3 -> 4.1     9.2 -> 6.9
+//     600 k           2.4 -> 2.8    3.3 -> 3.3    5.8 -> 4.2   10.6 -> 6.9     4.2 -> 4.2    6.2 -> 5.2    11.3 -> 8.6
+//     1.5 M           2.6 -> 3.5    4.7 -> 4.2    7.4 -> 5.7   12.7 -> 10.0    5.7 -> 5.4    7.4 -> 6.9    13.3 -> 12.3
+//     1.9 M           2.7 -> 3.8    5.0 -> 5.2    7.9 -> 7.0   13.5 -> 12.7    6.1 -> 6.2    8.0 -> 8.2    14.2 -> 15.6
+//     3.0 M           4.2 -> 6.0    6.0 -> 7.0    9.6 -> 9.9   16.5 -> 18.6    7.4 -> 8.2    9.8 -> 11.0   16.9 -> 21.3
+constexpr int64_t kSmallElems = (int64_t)768 * NarrowPass::kElems;
+constexpr int64_t kSmallSemiFrom = (int64_t)32 * NarrowPass::kElems;
+
+inline bool small_chain(int64_t n, int P) { return n <= kSmallElems && P >= 4; }
+inline bool small_semi(int64_t n, int P) { return n <= kSmallElems && n > kSmallSemiFrom && P >= 5; }
 
 // Launch shapes of the bandwidth kernels of the single-launch calls.  What a message of a few million elements pays
 // for is the last round of workgroups, so each shape is used where its rounds come out even:
@@ -203,16 +215,36 @@ void launch_chain_as(const PartialTable &tab, int P, int64_t n, bool rs, bool ag
 #undef EQUARX_CHAIN
 }
 
+template <int B, bool kSemi, bool kRS, bool kAG, bool kWire>
+void launch_small(const PartialTable &tab, int P, int64_t n, bool ring, uint16_t *out, int8_t *wire_codes,
+                  float *wire_scales, int64_t c_step, int64_t s_step, LaunchCtx &ctx)
+{
+    const ChainGrid g = chain_grid<NarrowPass>(n, B, P, ring);
+    if (P <= 8) {
+        ctx.launch2d(small_kernel<B, 8, false, kSemi, kRS, kAG, kWire>, g.x, g.y, kThreads, P, n, g.shard_elems, out,
+                     wire_codes, wire_scales, c_step, s_step, tab);
+    } else if (P <= 16) {
+        ctx.launch2d(small_kernel<B, 16, false, kSemi, kRS, kAG, kWire>, g.x, g.y, kThreads, P, n, g.shard_elems, out,
+                     wire_codes, wire_scales, c_step, s_step, tab);
+    } else {
+        ctx.launch2d(small_kernel<B, 16, true, kSemi, kRS, kAG, kWire>, g.x, g.y, kThreads, P, n, g.shard_elems, out,
+                     wire_codes, wire_scales, c_step, s_step, tab);
+    }
+}
+
 template <int B>
 void launch_chain(const PartialTable &tab, int P, int64_t n, bool rs, bool ag, bool ring, uint16_t *out,
                   int8_t *wire_codes, float *wire_scales, int64_t c_step, int64_t s_step, LaunchCtx &ctx)
 {
-    if (rs && ag && !ring && n <= kChainSmallElems) {
-        const unsigned grid = grid_for<Shape<kThreads, 1>>(n);
-        if (wire_codes) {
-            ctx.launch(chain_small_kernel<B, true>, grid, kThreads, P, n, out, wire_codes, wire_scales, c_step, s_step, tab);
+    if (small_chain(n, P)) {
+        if (rs && ag && wire_codes) {
+            launch_small<B, false, true, true, true>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
+        } else if (rs && ag) {
+            launch_small<B, false, true, true, false>(tab, P, n, ring, out, nullptr, nullptr, 0, 0, ctx);
+        } else if (rs) {
+            launch_small<B, false, true, false, false>(tab, P, n, ring, out, nullptr, nullptr, 0, 0, ctx);
         } else {
-            ctx.launch(chain_small_kernel<B, false>, grid, kThreads, P, n, out, wire_codes, wire_scales, c_step, s_step, tab);
+            launch_small<B, false, false, true, false>(tab, P, n, ring, out, nullptr, nullptr, 0, 0, ctx);
         }
     } else {
         with_chain_shape(n, wire_codes != nullptr, [&](auto shape) {
@@ -224,6 +256,14 @@ void launch_chain(const PartialTable &tab, int P, int64_t n, bool rs, bool ag, b
 template <int B>
 void launch_semi(const PartialTable &tab, int P, int64_t n, bool ag, bool ring, uint16_t *out, LaunchCtx &ctx)
 {
+    if (small_semi(n, P)) {
+        if (ag) {
+            launch_small<B, true, true, true, false>(tab, P, n, ring, out, nullptr, nullptr, 0, 0, ctx);
+        } else {
+            launch_small<B, true, true, false, false>(tab, P, n, ring, out, nullptr, nullptr, 0, 0, ctx);
+        }
+        return;
+    }
     with_semi_shape(n, [&](auto shape) {
         using S = decltype(shape);
         const ChainGrid g = chain_grid<S>(n, B, P, ring);
@@ -318,9 +358,9 @@ inline int check_partials(const void *const *partials_bf16, int32_t P, int64_t n
 // ... and copies them into the kernel's table.
 inline int fill_table(const void *const *partials_bf16, int32_t P, int64_t n, Aliasing &mem, PartialTable &tab)
 {
-    for (int32_t i = 0; i < kMaxPartials; ++i) tab.x[i] = nullptr;
     if (int st = check_partials(partials_bf16, P, n, mem)) return st;
     for (int32_t i = 0; i < P; ++i) tab.x[i] = static_cast<const uint16_t *>(partials_bf16[i]);
+    for (int32_t i = P; i < kMaxPartials; ++i) tab.x[i] = tab.x[i - P];     // small_kernel reads on around the ring
     return EQUARX_OK;
 }
 

@@ -176,22 +176,44 @@ __device__ __forceinline__ uint32_t narrow_bf16x2(float lo, float hi)
 }
 
 // ---------------------------------------------------------------- guarded tile I/O
-// `full` is a compile-time constant at every call: the whole tile lies inside [0, n).
+// A lane's 8 elements are those at [base + off, base + off + 8): `base`, the tile's first element, is the same in
+// every lane, so an access is one scalar base and one 32-bit lane offset.  `full` is a compile-time constant at every call: the whole tile lies inside [0, n).
+//
+// Otherwise the workgroup holds the end of the tensor, and its accesses go through buffer descriptors that end there:
+// the hardware drops the 32-bit words of an access that lie past the end (loads give zero), each on its own.  The
+// elements of a last, partial word are accessed one by one.  Nothing is behind a condition, so the loads of all tiles
+// stay in flight together; with a branch per access every load of this one workgroup waited for the one before, and a
+// message of odd length waited for it (MI355X, 344,063 elements, us with branches -> without: hop-by-hop chain of six
+// 16.3 -> 14.6, flat reduce of five wires 6.5 -> 3.9, eight partials in one launch 9.5 -> 3.4; 344,064, where no
+// workgroup is ragged: 14.6, 3.8 and 3.4).
 
-__device__ __forceinline__ u32x4 load_bf16x8(const uint16_t *p, int64_t at, int64_t n, bool full)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t bounded(const void *p, int bytes)
 {
-    if (full || at + kLaneElems <= n) {
-        const u32x4 *v = reinterpret_cast<const u32x4 *>(p + at);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
+}
+
+// Elements from `base` to the end; a workgroup's last tiles may lie past it.
+__device__ __forceinline__ int left_of(int64_t n, int64_t base) { return n > base ? (int)(n - base) : 0; }
+
+constexpr int kNonTemporal = 2;         // cache policy bits of a buffer access
+constexpr int kThroughL2 = 1 | 16;      // sc0 sc1
+constexpr int kNowhere = 0x7ffffff0;    // an offset past the end of every descriptor here
+
+__device__ __forceinline__ u32x4 load_bf16x8(const uint16_t *p, int64_t base, int off, int64_t n, bool full)
+{
+    if (full) {
+        const u32x4 *v = reinterpret_cast<const u32x4 *>(p + base + off);
         return EQUARX_NT_LOAD_BF16 ? __builtin_nontemporal_load(v) : *v;
     }
-    uint16_t e[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) e[i] = (at + i < n) ? p[at + i] : (uint16_t)0;
-    u32x4 w;
-    w.x = e[0] | ((uint32_t)e[1] << 16);
-    w.y = e[2] | ((uint32_t)e[3] << 16);
-    w.z = e[4] | ((uint32_t)e[5] << 16);
-    w.w = e[6] | ((uint32_t)e[7] << 16);
+    const int left = left_of(n, base);
+    const int whole = left & ~1;
+    constexpr int kPolicy = EQUARX_NT_LOAD_BF16 ? kNonTemporal : 0;
+    u32x4 w = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(bounded(p + base, whole * 2), off * 2, 0, kPolicy));
+    const uint32_t last = __builtin_amdgcn_raw_buffer_load_b16(bounded(p + base, left * 2), whole * 2, 0, 0);     // 0 if left is even
+    if (off == whole) w.x = last;
+    if (off + 2 == whole) w.y = last;
+    if (off + 4 == whole) w.z = last;
+    if (off + 6 == whole) w.w = last;
     return w;
 }
 
@@ -202,26 +224,30 @@ __device__ __forceinline__ u32x4 load_bf16x8(const uint16_t *p, int64_t at, int6
 // every wire cold, streaming accesses make a hop 15.8 us instead of 17.3 us; with a warm wire they make it 16.0 us
 // instead of 14.7 us, because the next launch then misses the cache.
 template <bool kStream = false>
-__device__ __forceinline__ u32x2 load_i8x8(const int8_t *p, int64_t at, int64_t n, bool full)
+__device__ __forceinline__ u32x2 load_i8x8(const int8_t *p, int64_t base, int off, int64_t n, bool full)
 {
-    if (full || at + kLaneElems <= n) {
-        const u32x2 *v = reinterpret_cast<const u32x2 *>(p + at);
+    if (full) {
+        const u32x2 *v = reinterpret_cast<const u32x2 *>(p + base + off);
         return kStream ? __builtin_nontemporal_load(v) : *v;
     }
-    uint32_t e[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) e[i] = (at + i < n) ? (uint32_t)(uint8_t)p[at + i] : 0u;
-    u32x2 w;
-    w.x = e[0] | (e[1] << 8) | (e[2] << 16) | (e[3] << 24);
-    w.y = e[4] | (e[5] << 8) | (e[6] << 16) | (e[7] << 24);
+    const int left = left_of(n, base);
+    const int whole = left & ~3;
+    u32x2 w = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(bounded(p + base, whole), off, 0, kStream ? kNonTemporal : 0));
+    const auto end = bounded(p + base, left);
+    const uint32_t b0 = __builtin_amdgcn_raw_buffer_load_b8(end, whole, 0, 0);
+    const uint32_t b1 = __builtin_amdgcn_raw_buffer_load_b8(end, whole + 1, 0, 0);
+    const uint32_t b2 = __builtin_amdgcn_raw_buffer_load_b8(end, whole + 2, 0, 0);
+    const uint32_t last = b0 | (b1 << 8) | (b2 << 16);
+    if (off == whole) w.x = last;
+    if (off + 4 == whole) w.y = last;
     return w;
 }
 
 template <bool kStream = false>
-__device__ __forceinline__ void store_i8x8(int8_t *p, int64_t at, int64_t n, bool full, const u32x2 &w)
+__device__ __forceinline__ void store_i8x8(int8_t *p, int64_t base, int off, int64_t n, bool full, const u32x2 &w)
 {
-    if (full || at + kLaneElems <= n) {
-        u32x2 *v = reinterpret_cast<u32x2 *>(p + at);
+    if (full) {
+        u32x2 *v = reinterpret_cast<u32x2 *>(p + base + off);
         if (kStream) {
             __builtin_nontemporal_store(w, v);
         } else {
@@ -229,27 +255,15 @@ __device__ __forceinline__ void store_i8x8(int8_t *p, int64_t at, int64_t n, boo
         }
         return;
     }
+    const int left = left_of(n, base);
+    const int whole = left & ~3;
+    __builtin_amdgcn_raw_buffer_store_b64(w, bounded(p + base, whole), off, 0, kStream ? kNonTemporal : 0);
+    const bool holds = off == whole || off + 4 == whole;        // the lane with the last, partial word
+    const uint32_t last = off == whole ? w.x : w.y;
+    const auto end = bounded(p + base, left);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        if (at + i < n) p[at + i] = (int8_t)(((i < 4 ? w.x : w.y) >> (8 * (i & 3))) & 0xFF);
-    }
-}
-
-__device__ __forceinline__ void store_bf16x8(uint16_t *p, int64_t at, int64_t n, bool full, const u32x4 &w)
-{
-    if (full || at + kLaneElems <= n) {
-        u32x4 *v = reinterpret_cast<u32x4 *>(p + at);
-        if (EQUARX_NT_STORE_BF16) {
-            __builtin_nontemporal_store(w, v);
-        } else {
-            *v = w;
-        }
-        return;
-    }
-    const uint32_t d[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        if (at + i < n) p[at + i] = (uint16_t)(d[i >> 1] >> (16 * (i & 1)));
+    for (int i = 0; i < 3; ++i) {
+        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(last >> (8 * i)), end, holds ? whole + i : kNowhere, 0, 0);
     }
 }
 
@@ -263,15 +277,29 @@ constexpr int64_t kCachedOutElems = (int64_t)32 << 20;      // 64 MiB of bf16, a
 
 __device__ __forceinline__ bool out_stays_cached(int64_t n) { return n <= kCachedOutElems; }
 
-// 8 bf16 values at out[base + off]; `base` is the same in every lane of the workgroup, the 8 lie inside the output.
-__device__ __forceinline__ void store_out_bf16x8(uint16_t *out, int64_t base, int off, bool cached, const u32x4 &w)
+// cached is looked at for a full tile only.
+__device__ __forceinline__ void store_bf16x8(uint16_t *p, int64_t base, int off, int64_t n, bool full, const u32x4 &w,
+                                             bool cached = false)
 {
-    if (cached) {
-        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(out + base, 0, 0x7fffffff, 0x00027000);
-        __builtin_amdgcn_raw_buffer_store_b128(w, rsrc, off * (int)sizeof(uint16_t), 0, 1 | 16);    // sc0 sc1
-    } else {
-        __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(out + base + off));
+    if (full) {
+        if (cached) {
+            __builtin_amdgcn_raw_buffer_store_b128(w, bounded(p + base, 0x7fffffff), off * 2, 0, kThroughL2);
+        } else {
+            u32x4 *v = reinterpret_cast<u32x4 *>(p + base + off);
+            if (EQUARX_NT_STORE_BF16) {
+                __builtin_nontemporal_store(w, v);
+            } else {
+                *v = w;
+            }
+        }
+        return;
     }
+    const int left = left_of(n, base);
+    const int whole = left & ~1;
+    __builtin_amdgcn_raw_buffer_store_b128(w, bounded(p + base, whole * 2), off * 2, 0, EQUARX_NT_STORE_BF16 ? kNonTemporal : 0);
+    const bool holds = off <= whole && whole < off + 8;         // the lane with the last element of an odd length
+    const uint32_t last = off == whole ? w.x : off + 2 == whole ? w.y : off + 4 == whole ? w.z : w.w;
+    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)last, bounded(p + base, left * 2), holds ? whole * 2 : kNowhere, 0, 0);
 }
 
 // With all K tiles of a thread in one basic block the instruction scheduler
@@ -279,6 +307,7 @@ __device__ __forceinline__ void store_out_bf16x8(uint16_t *out, int64_t base, in
 // registers; the kernels want every request in flight before the first wait.
 __device__ __forceinline__ void loads_first()
 {
+    asm volatile("" ::: "memory");      // nor may a load move into a conditional block that uses it
 #if EQUARX_SCHED_BARRIER
     __builtin_amdgcn_sched_barrier(0);
 #endif
@@ -430,7 +459,7 @@ __device__ __forceinline__ void store_group_scales(float *scales, const float (&
     if ((threadIdx.x % G) == 0) {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const int64_t blk = (wg_at + k * tile_elems<T> + threadIdx.x * kLaneElems) / B;
+            const int64_t blk = (wg_at + k * tile_elems<T>) / B + threadIdx.x / G;
             if (kFull || blk < nb) scales[blk] = scale[k];
         }
     }
@@ -445,17 +474,17 @@ __device__ __forceinline__ void quantize_body(const uint16_t *__restrict__ x, in
 
     u32x4 xv[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) xv[k] = load_bf16x8(x, wg_at + k * tile_elems<T> + lane_at, n, kFull);
+    for (int k = 0; k < K; ++k) xv[k] = load_bf16x8(x, wg_at + k * tile_elems<T>, lane_at, n, kFull);
     loads_first();
 
     float scale[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
+        const int64_t base = wg_at + k * tile_elems<T>;
         float t[8];
         widen_bf16x8(xv[k], t);
         const u32x2 w = quantize_lane<G>(t, scale[k]);
-        store_i8x8<kStream>(codes, at, n, kFull, w);
+        store_i8x8<kStream>(codes, base, lane_at, n, kFull, w);
     }
     store_group_scales<B, T, K, kFull>(scales, scale, wg_at, nb);
 }
@@ -513,25 +542,25 @@ __device__ __forceinline__ void hop_body(const int8_t *cin, const float *sin, co
     float sv[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
-        xv[k] = load_bf16x8(x, at, n, kFull);
-        cv[k] = load_i8x8<kStream>(cin, at, n, kFull);
-        const int64_t blk = at / B;
-        sv[k] = (kFull || blk < nb) ? sin[blk] : 0.0f;
+        const int64_t base = wg_at + k * tile_elems<T>;
+        xv[k] = load_bf16x8(x, base, lane_at, n, kFull);
+        cv[k] = load_i8x8<kStream>(cin, base, lane_at, n, kFull);
+        const int64_t blk = base / B + lane_at / B;
+        sv[k] = sin[kFull || blk < nb ? blk : nb - 1];
     }
     loads_first();
 
     float scale[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
+        const int64_t base = wg_at + k * tile_elems<T>;
         float xf[8], qf[8], t[8];
         widen_bf16x8(xv[k], xf);
         widen_i8x8(cv[k], qf);
 #pragma unroll
         for (int i = 0; i < 8; ++i) t[i] = __builtin_fmaf(qf[i], sv[k], xf[i]);
         const u32x2 w = quantize_lane<G>(t, scale[k]);
-        store_i8x8<kStream>(cout, at, n, kFull, w);
+        store_i8x8<kStream>(cout, base, lane_at, n, kFull, w);
     }
     store_group_scales<B, T, K, kFull>(sout, scale, wg_at, nb);
 }
@@ -564,15 +593,15 @@ __device__ __forceinline__ void dequantize_body(const int8_t *__restrict__ codes
     float sv[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
-        cv[k] = load_i8x8<kStream>(codes, at, n, kFull);
-        const int64_t blk = at / B;
-        sv[k] = (kFull || blk < nb) ? scales[blk] : 0.0f;
+        const int64_t base = wg_at + k * tile_elems<T>;
+        cv[k] = load_i8x8<kStream>(codes, base, lane_at, n, kFull);
+        const int64_t blk = base / B + lane_at / B;
+        sv[k] = scales[kFull || blk < nb ? blk : nb - 1];
     }
 
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
+        const int64_t base = wg_at + k * tile_elems<T>;
         float qf[8];
         widen_i8x8(cv[k], qf);
         u32x4 w;
@@ -580,7 +609,7 @@ __device__ __forceinline__ void dequantize_body(const int8_t *__restrict__ codes
         w.y = narrow_bf16x2(qf[2] * sv[k], qf[3] * sv[k]);
         w.z = narrow_bf16x2(qf[4] * sv[k], qf[5] * sv[k]);
         w.w = narrow_bf16x2(qf[6] * sv[k], qf[7] * sv[k]);
-        store_bf16x8(out, at, n, kFull, w);
+        store_bf16x8(out, base, lane_at, n, kFull, w);
     }
 }
 
@@ -626,19 +655,19 @@ __device__ __forceinline__ void load_tiles(const uint16_t *p, int64_t wg_at, int
 {
     const int lane_at = threadIdx.x * kLaneElems;
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = load_bf16x8(p, wg_at + k * tile_elems<T> + lane_at, n, kFull);
+    for (int k = 0; k < K; ++k) v[k] = load_bf16x8(p, wg_at + k * tile_elems<T>, lane_at, n, kFull);
 }
 
 // Writes what the wire carries after a quantization of one tile (8 codes per
-// lane starting at element `at`): row `row` of the kept wire.
+// lane starting at element base + off): row `row` of the kept wire.
 template <int B, bool kFull>
 __device__ __forceinline__ void store_wire_tile(int8_t *__restrict__ wire_codes, float *__restrict__ wire_scales,
-                                                int64_t c_step, int64_t s_step, int row, int64_t at, int64_t n,
-                                                const float (&r)[8], float s)
+                                                int64_t c_step, int64_t s_step, int row, int64_t base, int off,
+                                                int64_t n, const float (&r)[8], float s)
 {
     constexpr int G = B / kLaneElems;
-    store_i8x8(wire_codes + (int64_t)row * c_step, at, n, kFull, pack_codes(r));
-    if ((threadIdx.x % G) == 0 && (kFull || at < n)) wire_scales[(int64_t)row * s_step + at / B] = s;
+    store_i8x8(wire_codes + (int64_t)row * c_step, base, off, n, kFull, pack_codes(r));
+    if ((threadIdx.x % G) == 0 && (kFull || base + off < n)) wire_scales[(int64_t)row * s_step + (base + off) / B] = s;
 }
 
 // out = bf16(v) for the 8 fp32 values of one lane.
@@ -651,11 +680,7 @@ __device__ __forceinline__ void store_narrowed_tile(uint16_t *out, int64_t base,
     w.y = narrow_bf16x2(v[2], v[3]);
     w.z = narrow_bf16x2(v[4], v[5]);
     w.w = narrow_bf16x2(v[6], v[7]);
-    if (kFull) {
-        store_out_bf16x8(out, base, off, cached, w);
-    } else {
-        store_bf16x8(out, base + off, n, false, w);
-    }
+    store_bf16x8(out, base, off, n, kFull, w, cached);
 }
 
 // The last step of a chain for one tile: quantize the finished fp32 sum once
@@ -670,7 +695,7 @@ __device__ __forceinline__ void finish_tile(const float (&t)[8], uint16_t *out,
     if (kAG) {
         float r[8], s;
         quantize_lane_f<G, true>(t, r, s);      // +0.0 codes: the product below shows the sign of a zero
-        if (kWire) store_wire_tile<B, kFull>(wire_codes, wire_scales, c_step, s_step, row, base + off, n, r, s);
+        if (kWire) store_wire_tile<B, kFull>(wire_codes, wire_scales, c_step, s_step, row, base, off, n, r, s);
         float d[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) d[j] = r[j] * s;
@@ -703,7 +728,7 @@ __device__ __forceinline__ void head_body(const uint16_t *__restrict__ x0, const
     float scale[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
+        const int64_t base = wg_at + k * tile_elems<T>;
         float t[8], r[8], xf[8], s0;
         widen_bf16x8(av[k], t);
         quantize_lane_f<G, false>(t, r, s0);        // a -0.0 code only flips the sign of a zero sum, which Q_B ignores
@@ -711,7 +736,7 @@ __device__ __forceinline__ void head_body(const uint16_t *__restrict__ x0, const
 #pragma unroll
         for (int j = 0; j < 8; ++j) t[j] = __builtin_fmaf(r[j], s0, xf[j]);
         const u32x2 w = quantize_lane<G>(t, scale[k]);
-        store_i8x8(cout, at, n, kFull, w);
+        store_i8x8(cout, base, lane_at, n, kFull, w);
     }
     store_group_scales<B, T, K, kFull>(sout, scale, wg_at, nb);
 }
@@ -744,11 +769,11 @@ __device__ __forceinline__ void tail_body(const int8_t *__restrict__ cin, const 
     float sv[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
-        xv[k] = load_bf16x8(x, at, n, kFull);
-        cv[k] = load_i8x8(cin, at, n, kFull);
-        const int64_t blk = at / B;
-        sv[k] = (kFull || blk < nb) ? sin[blk] : 0.0f;
+        const int64_t base = wg_at + k * tile_elems<T>;
+        xv[k] = load_bf16x8(x, base, lane_at, n, kFull);
+        cv[k] = load_i8x8(cin, base, lane_at, n, kFull);
+        const int64_t blk = base / B + lane_at / B;
+        sv[k] = sin[kFull || blk < nb ? blk : nb - 1];
     }
     loads_first();
 #pragma unroll
@@ -758,7 +783,7 @@ __device__ __forceinline__ void tail_body(const int8_t *__restrict__ cin, const 
         widen_i8x8(cv[k], qf);
 #pragma unroll
         for (int j = 0; j < 8; ++j) t[j] = __builtin_fmaf(qf[j], sv[k], xf[j]);
-        finish_tile<B, kAG, false, kFull>(t, out, nullptr, nullptr, 0, 0, 0, wg_at, k * tile_elems<T> + lane_at, n);
+        finish_tile<B, kAG, false, kFull>(t, out, nullptr, nullptr, 0, 0, 0, wg_at + k * tile_elems<T>, lane_at, n);
     }
 }
 
@@ -804,7 +829,7 @@ __device__ __forceinline__ void hop_tiles(float (&t)[K][8], const u32x4 (&x)[K],
             quantize_lane_f<G, kPositiveZero>(t[k], r, s);
             if (kWire) {
                 store_wire_tile<B, kFull>(wire_codes, wire_scales, c_step, s_step, row,
-                                          wg_at + k * tile_elems<T> + lane_at, n, r, s);
+                                          wg_at + k * tile_elems<T>, lane_at, n, r, s);
             }
             float xf[8];
             widen_bf16x8(x[k], xf);
@@ -850,7 +875,7 @@ __device__ __forceinline__ void chain_body(const PartialTable &tab, int P, int r
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         finish_tile<B, kAG, kWire, kFull>(t[k], out, wire_codes, wire_scales, c_step, s_step, P - 1,
-                                          wg_at, k * tile_elems<T> + lane_at, n, cached);
+                                          wg_at + k * tile_elems<T>, lane_at, n, cached);
     }
 }
 
@@ -870,7 +895,6 @@ __device__ __forceinline__ void chain_body_paired(const PartialTable &tab, int P
     constexpr int Gh = B / 16;                      // lanes per block
     constexpr int kPairElems = 2 * tile_elems<T>;      // 4096 elements per pair of pieces
     const int lane_off = (threadIdx.x / Gh) * B + (threadIdx.x % Gh) * kLaneElems;
-    const int64_t lane_at = wg_at + lane_off;
     float t[K2][2][8];
     u32x4 x0[K2][2], xv[K2][2];
 
@@ -880,7 +904,7 @@ __device__ __forceinline__ void chain_body_paired(const PartialTable &tab, int P
 #pragma unroll
         for (int k = 0; k < K2; ++k) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) x0[k][h] = load_bf16x8(p, lane_at + k * kPairElems + h * (B / 2), 0, true);
+            for (int h = 0; h < 2; ++h) x0[k][h] = load_bf16x8(p, wg_at + k * kPairElems, lane_off + h * (B / 2), 0, true);
         }
     }
 #pragma unroll
@@ -894,7 +918,7 @@ __device__ __forceinline__ void chain_body_paired(const PartialTable &tab, int P
 #pragma unroll
         for (int k = 0; k < K2; ++k) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) xv[k][h] = load_bf16x8(p, lane_at + k * kPairElems + h * (B / 2), 0, true);
+            for (int h = 0; h < 2; ++h) xv[k][h] = load_bf16x8(p, wg_at + k * kPairElems, lane_off + h * (B / 2), 0, true);
         }
 #pragma unroll
         for (int k = 0; k < K2; ++k) {
@@ -947,12 +971,12 @@ __device__ __forceinline__ void chain_body_paired(const PartialTable &tab, int P
                 float d[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) d[e] = (__builtin_rintf(t[k][h][e] * inv) + 0.0f) * s;
-                store_narrowed_tile<true>(out, wg_at, lane_off + k * kPairElems + h * (B / 2), 0, d, cached);
+                store_narrowed_tile<true>(out, wg_at + k * kPairElems, lane_off + h * (B / 2), 0, d, cached);
             }
         } else {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                store_narrowed_tile<true>(out, wg_at, lane_off + k * kPairElems + h * (B / 2), 0, t[k][h], cached);
+                store_narrowed_tile<true>(out, wg_at + k * kPairElems, lane_off + h * (B / 2), 0, t[k][h], cached);
             }
         }
     }
@@ -984,9 +1008,9 @@ __device__ __forceinline__ Span workgroup_span(int64_t n, int64_t shard_elems, i
 
 template <int B, int T, int K, bool kRS, bool kAG, bool kWire>
 __global__ __launch_bounds__(T) void chain_kernel(int P, int64_t n, int64_t shard_elems, uint16_t *out,
-                                                         int8_t *__restrict__ wire_codes,
-                                                         float *__restrict__ wire_scales, int64_t c_step,
-                                                         int64_t s_step, const PartialTable tab)
+                  int8_t *__restrict__ wire_codes,
+                  float *__restrict__ wire_scales, int64_t c_step,
+                  int64_t s_step, const PartialTable tab)
 {
     const Span sp = workgroup_span<T, K>(n, shard_elems, 1);     // shard k: devices k+1, k+2, ..., k
     if (!sp.any) return;                                      // uniform over the workgroup
@@ -1063,75 +1087,87 @@ __global__ __launch_bounds__(pass_threads(K)) void tail_ring_kernel(const int8_t
     }
 }
 
-// Small messages: the same chain, organised for latency instead of bandwidth.
-// With few tiles the bandwidth-shaped kernel leaves most compute units idle
-// and pays one memory round trip per hop.  Here a workgroup takes ONE tile and
-// requests the tiles of kSmallBatch partials at a time, two batches in flight
-// (one being consumed, one arriving), so a chain of P hops costs about P /
-// kSmallBatch round trips.  Every load is unconditional -- positions past the
-// last partial re-read the last partial and are ignored -- because a load
-// behind a condition makes the compiler wait for all outstanding loads where
-// the paths join.
-constexpr int kSmallBatch = 8;
-
-template <int B, bool kWire, bool kFull>
-__device__ __forceinline__ void chain_small_body(const PartialTable &tab, int P, int64_t n,
-                                                 uint16_t *out, int8_t *__restrict__ wire_codes,
-                                                 float *__restrict__ wire_scales, int64_t c_step, int64_t s_step,
-                                                 int64_t wg_at)
+// Small messages: the same flavours, organised for latency instead of bandwidth.
+// With few tiles the bandwidth-shaped kernels leave most compute units idle
+// and pay one memory round trip per hop.  Here a workgroup takes ONE tile and
+// requests the tiles of N partials at once, so a chain of up to N partials
+// costs one round trip (a longer one ceil(P / N)).  Every load is
+// unconditional -- positions past the last one repeat it and are ignored --
+// because a load behind a condition makes the compiler wait for all
+// outstanding loads where the paths join.
+// What bounds it then is the chain of quantizations, 0.18 us per hop.
+//
+// The full loop (kSemi = false) takes position i at step i.  The semi-loop
+// takes the owner at step 0, positions h+1 .. P-1 at steps 1 .. na = P-1-h and
+// positions h .. 1 at the steps after that: at step i > na that is P - i.
+template <int B, int N, bool kMany, bool kSemi, bool kRS, bool kAG, bool kWire, bool kFull>
+__device__ __forceinline__ void small_body(const PartialTable &tab, int P, int rot, int64_t n, uint16_t *out,
+                                           int8_t *__restrict__ wire_codes, float *__restrict__ wire_scales,
+                                           int64_t c_step, int64_t s_step, int64_t wg_at)
 {
-    constexpr int D = kSmallBatch;
+    constexpr int T = kThreads, G = B / kLaneElems;
     const int lane_at = threadIdx.x * kLaneElems;
-    float t[1][8];
-    u32x4 a[D][1], b[D][1];
+    const int h = P / 2, na = kSemi ? P - 1 - h : 0;
+    float t[1][8], own[8];
+    u32x4 x[N][1];
 
+    for (int base = 0; base < P; base += N) {        // once, unless kMany
 #pragma unroll
-    for (int d = 0; d < D; ++d) load_tiles<kThreads, 1, kFull>(tab.x[d < P ? d : P - 1], wg_at, n, a[d]);
-
-    for (int base = 0; base < P; base += 2 * D) {
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const int i = base + D + d;
-            load_tiles<kThreads, 1, kFull>(tab.x[i < P ? i : P - 1], wg_at, n, b[d]);
-        }
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const int i = base + d;
-            if (i == 0) {
-                widen_bf16x8(a[0][0], t[0]);
-            } else if (i < P) {
-                hop_tiles<B, kThreads, 1, true, kWire, false, kFull>(t, a[d], wire_codes, wire_scales, c_step, s_step, i - 1,
-                                                           wg_at, n);
+        for (int u = 0; u < N; ++u) {
+            // The table repeats after P entries, so a position may run past P (rot <= P <= N, unless kMany).
+            int j = rot + base + u;
+            if (kMany) {
+                const int i = base + u < P ? base + u : P - 1;
+                j = rot + (!kSemi || i == 0 ? i : i <= na ? h + i : P - i);
+                if (j >= P) j -= P;
+            } else if (kSemi && u > 0) {
+                j = u <= na ? rot + h + u : rot + 2 * P - u;
+                if (j < 0) j = 0;               // u past 2 P: a repeat like any other
             }
+            load_tiles<T, 1, kFull>(tab.x[j], wg_at, n, x[u]);
         }
+        loads_first();
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const int i = base + 2 * D + d;
-            load_tiles<kThreads, 1, kFull>(tab.x[i < P ? i : P - 1], wg_at, n, a[d]);
-        }
+        for (int u = 0; u < N; ++u) {
+            const int i = base + u;
+            if (i >= P) break;                                      // uniform, as every condition here
+            if (i == 0) {
+                if (kSemi) {
+                    widen_bf16x8(x[0][0], own);
+                } else {
+                    widen_bf16x8(x[0][0], t[0]);
+                }
+                continue;
+            }
+            if (kSemi && (i == 1 || i == na + 1)) {
+                widen_bf16x8(x[u][0], t[0]);                        // a half chain starts
+            } else {
+                hop_tiles<B, T, 1, kRS, kWire, !kAG, kFull>(t, x[u], wire_codes, wire_scales, c_step, s_step, i - 1, wg_at, n);
+            }
+            if (kSemi && (i == na || i == P - 1)) {                 // ... and ends at the owner
+                float r[8], s;
+                quantize_lane_f<G, !kAG>(t[0], r, s);
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const int i = base + D + d;
-            if (i < P) {
-                hop_tiles<B, kThreads, 1, true, kWire, false, kFull>(t, b[d], wire_codes, wire_scales, c_step, s_step, i - 1,
-                                                           wg_at, n);
+                for (int e = 0; e < 8; ++e) own[e] = __builtin_fmaf(r[e], s, own[e]);
             }
         }
     }
-    finish_tile<B, true, kWire, kFull>(t[0], out, wire_codes, wire_scales, c_step, s_step, P - 1, wg_at, lane_at, n);
+    finish_tile<B, kAG, kWire, kFull>(kSemi ? own : t[0], out, wire_codes, wire_scales, c_step, s_step, P - 1, wg_at,
+                                      lane_at, n);
 }
 
-template <int B, bool kWire>
-__global__ __launch_bounds__(kThreads) void chain_small_kernel(int P, int64_t n, uint16_t *out,
-                                                               int8_t *__restrict__ wire_codes,
-                                                               float *__restrict__ wire_scales, int64_t c_step,
-                                                               int64_t s_step, const PartialTable tab)
+template <int B, int N, bool kMany, bool kSemi, bool kRS, bool kAG, bool kWire>
+__global__ __launch_bounds__(kThreads) void small_kernel(int P, int64_t n, int64_t shard_elems, uint16_t *out,
+                                                         int8_t *__restrict__ wire_codes,
+                                                         float *__restrict__ wire_scales, int64_t c_step,
+                                                         int64_t s_step, const PartialTable tab)
 {
-    const int64_t wg_at = (int64_t)blockIdx.x * tile_elems<kThreads>;
-    if (wg_at + tile_elems<kThreads> <= n) {
-        chain_small_body<B, kWire, true>(tab, P, n, out, wire_codes, wire_scales, c_step, s_step, wg_at);
+    const Span sp = workgroup_span<kThreads, 1>(n, shard_elems, kSemi ? 0 : 1);
+    if (!sp.any) return;
+    if (sp.wg_at + tile_elems<kThreads> <= sp.hi) {
+        small_body<B, N, kMany, kSemi, kRS, kAG, kWire, true>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step, s_step, sp.wg_at);
     } else {
-        chain_small_body<B, kWire, false>(tab, P, n, out, wire_codes, wire_scales, c_step, s_step, wg_at);
+        small_body<B, N, kMany, kSemi, kRS, kAG, kWire, false>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step, s_step, sp.wg_at);
     }
 }
 
@@ -1181,7 +1217,7 @@ __device__ __forceinline__ void semi_body(const PartialTable &tab, int P, int ro
 
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        finish_tile<B, kAG, false, kFull>(own[k], out, nullptr, nullptr, 0, 0, 0, wg_at, k * tile_elems<T> + lane_at, n,
+        finish_tile<B, kAG, false, kFull>(own[k], out, nullptr, nullptr, 0, 0, 0, wg_at + k * tile_elems<T>, lane_at, n,
                                           cached);
     }
 }
@@ -1215,9 +1251,9 @@ struct WireTable {
 // U received wires are requested at a time.  A wide launch has enough waves to cover the wait for one (U = 1: 36.1 us
 // for seven wires of 22 M elements on MI355X, 42.0 with U = 2, whose requests only queue); a narrow one has a wave or
 // two per SIMD, and asking for the next wire only when the last one has been added leaves it waiting R times over:
-// seven wires of 50 k elements 9.4 us with 256 threads x 4 tiles and U = 1, 4.1 with 256 x 1 and U = 8; of 2.75 M
-// 8.9 -> 7.7.  U = 2 for up to two wires (one wire of 50 k: 2.4 us, 2.9 with U = 4, 3.9 with U = 8), 4 for up to
-// four (three of 1.5 M: 4.4 us, 5.2 with U = 8).  Requests past the last wire repeat it and are ignored, so that no
+// seven wires of 50 k elements 9.4 us with 256 threads x 4 tiles and U = 1, 3.1 with 256 x 1 and U = 8; of 2.75 M
+// 8.9 -> 6.1.  U = 2 for up to two wires (one wire of 50 k: 2.4 us, 2.9 with U = 4, 3.9 with U = 8), 4 for up to
+// four (three of 1.5 M: 3.6 us, 5.2 with U = 8).  Requests past the last wire repeat it and are ignored, so that no
 // load is behind a condition.
 template <int B, int K, int U, bool kOutBf16, bool kOutWire, bool kAG, bool kFull, bool kStream = false>
 __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable &tab, int R, int64_t n,
@@ -1242,12 +1278,13 @@ __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable
             const float *sc = tab.scales[r];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                const int64_t at = wg_at + k * tile_elems<T> + lane_at;
-                cv[u][k] = load_i8x8<kStream>(c, at, n, kFull);
-                const int64_t blk = at / B;
-                sv[u][k] = (kFull || blk < nb) ? sc[blk] : 0.0f;
+                const int64_t base = wg_at + k * tile_elems<T>;
+                cv[u][k] = load_i8x8<kStream>(c, base, lane_at, n, kFull);
+                const int64_t blk = base / B + lane_at / B;
+                sv[u][k] = sc[kFull || blk < nb ? blk : nb - 1];
             }
         }
+        if (U > 1) loads_first();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (r0 + u >= R) break;             // uniform
@@ -1263,22 +1300,22 @@ __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable
 
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
+        const int64_t base = wg_at + k * tile_elems<T>;
         if (!kAG) {                 // all-gather left unquantized (the semi-loop's owner, Sec. 3.3/3.4): no wire out
-            store_narrowed_tile<kFull>(out, wg_at, k * tile_elems<T> + lane_at, n, acc[k]);
+            store_narrowed_tile<kFull>(out, base, lane_at, n, acc[k]);
             continue;
         }
         float q[8], s;
         quantize_lane_f<G, true>(acc[k], q, s);
         if (kOutWire) {
-            store_i8x8<kStream>(codes_out, at, n, kFull, pack_codes(q));
-            if ((threadIdx.x % G) == 0 && (kFull || at < n)) scales_out[at / B] = s;
+            store_i8x8<kStream>(codes_out, base, lane_at, n, kFull, pack_codes(q));
+            if ((threadIdx.x % G) == 0 && (kFull || base + lane_at < n)) scales_out[base / B + lane_at / B] = s;
         }
         if (kOutBf16) {
             float d[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) d[j] = q[j] * s;
-            store_narrowed_tile<kFull>(out, wg_at, k * tile_elems<T> + lane_at, n, d);
+            store_narrowed_tile<kFull>(out, base, lane_at, n, d);
         }
     }
 }
@@ -1292,7 +1329,7 @@ __global__ __launch_bounds__(pass_threads(K)) void flat_kernel(const uint16_t *l
     if (wg_at + tile_elems<pass_threads(K)> * K <= n) {
         flat_body<B, K, U, kOutBf16, kOutWire, kAG, true, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
     } else {
-        flat_body<B, K, U, kOutBf16, kOutWire, kAG, false, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
+        flat_body<B, K, (U > 2 ? 2 : U), kOutBf16, kOutWire, kAG, false, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
     }
 }
 

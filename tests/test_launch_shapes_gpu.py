@@ -114,3 +114,55 @@ def test_flat_batches_of_received_wires(gpu, oracle, values, n, R):  # noqa: F81
     c, s = torch.empty(n, dtype=torch.int8, device="cuda"), torch.empty(eq.num_blocks(n, B), device="cuda")
     eq.equarx_reduce_flat(gpu.dev_bf16(local), dev[:R], dev[R:], B, got, c, s)
     assert (gpu.host_u16(got) == out).all() and (c.cpu().numpy() == wc).all() and (_bits(s) == ws.view(np.uint32)).all()
+
+
+SMALL = 768 * 2048              # single-launch calls of few partials: up to here the batched kernel
+ALL_SINGLE = SINGLE + (eq.SEMI_LOOP | eq.RING_ORDER, eq.AG_UNQUANTIZED | eq.RING_ORDER, eq.RS_UNQUANTIZED)
+
+
+@pytest.mark.parametrize("flags", ALL_SINGLE)
+@pytest.mark.parametrize("P", (3, 4, 5, 7, 8, 9, 15, 16, 17, 64))
+def test_small_kernel_batches(gpu, oracle, P, flags):  # noqa: F811
+    """Batches of 8 and 16 partials, one that loops, and what stays below or above them; odd and even lengths."""
+    rng = np.random.default_rng(P + flags)
+    for n, B in ((2048 * 33 + 9, 64), (2048 * 34, 512), (2048 * 40 + 6, 32), (5, 32)):
+        x = [gpu.bf16_of(rng.standard_normal(n, dtype=np.float32)) for _ in range(P)]
+        assert (gpu.gpu_variant(x, B, flags) == _oracle_variant(oracle, x, B, flags)).all(), (n, B)
+        if flags == 0:
+            want, wc, ws = oracle.reduce_chain(x, B, keep_wire=True)
+            got, c, s = gpu.gpu_chain_fused(x, B)
+            assert (got == want).all() and (c == wc).all() and (s.view(np.uint32) == ws.view(np.uint32)).all(), (n, B)
+
+
+@pytest.mark.parametrize("n", (SMALL, SMALL + 1))
+@pytest.mark.parametrize("flags", (0, eq.SEMI_LOOP | eq.RING_ORDER))
+def test_single_launch_around_the_small_limit(gpu, oracle, values, n, flags):  # noqa: F811
+    x = [values[i % 4][:n] for i in range(6)]
+    assert (gpu.gpu_variant(x, 128, flags) == _oracle_variant(oracle, x, 128, flags)).all()
+
+
+@pytest.mark.parametrize("tail", range(1, 17))
+def test_ends_of_odd_length(gpu, oracle, tail):  # noqa: F811
+    """Every remainder of the last words, at the end of a lane, a wave and a tile; nothing past the end is written."""
+    rng = np.random.default_rng(tail)
+    for n in (tail, 512 - 8 + tail, 2048 - 16 + tail, 2048 * 3 + tail):
+        x = [gpu.bf16_of(rng.standard_normal(n, dtype=np.float32)) for _ in range(3)]
+        dev = [gpu.dev_bf16(p) for p in x]
+        room = n + 32
+        nb = eq.num_blocks(n, 32)
+        want, wc, ws = oracle.reduce_chain(x, 32, keep_wire=True)
+        codes = torch.full((2, -(-room // 16) * 16), 77, dtype=torch.int8, device="cuda")
+        scales = torch.full((2, -(-(nb + 8) // 4) * 4), -5.0, device="cuda")
+        eq.equarx_quantize(dev[0], 32, codes[0], scales[0])
+        eq.equarx_reduce_stage(codes[0], scales[0], dev[1], 32, codes[1], scales[1])
+        eq.equarx_reduce_stage(codes[1], scales[1], dev[2], 32, codes[1], scales[1])        # in place
+        assert (codes[0, :n].cpu().numpy() == wc[0]).all() and (codes[1, :n].cpu().numpy() == wc[2]).all(), n
+        assert (_bits(scales[0, :nb]) == ws[0].view(np.uint32)).all() and (_bits(scales[1, :nb]) == ws[2].view(np.uint32)).all()
+        assert (codes[:, n:] == 77).all() and (scales[:, nb:] == -5.0).all(), n
+        twice = oracle.reduce_chain(x + x, 32)
+        for expected, run in ((want, lambda o: eq.equarx_reduce_fused(dev, 32, o)),
+                              (twice, lambda o: eq.equarx_reduce_fused(dev + dev, 32, o)),
+                              (want, lambda o: eq.equarx_dequantize(codes[1, :n], scales[1, :nb], 32, o))):
+            out = torch.full((room,), 3.0, dtype=torch.bfloat16, device="cuda")
+            run(out)
+            assert (gpu.host_u16(out[:n]) == expected).all() and (out[n:] == 3.0).all(), n
