@@ -150,8 +150,9 @@ inline bool small_semi(int64_t n, int P) { return n <= kSmallElems && n > kSmall
 //             chain that writes its wire out: every hop stores there, 29.7 us with 256 x 4, 31.0 with 512 x 2, 28.2
 //             with 1024 x 1 at 6 M elements;
 //   1024 x 1  above: sixteen waves walk one 16 KiB piece of every partial together, each with a single load in flight;
-//   256 x 4   for the chain from 21 M elements on, where two pieces of a block per lane (chain_body_paired) save
-//             arithmetic that 1024 x 1 has to spend; the semi-loop, with its two sums per element, stays at 1024 x 1.
+//   256 x 4   for the chain from 21 M elements on, two waves per SIMD (chain_waves); two pieces of a block per lane
+//             (chain_body_paired) save arithmetic that 1024 x 1 has to spend.  The semi-loop, with its two sums per
+//             element, stays at 1024 x 1 (22 M elements: 61.3 us, 78.5 with 256 x 4 held to two waves).
 // Measured on MI355X, us, P = 8, block 256 (semi-loop: P = 7, block 64):
 //     elements      256 x 4   512 x 2   1024 x 1     semi-loop: 256 x 2   512 x 2   1024 x 1
 //     5.0 M           18.1      15.5      17.9                     14.3      14.2      16.1
@@ -162,8 +163,9 @@ inline bool small_semi(int64_t n, int P) { return n <= kSmallElems && n > kSmall
 //     12.5 M          36.4      36.4      35.2                     33.2      32.5      31.6
 //     16 M            45.4      45.1      44.1                     42.3      40.4      39.9
 //     20 M            58.4      56.7      54.9                     52.0      50.1      49.3
-//     22 M            60.7      61.4      61.2                     58.0      54.8      55.3
-//     33.5 M          91.6      93.9      92.2                     85.2      83.1      81.9
+//     22 M            60.8      61.4      61.2                     58.0      54.8      55.3
+//     33.5 M          90.0      93.9      92.2                     85.2      83.1      81.9
+//     88 M           247.5       264       262
 constexpr int64_t kOneWideRound = (int64_t)768 * Shape<512, 2>::kElems;
 constexpr int64_t kPairedFrom = (int64_t)2560 * Shape<1024, 1>::kElems;
 

@@ -849,7 +849,7 @@ __device__ __forceinline__ void hop_tiles(float (&t)[K][8], const u32x4 (&x)[K],
 // loads its partial and then computes; the quantization of the running sum
 // does not need the new data and runs while it arrives.  Starting the loads a
 // hop (or several) ahead was measured and is SLOWER on MI355X (63 -> 67..72 us
-// at the 27B-shaped size): with three waves per SIMD and four 16-byte loads
+// at the 27B-shaped size): with two waves per SIMD and four 16-byte loads
 // per lane in flight the memory system is already saturated, and more
 // outstanding requests only lengthen its queues.
 template <int B, int T, int K, bool kRS, bool kAG, bool kWire, bool kFull>
@@ -1006,8 +1006,16 @@ __device__ __forceinline__ Span workgroup_span(int64_t n, int64_t shard_elems, i
     return sp;
 }
 
+// Waves per SIMD the compiler may plan for.  The shape for the largest messages is held to two, of the five its
+// registers would allow: eight tiles of one partial after the other are enough requests in flight, and the fewer
+// places of memory are read at once the better they stream.  Measured on MI355X, P = 8, us with five / four / three /
+// two / one: 255.9 / 258.2 / 258.8 / 247.5 / 332 at 88 M elements, 93.7 / 91.0 / 91.9 / 90.0 / 139 at 33.5 M; 6 tiles
+// or 512 threads under the same cap 264 at 88 M, 3 tiles 264, 8 tiles and one wave 252.
+constexpr int chain_waves(int K) { return K == 4 ? 2 : 8; }
+
 template <int B, int T, int K, bool kRS, bool kAG, bool kWire>
-__global__ __launch_bounds__(T) void chain_kernel(int P, int64_t n, int64_t shard_elems, uint16_t *out,
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(1, chain_waves(K))))
+void chain_kernel(int P, int64_t n, int64_t shard_elems, uint16_t *out,
                   int8_t *__restrict__ wire_codes,
                   float *__restrict__ wire_scales, int64_t c_step,
                   int64_t s_step, const PartialTable tab)
