@@ -454,11 +454,30 @@ inline unsigned strided_grid(int64_t n, int32_t chunks)
 
 #define EQUARX_DISPATCH_CHUNKS(chunks, CALL) \
     switch (chunks) {                        \
-        case 32: CALL(32 / kChunkGroups); break;   \
-        case 64: CALL(64 / kChunkGroups); break;   \
-        case 128: CALL(128 / kChunkGroups); break; \
+        case 32: CALL(32); break;            \
+        case 64: CALL(64); break;            \
+        case 128: CALL(128); break;          \
         default: break;                      \
     }
+
+// Messages of up to this many minishards take the small layouts of equarx_strided.hpp, whose waves have a quarter or an
+// eighth of the work: with more minishards than that every CU is busy, and the larger layouts do less work in all.
+// Measured on MI355X, us, large -> small layout, by minishards of 64 chunks:
+//                            1               4               16              32
+//     chain, P = 8       10.6 -> 5.6     12.1 -> 7.3     12.9 -> 8.7     13.5 -> 14.4
+//     hops, P = 4        14.9 -> 12.9    16.7 -> 14.4    19.3 -> 16.6    21.5 -> 21.2
+//     semi-loop, P = 6   14.7 -> 12.0    16.9 -> 14.2    18.8 -> 17.4    20.8 -> 23.5
+// (32 chunks, 16 minishards: chain 10.0 -> 7.1, hops 16.8 -> 14.4; 128 chunks: 14.5 -> 14.3, 25.6 -> 20.6).
+constexpr int64_t kStridedSmall = 16;
+// Between the two, for 64 chunks: half the work per wave (chain, 24 minishards 13.3 -> 10.1, 32 13.5 -> 10.9, 48 14.7 -> 15.3).
+constexpr int64_t kStridedMedium = 32;
+
+inline bool strided_small(int64_t n, int32_t chunks) { return n / ((int64_t)kChunk * chunks) <= kStridedSmall; }
+
+inline unsigned strided_small_grid(int64_t n, int32_t chunks)       // of the per-pass kernels
+{
+    return (unsigned)(n / ((int64_t)kChunk * chunks) * wave_layout_wgs<4, 8>);
+}
 
 // One tensor as the source of a per-pass strided kernel.
 inline StridedSource one_tensor(const void *x)
@@ -486,7 +505,15 @@ inline StridedSource chain_source(const PartialTable &tab, int P, int per_shard,
 
 void do_quantize_strided(const StridedSource &src, int64_t n, int32_t chunks, int8_t *codes, float *scales, LaunchCtx &ctx)
 {
-#define CALL(RR) ctx.launch(quantize_strided_kernel<RR>, strided_grid(n, chunks), kThreads, codes, scales, src)
+    if (strided_small(n, chunks)) {
+#define CALL(CC)                                                                                                        \
+    ctx.launch(pass_strided_small_kernel<CC / 32, false>, strided_small_grid(n, chunks), kThreads, nullptr, nullptr, codes, \
+               scales, src)
+        EQUARX_DISPATCH_CHUNKS(chunks, CALL)
+#undef CALL
+        return;
+    }
+#define CALL(CC) ctx.launch(quantize_strided_kernel<CC / kChunkGroups>, strided_grid(n, chunks), kThreads, codes, scales, src)
     EQUARX_DISPATCH_CHUNKS(chunks, CALL)
 #undef CALL
 }
@@ -494,7 +521,30 @@ void do_quantize_strided(const StridedSource &src, int64_t n, int32_t chunks, in
 void do_hop_strided(const int8_t *cin, const float *sin, const StridedSource &src, int64_t n, int32_t chunks, int8_t *cout,
                     float *sout, LaunchCtx &ctx)
 {
-#define CALL(RR) ctx.launch(hop_strided_kernel<RR>, strided_grid(n, chunks), kThreads, cin, sin, cout, sout, src)
+    if (strided_small(n, chunks)) {
+#define CALL(CC) \
+    ctx.launch(pass_strided_small_kernel<CC / 32, true>, strided_small_grid(n, chunks), kThreads, cin, sin, cout, sout, src)
+        EQUARX_DISPATCH_CHUNKS(chunks, CALL)
+#undef CALL
+        return;
+    }
+#define CALL(CC) ctx.launch(hop_strided_kernel<CC / kChunkGroups>, strided_grid(n, chunks), kThreads, cin, sin, cout, sout, src)
+    EQUARX_DISPATCH_CHUNKS(chunks, CALL)
+#undef CALL
+}
+
+void do_semi_step_strided(const StridedDirections &dirs, const PartialTable &tab, int P, int per_shard, int64_t n,
+                          int32_t chunks, LaunchCtx &ctx)
+{
+    if (strided_small(n, chunks)) {
+#define CALL(CC)                                                                                                      \
+    ctx.launch2d(semi_step_strided_small_kernel<CC / 32>, strided_small_grid(n, chunks), 2u, kThreads, P, per_shard, dirs, tab)
+        EQUARX_DISPATCH_CHUNKS(chunks, CALL)
+#undef CALL
+        return;
+    }
+#define CALL(CC)                                                                                                      \
+    ctx.launch2d(semi_step_strided_kernel<CC / kChunkGroups>, strided_grid(n, chunks), 2u, kThreads, P, per_shard, dirs, tab)
     EQUARX_DISPATCH_CHUNKS(chunks, CALL)
 #undef CALL
 }
@@ -502,38 +552,61 @@ void do_hop_strided(const int8_t *cin, const float *sin, const StridedSource &sr
 void do_owner_strided(const StridedSource &own, const StridedWires &wires, int received, int64_t n, int32_t chunks, bool ag,
                       uint16_t *out, LaunchCtx &ctx)
 {
-#define CALL(RR)                                                                                                           \
+    if (strided_small(n, chunks)) {
+#define CALL(CC)                                                                                                           \
     do {                                                                                                                   \
-        if (ag) ctx.launch(owner_strided_kernel<RR, true>, strided_grid(n, chunks), kThreads, received, out, wires, own);  \
-        else ctx.launch(owner_strided_kernel<RR, false>, strided_grid(n, chunks), kThreads, received, out, wires, own);    \
+        const unsigned grid = strided_small_grid(n, chunks);                                                               \
+        if (ag) ctx.launch(owner_strided_small_kernel<CC / 32, true>, grid, kThreads, received, out, wires, own);          \
+        else ctx.launch(owner_strided_small_kernel<CC / 32, false>, grid, kThreads, received, out, wires, own);            \
+    } while (0)
+        EQUARX_DISPATCH_CHUNKS(chunks, CALL)
+#undef CALL
+        return;
+    }
+#define CALL(CC)                                                                                                           \
+    do {                                                                                                                   \
+        const unsigned grid = strided_grid(n, chunks);                                                                     \
+        if (ag) ctx.launch(owner_strided_kernel<CC / kChunkGroups, true>, grid, kThreads, received, out, wires, own);      \
+        else ctx.launch(owner_strided_kernel<CC / kChunkGroups, false>, grid, kThreads, received, out, wires, own);        \
     } while (0)
     EQUARX_DISPATCH_CHUNKS(chunks, CALL)
 #undef CALL
 }
 
-// The single-launch chain and its flavours: chunks = 8 * W * R (see chain_strided_kernel), 4 * W workgroups per minishard.
-template <int R, int W>
-void launch_chain_strided_as(const PartialTable &tab, int P, unsigned grid, int per_shard, bool semi, bool rs, bool ag,
+// The single-launch chain and its flavours: chunks = 8 * W * R (see chain_strided_kernel).
+template <int R, int W, int V>
+void launch_chain_strided_as(const PartialTable &tab, int P, int64_t minishards, int per_shard, bool semi, bool rs, bool ag,
                              uint16_t *out, LaunchCtx &ctx)
 {
-    if (semi && ag) ctx.launch(chain_strided_kernel<R, W, true, true, true>, grid, kThreads, P, per_shard, out, tab);
-    else if (semi) ctx.launch(chain_strided_kernel<R, W, true, true, false>, grid, kThreads, P, per_shard, out, tab);
-    else if (rs && ag) ctx.launch(chain_strided_kernel<R, W, false, true, true>, grid, kThreads, P, per_shard, out, tab);
-    else if (rs) ctx.launch(chain_strided_kernel<R, W, false, true, false>, grid, kThreads, P, per_shard, out, tab);
-    else ctx.launch(chain_strided_kernel<R, W, false, false, true>, grid, kThreads, P, per_shard, out, tab);
+    const unsigned grid = (unsigned)(minishards * wave_layout_wgs<W, V>);
+    if (semi && ag) ctx.launch(chain_strided_kernel<R, W, V, true, true, true>, grid, kThreads, P, per_shard, out, tab);
+    else if (semi) ctx.launch(chain_strided_kernel<R, W, V, true, true, false>, grid, kThreads, P, per_shard, out, tab);
+    else if (rs && ag) ctx.launch(chain_strided_kernel<R, W, V, false, true, true>, grid, kThreads, P, per_shard, out, tab);
+    else if (rs) ctx.launch(chain_strided_kernel<R, W, V, false, true, false>, grid, kThreads, P, per_shard, out, tab);
+    else ctx.launch(chain_strided_kernel<R, W, V, false, false, true>, grid, kThreads, P, per_shard, out, tab);
 }
 
 // ring: shards of ceil(minishards / P) whole minishards, shard k in the order a ring gives it.
 void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chunks, bool semi, bool rs, bool ag,
                           bool ring, uint16_t *out, LaunchCtx &ctx)
 {
-    const int64_t minishards = n / ((int64_t)kChunk * chunks);
-    const int per_shard = ring ? (int)((minishards + P - 1) / P) : 0;
-    const unsigned ms = (unsigned)minishards;
+    const int64_t ms = n / ((int64_t)kChunk * chunks);
+    const int per_shard = ring ? (int)((ms + P - 1) / P) : 0;
+    const bool small = strided_small(n, chunks);
     switch (chunks) {
-        case 32: launch_chain_strided_as<4, 1>(tab, P, ms * 4, per_shard, semi, rs, ag, out, ctx); break;
-        case 64: launch_chain_strided_as<8, 1>(tab, P, ms * 4, per_shard, semi, rs, ag, out, ctx); break;
-        case 128: launch_chain_strided_as<8, 2>(tab, P, ms * 8, per_shard, semi, rs, ag, out, ctx); break;
+        case 32:
+            if (small) launch_chain_strided_as<1, 4, 4>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
+            else launch_chain_strided_as<4, 1, 8>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
+            break;
+        case 64:
+            if (small) launch_chain_strided_as<2, 4, 4>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
+            else if (ms <= kStridedMedium) launch_chain_strided_as<4, 2, 4>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
+            else launch_chain_strided_as<8, 1, 8>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
+            break;
+        case 128:
+            if (small) launch_chain_strided_as<4, 4, 4>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
+            else launch_chain_strided_as<8, 2, 8>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
+            break;
         default: break;
     }
 }
@@ -1193,9 +1266,7 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
         dirs.d[0] = {h + 1 + t, t ? c[0] : nullptr, t ? s[0] : nullptr, c[0], s[0]};
         dirs.d[1] = {h - t, t ? c[1] : nullptr, t ? s[1] : nullptr, c[1], s[1]};
         if (t < na) {
-#define CALL(RR) ctx.launch2d(semi_step_strided_kernel<RR>, strided_grid(n, chunks), 2u, kThreads, (int)P, per_shard, dirs, tab)
-            EQUARX_DISPATCH_CHUNKS(chunks, CALL)
-#undef CALL
+            do_semi_step_strided(dirs, tab, P, per_shard, n, chunks, ctx);
         } else if (t == 0) {
             do_quantize_strided(around(h), n, chunks, c[1], s[1], ctx);
         } else {

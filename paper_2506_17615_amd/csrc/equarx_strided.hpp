@@ -97,10 +97,11 @@ __device__ __forceinline__ void across_chunks_max(uint32_t (&m)[8], uint32_t (*r
     }
 }
 
-__device__ __forceinline__ void note_absmax(const float (&t)[8], uint32_t (&m)[8])
+template <int V>
+__device__ __forceinline__ void note_absmax(const float (&t)[V], uint32_t (&m)[V])
 {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) m[j] = umax(m[j], __float_as_uint(t[j]) & 0x7FFFFFFFu);
+    for (int j = 0; j < V; ++j) m[j] = umax(m[j], __float_as_uint(t[j]) & 0x7FFFFFFFu);
 }
 
 __device__ __forceinline__ u32x2 scale_and_pack(const float (&t)[8], const float (&inv)[8])
@@ -357,26 +358,35 @@ __global__ __launch_bounds__(kThreads) void owner_strided_kernel(int received, u
 // send also separates this send's reads from the writes of the one after).
 // Same operations in the same order as the hop-by-hop strided chain, hence
 // the same bits.
+//
+// A message of few minishards is bound by the time one wave takes per send,
+// not by memory: W = 4 waves share a piece and a lane has V = 4 positions
+// instead of 8, so a wave has an eighth of the rows and quotients and a
+// minishard 32 workgroups instead of 4 (one minishard of 64 chunks, P = 8:
+// 10.6 -> 5.6 us on MI355X).
 
 struct WaveSpot {
     int64_t minishard;  // which minishard the workgroup works on
     int64_t elem;       // first element of the lane in the first of its chunks
     int64_t scale;      // index of the lane's first scale
     int64_t row_step;   // elements between two consecutive chunks of the lane
-    bool first_group;   // the lane stores the scales of its 8 positions
+    bool first_group;   // the lane stores the scales of its positions
 };
 
-// W waves per position piece; a 256-thread workgroup covers (4 / W) * 64 positions: 4 * W workgroups per minishard.
-template <int W>
+// W waves per position piece, V positions per lane; a 256-thread workgroup covers (4 / W) * 8 V positions.
+template <int W, int V>
+constexpr int wave_layout_wgs = kChunk / ((kThreads / 64) / W * 8 * V);      // workgroups per minishard
+
+template <int W, int V>
 __device__ __forceinline__ WaveSpot wave_spot(int chunks)
 {
-    static_assert(W == 1 || W == 2, "waves per position piece");
+    static_assert((W == 1 || W == 2 || W == 4) && (V == 4 || V == 8), "waves per position piece, positions per lane");
     constexpr int kPieces = (kThreads / 64) / W;                // position pieces per workgroup
-    constexpr int kPerChunk = kChunk / (kPieces * 64);          // workgroups per minishard
+    constexpr int kPerChunk = wave_layout_wgs<W, V>;
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const int g = (wave % W) * 8 + lane / 8;                    // chunk group, 0 .. 8W-1
     const int64_t ms = blockIdx.x / kPerChunk;
-    const int pos = (blockIdx.x % kPerChunk) * (kPieces * 64) + (wave / W) * 64 + (lane % 8) * kLaneElems;
+    const int pos = (blockIdx.x % kPerChunk) * (kPieces * 8 * V) + (wave / W) * (8 * V) + (lane % 8) * V;
     WaveSpot sp;
     sp.minishard = ms;
     sp.elem = ms * ((int64_t)kChunk * chunks) + (int64_t)g * kChunk + pos;
@@ -386,15 +396,26 @@ __device__ __forceinline__ WaveSpot wave_spot(int chunks)
     return sp;
 }
 
-constexpr int strided_wave_share(int chunks) { return chunks > 64 ? 2 : 1; }       // W for a minishard of `chunks`
 
-// Max over all chunk groups for each of the lane's 8 positions.  Every thread of the workgroup calls this; `red`
-// and `parity` matter for W = 2 only.
-template <int W>
-__device__ __forceinline__ void across_chunks_max_wave(uint32_t (&m)[8], uint32_t (*red)[kThreads / 64][64], int &parity)
+// A maximum that waves exchange: one row per wave, two buffers in turn.
+template <int W, int V>
+struct ChunkMaxRows {
+    uint32_t row[W > 1 ? 2 : 1][kThreads / 64][8 * V];
+};
+
+template <int W, int V>
+struct ChunkMaxState {
+    ChunkMaxRows<W, V> &red;
+    int parity;
+};
+
+// Max over all chunk groups for each of the lane's V positions.  Every thread of the workgroup calls this; the state
+// matters for W > 1 only.
+template <int W, int V>
+__device__ __forceinline__ void across_chunks_max_wave(uint32_t (&m)[V], ChunkMaxState<W, V> &st)
 {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < V; ++j) {
         uint32_t v = m[j];
         v = umax(v, dpp_read<0x128>(v));                                    // row_ror:8: lane ^ 8 within a row of 16
         auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);      // lane ^ 16
@@ -402,55 +423,91 @@ __device__ __forceinline__ void across_chunks_max_wave(uint32_t (&m)[8], uint32_
         auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);      // lane ^ 32
         m[j] = umax(b[0], b[1]);
     }
-    if (W == 2) {
+    if (W > 1) {
         const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-        const int at = (lane % 8) * kLaneElems;
+        const int at = (lane % 8) * V;
         if (lane < 8) {
-            u32x4 *row = reinterpret_cast<u32x4 *>(&red[parity][wave][at]);
-            row[0] = u32x4{m[0], m[1], m[2], m[3]};
-            row[1] = u32x4{m[4], m[5], m[6], m[7]};
+            u32x4 *row = reinterpret_cast<u32x4 *>(&st.red.row[st.parity][wave][at]);
+#pragma unroll
+            for (int q = 0; q < V / 4; ++q) row[q] = u32x4{m[4 * q], m[4 * q + 1], m[4 * q + 2], m[4 * q + 3]};
         }
         __syncthreads();
-        const u32x4 *other = reinterpret_cast<const u32x4 *>(&red[parity][wave ^ 1][at]);
-        const u32x4 a = other[0], b = other[1];
-        m[0] = umax(m[0], a.x); m[1] = umax(m[1], a.y); m[2] = umax(m[2], a.z); m[3] = umax(m[3], a.w);
-        m[4] = umax(m[4], b.x); m[5] = umax(m[5], b.y); m[6] = umax(m[6], b.z); m[7] = umax(m[7], b.w);
-        parity ^= 1;
+#pragma unroll
+        for (int w = 1; w < W; ++w) {
+            const u32x4 *other = reinterpret_cast<const u32x4 *>(&st.red.row[st.parity][wave ^ w][at]);
+#pragma unroll
+            for (int q = 0; q < V / 4; ++q) {
+                const u32x4 a = other[q];
+                m[4 * q] = umax(m[4 * q], a.x);
+                m[4 * q + 1] = umax(m[4 * q + 1], a.y);
+                m[4 * q + 2] = umax(m[4 * q + 2], a.z);
+                m[4 * q + 3] = umax(m[4 * q + 3], a.w);
+            }
+        }
+        st.parity ^= 1;
     }
 }
 
-struct ChunkMaxState {
-    uint32_t (*red)[kThreads / 64][64];
-    int parity;
+// What a lane loads of one chunk row: V bf16 values.
+template <int V>
+struct PieceOf;
+template <>
+struct PieceOf<8> {
+    typedef u32x4 type;
 };
+template <>
+struct PieceOf<4> {
+    typedef u32x2 type;
+};
+template <int V>
+using Piece = typename PieceOf<V>::type;
 
-template <int R>
-__device__ __forceinline__ void load_strided(const uint16_t *x, const WaveSpot &sp, u32x4 (&xv)[R])
+template <int R, int V>
+__device__ __forceinline__ void load_strided(const uint16_t *x, const WaveSpot &sp, Piece<V> (&xv)[R])
 {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        xv[r] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(x + sp.elem + r * sp.row_step));
+        xv[r] = __builtin_nontemporal_load(reinterpret_cast<const Piece<V> *>(x + sp.elem + r * sp.row_step));
     }
 }
 
-template <int R>
-__device__ __forceinline__ void widen_strided(const u32x4 (&xv)[R], float (&t)[R][8])
+template <int V>
+__device__ __forceinline__ void widen_piece(const Piece<V> &w, float (&f)[V])
 {
 #pragma unroll
-    for (int r = 0; r < R; ++r) widen_bf16x8(xv[r], t[r]);
+    for (int i = 0; i < V / 2; ++i) {
+        f[2 * i] = __uint_as_float(w[i] << 16);
+        f[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
+    }
 }
 
-// scale and inverse scale of the lane's 8 blocks for the sums t.
-template <int R, int W>
-__device__ __forceinline__ void strided_quotients(const float (&t)[R][8], ChunkMaxState &st, float (&scale)[8],
-                                                  float (&inv)[8])
+template <int V>
+__device__ __forceinline__ void store_piece(uint16_t *out, const float (&d)[V])
 {
-    uint32_t m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    Piece<V> w;
+#pragma unroll
+    for (int i = 0; i < V / 2; ++i) w[i] = narrow_bf16x2(d[2 * i], d[2 * i + 1]);
+    __builtin_nontemporal_store(w, reinterpret_cast<Piece<V> *>(out));
+}
+
+template <int R, int V>
+__device__ __forceinline__ void widen_strided(const Piece<V> (&xv)[R], float (&t)[R][V])
+{
+#pragma unroll
+    for (int r = 0; r < R; ++r) widen_piece<V>(xv[r], t[r]);
+}
+
+// scale and inverse scale of the lane's V blocks for the sums t.
+template <int R, int W, int V>
+__device__ __forceinline__ void strided_quotients(const float (&t)[R][V], ChunkMaxState<W, V> &st, float (&scale)[V],
+                                                  float (&inv)[V])
+{
+    uint32_t m[V] = {};
 #pragma unroll
     for (int r = 0; r < R; ++r) note_absmax(t[r], m);
-    across_chunks_max_wave<W>(m, st.red, st.parity);
+    across_chunks_max_wave<W, V>(m, st);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) block_quotients(__uint_as_float(m[j]), scale[j], inv[j]);
+    for (int j = 0; j < V; ++j) block_quotients(__uint_as_float(m[j]), scale[j], inv[j]);
 }
 
 // The code of v as a float.  kPositiveZero: a value that rounds to zero from below gives +0.0, as the integer
@@ -464,30 +521,30 @@ __device__ __forceinline__ float code_of(float v, float inv)
 }
 
 // One hop: t <- fma(code(t), scale, x), what the device holding x has after it received the quantized t.
-template <int R, int W, bool kPositiveZero>
-__device__ __forceinline__ void strided_hop(float (&t)[R][8], const u32x4 (&xv)[R], ChunkMaxState &st)
+template <int R, int W, int V, bool kPositiveZero>
+__device__ __forceinline__ void strided_hop(float (&t)[R][V], const Piece<V> (&xv)[R], ChunkMaxState<W, V> &st)
 {
-    float scale[8], inv[8];
-    strided_quotients<R, W>(t, st, scale, inv);
+    float scale[V], inv[V];
+    strided_quotients<R, W, V>(t, st, scale, inv);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        float xf[8];
-        widen_bf16x8(xv[r], xf);
+        float xf[V];
+        widen_piece<V>(xv[r], xf);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) t[r][j] = __builtin_fmaf(code_of<kPositiveZero>(t[r][j], inv[j]), scale[j], xf[j]);
+        for (int j = 0; j < V; ++j) t[r][j] = __builtin_fmaf(code_of<kPositiveZero>(t[r][j], inv[j]), scale[j], xf[j]);
     }
 }
 
 // The send that ends a half chain of the semi-loop: acc <- fma(code(t), scale, acc).
-template <int R, int W, bool kPositiveZero>
-__device__ __forceinline__ void strided_send_into(const float (&t)[R][8], float (&acc)[R][8], ChunkMaxState &st)
+template <int R, int W, int V, bool kPositiveZero>
+__device__ __forceinline__ void strided_send_into(const float (&t)[R][V], float (&acc)[R][V], ChunkMaxState<W, V> &st)
 {
-    float scale[8], inv[8];
-    strided_quotients<R, W>(t, st, scale, inv);
+    float scale[V], inv[V];
+    strided_quotients<R, W, V>(t, st, scale, inv);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[r][j] = __builtin_fmaf(code_of<kPositiveZero>(t[r][j], inv[j]), scale[j], acc[r][j]);
+        for (int j = 0; j < V; ++j) acc[r][j] = __builtin_fmaf(code_of<kPositiveZero>(t[r][j], inv[j]), scale[j], acc[r][j]);
     }
 }
 
@@ -495,7 +552,8 @@ __device__ __forceinline__ void strided_send_into(const float (&t)[R][8], float 
 // 63-75 at the 27B-shaped size) held to two waves than at the four its ~120 registers would allow: the loads of one
 // partial per wave already fill the memory queues, and more waves only lengthen them.  The semi-loop (two dependent
 // half chains) and the unquantized reduce-scatter measured the other way round and keep the default.
-constexpr int strided_chain_waves(bool semi, bool rs) { return (!semi && rs) ? 2 : 8; }
+// The small-message layout keeps the default, too.
+constexpr int strided_chain_waves(bool semi, bool rs, int V) { return (!semi && rs && V == 8) ? 2 : 8; }
 
 // chunks = 8 * W * R.  kSemi: the semi-loop with partials[0] as the owner (always a quantized reduce-scatter);
 // otherwise the full loop in array order with the reduce-scatter quantized (kRS) or added in plain fp32.  kAG: the
@@ -503,15 +561,15 @@ constexpr int strided_chain_waves(bool semi, bool rs) { return (!semi && rs) ? 2
 // Ring layout (Sec. 3): with per_shard > 0 the tensor is cut into shards of per_shard minishards and shard k ends
 // on device k: the full loop takes the partials in the order k+1, k+2, ..., k (mod P), the semi-loop has device k
 // as its owner and the devices k+1, k+2, ... around it.  per_shard == 0: array order everywhere.
-template <int R, int W, bool kSemi, bool kRS, bool kAG>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, strided_chain_waves(kSemi, kRS))))
+template <int R, int W, int V, bool kSemi, bool kRS, bool kAG>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, strided_chain_waves(kSemi, kRS, V))))
 void chain_strided_kernel(int P, int per_shard, uint16_t *out, const PartialTable tab)
 {
     static_assert(kRS || !kSemi, "the semi-loop is a quantized reduce-scatter");
-    __shared__ __align__(16) uint32_t red[W > 1 ? 2 : 1][kThreads / 64][64];
-    ChunkMaxState st{red, 0};
+    __shared__ __align__(16) ChunkMaxRows<W, V> red;
+    ChunkMaxState<W, V> st{red, 0};
     constexpr int chunks = 8 * W * R;
-    const WaveSpot sp = wave_spot<W>(chunks);
+    const WaveSpot sp = wave_spot<W, V>(chunks);
     // position i of the chain -> partial; `first` <= P and i < P, so one conditional subtraction wraps
     const int first = per_shard > 0 ? (int)(sp.minishard / per_shard) + (kSemi ? 0 : 1) : 0;
     const auto part = [&](int i) {
@@ -519,61 +577,159 @@ void chain_strided_kernel(int P, int per_shard, uint16_t *out, const PartialTabl
         return tab.x[j >= P ? j - P : j];
     };
 
-    float sum[R][8];
-    u32x4 xv[R];
-    load_strided<R>(part(0), sp, xv);
-    widen_strided<R>(xv, sum);
+    float sum[R][V];
+    Piece<V> xv[R];
+    load_strided<R, V>(part(0), sp, xv);
+    widen_strided<R, V>(xv, sum);
     if (kSemi) {
         const int h = P / 2;
-        float t[R][8];
+        float t[R][V];
         if (h + 1 <= P - 1) {                       // h+1 -> h+2 -> ... -> P-1 -> owner: the shorter chain arrives first
-            load_strided<R>(part(h + 1), sp, xv);
-            widen_strided<R>(xv, t);
+            load_strided<R, V>(part(h + 1), sp, xv);
+            widen_strided<R, V>(xv, t);
             for (int i = h + 2; i <= P - 1; ++i) {
-                load_strided<R>(part(i), sp, xv);
-                strided_hop<R, W, !kAG>(t, xv, st);
+                load_strided<R, V>(part(i), sp, xv);
+                strided_hop<R, W, V, !kAG>(t, xv, st);
             }
-            strided_send_into<R, W, !kAG>(t, sum, st);
+            strided_send_into<R, W, V, !kAG>(t, sum, st);
         }
         if (h >= 1) {                               // h -> h-1 -> ... -> 1 -> owner
-            load_strided<R>(part(h), sp, xv);
-            widen_strided<R>(xv, t);
+            load_strided<R, V>(part(h), sp, xv);
+            widen_strided<R, V>(xv, t);
             for (int i = h - 1; i >= 1; --i) {
-                load_strided<R>(part(i), sp, xv);
-                strided_hop<R, W, !kAG>(t, xv, st);
+                load_strided<R, V>(part(i), sp, xv);
+                strided_hop<R, W, V, !kAG>(t, xv, st);
             }
-            strided_send_into<R, W, !kAG>(t, sum, st);
+            strided_send_into<R, W, V, !kAG>(t, sum, st);
         }
     } else {
         for (int i = 1; i < P; ++i) {
-            load_strided<R>(part(i), sp, xv);
+            load_strided<R, V>(part(i), sp, xv);
             if (kRS) {
-                strided_hop<R, W, !kAG>(sum, xv, st);
+                strided_hop<R, W, V, !kAG>(sum, xv, st);
             } else {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    float xf[8];
-                    widen_bf16x8(xv[r], xf);
+                    float xf[V];
+                    widen_piece<V>(xv[r], xf);
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) sum[r][j] = sum[r][j] + xf[j];
+                    for (int j = 0; j < V; ++j) sum[r][j] = sum[r][j] + xf[j];
                 }
             }
         }
     }
 
+    float scale[V], inv[V];
+    if (kAG) strided_quotients<R, W, V>(sum, st, scale, inv);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        float d[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) d[j] = kAG ? code_of<true>(sum[r][j], inv[j]) * scale[j] : sum[r][j];
+        store_piece<V>(out + sp.elem + r * sp.row_step, d);
+    }
+}
+
+// ---------------------------------------------------------------- the per-pass kernels for few minishards
+//
+// The same passes in the wave layout: W = 4 waves share a piece of 64 positions, R = chunks / 32 rows per thread
+// instead of chunks / 8, 16 workgroups per minishard instead of 4.  Code pieces are 64 bytes, half a line, which is
+// why the per-pass kernels above have another layout; a message of few minishards is not bound by that but by the
+// time one wave takes (MI355X, hop-by-hop chain of four, five passes, 8 minishards: 64 chunks 17.9 -> 15.0 us, 128
+// chunks 24.4 -> 17.6).
+
+template <int R>
+struct WavePass {
+    static constexpr int W = 4, V = 8, kChunks = 8 * W * R;
+    WaveSpot sp;
+    ChunkMaxState<W, V> st;
+
+    __device__ __forceinline__ explicit WavePass(ChunkMaxRows<W, V> &red) : sp(wave_spot<W, V>(kChunks)), st{red, 0} {}
+
+    __device__ __forceinline__ void load(const uint16_t *x, float (&t)[R][V]) const
+    {
+        Piece<V> xv[R];
+        load_strided<R, V>(x, sp, xv);
+        widen_strided<R, V>(xv, t);
+    }
+
+    // t += codes * scales, one fused multiply-add per element
+    __device__ __forceinline__ void add_wire(const int8_t *codes, const float *scales, float (&t)[R][V]) const
+    {
+        u32x2 cv[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) cv[r] = *reinterpret_cast<const u32x2 *>(codes + sp.elem + r * sp.row_step);
+        const u32x4 a = *reinterpret_cast<const u32x4 *>(scales + sp.scale);
+        const u32x4 b = *reinterpret_cast<const u32x4 *>(scales + sp.scale + 4);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float qf[V];
+            widen_i8x8(cv[r], qf);
+#pragma unroll
+            for (int j = 0; j < V; ++j) t[r][j] = __builtin_fmaf(qf[j], __uint_as_float(j < 4 ? a[j & 3] : b[j & 3]), t[r][j]);
+        }
+    }
+
+    __device__ __forceinline__ void send(const float (&t)[R][V], int8_t *codes, float *scales)
+    {
+        float scale[V], inv[V];
+        strided_quotients<R, W, V>(t, st, scale, inv);
+#pragma unroll
+        for (int r = 0; r < R; ++r) *reinterpret_cast<u32x2 *>(codes + sp.elem + r * sp.row_step) = scale_and_pack(t[r], inv);
+        if (sp.first_group) {
+            u32x4 *s = reinterpret_cast<u32x4 *>(scales + sp.scale);
+            s[0] = u32x4{__float_as_uint(scale[0]), __float_as_uint(scale[1]), __float_as_uint(scale[2]), __float_as_uint(scale[3])};
+            s[1] = u32x4{__float_as_uint(scale[4]), __float_as_uint(scale[5]), __float_as_uint(scale[6]), __float_as_uint(scale[7])};
+        }
+    }
+};
+
+// kWire: a hop; otherwise the chain's first shard is quantized.  The output wire may be the input wire: the waves of a
+// piece meet at a barrier between their last load and their first store.
+template <int R, bool kWire>
+__global__ __launch_bounds__(kThreads) void pass_strided_small_kernel(const int8_t *cin, const float *sin, int8_t *cout,
+                                                                      float *sout, const StridedSource src)
+{
+    __shared__ __align__(16) ChunkMaxRows<4, 8> red;
+    WavePass<R> pass(red);
+    float t[R][8];
+    pass.load(strided_source(src, pass.sp.minishard), t);
+    if (kWire) pass.add_wire(cin, sin, t);
+    pass.send(t, cout, sout);
+}
+
+template <int R>
+__global__ __launch_bounds__(kThreads) void semi_step_strided_small_kernel(int P, int per_shard,
+                                                                           const StridedDirections dirs,
+                                                                           const PartialTable tab)
+{
+    __shared__ __align__(16) ChunkMaxRows<4, 8> red;
+    WavePass<R> pass(red);
+    const StridedDirection d = blockIdx.y == 0 ? dirs.d[0] : dirs.d[1];
+    const int j = (per_shard > 0 ? (int)(pass.sp.minishard / per_shard) : 0) + d.offset;     // < 2P
+    float t[R][8];
+    pass.load(tab.x[j >= P ? j - P : j], t);
+    if (d.cin != nullptr) pass.add_wire(d.cin, d.sin, t);       // uniform over the workgroup
+    pass.send(t, d.cout, d.sout);
+}
+
+template <int R, bool kAG>
+__global__ __launch_bounds__(kThreads) void owner_strided_small_kernel(int received, uint16_t *out,
+                                                                       const StridedWires wires, const StridedSource src)
+{
+    __shared__ __align__(16) ChunkMaxRows<4, 8> red;
+    WavePass<R> pass(red);
+    float t[R][8];
+    pass.load(strided_source(src, pass.sp.minishard), t);
+    for (int k = 0; k < received; ++k) pass.add_wire(wires.codes[k], wires.scales[k], t);
     float scale[8], inv[8];
-    if (kAG) strided_quotients<R, W>(sum, st, scale, inv);
+    if (kAG) strided_quotients<R, 4, 8>(t, pass.st, scale, inv);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         float d[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) d[j] = kAG ? code_of<true>(sum[r][j], inv[j]) * scale[j] : sum[r][j];
-        u32x4 w;
-        w.x = narrow_bf16x2(d[0], d[1]);
-        w.y = narrow_bf16x2(d[2], d[3]);
-        w.z = narrow_bf16x2(d[4], d[5]);
-        w.w = narrow_bf16x2(d[6], d[7]);
-        __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(out + sp.elem + r * sp.row_step));
+        for (int j = 0; j < 8; ++j) d[j] = kAG ? code_of<true>(t[r][j], inv[j]) * scale[j] : t[r][j];
+        store_piece<8>(out + pass.sp.elem + r * pass.sp.row_step, d);
     }
 }
 

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 from paper_2506_17615_amd import binding as eq
-from test_parity_gpu import _oracle_variant, gpu  # noqa: F401  (the fixture that loads the library)
+from test_parity_gpu import _oracle_variant, _oracle_variant_strided, gpu  # noqa: F401  (the fixture that loads the library)
 
 pytestmark = pytest.mark.gpu
 
@@ -114,6 +114,41 @@ def test_flat_batches_of_received_wires(gpu, oracle, values, n, R):  # noqa: F81
     c, s = torch.empty(n, dtype=torch.int8, device="cuda"), torch.empty(eq.num_blocks(n, B), device="cuda")
     eq.equarx_reduce_flat(gpu.dev_bf16(local), dev[:R], dev[R:], B, got, c, s)
     assert (gpu.host_u16(got) == out).all() and (c.cpu().numpy() == wc).all() and (_bits(s) == ws.view(np.uint32)).all()
+
+
+STRIDED_FLAGS = (0, eq.AG_UNQUANTIZED, eq.RS_UNQUANTIZED, eq.SEMI_LOOP, eq.RING_ORDER, eq.SEMI_LOOP | eq.RING_ORDER,
+                 eq.SEMI_LOOP | eq.RING_ORDER | eq.AG_UNQUANTIZED)
+
+
+@pytest.mark.parametrize("chunks,minishards", ((32, 1), (32, 16), (32, 17), (64, 3), (64, 16), (64, 17), (64, 32), (64, 33),
+                                               (128, 2), (128, 16), (128, 17)))
+@pytest.mark.parametrize("P", (1, 2, 5))
+def test_strided_layouts(gpu, oracle, chunks, minishards, P):  # noqa: F811
+    """Small, medium and large layouts of every strided call, on both sides of the lines between them."""
+    n = 1024 * chunks * minishards
+    rng = np.random.default_rng(n % 1000 + P)
+    x = [gpu.bf16_of(rng.standard_normal(n, dtype=np.float32) * np.exp2(rng.integers(-3, 4, n)).astype(np.float32))
+         for _ in range(P)]
+    dev = [gpu.dev_bf16(p) for p in x]
+    c, s = torch.empty(n, dtype=torch.int8, device="cuda"), torch.empty(n // chunks, device="cuda")
+    eq.equarx_quantize_strided(dev[0], chunks, c, s)
+    wc, ws = oracle.quantize_bf16_strided(x[0], chunks)
+    assert (c.cpu().numpy() == wc).all() and (_bits(s) == ws.view(np.uint32)).all()
+    if P > 1:                                               # a hop in place
+        eq.equarx_reduce_stage_strided(c, s, dev[1], chunks, c, s)
+        wc, ws = oracle.hop_strided(wc, ws, x[1], chunks)
+        assert (c.cpu().numpy() == wc).all() and (_bits(s) == ws.view(np.uint32)).all()
+    out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    eq.equarx_reduce_quantized_strided(dev, chunks, out, eq.alloc_workspace(P, n, chunks))
+    assert (gpu.host_u16(out) == oracle.reduce_chain_strided(x, chunks)).all()
+    for flags in STRIDED_FLAGS:
+        want = _oracle_variant_strided(oracle, x, chunks, flags)
+        eq.equarx_reduce_variant_strided(dev, chunks, flags, out.fill_(5.0))
+        assert (gpu.host_u16(out) == want).all(), flags
+        if not flags & eq.RS_UNQUANTIZED:
+            work = eq.alloc_variant_workspace(flags & ~eq.RING_ORDER, P, n, chunks)
+            eq.equarx_reduce_variant_hops_strided(dev, chunks, flags, out.fill_(5.0), work)
+            assert (gpu.host_u16(out) == want).all(), flags
 
 
 SMALL = 768 * 2048              # single-launch calls of few partials: up to here the batched kernel
