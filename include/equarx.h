@@ -21,8 +21,10 @@
  *     nothing and touches no memory.  n == 0 is valid and does nothing;
  *     n above 2^40 is EQUARX_BAD_SHAPE.  EQUARX_DEVICE_ERROR reports what the
  *     call's own kernel launches returned (a chain stops launching at the
- *     first failure); an error some earlier HIP call left pending on the
- *     thread is neither reported nor cleared.
+ *     first failure), and a message too long for a call that is one launch
+ *     (2^36 elements or more for the semi-loop, 2^37 otherwise; in ring order
+ *     per shard); an error some earlier HIP call left pending on the thread is
+ *     neither reported nor cleared.
  *   - Sharing memory between the buffers of one call: a buffer the call
  *     WRITES (an output, the workspace, a kept wire) may not overlap any other
  *     buffer of the call, not even partly -- EQUARX_BAD_SHAPE -- except where

@@ -46,9 +46,12 @@ int static_scratch(unsigned char **ptr)
 template <int B>
 void launch_head(const uint16_t *x0, const uint16_t *x1, int64_t n, int8_t *cout, float *sout, LaunchCtx &ctx)
 {
-    with_pass_shape(n, [&](auto shape) {
-        using S = decltype(shape);
-        ctx.launch(head_kernel<B, S::K>, grid_for<S>(n), S::T, x0, x1, n, cout, sout, blocks_of(n, B));
+    in_pieces(n, [&](int64_t at, int64_t m) {
+        with_pass_shape(m, [&](auto shape) {
+            using S = decltype(shape);
+            ctx.launch(head_kernel<B, S::K>, grid_for<S>(m), S::T, x0 + at, x1 + at, m, cout + at, sout + at / B,
+                       blocks_of(m, B));
+        });
     });
 }
 
@@ -56,13 +59,12 @@ template <int B>
 void launch_tail(const int8_t *cin, const float *sin, const uint16_t *x, int64_t n, uint16_t *out, LaunchCtx &ctx,
                  bool ag = true)
 {
-    with_pass_shape(n, [&](auto shape) {
-        using S = decltype(shape);
-        if (ag) {
-            ctx.launch(tail_kernel<B, S::K, true>, grid_for<S>(n), S::T, cin, sin, x, n, out, blocks_of(n, B));
-        } else {
-            ctx.launch(tail_kernel<B, S::K, false>, grid_for<S>(n), S::T, cin, sin, x, n, out, blocks_of(n, B));
-        }
+    in_pieces(n, [&](int64_t at, int64_t m) {
+        with_pass_shape(m, [&](auto shape) {
+            using S = decltype(shape);
+            ctx.launch(ag ? tail_kernel<B, S::K, true> : tail_kernel<B, S::K, false>, grid_for<S>(m), S::T, cin + at,
+                       sin + at / B, x + at, m, out + at, blocks_of(m, B));
+        });
     });
 }
 
@@ -188,7 +190,7 @@ void with_semi_shape(int64_t n, F f)
 {
     if (n <= kOneRound) {
         f(Shape<256, 1>{});
-    } else if (n <= kOneWideRound) {
+    } else if (n <= kOneWideRound || n >= kPieceElems) {        // longer, 1024 x 1 has more threads than a grid holds
         f(Shape<512, 2>{});
     } else {
         f(Shape<1024, 1>{});
@@ -323,19 +325,24 @@ template <int B>
 void launch_flat(const uint16_t *local, const WireTable &tab, int R, int64_t n, uint16_t *out, int8_t *codes_out,
                  float *scales_out, LaunchCtx &ctx)
 {
-    const int64_t nb = blocks_of(n, B);
-    with_flat_shape(n, R, [&](auto shape, auto batch) {
-        using S = decltype(shape);
-        constexpr int U = decltype(batch)::value;
-        constexpr bool kStream = kWireLeavesTheDevice;
-        const unsigned grid = grid_for<S>(n);
-        if (out && codes_out) {
-            ctx.launch(flat_kernel<B, S::K, U, true, true, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
-        } else if (out) {
-            ctx.launch(flat_kernel<B, S::K, U, true, false, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
-        } else {
-            ctx.launch(flat_kernel<B, S::K, U, false, true, true, kStream>, grid, S::T, local, R, n, out, codes_out, scales_out, nb, tab);
+    in_pieces(n, [&](int64_t at, int64_t m) {
+        WireTable part = tab;
+        for (int r = 0; at > 0 && r < R; ++r) {
+            part.codes[r] += at;
+            part.scales[r] += at / B;
         }
+        uint16_t *o = out ? out + at : nullptr;
+        int8_t *co = codes_out ? codes_out + at : nullptr;
+        float *so = codes_out ? scales_out + at / B : nullptr;
+        with_flat_shape(m, R, [&](auto shape, auto batch) {
+            using S = decltype(shape);
+            constexpr int U = decltype(batch)::value;
+            constexpr bool kStream = kWireLeavesTheDevice;
+            ctx.launch(o && co ? flat_kernel<B, S::K, U, true, true, true, kStream>
+                       : o     ? flat_kernel<B, S::K, U, true, false, true, kStream>
+                               : flat_kernel<B, S::K, U, false, true, true, kStream>,
+                       grid_for<S>(m), S::T, local + at, R, m, o, co, so, blocks_of(m, B), part);
+        });
     });
 }
 
@@ -614,10 +621,12 @@ void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chu
 void do_dequantize_strided(const int8_t *codes, const float *scales, int64_t n, int32_t chunks, void *out,
                            LaunchCtx &ctx)
 {
-    with_pass_shape(n, [&](auto shape) {
-        using S = decltype(shape);
-        ctx.launch(dequantize_strided_kernel<S::K>, grid_for<S>(n), S::T, codes, scales, n, (int)chunks,
-                   static_cast<uint16_t *>(out));
+    in_pieces(n, [&](int64_t at, int64_t m) {
+        with_pass_shape(m, [&](auto shape) {
+            using S = decltype(shape);
+            ctx.launch(dequantize_strided_kernel<S::K>, grid_for<S>(m), S::T, codes + at, scales + at / chunks, m, (int)chunks,
+                       static_cast<uint16_t *>(out) + at);
+        });
     });
 }
 
@@ -710,14 +719,21 @@ int equarx_quantize_batch(const void *const *x_bf16, int8_t *const *codes, float
         tab.scales[i] = scales[i];
     }
     if (int st = mem.check()) return st;      // two tensors sharing an output, or an output inside an input
+    in_pieces(n, [&](int64_t at, int64_t m) {
+        for (int32_t i = 0; at > 0 && i < count; ++i) {
+            tab.x[i] += kPieceElems;
+            tab.codes[i] += kPieceElems;
+            tab.scales[i] += kPieceElems / block;
+        }
 #define CALL(BB)                                                                                                  \
-    with_pass_shape(count * n, [&](auto shape) {                                                                  \
+    with_pass_shape(count * m, [&](auto shape) {                                                                  \
         using S = decltype(shape);                                                                                \
-        ctx.launch2d(quantize_batch_kernel<BB, S::K, kWireLeavesTheDevice>, grid_for<S>(n), (unsigned)count,    \
-                     S::T, n, blocks_of(n, BB), tab);                                                             \
+        ctx.launch2d(quantize_batch_kernel<BB, S::K, kWireLeavesTheDevice>, grid_for<S>(m), (unsigned)count,    \
+                     S::T, m, blocks_of(m, BB), tab);                                                             \
     })
-    EQUARX_DISPATCH_BLOCK(block, CALL)
+        EQUARX_DISPATCH_BLOCK(block, CALL)
 #undef CALL
+    });
     return ctx.status();
 }
 

@@ -31,8 +31,21 @@ inline int64_t blocks_of(int64_t n, int32_t block) { return (n + block - 1) / bl
 
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// The grid is a 32-bit count of workgroups of at least 2048 elements each.
 inline bool too_long(int64_t n) { return n > ((int64_t)1 << 40); }
+
+// A dimension of a grid holds fewer than 2^32 threads, and of a larger one the runtime launches the part that is left
+// after a wrap to 32 bits, without an error: on MI355X a quantization of 2^36 + 8192 elements by 512 threads x 2 tiles
+// wrote its first workgroup's 8192 elements and returned success.  So launches check the limit (LaunchCtx), and the
+// passes over a longer message are made piece by piece: f(first element, count) per piece, whose length is a multiple
+// of every block and minishard.
+constexpr uint64_t kGridThreads = ((uint64_t)1 << 32) - 1;
+constexpr int64_t kPieceElems = (int64_t)1 << 35;
+
+template <typename F>
+inline void in_pieces(int64_t n, F f)
+{
+    for (int64_t at = 0; at < n; at += kPieceElems) f(at, n - at < kPieceElems ? n - at : kPieceElems);
+}
 
 inline int check_shape(int64_t n, int32_t block)
 {
@@ -139,6 +152,10 @@ public:
     {
         static_assert(sizeof...(KArgs) == sizeof...(Args), "kernel argument count");
         if (error_ != hipSuccess) return;
+        if ((uint64_t)grid_x * threads > kGridThreads) {
+            error_ = hipErrorInvalidConfiguration;
+            return;
+        }
         const int index = launches_++;
         if (hooks_.span_start && index == hooks_.span_first) note(hipEventRecord(hooks_.span_start, stream_));
         if (error_ != hipSuccess) return;

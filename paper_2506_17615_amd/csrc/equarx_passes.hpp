@@ -13,13 +13,12 @@ namespace host {
 template <int B>
 void launch_quantize(const uint16_t *x, int64_t n, int8_t *codes, float *scales, LaunchCtx &ctx, bool streaming = false)
 {
-    with_pass_shape(n, [&](auto shape) {
-        using S = decltype(shape);
-        if (streaming) {
-            ctx.launch(quantize_kernel<B, S::K, true>, grid_for<S>(n), S::T, x, n, codes, scales, blocks_of(n, B));
-        } else {
-            ctx.launch(quantize_kernel<B, S::K, false>, grid_for<S>(n), S::T, x, n, codes, scales, blocks_of(n, B));
-        }
+    in_pieces(n, [&](int64_t at, int64_t m) {
+        with_pass_shape(m, [&](auto shape) {
+            using S = decltype(shape);
+            ctx.launch(streaming ? quantize_kernel<B, S::K, true> : quantize_kernel<B, S::K, false>, grid_for<S>(m), S::T,
+                       x + at, m, codes + at, scales + at / B, blocks_of(m, B));
+        });
     });
 }
 
@@ -27,13 +26,12 @@ template <int B>
 void launch_hop(const int8_t *cin, const float *sin, const uint16_t *x, int64_t n, int8_t *cout, float *sout,
                 LaunchCtx &ctx, bool streaming = false)
 {
-    with_pass_shape(n, [&](auto shape) {
-        using S = decltype(shape);
-        if (streaming) {
-            ctx.launch(hop_kernel<B, S::K, true>, grid_for<S>(n), S::T, cin, sin, x, n, cout, sout, blocks_of(n, B));
-        } else {
-            ctx.launch(hop_kernel<B, S::K, false>, grid_for<S>(n), S::T, cin, sin, x, n, cout, sout, blocks_of(n, B));
-        }
+    in_pieces(n, [&](int64_t at, int64_t m) {
+        with_pass_shape(m, [&](auto shape) {
+            using S = decltype(shape);
+            ctx.launch(streaming ? hop_kernel<B, S::K, true> : hop_kernel<B, S::K, false>, grid_for<S>(m), S::T, cin + at,
+                       sin + at / B, x + at, m, cout + at, sout + at / B, blocks_of(m, B));
+        });
     });
 }
 
@@ -41,13 +39,12 @@ template <int B>
 void launch_dequantize(const int8_t *codes, const float *scales, int64_t n, uint16_t *out, LaunchCtx &ctx,
                        bool streaming = false)
 {
-    with_pass_shape(n, [&](auto shape) {
-        using S = decltype(shape);
-        if (streaming) {
-            ctx.launch(dequantize_kernel<B, S::K, true>, grid_for<S>(n), S::T, codes, scales, n, out, blocks_of(n, B));
-        } else {
-            ctx.launch(dequantize_kernel<B, S::K, false>, grid_for<S>(n), S::T, codes, scales, n, out, blocks_of(n, B));
-        }
+    in_pieces(n, [&](int64_t at, int64_t m) {
+        with_pass_shape(m, [&](auto shape) {
+            using S = decltype(shape);
+            ctx.launch(streaming ? dequantize_kernel<B, S::K, true> : dequantize_kernel<B, S::K, false>, grid_for<S>(m), S::T,
+                       codes + at, scales + at / B, m, out + at, blocks_of(m, B));
+        });
     });
 }
 
