@@ -199,21 +199,73 @@ constexpr int kNonTemporal = 2;         // cache policy bits of a buffer access
 constexpr int kThroughL2 = 1 | 16;      // sc0 sc1
 constexpr int kNowhere = 0x7ffffff0;    // an offset past the end of every descriptor here
 
+// A lane's access at the end of a tensor: its whole words, and the elements of a last, partial word (0 if there are none),
+// which whole_end puts in the lane they belong to.  Two steps, so that a thread with several tiles can request all of
+// them before it looks at the first: with both in one the compiler waited for a tile before it asked for the next, in
+// the semi-loop once per partial (MI355X: 16 partials of 4.3 M elements, blocks of 512, 30.0 us, 27.1 in two steps;
+// dequantization of 4.2 M 4.0 -> 3.3, of 6.2 M 4.7 -> 4.2).
+struct EndOfBf16 {
+    u32x4 words;
+    uint32_t last;
+    int whole;      // elements in whole words, from the tile's first
+};
+
+__device__ __forceinline__ EndOfBf16 request_end(const uint16_t *p, int64_t base, int off, int64_t n)
+{
+    const int left = left_of(n, base);
+    const int whole = left & ~1;
+    constexpr int kPolicy = EQUARX_NT_LOAD_BF16 ? kNonTemporal : 0;
+    EndOfBf16 e;
+    e.words = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(bounded(p + base, whole * 2), off * 2, 0, kPolicy));
+    e.last = __builtin_amdgcn_raw_buffer_load_b16(bounded(p + base, left * 2), whole * 2, 0, 0);
+    e.whole = whole;
+    return e;
+}
+
+__device__ __forceinline__ u32x4 whole_end(const EndOfBf16 &e, int off)
+{
+    u32x4 w = e.words;
+    if (off == e.whole) w.x = e.last;
+    if (off + 2 == e.whole) w.y = e.last;
+    if (off + 4 == e.whole) w.z = e.last;
+    if (off + 6 == e.whole) w.w = e.last;
+    return w;
+}
+
 __device__ __forceinline__ u32x4 load_bf16x8(const uint16_t *p, int64_t base, int off, int64_t n, bool full)
 {
     if (full) {
         const u32x4 *v = reinterpret_cast<const u32x4 *>(p + base + off);
         return EQUARX_NT_LOAD_BF16 ? __builtin_nontemporal_load(v) : *v;
     }
+    return whole_end(request_end(p, base, off, n), off);
+}
+
+struct EndOfI8 {
+    u32x2 words;
+    uint32_t last[3];
+    int whole;
+};
+
+template <bool kStream>
+__device__ __forceinline__ EndOfI8 request_end(const int8_t *p, int64_t base, int off, int64_t n)
+{
     const int left = left_of(n, base);
-    const int whole = left & ~1;
-    constexpr int kPolicy = EQUARX_NT_LOAD_BF16 ? kNonTemporal : 0;
-    u32x4 w = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(bounded(p + base, whole * 2), off * 2, 0, kPolicy));
-    const uint32_t last = __builtin_amdgcn_raw_buffer_load_b16(bounded(p + base, left * 2), whole * 2, 0, 0);     // 0 if left is even
-    if (off == whole) w.x = last;
-    if (off + 2 == whole) w.y = last;
-    if (off + 4 == whole) w.z = last;
-    if (off + 6 == whole) w.w = last;
+    EndOfI8 e;
+    e.whole = left & ~3;
+    e.words = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(bounded(p + base, e.whole), off, 0, kStream ? kNonTemporal : 0));
+    const auto end = bounded(p + base, left);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) e.last[i] = __builtin_amdgcn_raw_buffer_load_b8(end, e.whole + i, 0, 0);
+    return e;
+}
+
+__device__ __forceinline__ u32x2 whole_end(const EndOfI8 &e, int off)
+{
+    u32x2 w = e.words;
+    const uint32_t last = e.last[0] | (e.last[1] << 8) | (e.last[2] << 16);
+    if (off == e.whole) w.x = last;
+    if (off + 4 == e.whole) w.y = last;
     return w;
 }
 
@@ -230,17 +282,7 @@ __device__ __forceinline__ u32x2 load_i8x8(const int8_t *p, int64_t base, int of
         const u32x2 *v = reinterpret_cast<const u32x2 *>(p + base + off);
         return kStream ? __builtin_nontemporal_load(v) : *v;
     }
-    const int left = left_of(n, base);
-    const int whole = left & ~3;
-    u32x2 w = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(bounded(p + base, whole), off, 0, kStream ? kNonTemporal : 0));
-    const auto end = bounded(p + base, left);
-    const uint32_t b0 = __builtin_amdgcn_raw_buffer_load_b8(end, whole, 0, 0);
-    const uint32_t b1 = __builtin_amdgcn_raw_buffer_load_b8(end, whole + 1, 0, 0);
-    const uint32_t b2 = __builtin_amdgcn_raw_buffer_load_b8(end, whole + 2, 0, 0);
-    const uint32_t last = b0 | (b1 << 8) | (b2 << 16);
-    if (off == whole) w.x = last;
-    if (off + 4 == whole) w.y = last;
-    return w;
+    return whole_end(request_end<kStream>(p, base, off, n), off);
 }
 
 template <bool kStream = false>
@@ -590,15 +632,21 @@ __device__ __forceinline__ void dequantize_body(const int8_t *__restrict__ codes
     const int lane_at = threadIdx.x * kLaneElems;
 
     u32x2 cv[K];
+    EndOfI8 end[K];
     float sv[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int64_t base = wg_at + k * tile_elems<T>;
-        cv[k] = load_i8x8<kStream>(codes, base, lane_at, n, kFull);
+        if (kFull) cv[k] = load_i8x8<kStream>(codes, base, lane_at, n, true);
+        else end[k] = request_end<kStream>(codes, base, lane_at, n);
         const int64_t blk = base / B + lane_at / B;
         sv[k] = scales[kFull || blk < nb ? blk : nb - 1];
     }
-
+    if (!kFull) {
+        loads_first();
+#pragma unroll
+        for (int k = 0; k < K; ++k) cv[k] = whole_end(end[k], lane_at);
+    }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int64_t base = wg_at + k * tile_elems<T>;
@@ -654,8 +702,17 @@ template <int T, int K, bool kFull>
 __device__ __forceinline__ void load_tiles(const uint16_t *p, int64_t wg_at, int64_t n, u32x4 (&v)[K])
 {
     const int lane_at = threadIdx.x * kLaneElems;
+    if (kFull || K == 1) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = load_bf16x8(p, wg_at + k * tile_elems<T>, lane_at, n, kFull);
+        for (int k = 0; k < K; ++k) v[k] = load_bf16x8(p, wg_at + k * tile_elems<T>, lane_at, n, kFull);
+        return;
+    }
+    EndOfBf16 e[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) e[k] = request_end(p, wg_at + k * tile_elems<T>, lane_at, n);
+    loads_first();
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = whole_end(e[k], lane_at);
 }
 
 // Writes what the wire carries after a quantization of one tile (8 codes per

@@ -49,3 +49,22 @@ def test_leading_kernel_arguments_are_preloaded(device_asm):
                            ("chain_kernelILi256E", 14), ("flat_kernelILi256E", 14)):
         found = re.findall(r"^\s*\.amdhsa_kernel _ZN6equarx\d+" + kernel + r".*?preload_length (\d+)", asm, flags=re.M | re.S)
         assert found and all(int(f) == dwords for f in found), (kernel, found)
+
+
+def test_the_tiles_of_a_thread_at_the_end_are_requested_together(device_asm):
+    """A thread with several tiles waits for none of them before it has asked for all: in the workgroup that holds the
+    end of a tensor (the buffer loads) no wait stands between two requests of one straight run of instructions."""
+    bodies = re.findall(r"^(_ZN6equarx\d+(?:(?:quantize|hop|dequantize|head|tail)_kernelILi\d+ELi2E|"
+                        r"(?:chain|semi)_kernelILi\d+ELi\d+ELi[24]E)\S*):(.*?)^\.Lfunc_end",
+                        device_asm["equarx_api.hip"], flags=re.M | re.S)
+    assert len({name.split("ILi")[0] for name, _ in bodies}) == 7
+    for name, body in bodies:
+        requested = waited = False
+        for line in body.splitlines():
+            if re.match(r"\.L|\s+s_c?branch", line):
+                requested = waited = False
+            elif "buffer_load" in line:
+                assert not waited, name
+                requested = True
+            elif "vmcnt" in line:
+                waited = requested
