@@ -148,6 +148,9 @@ inline bool small_semi(int64_t n, int P) { return n <= kSmallElems && n > kSmall
 // Launch shapes of the bandwidth kernels of the single-launch calls.  What a message of a few million elements pays
 // for is the last round of workgroups, so each shape is used where its rounds come out even:
 //   256 x 1   while that is one round on the chip (2048 workgroups, 4.2 M elements);
+//   256 x 2   while that gives no CU more than five (1280 workgroups, 5.2 M elements), where 512 x 2 gives some CUs three
+//             of its workgroups and others two: with many partials, whose every hop waits for the slower CUs, it costs
+//             up to 8 % (table below);
 //   512 x 2   while that is one round (768 workgroups, 6.3 M elements; their registers allow three per CU).  Not for a
 //             chain that writes its wire out: every hop stores there, 29.7 us with 256 x 4, 31.0 with 512 x 2, 28.2
 //             with 1024 x 1 at 6 M elements;
@@ -168,6 +171,13 @@ inline bool small_semi(int64_t n, int P) { return n <= kSmallElems && n > kSmall
 //     22 M            60.8      61.4      61.2                     58.0      54.8      55.3
 //     33.5 M          90.0      93.9      92.2                     85.2      83.1      81.9
 //     88 M           247.5       264       262
+// and around the line between 256 x 2 and 512 x 2, 512 x 2 -> 256 x 2:
+//     elements      chain, P = 8, B = 256    P = 16, B = 32    semi-loop, P = 8, B = 64    P = 16, B = 512
+//     4.25 M             13.9 -> 12.9         25.4 -> 23.7            14.3 -> 13.2           26.5 -> 24.6
+//     4.6 M              15.0 -> 13.9         26.8 -> 25.1            15.2 -> 14.1           27.5 -> 25.8
+//     5.1 M              15.6 -> 14.9         28.4 -> 27.1            16.0 -> 15.3           28.9 -> 27.6
+//     5.6 M              16.8 -> 16.8         30.1 -> 30.7            16.9 -> 17.3           30.7 -> 31.3
+constexpr int64_t kFivePerCU = (int64_t)5 * 256 * Shape<256, 2>::kElems;
 constexpr int64_t kOneWideRound = (int64_t)768 * Shape<512, 2>::kElems;
 constexpr int64_t kPairedFrom = (int64_t)2560 * Shape<1024, 1>::kElems;
 
@@ -176,6 +186,8 @@ void with_chain_shape(int64_t n, bool keeps_wire, F f)
 {
     if (n <= kOneRound) {
         f(Shape<256, 1>{});
+    } else if (n <= kFivePerCU && !keeps_wire) {
+        f(Shape<256, 2>{});
     } else if (n <= kOneWideRound && !keeps_wire) {
         f(Shape<512, 2>{});
     } else if (n <= kPairedFrom) {
@@ -190,6 +202,8 @@ void with_semi_shape(int64_t n, F f)
 {
     if (n <= kOneRound) {
         f(Shape<256, 1>{});
+    } else if (n <= kFivePerCU) {
+        f(Shape<256, 2>{});
     } else if (n <= kOneWideRound || n >= kPieceElems) {        // longer, 1024 x 1 has more threads than a grid holds
         f(Shape<512, 2>{});
     } else {

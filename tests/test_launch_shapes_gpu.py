@@ -8,6 +8,7 @@ from test_parity_gpu import _oracle_variant, _oracle_variant_strided, gpu  # noq
 
 pytestmark = pytest.mark.gpu
 
+FIVE_PER_CU = 5 * 256 * 4096    # single-launch calls: up to here 256 threads x 2 tiles
 WIDE_ROUND = 768 * 8192         # single-launch calls: up to here 512 threads x 2 tiles, above 1024 x 1
 PAIRED_FROM = 2560 * 8192       # single-launch chain: above, 256 threads x 4 tiles
 CACHED_OUT = 32 << 20           # single-launch calls: up to here the output stays in the Infinity Cache
@@ -80,6 +81,15 @@ def test_single_launch_around_its_shapes(gpu, oracle, n, flags):  # noqa: F811
     rng = np.random.default_rng(n % 1000 + flags)
     x = [gpu.bf16_of(rng.standard_normal(n, dtype=np.float32)) for _ in range(3)]
     B = 64 if flags & eq.RING_ORDER else 256
+    assert (gpu.gpu_variant(x, B, flags) == _oracle_variant(oracle, x, B, flags)).all()
+
+
+@pytest.mark.parametrize("n", (FIVE_PER_CU, FIVE_PER_CU - 4096 + 37, FIVE_PER_CU + 1))
+@pytest.mark.parametrize("flags", SINGLE)
+def test_single_launch_around_five_workgroups_per_cu(gpu, oracle, n, flags):  # noqa: F811
+    rng = np.random.default_rng(n % 1000 + flags)
+    x = [gpu.bf16_of(rng.standard_normal(n, dtype=np.float32)) for _ in range(3)]
+    B = 512 if flags & eq.RING_ORDER else 32
     assert (gpu.gpu_variant(x, B, flags) == _oracle_variant(oracle, x, B, flags)).all()
 
 
