@@ -151,9 +151,11 @@ inline bool small_semi(int64_t n, int P) { return n <= kSmallElems && n > kSmall
 //   256 x 2   while that gives no CU more than five (1280 workgroups, 5.2 M elements), where 512 x 2 gives some CUs three
 //             of its workgroups and others two: with many partials, whose every hop waits for the slower CUs, it costs
 //             up to 8 % (table below);
-//   512 x 2   while that is one round (768 workgroups, 6.3 M elements; their registers allow three per CU).  Not for a
-//             chain that writes its wire out: every hop stores there, 29.7 us with 256 x 4, 31.0 with 512 x 2, 28.2
-//             with 1024 x 1 at 6 M elements;
+//   512 x 2   while that is one round (768 workgroups, 6.3 M elements; their registers allow three per CU).  A chain
+//             that writes its wire out stores at every hop, and with more than six partials 1024 x 1 does that better,
+//             before the one round ends (512 x 2 -> 1024 x 1, P = 2, 4, 8, 12 and 16: 10.0 -> 11.0, 15.0 -> 16.5, 26.2
+//             -> 26.1, 39.0 -> 38.8 and 61.5 -> 58.3 us at 6 M elements; 10.3 -> 11.5, 15.4 -> 17.6, 27.1 -> 27.2, 39.7 ->
+//             39.6 and 62.0 -> 60.6 at 6.2 M);
 //   1024 x 1  above: sixteen waves walk one 16 KiB piece of every partial together, each with a single load in flight;
 //   256 x 4   for the chain from 21 M elements on, two waves per SIMD (chain_waves); two pieces of a block per lane
 //             (chain_body_paired) save arithmetic that 1024 x 1 has to spend.  The semi-loop, with its two sums per
@@ -182,13 +184,13 @@ constexpr int64_t kOneWideRound = (int64_t)768 * Shape<512, 2>::kElems;
 constexpr int64_t kPairedFrom = (int64_t)2560 * Shape<1024, 1>::kElems;
 
 template <typename F>
-void with_chain_shape(int64_t n, bool keeps_wire, F f)
+void with_chain_shape(int64_t n, int P, bool keeps_wire, F f)
 {
     if (n <= kOneRound) {
         f(Shape<256, 1>{});
-    } else if (n <= kFivePerCU && !keeps_wire) {
+    } else if (n <= kFivePerCU) {
         f(Shape<256, 2>{});
-    } else if (n <= kOneWideRound && !keeps_wire) {
+    } else if (n <= kOneWideRound && (!keeps_wire || P <= 6)) {
         f(Shape<512, 2>{});
     } else if (n <= kPairedFrom) {
         f(Shape<1024, 1>{});
@@ -265,7 +267,7 @@ void launch_chain(const PartialTable &tab, int P, int64_t n, bool rs, bool ag, b
             launch_small<B, false, false, true, false>(tab, P, n, ring, out, nullptr, nullptr, 0, 0, ctx);
         }
     } else {
-        with_chain_shape(n, wire_codes != nullptr, [&](auto shape) {
+        with_chain_shape(n, P, wire_codes != nullptr, [&](auto shape) {
             launch_chain_as<B, decltype(shape)>(tab, P, n, rs, ag, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
         });
     }
