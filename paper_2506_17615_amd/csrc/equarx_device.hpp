@@ -702,11 +702,21 @@ template <int T, int K, bool kFull>
 __device__ __forceinline__ void load_tiles(const uint16_t *p, int64_t wg_at, int64_t n, u32x4 (&v)[K])
 {
     const int lane_at = threadIdx.x * kLaneElems;
-    if (kFull || K == 1) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = load_bf16x8(p, wg_at + k * tile_elems<T>, lane_at, n, kFull);
+    for (int k = 0; k < K; ++k) v[k] = load_bf16x8(p, wg_at + k * tile_elems<T>, lane_at, n, kFull);
+}
+
+// load_tiles with the end of a tensor in the two steps above, for a loop in which the compiler would not keep the tiles'
+// requests together by itself (semi_body).  Not for the full loop: there it does, and in two steps it waits for the tiles
+// before the quantization that could have run meanwhile (MI355X, eight partials of 4.2 M elements 13.4 -> 13.9 us).
+template <int T, int K, bool kFull>
+__device__ __forceinline__ void load_tiles_together(const uint16_t *p, int64_t wg_at, int64_t n, u32x4 (&v)[K])
+{
+    if (kFull || K == 1) {
+        load_tiles<T, K, kFull>(p, wg_at, n, v);
         return;
     }
+    const int lane_at = threadIdx.x * kLaneElems;
     EndOfBf16 e[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) e[k] = request_end(p, wg_at + k * tile_elems<T>, lane_at, n);
@@ -1267,7 +1277,7 @@ __device__ __forceinline__ void semi_body(const PartialTable &tab, int P, int ro
         for (int k = 0; k < K; ++k) widen_bf16x8(xv[k], t[k]);
         for (int c = 1; c < count; ++c) {
             j = dir == 0 ? ring_next(j, P) : ring_prev(j, P);
-            load_tiles<T, K, kFull>(tab.x[j], wg_at, n, xv);
+            load_tiles_together<T, K, kFull>(tab.x[j], wg_at, n, xv);
             hop_tiles<B, T, K, true, false, !kAG, kFull>(t, xv, nullptr, nullptr, 0, 0, 0, wg_at, n);
         }
 #pragma unroll
