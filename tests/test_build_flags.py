@@ -68,3 +68,10 @@ def test_the_tiles_of_a_thread_at_the_end_are_requested_together(device_asm):
                 requested = True
             elif "vmcnt" in line:
                 waited = requested
+
+
+def test_the_loop_of_the_128_chunk_chain_keeps_its_alignment(device_asm):
+    for ag in "01":
+        body = re.search(r"^_ZN6equarx\d+chain_strided_kernelILi8ELi2ELi8ELb0ELb1ELb" + ag + r"E\S*:(.*?)^\.Lfunc_end",
+                         device_asm["equarx_api.hip"], flags=re.M | re.S).group(1)
+        assert len(re.findall(r"\.p2align\s+3\n", body)) == 1
