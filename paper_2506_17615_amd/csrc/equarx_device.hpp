@@ -317,15 +317,23 @@ __device__ __forceinline__ void store_i8x8(int8_t *p, int64_t base, int off, int
 // again, 23.4 -> 23.0, 62.5 -> 62.5, 97.0 -> 96.2, 132.0 -> 132.3, 179.0 -> 181.4.
 constexpr int64_t kCachedOutElems = (int64_t)32 << 20;      // 64 MiB of bf16, a quarter of the cache
 
-__device__ __forceinline__ bool out_stays_cached(int64_t n) { return n <= kCachedOutElems; }
+// A call that keeps its wire writes P rows of codes, too, which the cache holds as long as they fit with everything else
+// that is in use; there the rows count instead of the output.  MI355X, us, output cached -> streamed, three sets of
+// buffers in turn: six partials of 14 M elements 50.5 -> 45.5, four of 20.9 M 54.0 -> 48.3, two of 28 M 40.5 -> 38.3, but
+// two of 1 M 3.0 -> 3.3 and four of 8 M 21.5 -> 21.9.
+__device__ __forceinline__ bool out_stays_cached(int64_t n, int rows) { return n * rows <= kCachedOutElems; }
 
-// cached is looked at for a full tile only.
+// cached is looked at for a full tile only.  kKeepsHint: streamed by an access that keeps its hint also where the compiler
+// joins two copies of a store, unlike __builtin_nontemporal_store.
+template <bool kKeepsHint = false>
 __device__ __forceinline__ void store_bf16x8(uint16_t *p, int64_t base, int off, int64_t n, bool full, const u32x4 &w,
                                              bool cached = false)
 {
     if (full) {
         if (cached) {
             __builtin_amdgcn_raw_buffer_store_b128(w, bounded(p + base, 0x7fffffff), off * 2, 0, kThroughL2);
+        } else if (kKeepsHint) {
+            __builtin_amdgcn_raw_buffer_store_b128(w, bounded(p + base, 0x7fffffff), off * 2, 0, kNonTemporal);
         } else {
             u32x4 *v = reinterpret_cast<u32x4 *>(p + base + off);
             if (EQUARX_NT_STORE_BF16) {
@@ -738,7 +746,7 @@ __device__ __forceinline__ void store_wire_tile(int8_t *__restrict__ wire_codes,
 }
 
 // out = bf16(v) for the 8 fp32 values of one lane.
-template <bool kFull>
+template <bool kFull, bool kKeepsHint = false>
 __device__ __forceinline__ void store_narrowed_tile(uint16_t *out, int64_t base, int off, int64_t n,
                                                     const float (&v)[8], bool cached = false)
 {
@@ -747,7 +755,7 @@ __device__ __forceinline__ void store_narrowed_tile(uint16_t *out, int64_t base,
     w.y = narrow_bf16x2(v[2], v[3]);
     w.z = narrow_bf16x2(v[4], v[5]);
     w.w = narrow_bf16x2(v[6], v[7]);
-    store_bf16x8(out, base, off, n, kFull, w, cached);
+    store_bf16x8<kKeepsHint>(out, base, off, n, kFull, w, cached);
 }
 
 // The last step of a chain for one tile: quantize the finished fp32 sum once
@@ -766,9 +774,9 @@ __device__ __forceinline__ void finish_tile(const float (&t)[8], uint16_t *out,
         float d[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) d[j] = r[j] * s;
-        store_narrowed_tile<kFull>(out, base, off, n, d, cached);
+        store_narrowed_tile<kFull, kWire>(out, base, off, n, d, cached);
     } else {
-        store_narrowed_tile<kFull>(out, base, off, n, t, cached);
+        store_narrowed_tile<kFull, kWire>(out, base, off, n, t, cached);
     }
 }
 
@@ -1092,14 +1100,14 @@ void chain_kernel(int P, int64_t n, int64_t shard_elems, uint16_t *out,
     if (sp.wg_at + tile_elems<T> * K <= sp.hi) {
         if (EQUARX_CHAIN_PAIRED && B >= 128 && K % 2 == 0 && !kWire) {
             chain_body_paired<(B >= 128 ? B : 128), T, (K >= 2 ? K / 2 : 1), kRS, kAG>(tab, P, sp.rot, out, sp.wg_at,
-                                                                                            out_stays_cached(n));
+                                                                                            out_stays_cached(n, kWire ? P : 1));
         } else {
             chain_body<B, T, K, kRS, kAG, kWire, true>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step,
-                                                    s_step, sp.wg_at, out_stays_cached(n));
+                                                    s_step, sp.wg_at, out_stays_cached(n, kWire ? P : 1));
         }
     } else {
         chain_body<B, T, K, kRS, kAG, kWire, false>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step, s_step,
-                                                 sp.wg_at, out_stays_cached(n));
+                                                 sp.wg_at, out_stays_cached(n, kWire ? P : 1));
     }
 }
 
@@ -1304,9 +1312,9 @@ __global__ __launch_bounds__(T) void semi_kernel(int P, int64_t n, int64_t shard
     const Span sp = workgroup_span<T, K>(n, shard_elems, 0);     // shard k: owner is device k
     if (!sp.any) return;
     if (sp.wg_at + tile_elems<T> * K <= sp.hi) {
-        semi_body<B, T, K, kAG, true>(tab, P, sp.rot, sp.hi, out, sp.wg_at, out_stays_cached(n));
+        semi_body<B, T, K, kAG, true>(tab, P, sp.rot, sp.hi, out, sp.wg_at, out_stays_cached(n, 1));
     } else {
-        semi_body<B, T, K, kAG, false>(tab, P, sp.rot, sp.hi, out, sp.wg_at, out_stays_cached(n));
+        semi_body<B, T, K, kAG, false>(tab, P, sp.rot, sp.hi, out, sp.wg_at, out_stays_cached(n, 1));
     }
 }
 

@@ -102,7 +102,8 @@ def test_kept_wire_above_one_round(gpu, oracle, n):  # noqa: F811
     assert (got == want).all() and (c == wc).all() and (s.view(np.uint32) == ws.view(np.uint32)).all()
 
 
-@pytest.mark.parametrize("n,P", ((FIVE_PER_CU - 5, 2), (FIVE_PER_CU + 19, 6), (FIVE_PER_CU + 19, 7), (WIDE_ROUND, 2)))
+@pytest.mark.parametrize("n,P", ((FIVE_PER_CU - 5, 2), (FIVE_PER_CU + 19, 6), (FIVE_PER_CU + 19, 7), (WIDE_ROUND, 2),
+                                 (CACHED_OUT // 4, 4), (CACHED_OUT // 4 + 1, 4)))
 def test_kept_wire_around_its_shapes(gpu, oracle, values, n, P):  # noqa: F811
     x = [np.concatenate([values[i % 4], values[(i + 1) % 4]])[:n] for i in range(P)]
     want, wc, ws = oracle.reduce_chain(x, 32, keep_wire=True)
