@@ -157,9 +157,10 @@ inline bool small_semi(int64_t n, int P) { return n <= kSmallElems && n > kSmall
 //             -> 26.1, 39.0 -> 38.8 and 61.5 -> 58.3 us at 6 M elements; 10.3 -> 11.5, 15.4 -> 17.6, 27.1 -> 27.2, 39.7 ->
 //             39.6 and 62.0 -> 60.6 at 6.2 M);
 //   1024 x 1  above: sixteen waves walk one 16 KiB piece of every partial together, each with a single load in flight;
-//   256 x 4   for the chain from 21 M elements on, two waves per SIMD (chain_waves); two pieces of a block per lane
-//             (chain_body_paired) save arithmetic that 1024 x 1 has to spend.  The semi-loop, with its two sums per
-//             element, stays at 1024 x 1 (22 M elements: 61.3 us, 78.5 with 256 x 4 held to two waves).
+//   256 x 4   for the chain from 21 M elements on, two waves per SIMD (chain_waves) with all tiles of one partial after the
+//             other; blocks of 128 and more hold two pieces of a block per lane (chain_body_paired).  Not for few partials
+//             (few_partials): there a workgroup ends soon, and 1024 x 1 overlaps the ends of more of them.  The semi-loop,
+//             with its two sums per element, stays at 1024 x 1 (22 M elements: 61.3 us, 78.5 with 256 x 4 and two waves).
 // Measured on MI355X, us, P = 8, block 256 (semi-loop: P = 7, block 64):
 //     elements      256 x 4   512 x 2   1024 x 1     semi-loop: 256 x 2   512 x 2   1024 x 1
 //     5.0 M           18.1      15.5      17.9                     14.3      14.2      16.1
@@ -183,6 +184,17 @@ constexpr int64_t kFivePerCU = (int64_t)5 * 256 * Shape<256, 2>::kElems;
 constexpr int64_t kOneWideRound = (int64_t)768 * Shape<512, 2>::kElems;
 constexpr int64_t kPairedFrom = (int64_t)2560 * Shape<1024, 1>::kElems;
 
+// Two or three partials, or up to seven of less than 168 M elements in all (not with a kept wire: four of 33.5 M 84.0 us
+// with 256 x 4, 86.4 with 1024 x 1).  Measured on MI355X, us, 256 x 4 -> 1024 x 1, block 32:
+//     elements       P = 2            3               4               5               6                7
+//     21.5 M      23.1 -> 21.3   30.2 -> 27.8    36.4 -> 34.0    42.7 -> 40.6    49.0 -> 47.0     55.6 -> 53.5
+//     33.5 M      33.4 -> 31.3   43.1 -> 40.4    54.0 -> 51.0    63.6 -> 61.6    73.5 -> 73.4     83.3 -> 83.4
+//     60 M        59.7 -> 56.7   77.4 -> 75.6
+inline bool few_partials(int64_t n, int P, bool keeps_wire)
+{
+    return P < 4 || (P < 8 && !keeps_wire && P * n <= 8 * kPairedFrom);
+}
+
 template <typename F>
 void with_chain_shape(int64_t n, int P, bool keeps_wire, F f)
 {
@@ -192,7 +204,7 @@ void with_chain_shape(int64_t n, int P, bool keeps_wire, F f)
         f(Shape<256, 2>{});
     } else if (n <= kOneWideRound && (!keeps_wire || P <= 6)) {
         f(Shape<512, 2>{});
-    } else if (n <= kPairedFrom) {
+    } else if (n <= kPairedFrom || (n < kPieceElems && few_partials(n, P, keeps_wire))) {
         f(Shape<1024, 1>{});
     } else {
         f(Shape<256, 4>{});

@@ -84,6 +84,35 @@ def test_single_launch_around_its_shapes(gpu, oracle, n, flags):  # noqa: F811
     assert (gpu.gpu_variant(x, B, flags) == _oracle_variant(oracle, x, B, flags)).all()
 
 
+@pytest.fixture(scope="module")
+def long_values(gpu):  # noqa: F811
+    rng = np.random.default_rng(78)
+    return [gpu.bf16_of(rng.standard_normal(PAIRED_FROM + 5, dtype=np.float32)) for _ in range(3)]
+
+
+@pytest.mark.parametrize("P,cut", ((3, 0), (7, 0), (8, 0), (8, 5), (8, 5 + 2048 * 3)))
+@pytest.mark.parametrize("B,flags", ((128, 0), (64, eq.RING_ORDER), (128, eq.RING_ORDER | eq.AG_UNQUANTIZED),
+                                     (256, eq.RS_UNQUANTIZED), (32, eq.AG_UNQUANTIZED), (512, eq.RS_UNQUANTIZED | eq.RING_ORDER)))
+def test_longest_messages_by_partials(gpu, oracle, long_values, P, cut, B, flags):  # noqa: F811
+    """256 threads x 4 tiles, with and without two pieces of a block per lane, and what stays below: every flavour."""
+    x = [long_values[i % 3][:PAIRED_FROM + 5 - cut] for i in range(P)]
+    assert (gpu.gpu_variant(x, B, flags) == _oracle_variant(oracle, x, B, flags)).all()
+
+
+@pytest.mark.parametrize("B", (64, 256))
+def test_longest_messages_in_place_and_with_their_wire(gpu, oracle, long_values, B):  # noqa: F811
+    x = [long_values[i % 3] for i in range(8)]
+    want = oracle.reduce_chain(x, B)
+    dev = [gpu.dev_bf16(v) for v in long_values]
+    out = dev[1].clone()
+    eq.equarx_reduce_fused([dev[0], out] + [dev[i % 3] for i in range(2, 8)], B, out)
+    assert (gpu.host_u16(out) == want).all()
+    x = x[:4]
+    want, wc, ws = oracle.reduce_chain(x, B, keep_wire=True)
+    got, c, s = gpu.gpu_chain_fused(x, B)
+    assert (got == want).all() and (c == wc).all() and (s.view(np.uint32) == ws.view(np.uint32)).all()
+
+
 @pytest.mark.parametrize("n", (FIVE_PER_CU, FIVE_PER_CU - 4096 + 37, FIVE_PER_CU + 1))
 @pytest.mark.parametrize("flags", SINGLE)
 def test_single_launch_around_five_workgroups_per_cu(gpu, oracle, n, flags):  # noqa: F811
