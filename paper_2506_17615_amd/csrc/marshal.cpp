@@ -34,6 +34,7 @@ struct Library {
     EQUARX_CALLS(X)
 #undef X
 } lib;
+bool bound = false;
 
 // A tensor whose memory can be handed on as it is.
 const at::Tensor *plain(PyObject *o)
@@ -305,6 +306,10 @@ template <int kArgs, typename F>
 PyObject *enter(PyObject *const *a, Py_ssize_t count, F f)
 {
     int status = kNotPlain;
+    if (!bound) {
+        PyErr_SetString(PyExc_RuntimeError, "not bound to a library");
+        return nullptr;
+    }
     if (count == kArgs) {
         try {
             status = f(a);
@@ -357,6 +362,7 @@ PyObject *bind(PyObject *, PyObject *table)
     EQUARX_CALLS(X)
 #undef X
     lib = found;
+    bound = true;
     Py_RETURN_NONE;
 }
 

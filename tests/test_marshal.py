@@ -1,8 +1,15 @@
 """The binding's native marshalling against the checks in Python: what one accepts and refuses the other does too."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
 from paper_2506_17615_amd import binding as eq
+
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 class Subclass(torch.Tensor):
@@ -91,6 +98,26 @@ def test_host_tensors_are_handed_back(name):
     assert getattr(eq._native, name)(*args[:-1]) == -1
     with pytest.raises(ValueError):
         getattr(eq, name)(*args)
+
+
+def _child(code):
+    """Runs code in an interpreter of its own, on the CPU; what it printed."""
+    env = dict(os.environ, PYTHONPATH=ROOT)
+    run = subprocess.run([sys.executable, "-W", "always", "-c", code], env=env, capture_output=True, text=True, timeout=300, cwd=ROOT)
+    assert run.returncode == 0, run.stdout + run.stderr
+    return run.stdout
+
+
+def test_an_unbound_extension_calls_nothing():
+    assert _child("""
+import torch
+from paper_2506_17615_amd import _marshal
+x = torch.zeros(64, dtype=torch.bfloat16)
+try:
+    print(_marshal.equarx_quantize(x, 32, x, x))
+except RuntimeError as e:
+    print(e)
+""") == "not bound to a library\n"
 
 
 @pytest.mark.gpu
