@@ -11,7 +11,9 @@ fallback: if the HIP library is missing, loading raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -29,6 +31,32 @@ class _Unloaded:
 
 
 _native = _Unloaded()
+
+
+class _PythonOnly:
+    """In the extension's place where there is none for this interpreter and this torch: hands every call to the checks here."""
+
+    def __getattr__(self, name):
+        return lambda *args: -1
+
+
+def _extension(addresses):
+    """The extension, bound to the library; or, with a warning that says why, _PythonOnly."""
+    path = _build.MARSHAL_PATH
+    try:
+        if not os.path.exists(path):
+            raise ImportError(f"{path} is missing: build it (python -m paper_2506_17615_amd.build)")
+        spec = importlib.util.spec_from_file_location(__package__ + "._marshal", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        if module.torch_version != torch.__version__:
+            raise ImportError(f"{path} was built for torch {module.torch_version}, this is {torch.__version__}: build it again")
+        module.bind(addresses)
+        return module
+    except ImportError as e:
+        warnings.warn(f"calls are marshalled in Python, 5 to 11 us each: {e}", RuntimeWarning, stacklevel=3)
+        return _PythonOnly()
+
 
 STATUS_OK = 0
 STATUS_NULL_POINTER = 1
@@ -111,9 +139,8 @@ def load() -> ctypes.CDLL:
             fn = getattr(lib, name)
             fn.restype = res
             fn.argtypes = args
-        from . import _marshal
-        _marshal.bind({name: ctypes.cast(getattr(lib, name), _vp).value for name in SIGNATURES})
-        _lib, _native = lib, _marshal
+        native = _extension({name: ctypes.cast(getattr(lib, name), _vp).value for name in SIGNATURES})
+        _lib, _native = lib, native
     return _lib
 
 

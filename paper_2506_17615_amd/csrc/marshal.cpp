@@ -378,4 +378,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__marshal()
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", EQUARX_TORCH) < 0) Py_CLEAR(m);
+    return m;
+}

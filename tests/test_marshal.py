@@ -2,6 +2,7 @@
 import os
 import subprocess
 import sys
+import sysconfig
 
 import pytest
 import torch
@@ -118,6 +119,70 @@ try:
 except RuntimeError as e:
     print(e)
 """) == "not bound to a library\n"
+
+
+def _load_child(setup):
+    return _child(f"""
+import warnings
+import torch
+from paper_2506_17615_amd import binding as eq, build
+{setup}
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    eq.load()
+    eq.load()
+print([str(w.message).split(": ")[0] for w in seen], eq.num_blocks(1000, 32), eq._native.equarx_quantize(None, 32, None, None))
+try:
+    eq.equarx_quantize(torch.zeros(64, dtype=torch.bfloat16), 32, None, None)
+except ValueError as e:
+    print(str(e).split(":")[0])
+""")
+
+
+@pytest.mark.parametrize("setup", ("build.MARSHAL_PATH += '.gone'", "torch.__version__ = '1.0.0'",
+                                   "build.MARSHAL_PATH = build.LIB_PATH"))
+def test_without_its_extension_the_binding_marshals_in_python(setup):
+    """None there, one for another torch, a file that is none: the library is all a call needs."""
+    assert _load_child(setup) == "['calls are marshalled in Python, 5 to 11 us each'] 32 -1\nx_bf16\n"
+    assert _load_child("") == "[] 32 -1\nx_bf16\n"
+
+
+def test_an_extension_of_another_interpreter_or_compiler_abi_is_stale(monkeypatch):
+    from paper_2506_17615_amd import build
+    assert os.path.basename(build.MARSHAL_PATH) == "_marshal" + sysconfig.get_config_var("EXT_SUFFIX")
+    now = build._marshal_digest()
+    real = sysconfig.get_config_var
+    with monkeypatch.context() as m:
+        m.setattr(sysconfig, "get_config_var", lambda k: "cpython-399" if k == "SOABI" else real(k))
+        assert build._marshal_digest() != now
+    with monkeypatch.context() as m:
+        m.setattr(torch._C, "_GLIBCXX_USE_CXX11_ABI", not torch._C._GLIBCXX_USE_CXX11_ABI)
+        assert build._marshal_digest() != now
+    assert build._marshal_digest() == now
+
+
+def test_only_what_differs_is_built(monkeypatch):
+    from paper_2506_17615_amd import build
+    for library, extension in ((False, False), (True, False), (False, True)):
+        made = []
+        with monkeypatch.context() as m:
+            m.setattr(build, "library_is_stale", lambda: library)
+            m.setattr(build, "extension_is_stale", lambda: extension)
+            m.setattr(build, "_build_library", lambda verbose: made.append("library"))
+            m.setattr(build, "_build_marshal", lambda: made.append("extension"))
+            build.build(force=False)
+        assert made == ["library"] * library + ["extension"] * extension
+
+
+def test_the_library_needs_no_torch_to_be_built():
+    assert _child("""
+import sys
+sys.modules["torch"] = None
+from paper_2506_17615_amd import build
+build._build_library = lambda verbose: print("library")
+print(build.extension_is_stale())
+build.build()
+""") == "False\nlibrary\ntorch is not installed: the library is built without the binding's extension\n"
 
 
 @pytest.mark.gpu
