@@ -4,7 +4,7 @@ import pytest
 import torch
 
 from paper_2506_17615_amd import binding as eq
-from test_parity_gpu import _oracle_variant, _oracle_variant_strided, gpu  # noqa: F401  (the fixture that loads the library)
+from test_parity_gpu import _oracle_variant, _oracle_variant_strided, _values, gpu  # noqa: F401  (the fixture that loads the library)
 
 pytestmark = pytest.mark.gpu
 
@@ -197,6 +197,23 @@ def test_strided_layouts(gpu, oracle, chunks, minishards, P):  # noqa: F811
             work = eq.alloc_variant_workspace(flags & ~eq.RING_ORDER, P, n, chunks)
             eq.equarx_reduce_variant_hops_strided(dev, chunks, flags, out.fill_(5.0), work)
             assert (gpu.host_u16(out) == want).all(), flags
+
+
+@pytest.mark.parametrize("chunks,minishards", ((32, 17), (64, 17), (64, 33), (128, 17)))
+@pytest.mark.parametrize("kind", ("sparse", "tiny", "huge"))
+def test_strided_layouts_above_the_small_ones_with_extreme_values(gpu, oracle, chunks, minishards, kind):  # noqa: F811
+    """Signed zeros, scales at the ends of the range, and an output that is one of the partials."""
+    n, P = 1024 * chunks * minishards, 4
+    x = [gpu.bf16_of(_values(kind, n, 60 + p)) for p in range(P)]
+    for flags in (0, eq.AG_UNQUANTIZED, eq.SEMI_LOOP, eq.SEMI_LOOP | eq.RING_ORDER | eq.AG_UNQUANTIZED):
+        want = _oracle_variant_strided(oracle, x, chunks, flags)
+        dev = [gpu.dev_bf16(p) for p in x]
+        eq.equarx_reduce_variant_strided(dev, chunks, flags, dev[1])
+        assert (gpu.host_u16(dev[1]) == want).all(), flags
+        dev[1] = gpu.dev_bf16(x[1])
+        work = eq.alloc_variant_workspace(flags & ~eq.RING_ORDER, P, n, chunks)
+        eq.equarx_reduce_variant_hops_strided(dev, chunks, flags, dev[2], work)
+        assert (gpu.host_u16(dev[2]) == want).all(), flags
 
 
 SMALL = 768 * 2048              # single-launch calls of few partials: up to here the batched kernel

@@ -210,8 +210,8 @@ def test_chain_parity_heavy_tails(gpu, oracle, B):
 
 @pytest.mark.parametrize("tiles", (513, 600, 2048, 2049, 2300))
 def test_chain_parity_kernel_shapes(gpu, oracle, tiles):
-    """The single-launch chain picks its kernel by message size (small / one tile per thread / several):
-    lengths on both sides of the two thresholds, ragged, with the wire kept."""
+    """The single-launch chain picks its kernel by message size: lengths below and above one round of workgroups
+    (one tile per thread, two), ragged, with the wire kept."""
     n, B = 2048 * tiles - 2048 + 1500 + 3, 128
     parts = [gpu.bf16_of(_values("lognormal", n, 700 + p)) for p in range(3)]
     oracle.set_threads(8)
@@ -680,7 +680,7 @@ def test_variant_parity(gpu, oracle, name):
 
 
 def test_variant_parity_large_message(gpu, oracle):
-    """Above the size where the chain kernels switch to several tiles per thread."""
+    """Above one round of workgroups, where the chain kernels take two tiles per thread."""
     P, n, B = 3, 2048 * 2100 + 2048 * 2 + 24, 256
     parts = [gpu.bf16_of(_values("normal", n, 1300 + p)) for p in range(P)]
     oracle.set_threads(8)
@@ -886,8 +886,7 @@ def test_side_stream_and_repetition(gpu, oracle):
 @pytest.mark.parametrize("tiles", (3, 700, 2100))
 def test_in_place_output(gpu, oracle, tiles):
     """The output may be one of the partials (an AllReduce is usually called in place): every schedule, each of
-    the single-launch kernel shapes (small / one tile per thread / several, paired), output = first, middle and
-    last partial."""
+    them at small_kernel's sizes and with two tiles per thread, output = first, middle and last partial."""
     n, B, P = 2048 * tiles - 700, 128, 4
     host = [gpu.bf16_of(_values("lognormal", n, 8100 + p)) for p in range(P)]
     oracle.set_threads(8)

@@ -100,3 +100,32 @@ print({CLEAN!r})
     run = _child(code, runtimes[0])
     assert run.returncode == 0 and CLEAN in run.stdout, run.stdout[-2000:] + run.stderr[-4000:]
     assert "ERROR: AddressSanitizer" not in run.stderr and "runtime error:" not in run.stderr, run.stderr[-4000:]
+
+
+def test_the_bindings_extension_under_asan_and_ubsan(tmp_path):
+    """Every altered call of the marshalling tests, with host tensors: checked by the extension, then handed back."""
+    runtime = subprocess.run(["gcc", "-print-file-name=libasan.so"], capture_output=True, text=True).stdout.strip()
+    if not os.path.isabs(runtime) or not os.path.exists(runtime):
+        pytest.skip("gcc's AddressSanitizer runtime is not installed")
+    lib = str(tmp_path / os.path.basename(build.MARSHAL_PATH))
+    cmd = build._marshal_command()
+    cmd[cmd.index(build.MARSHAL_PATH)] = lib
+    made = subprocess.run(cmd + ["-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined"],
+                          capture_output=True, text=True)
+    assert made.returncode == 0, made.stderr[-3000:]
+    code = f"""
+from paper_2506_17615_amd import binding as eq, build
+build.MARSHAL_PATH = {lib!r}
+eq.load()
+assert eq._native.__file__ == {lib!r}
+import test_marshal
+for name in test_marshal.NAMES:
+    args, _ = test_marshal._calls("cpu")[name]
+    call = getattr(eq._native, name)
+    assert call(*args) == call(*args[:-1]) == call() == -1
+    assert all(call(*bad) == -1 for bad in test_marshal._altered(args))
+print({CLEAN!r})
+"""
+    run = _child(code, runtime)
+    assert run.returncode == 0 and CLEAN in run.stdout, run.stdout[-2000:] + run.stderr[-4000:]
+    assert "ERROR: AddressSanitizer" not in run.stderr and "runtime error:" not in run.stderr, run.stderr[-4000:]
