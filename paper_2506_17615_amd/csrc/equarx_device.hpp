@@ -309,10 +309,11 @@ __device__ __forceinline__ void store_i8x8(int8_t *p, int64_t base, int off, int
     }
 }
 
-// The output of the single-launch kernels is either streamed (non-temporal, straight to memory) or cached: written
-// through L2 (sc0 sc1) so that it stays in the 256 MB Infinity Cache, where the next kernel that reads it, or the next call
-// that writes the same buffer, finds it; worth it while the output is a modest part of that cache.  Measured on
-// MI355X, P = 8, us streamed -> cached: three output buffers in turn 23.0 -> 22.6 (7.9 M elements), 61.8 -> 60.1
+// The output of chain_kernel and semi_kernel is, for full workgroups, either streamed (non-temporal, straight to memory)
+// or cached: written through L2 (sc0 sc1) so that it stays in the 256 MB Infinity Cache, where the next kernel that reads
+// it, or the next call that writes the same buffer, finds it; worth it while the output is a modest part of that cache.
+// small_kernel, the strided chain (cached 64.6 us instead of 63.9 at the 27B shape) and the end of a message stream.
+// Measured on MI355X, P = 8, us streamed -> cached: three output buffers in turn 23.0 -> 22.6 (7.9 M elements), 61.8 -> 60.1
 // (22 M), 96.4 -> 92.3 (33.5 M), 131.4 -> 125.8 (44 M), 176.9 -> 182.4 (60 M); nine in turn, so that none is found
 // again, 23.4 -> 23.0, 62.5 -> 62.5, 97.0 -> 96.2, 132.0 -> 132.3, 179.0 -> 181.4.
 constexpr int64_t kCachedOutElems = (int64_t)32 << 20;      // 64 MiB of bf16, a quarter of the cache
@@ -923,10 +924,9 @@ __device__ __forceinline__ void hop_tiles(float (&t)[K][8], const u32x4 (&x)[K],
 // Per tile the only state carried from hop to hop is the fp32 sum t.  Each hop
 // loads its partial and then computes; the quantization of the running sum
 // does not need the new data and runs while it arrives.  Starting the loads a
-// hop (or several) ahead was measured and is SLOWER on MI355X (63 -> 67..72 us
-// at the 27B-shaped size): with two waves per SIMD and four 16-byte loads
-// per lane in flight the memory system is already saturated, and more
-// outstanding requests only lengthen its queues.
+// hop (or several) ahead was measured with four tiles per thread and is SLOWER
+// on MI355X (63 -> 67..72 us at the 27B-shaped size): the memory system is
+// saturated as it is, and more outstanding requests only lengthen its queues.
 template <int B, int T, int K, bool kRS, bool kAG, bool kWire, bool kFull>
 __device__ __forceinline__ void chain_body(const PartialTable &tab, int P, int rot, int64_t n,
                                            uint16_t *out, int8_t *__restrict__ wire_codes,
@@ -968,7 +968,7 @@ __device__ __forceinline__ void chain_body_paired(const PartialTable &tab, int P
                                                   uint16_t *out, int64_t wg_at, bool cached)
 {
     constexpr int Gh = B / 16;                      // lanes per block
-    constexpr int kPairElems = 2 * tile_elems<T>;      // 4096 elements per pair of pieces
+    constexpr int kPairElems = 2 * tile_elems<T>;      // the workgroup's pairs of pieces: 16 T elements
     const int lane_off = (threadIdx.x / Gh) * B + (threadIdx.x % Gh) * kLaneElems;
     float t[K2][2][8];
     u32x4 x0[K2][2], xv[K2][2];
@@ -1083,9 +1083,16 @@ __device__ __forceinline__ Span workgroup_span(int64_t n, int64_t shard_elems, i
 
 // Waves per SIMD the compiler may plan for.  The shape for the largest messages is held to two, of the five its
 // registers would allow: eight tiles of one partial after the other are enough requests in flight, and the fewer
-// places of memory are read at once the better they stream.  Measured on MI355X, P = 8, us with five / four / three /
-// two / one: 255.9 / 258.2 / 258.8 / 247.5 / 332 at 88 M elements, 93.7 / 91.0 / 91.9 / 90.0 / 139 at 33.5 M; 6 tiles
-// or 512 threads under the same cap 264 at 88 M, 3 tiles 264, 8 tiles and one wave 252.
+// places of memory are read at once the better they stream.  Measured on MI355X, P = 8, block 256, us with five / four /
+// three / two / one: 255.9 / 258.2 / 258.8 / 247.5 / 332 at 88 M elements, 93.7 / 91.0 / 91.9 / 90.0 / 139 at 33.5 M; 6
+// tiles or 512 threads under the same cap 264 at 88 M, 3 tiles 264, 8 tiles and one wave 252.  The other flavours, with
+// all the registers allow -> with two (and 1024 x 1 instead):
+//                                    22 M                   33.5 M                    88 M
+//     block 32                62.2 -> 62.8 (60.9)     94.0 ->  91.3 (93.2)    262.9 -> 246.5 (260.6)
+//     block 64, ring order    62.1 -> 62.6 (61.1)     94.1 ->  91.1 (91.8)    261.0 -> 245.2 (258.7)
+//     block 64, kept wire    107.6 -> 106.1 (106.6)  164.1 -> 162.6 (165.7)   431.4 -> 422.9 (429.8)
+//     block 64, RS in fp32    62.6 -> 62.5 (61.1)     93.8 ->  90.9 (91.8)    264.4 -> 252.4 (260.0)
+//     block 256, AG in bf16   62.1 -> 61.1 (61.4)     93.9 ->  89.6 (91.5)    261.5 -> 244.3 (257.4)
 constexpr int chain_waves(int K) { return K == 4 ? 2 : 8; }
 
 template <int B, int T, int K, bool kRS, bool kAG, bool kWire>
