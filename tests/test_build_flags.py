@@ -75,3 +75,14 @@ def test_the_loop_of_the_128_chunk_chain_keeps_its_alignment(device_asm):
         body = re.search(r"^_ZN6equarx\d+chain_strided_kernelILi8ELi2ELi8ELb0ELb1ELb" + ag + r"E\S*:(.*?)^\.Lfunc_end",
                          device_asm["equarx_api.hip"], flags=re.M | re.S).group(1)
         assert len(re.findall(r"\.p2align\s+3\n", body)) == 1
+
+
+def test_a_wire_that_leaves_is_stored_with_its_hint(device_asm):
+    """The per-step kernels' code stores, of whole tiles and of the end of a message, are non-temporal at every shape."""
+    bodies = re.findall(r"^(_ZN6equarx\d+(?:(?:quantize|hop|quantize_batch)_kernelILi\d+ELi[12]ELb1E|"
+                        r"flat_kernelILi\d+ELi[12]ELi\dELb[01]ELb1ELb1ELb1E)\S*):(.*?)^\.Lfunc_end",
+                        device_asm["equarx_api.hip"], flags=re.M | re.S)
+    assert len(bodies) == 5 * (3 * 2 + 2 * 4)
+    for name, body in bodies:
+        stores = [line for line in body.splitlines() if re.search(r"(global|buffer)_store_dwordx2", line)]
+        assert len(stores) >= 2 and all(line.split(";")[0].rstrip().endswith(" nt") for line in stores), name
