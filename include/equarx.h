@@ -142,8 +142,10 @@ int equarx_reduce_stage(const int8_t *codes_in, const float *scales_in, const vo
  *                   coinciding with it is rejected (EQUARX_BAD_SHAPE).  The
  *                   same holds for every chain entry point below.
  *   workspace       device, at least equarx_workspace_bytes(P, n, block)
- *                   bytes, 256-byte aligned; holds the two ping-pong wire
- *                   buffers.  Not needed (may be NULL) when both wire_* are given.
+ *                   bytes, 256-byte aligned; holds the wire, which the hops
+ *                   rewrite in place (its contents after the call are
+ *                   unspecified).  Not needed (may be NULL) when both wire_*
+ *                   are given.
  *   wire_codes      NULL, or device int8 [P][equarx_wire_row_codes(n)]:
  *                   receives the codes on the wire after every quantization
  *                   (row i = c_i in its first n entries; rows are padded so
@@ -160,7 +162,7 @@ int equarx_reduce_quantized(const void *const *partials_bf16, int32_t P, int64_t
  * equarx_reduce_quantized for callers that cannot allocate device memory and
  * have no workspace to hand in: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same kernels, same P+1 launches,
- * same bits; the two ping-pong wire buffers live in a static device array of
+ * same bits; the wire lives in a static device array of
  * EQUARX_STATIC_WORKSPACE_BYTES that each GPU the library runs on holds from
  * the moment the library is loaded there until the process ends.  The call
  * allocates and frees nothing, on the device or through any library.
@@ -271,9 +273,7 @@ int equarx_reduce_variant(const void *const *partials_bf16, int32_t P, int64_t n
  *           of every shard advance one device per launch, as both directions
  *           of a ring do -- then the owners' launch: P/2 + 1 launches.
  *   workspace  equarx_variant_workspace_bytes(flags, P, n, block) bytes, 256-byte
- *           aligned (the semi-loop keeps one chain's last wire while the other
- *           chain runs: three wire buffers instead of two; in ring order each
- *           direction ping-pongs between two of its own: four).
+ *           aligned (more for the semi-loop, and more again in ring order).
  * Other arguments as for equarx_reduce_quantized (out_bf16 may be a partial).
  */
 int equarx_reduce_variant_hops(const void *const *partials_bf16, int32_t P, int64_t n, int32_t block,

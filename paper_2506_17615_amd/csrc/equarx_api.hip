@@ -57,49 +57,52 @@ void launch_head(const uint16_t *x0, const uint16_t *x1, int64_t n, int8_t *cout
 
 template <int B>
 void launch_tail(const int8_t *cin, const float *sin, const uint16_t *x, int64_t n, uint16_t *out, LaunchCtx &ctx,
-                 bool ag = true)
+                 bool ag, bool backward)
 {
     in_pieces(n, [&](int64_t at, int64_t m) {
         with_pass_shape(m, [&](auto shape) {
             using S = decltype(shape);
             ctx.launch(ag ? tail_kernel<B, S::K, true> : tail_kernel<B, S::K, false>, grid_for<S>(m), S::T, cin + at,
-                       sin + at / B, x + at, m, out + at, blocks_of(m, B));
+                       sin + at / B, x + at, m, out + at, mirrored<S>(m, backward));
         });
     });
 }
 
-// P >= 3: [Q_B(x_0) + hop 1], hops 2 .. P-2, [hop P-1 + quantize/dequantize pair]; c_i lives in wire buffer i & 1.
+// P >= 3: [Q_B(x_0) + hop 1], hops 2 .. P-2, [hop P-1 + quantize/dequantize pair]
 template <int B>
-void launch_fused_ends(const PartialTable &tab, int P, int64_t n, int8_t *const (&c)[2], float *const (&s)[2],
-                       uint16_t *out, LaunchCtx &ctx)
+void launch_fused_ends(const PartialTable &tab, int P, int64_t n, int8_t *c, float *s, uint16_t *out, LaunchCtx &ctx)
 {
-    launch_head<B>(tab.x[0], tab.x[1], n, c[1], s[1], ctx);
-    for (int i = 2; i + 1 < P; ++i) launch_hop<B>(c[(i - 1) & 1], s[(i - 1) & 1], tab.x[i], n, c[i & 1], s[i & 1], ctx);
-    launch_tail<B>(c[(P - 2) & 1], s[(P - 2) & 1], tab.x[P - 1], n, out, ctx);
+    launch_head<B>(tab.x[0], tab.x[1], n, c, s, ctx);
+    for (int i = 2; i + 1 < P; ++i) launch_hop<B>(c, s, tab.x[i], n, c, s, ctx, false, walks_back(n, i - 1));
+    launch_tail<B>(c, s, tab.x[P - 1], n, out, ctx, true, walks_back(n, P - 2));
+}
+
+// Workgroups per shard of a launch in the ring layout, one grid row per shard (wire_elems: see walks_back).
+template <typename S>
+inline unsigned ring_grid(int64_t shard_elems, int64_t wire_elems)
+{
+    return wire_elems >= kTurnFrom ? (unsigned)ring_groups<S>(shard_elems) : grid_for<S>(shard_elems);
 }
 
 // Full loop in ring order, hop by hop: P launches, each over all P shards (one grid row per shard).
 template <int B>
-void launch_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, int8_t *const (&c)[3], float *const (&s)[3],
-                      uint16_t *out, LaunchCtx &ctx)
+void launch_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, int8_t *c, float *s, uint16_t *out,
+                      LaunchCtx &ctx)
 {
     const int64_t nb = blocks_of(n, B);
     const int64_t shard_elems = (nb + P - 1) / P * B;       // ceil(nb / P) blocks per shard, as the single launch
     const unsigned gy = (unsigned)P;
     with_pass_shape(n, [&](auto shape) {
         using S = decltype(shape);
-        const unsigned gx = grid_for<S>(shard_elems);
-        ctx.launch2d(quantize_ring_kernel<B, S::K>, gx, gy, S::T, P, n, shard_elems, c[0], s[0], tab);
+        const unsigned gx = ring_grid<S>(shard_elems, n);
+        ctx.launch2d(quantize_ring_kernel<B, S::K>, gx, gy, S::T, P, n, shard_elems, c, s, tab);
         for (int i = 1; i + 1 < P; ++i) {
-            ctx.launch2d(hop_ring_kernel<B, S::K>, gx, gy, S::T, c[(i - 1) & 1], s[(i - 1) & 1], P, i, n,
-                         shard_elems, c[i & 1], s[i & 1], tab);
+            ctx.launch2d(hop_ring_kernel<B, S::K>, gx, gy, S::T, c, s, P, i, n, shard_elems, c, s, tab);
         }
         if (ag) {
-            ctx.launch2d(tail_ring_kernel<B, S::K, true>, gx, gy, S::T, c[(P - 2) & 1], s[(P - 2) & 1], P, P - 1,
-                         n, shard_elems, out, tab);
+            ctx.launch2d(tail_ring_kernel<B, S::K, true>, gx, gy, S::T, c, s, P, P - 1, n, shard_elems, out, tab);
         } else {
-            ctx.launch2d(tail_ring_kernel<B, S::K, false>, gx, gy, S::T, c[(P - 2) & 1], s[(P - 2) & 1], P,
-                         P - 1, n, shard_elems, out, tab);
+            ctx.launch2d(tail_ring_kernel<B, S::K, false>, gx, gy, S::T, c, s, P, P - 1, n, shard_elems, out, tab);
         }
     });
 }
@@ -325,7 +328,8 @@ void with_flat_shape(int64_t n, int R, F f)
 
 // The owner's launch of a semi-loop: at most two wires, from this device, kept cacheable.
 template <int B>
-void launch_flat_owner(const uint16_t *local, const WireTable &tab, int R, int64_t n, uint16_t *out, LaunchCtx &ctx, bool ag)
+void launch_flat_owner(const uint16_t *local, const WireTable &tab, int R, int64_t n, uint16_t *out, LaunchCtx &ctx, bool ag,
+                       bool backward)
 {
     with_flat_shape(n, 2, [&](auto shape, auto batch) {
         using S = decltype(shape);
@@ -333,10 +337,10 @@ void launch_flat_owner(const uint16_t *local, const WireTable &tab, int R, int64
         if constexpr (U <= 2) {
             if (ag) {
                 ctx.launch(flat_kernel<B, S::K, U, true, false, true, false>, grid_for<S>(n), S::T, local, R, n, out,
-                           nullptr, nullptr, blocks_of(n, B), tab);
+                           nullptr, nullptr, mirrored<S>(n, backward), tab);
             } else {
                 ctx.launch(flat_kernel<B, S::K, U, true, false, false, false>, grid_for<S>(n), S::T, local, R, n, out,
-                           nullptr, nullptr, blocks_of(n, B), tab);
+                           nullptr, nullptr, mirrored<S>(n, backward), tab);
             }
         }
     });
@@ -369,7 +373,7 @@ void launch_flat(const uint16_t *local, const WireTable &tab, int R, int64_t n, 
             ctx.launch(o && co ? flat_kernel<B, S::K, U, true, true, true, kStream>
                        : o     ? flat_kernel<B, S::K, U, true, false, true, kStream>
                                : flat_kernel<B, S::K, U, false, true, true, kStream>,
-                       grid_for<S>(m), S::T, local + at, R, m, o, co, so, blocks_of(m, B), part);
+                       grid_for<S>(m), S::T, local + at, R, m, o, co, so, 0, part);
         });
     });
 }
@@ -401,11 +405,11 @@ inline int fill_table(const void *const *partials_bf16, int32_t P, int64_t n, Al
     return EQUARX_OK;
 }
 
-// The two (semi-loop: three, semi-loop in ring order: four) wire buffers inside a workspace: codes, then scales, each part rounded up to
-// the workspace alignment.
+// The two wire buffers at the front of a workspace: codes, then scales, each part rounded up to the workspace alignment.
+// A chain rewrites one of them in place; the two chains of a semi-loop take one each.
 struct WireBuffers {
-    int8_t *c[4];
-    float *s[4];
+    int8_t *c[2];
+    float *s[2];
 };
 
 inline WireBuffers carve_workspace(void *workspace, int64_t n, int64_t scales_count)
@@ -414,7 +418,7 @@ inline WireBuffers carve_workspace(void *workspace, int64_t n, int64_t scales_co
     const size_t scales = round_up((size_t)scales_count * sizeof(float), kWorkspaceAlign);
     char *w = static_cast<char *>(workspace);
     WireBuffers b;
-    for (int i = 0; i < 4; ++i) {       // pairs beyond the second exist only in the semi-loop's larger workspaces
+    for (int i = 0; i < 2; ++i) {
         b.c[i] = reinterpret_cast<int8_t *>(w + (size_t)i * (codes + scales));
         b.s[i] = reinterpret_cast<float *>(w + (size_t)i * (codes + scales) + codes);
     }
@@ -422,8 +426,7 @@ inline WireBuffers carve_workspace(void *workspace, int64_t n, int64_t scales_co
 }
 
 // Semi-loop in ring order, hop by hop: h = P/2 launches in which both chains of every shard advance one device
-// (grid row = shard, grid layer = direction), then the owners' launch.  Wire buffers: direction d ping-pongs between
-// buffers 2d and 2d + 1.
+// (grid row = shard, grid layer = direction), then the owners' launch.  Direction d rewrites wire buffer d in place.
 template <int B>
 void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, const WireBuffers &w, uint16_t *out,
                            LaunchCtx &ctx)
@@ -432,18 +435,12 @@ void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, c
     const int64_t shard_elems = (nb + P - 1) / P * B;       // ceil(nb / P) blocks per shard, as the single launch
     const unsigned gy = (unsigned)P;
     const int h = P / 2, count[2] = {P - 1 - h, h};
+    const WirePair wire = {{w.c[0], w.c[1]}, {w.s[0], w.s[1]}};
     for (int t = 0; t < h; ++t) {
-        WirePair in, to;
-        for (int d = 0; d < 2; ++d) {
-            in.codes[d] = w.c[2 * d + ((t + 1) & 1)];
-            in.scales[d] = w.s[2 * d + ((t + 1) & 1)];
-            to.codes[d] = w.c[2 * d + (t & 1)];
-            to.scales[d] = w.s[2 * d + (t & 1)];
-        }
         with_pass_shape(2 * n, [&](auto shape) {        // two shards' worth of work per shard: one per direction
             using S = decltype(shape);
-            ctx.launch3d(semi_ring_step_kernel<B, S::K>, grid_for<S>(shard_elems), gy, 2u, S::T, P, t, n, shard_elems,
-                         in, to, tab);
+            ctx.launch3d(semi_ring_step_kernel<B, S::K>, ring_grid<S>(shard_elems, 2 * n), gy, 2u, S::T, P, t, n, shard_elems,
+                         wire, tab);
         });
     }
     WireTable wires;
@@ -454,14 +451,14 @@ void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, c
     int received = 0;
     for (int d = 0; d < 2; ++d) {       // counter-clockwise first, as the single launch adds them
         if (count[d] == 0) continue;
-        wires.codes[received] = w.c[2 * d + ((count[d] - 1) & 1)];
-        wires.scales[received] = w.s[2 * d + ((count[d] - 1) & 1)];
+        wires.codes[received] = w.c[d];
+        wires.scales[received] = w.s[d];
         ++received;
     }
     with_flat_shape(n, 2, [&](auto shape, auto batch) {
         using S = decltype(shape);
         constexpr int U = decltype(batch)::value;
-        const unsigned gx = grid_for<S>(shard_elems);
+        const unsigned gx = ring_grid<S>(shard_elems, 2 * n);
         if constexpr (U <= 2) {
             if (ag) {
                 ctx.launch2d(semi_ring_owner_kernel<B, S::K, U, true>, gx, gy, S::T, P, n, shard_elems, received, out, wires, tab);
@@ -830,7 +827,7 @@ int equarx_reduce_quantized(const void *const *partials_bf16, int32_t P, int64_t
     mem.writes(out_bf16, (size_t)n * 2, kInPlace);
     const int64_t nb = blocks_of(n, block);
     WireBuffers w{};
-    int64_t c_step = 0, s_step = 0;     // distance between successive wire rows when they are kept
+    int64_t c_step = 0, s_step = 0;     // from one wire to the next: rows when they are kept, in place otherwise
     if (keep_wire) {
         if (misaligned(wire_codes, kAlign) || misaligned(wire_scales, kAlign)) return EQUARX_MISALIGNED;
         c_step = equarx_wire_row_codes(n);
@@ -846,17 +843,17 @@ int equarx_reduce_quantized(const void *const *partials_bf16, int32_t P, int64_t
     }
     if (int st = mem.check()) return st;
 
-    int8_t *c_prev = keep_wire ? wire_codes : w.c[0];
-    float *s_prev = keep_wire ? wire_scales : w.s[0];
-    do_quantize(partials_bf16[0], n, block, c_prev, s_prev, ctx);
+    int8_t *c = keep_wire ? wire_codes : w.c[0];
+    float *sc = keep_wire ? wire_scales : w.s[0];
+    do_quantize(partials_bf16[0], n, block, c, sc, ctx);
     for (int32_t i = 1; i < P; ++i) {
-        int8_t *c_next = keep_wire ? wire_codes + i * c_step : w.c[i & 1];
-        float *s_next = keep_wire ? wire_scales + i * s_step : w.s[i & 1];
-        do_hop(c_prev, s_prev, partials_bf16[i], n, block, c_next, s_next, ctx);
-        c_prev = c_next;
-        s_prev = s_next;
+        int8_t *c_next = c + c_step;
+        float *s_next = sc + s_step;
+        do_hop(c, sc, partials_bf16[i], n, block, c_next, s_next, ctx, false, !keep_wire && walks_back(n, i));
+        c = c_next;
+        sc = s_next;
     }
-    do_dequantize(c_prev, s_prev, n, block, out_bf16, ctx);
+    do_dequantize(c, sc, n, block, out_bf16, ctx, false, !keep_wire && walks_back(n, P));
     return ctx.status();
 }
 
@@ -877,14 +874,14 @@ int equarx_reduce_quantized_static(const void *const *partials_bf16, int32_t P, 
     if (int st = mem.check()) return st;
     unsigned char *wire = nullptr;
     if (int st = static_scratch(&wire)) return st;
-    // Nothing in the array has to start at zero: pass 0 writes wire buffer 0 completely before hop 1 reads it,
+    // Nothing in the array has to start at zero: pass 0 writes the wire buffer completely before hop 1 reads it,
     // and every later hop reads only what the launch before it wrote.
     const WireBuffers w = carve_workspace(wire, n, blocks_of(n, block));
     do_quantize(partials_bf16[0], n, block, w.c[0], w.s[0], ctx);
     for (int32_t i = 1; i < P; ++i) {
-        do_hop(w.c[(i - 1) & 1], w.s[(i - 1) & 1], partials_bf16[i], n, block, w.c[i & 1], w.s[i & 1], ctx);
+        do_hop(w.c[0], w.s[0], partials_bf16[i], n, block, w.c[0], w.s[0], ctx, false, walks_back(n, i));
     }
-    do_dequantize(w.c[(P - 1) & 1], w.s[(P - 1) & 1], n, block, out_bf16, ctx);
+    do_dequantize(w.c[0], w.s[0], n, block, out_bf16, ctx, false, walks_back(n, P));
     return ctx.status();
 }
 
@@ -917,9 +914,7 @@ int equarx_reduce_quantized_fused_ends(const void *const *partials_bf16, int32_t
     mem.writes(workspace, need);
     if (int st = mem.check()) return st;
     const WireBuffers w = carve_workspace(workspace, n, blocks_of(n, block));
-    int8_t *const c[2] = {w.c[0], w.c[1]};
-    float *const s[2] = {w.s[0], w.s[1]};
-#define CALL(BB) launch_fused_ends<BB>(tab, P, n, c, s, out, ctx)
+#define CALL(BB) launch_fused_ends<BB>(tab, P, n, w.c[0], w.s[0], out, ctx)
     EQUARX_DISPATCH_BLOCK(block, CALL)
 #undef CALL
     return ctx.status();
@@ -992,8 +987,8 @@ size_t equarx_variant_workspace_bytes(uint32_t flags, int32_t P, int64_t n, int3
 {
     const size_t two = equarx_workspace_bytes(P, n, block);
     if (!(flags & EQUARX_SEMI_LOOP)) return two;
-    // the semi-loop keeps one chain's wire while the other runs (three buffers); in ring order both chains advance
-    // in the same launch and each ping-pongs between two buffers of its own (four)
+    // sized for two buffers per chain that is under way, and one for a wire that waits: three, in ring order four.  The
+    // chains rewrite one buffer each in place (kTurnFrom), so the launches use the first two.
     return (flags & EQUARX_RING_ORDER) ? two * 2 : two / 2 * 3;
 }
 
@@ -1020,8 +1015,8 @@ int equarx_reduce_variant_hops(const void *const *partials_bf16, int32_t P, int6
     if (int st = mem.check()) return st;
 
     const WireBuffers w = carve_workspace(workspace, n, blocks_of(n, block));
-    int8_t *const c[3] = {w.c[0], w.c[1], w.c[2]};
-    float *const s[3] = {w.s[0], w.s[1], w.s[2]};
+    int8_t *const c = w.c[0];
+    float *const s = w.s[0];
     uint16_t *out = static_cast<uint16_t *>(out_bf16);
 
     if (semi && ring) {     // every launch is one semi-loop iteration of the ring on all P shards, both directions
@@ -1044,9 +1039,9 @@ int equarx_reduce_variant_hops(const void *const *partials_bf16, int32_t P, int6
             return ctx.status();
         }
         // Q_B(x_0), hops 1 .. P-2, then the last hop with or without the all-gather's quantize/dequantize pair
-        do_quantize(tab.x[0], n, block, c[0], s[0], ctx);
-        for (int32_t i = 1; i + 1 < P; ++i) do_hop(c[(i - 1) & 1], s[(i - 1) & 1], tab.x[i], n, block, c[i & 1], s[i & 1], ctx);
-#define CALL(BB) launch_tail<BB>(c[(P - 2) & 1], s[(P - 2) & 1], tab.x[P - 1], n, out, ctx, ag)
+        do_quantize(tab.x[0], n, block, c, s, ctx);
+        for (int32_t i = 1; i + 1 < P; ++i) do_hop(c, s, tab.x[i], n, block, c, s, ctx, false, walks_back(n, i));
+#define CALL(BB) launch_tail<BB>(c, s, tab.x[P - 1], n, out, ctx, ag, walks_back(n, P - 1))
         EQUARX_DISPATCH_BLOCK(block, CALL)
 #undef CALL
         return ctx.status();
@@ -1055,33 +1050,25 @@ int equarx_reduce_variant_hops(const void *const *partials_bf16, int32_t P, int6
     // Semi-loop (Sec. 3.3): partial 0 owns the result; the counter-clockwise chain h+1, ..., P-1 and the clockwise
     // chain h, h-1, ..., 1 each run hop by hop and end in a wire the owner receives; the owner adds them to its
     // own shard, counter-clockwise first.
-    const int32_t h = P / 2, na = P - 1 - h, nbk = h;
+    const int32_t h = P / 2, count[2] = {P - 1 - h, h};
     WireTable wires;
     for (int32_t r = 0; r < kMaxPartials; ++r) {
         wires.codes[r] = nullptr;
         wires.scales[r] = nullptr;
     }
     int32_t received = 0;
-    int last_a = -1;
-    if (na > 0) {
-        do_quantize(tab.x[h + 1], n, block, c[0], s[0], ctx);
-        for (int32_t k = 1; k < na; ++k) do_hop(c[(k - 1) & 1], s[(k - 1) & 1], tab.x[h + 1 + k], n, block, c[k & 1], s[k & 1], ctx);
-        last_a = (na - 1) & 1;
-        wires.codes[received] = c[last_a];
-        wires.scales[received] = s[last_a];
-        ++received;
-    }
-    if (nbk > 0) {
-        const int u[2] = {last_a == 0 ? 1 : 0, 2};      // two buffers that do not hold the first chain's wire
-        do_quantize(tab.x[h], n, block, c[u[0]], s[u[0]], ctx);
-        for (int32_t k = 1; k < nbk; ++k) {
-            do_hop(c[u[(k - 1) & 1]], s[u[(k - 1) & 1]], tab.x[h - k], n, block, c[u[k & 1]], s[u[k & 1]], ctx);
+    for (int32_t d = 0; d < 2; ++d) {
+        if (count[d] == 0) continue;
+        const int32_t first = d == 0 ? h + 1 : h, step = d == 0 ? 1 : -1;
+        do_quantize(tab.x[first], n, block, w.c[d], w.s[d], ctx);
+        for (int32_t k = 1; k < count[d]; ++k) {
+            do_hop(w.c[d], w.s[d], tab.x[first + k * step], n, block, w.c[d], w.s[d], ctx, false, walks_back(n, k));
         }
-        wires.codes[received] = c[u[(nbk - 1) & 1]];
-        wires.scales[received] = s[u[(nbk - 1) & 1]];
+        wires.codes[received] = w.c[d];
+        wires.scales[received] = w.s[d];
         ++received;
     }
-#define CALL(BB) launch_flat_owner<BB>(tab.x[0], wires, received, n, out, ctx, ag)
+#define CALL(BB) launch_flat_owner<BB>(tab.x[0], wires, received, n, out, ctx, ag, walks_back(n, h))
     EQUARX_DISPATCH_BLOCK(block, CALL)
 #undef CALL
     return ctx.status();
@@ -1271,8 +1258,8 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
     if (int st = mem.check()) return st;
 
     const WireBuffers w = carve_workspace(workspace, n, n / chunks);
-    int8_t *const c[3] = {w.c[0], w.c[1], w.c[2]};
-    float *const s[3] = {w.s[0], w.s[1], w.s[2]};
+    int8_t *const c[2] = {w.c[0], w.c[1]};
+    float *const s[2] = {w.s[0], w.s[1]};
     uint16_t *out = static_cast<uint16_t *>(out_bf16);
     StridedWires wires = {{nullptr, nullptr}, {nullptr, nullptr}};
     // Ring layout: shards of ceil(M / P) whole minishards; every launch is one ring step on all P shards at once,

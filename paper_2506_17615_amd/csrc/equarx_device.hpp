@@ -105,6 +105,47 @@ inline void with_pass_shape(int64_t n, F f)
     }
 }
 
+// The chains that walk their wire through memory, hop by hop, rewrite ONE wire buffer in place, and from kTurnFrom
+// elements of wire on every second launch takes its tiles in the opposite order.  What bounds a hop is what it moves
+// beyond the L2s (8 x 4 MB, write-back, and the lines stay from one launch to the next; workgroup b runs on XCD b % 8,
+// so a tile comes back to the L2 that holds it): with two buffers in turn a message of more than 16 M elements finds
+// nothing of its wire there, with one it finds it up to 28 M, and beyond that a launch that begins where the last one
+// ended still finds the 25 MB written last, where one that begins at the front again has always just lost what it asks
+// for.  Measured on MI355X, us per hop-by-hop chain:
+//     P, elements, block       two buffers    one, always forward    one, turning
+//     6, 4.4 M, 256                28.6              27.7                28.0
+//     8, 12.6 M, 256               72.7              69.9                70.5
+//     8, 16.8 M, 64                98.4              86.9                87.1
+//     8, 22 M, 256                122.5             109.1               108.3
+//     8, 30 M, 256                163.0             152.1               143.3
+//     8, 33.5 M, 32               190.1             189.8               166.9
+//     8, 42 M, 64                 223.9             227.3               206.5
+//     4, 60 M, 256                163.8             164.3               156.7
+//     2, 90 M, 256                139.9             133.5               130.3
+// (Turning with two buffers: no gain.  One buffer, the part past 23 M accessed with non-temporal hints: 148.5 at 30 M,
+// 177.2 at 33.5 M, 165.1 at 60 M.)
+constexpr int64_t kTurnFrom = (int64_t)20 << 20;
+
+__host__ __device__ inline bool walks_back(int64_t wire_elems, int pass) { return wire_elems >= kTurnFrom && (pass & 1) != 0; }
+
+// A launch that walks back takes its workgroups' tiles in groups of eight, the last group first, so that every tile stays
+// on its XCD; what a last, partial group would take stays where it is.  `mirror` is the number of elements in whole groups
+// (mirrored), 0 in a launch that walks forward.
+template <typename S>
+inline int64_t mirrored(int64_t n, bool backward)
+{
+    return backward ? (int64_t)(grid_for<S>(n) & ~7u) * S::kElems : 0;
+}
+
+// The workgroup's first element.
+template <int T, int K>
+__device__ __forceinline__ int64_t first_element(int64_t mirror)
+{
+    constexpr int64_t kSpan = T * K * kLaneElems;
+    const int64_t at = blockIdx.x * kSpan;
+    return at < mirror ? mirror - 8 * kSpan - at + 2 * (int64_t)(blockIdx.x & 7u) * kSpan : at;
+}
+
 // Smallest max-abs that still gets a non-zero scale: 127 * 2^-126, so that
 // scale = absmax/127 stays a normal number and 127/absmax stays finite.
 constexpr float kTinyAbsmax = 127.0f * 1.17549435e-38f;
@@ -628,10 +669,11 @@ __device__ __forceinline__ void hop_body(const int8_t *cin, const float *sin, co
 template <int B, int K, bool kStream = false>
 __global__ __launch_bounds__(pass_threads(K)) void hop_kernel(const int8_t *cin, const float *sin,
                                                        const uint16_t *__restrict__ x, int64_t n,
-                                                       int8_t *cout, float *sout, int64_t nb)
+                                                       int8_t *cout, float *sout, int64_t mirror)
 {
     constexpr int T = pass_threads(K);
-    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
+    const int64_t wg_at = first_element<T, K>(mirror);
+    const int64_t nb = (n + B - 1) / B;
     if (wg_at + tile_elems<T> * K <= n) {
         hop_body<B, T, K, true, kStream>(cin, sin, x, n, cout, sout, nb, wg_at);
     } else {
@@ -679,10 +721,11 @@ __device__ __forceinline__ void dequantize_body(const int8_t *__restrict__ codes
 template <int B, int K, bool kStream = false>
 __global__ __launch_bounds__(pass_threads(K)) void dequantize_kernel(const int8_t *__restrict__ codes,
                                                               const float *__restrict__ scales, int64_t n,
-                                                              uint16_t *__restrict__ out, int64_t nb)
+                                                              uint16_t *__restrict__ out, int64_t mirror)
 {
     constexpr int T = pass_threads(K);
-    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
+    const int64_t wg_at = first_element<T, K>(mirror);
+    const int64_t nb = (n + B - 1) / B;
     if (wg_at + tile_elems<T> * K <= n) {
         dequantize_body<B, T, K, true, kStream>(codes, scales, n, out, nb, wg_at);
     } else {
@@ -871,10 +914,11 @@ __device__ __forceinline__ void tail_body(const int8_t *__restrict__ cin, const 
 template <int B, int K, bool kAG>
 __global__ __launch_bounds__(pass_threads(K)) void tail_kernel(const int8_t *__restrict__ cin, const float *__restrict__ sin,
                                                         const uint16_t *x, int64_t n,      // out may be x (in place)
-                                                        uint16_t *out, int64_t nb)
+                                                        uint16_t *out, int64_t mirror)
 {
     constexpr int T = pass_threads(K);
-    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
+    const int64_t wg_at = first_element<T, K>(mirror);
+    const int64_t nb = (n + B - 1) / B;
     if (wg_at + tile_elems<T> * K <= n) {
         tail_body<B, T, K, kAG, true>(cin, sin, x, n, out, nb, wg_at);
     } else {
@@ -1069,19 +1113,26 @@ struct Span {
     bool any;
 };
 
+// Workgroups per shard in a launch whose shards are walked back (ring layout): whole groups of eight, so that a
+// workgroup's XCD follows from its place in the row whatever the row.
+template <typename S>
+__host__ __device__ inline int64_t ring_groups(int64_t shard_elems) { return ((shard_elems + S::kElems - 1) / S::kElems + 7) & ~(int64_t)7; }
+
+// back: 0, or (ring layout) the number of shards if the launch walks back, the last shard first and each from its end.
 template <int T, int K>
-__device__ __forceinline__ Span workgroup_span(int64_t n, int64_t shard_elems, int rot_bias)
+__device__ __forceinline__ Span workgroup_span(int64_t n, int64_t shard_elems, int rot_bias, int back = 0)
 {
     Span sp;
     int64_t lo = 0;
     sp.hi = n;
     sp.rot = 0;
     if (shard_elems > 0) {
-        lo = (int64_t)blockIdx.y * shard_elems;
+        const int shard = back ? back - 1 - (int)blockIdx.y : (int)blockIdx.y;
+        lo = (int64_t)shard * shard_elems;
         sp.hi = lo + shard_elems < n ? lo + shard_elems : n;
-        sp.rot = (int)blockIdx.y + rot_bias;
+        sp.rot = shard + rot_bias;
     }
-    sp.wg_at = lo + (int64_t)blockIdx.x * (tile_elems<T> * K);
+    sp.wg_at = lo + first_element<T, K>(back ? ring_groups<Shape<T, K>>(shard_elems) * Shape<T, K>::kElems : 0);
     sp.any = sp.wg_at < sp.hi;
     return sp;
 }
@@ -1153,7 +1204,7 @@ __global__ __launch_bounds__(pass_threads(K)) void hop_ring_kernel(const int8_t 
                                                             const PartialTable tab)
 {
     constexpr int T = pass_threads(K);
-    const Span sp = workgroup_span<T, K>(n, shard_elems, 1 + step);    // row + 1 + step < 2P
+    const Span sp = workgroup_span<T, K>(n, shard_elems, 1 + step, walks_back(n, step) ? P : 0);    // row + 1 + step < 2P
     if (!sp.any) return;
     const uint16_t *x = tab.x[sp.rot >= P ? sp.rot - P : sp.rot];
     const int64_t nb = (sp.hi + B - 1) / B;
@@ -1171,7 +1222,7 @@ __global__ __launch_bounds__(pass_threads(K)) void tail_ring_kernel(const int8_t
                                                              const PartialTable tab)
 {
     constexpr int T = pass_threads(K);
-    const Span sp = workgroup_span<T, K>(n, shard_elems, 1 + step);
+    const Span sp = workgroup_span<T, K>(n, shard_elems, 1 + step, walks_back(n, step) ? P : 0);
     if (!sp.any) return;
     const uint16_t *x = tab.x[sp.rot >= P ? sp.rot - P : sp.rot];
     const int64_t nb = (sp.hi + B - 1) / B;
@@ -1418,9 +1469,10 @@ __device__ __forceinline__ void flat_body(const uint16_t *local, const WireTable
 template <int B, int K, int U, bool kOutBf16, bool kOutWire, bool kAG = true, bool kStream = false>
 __global__ __launch_bounds__(pass_threads(K)) void flat_kernel(const uint16_t *local, int R, int64_t n, uint16_t *out,
                                                         int8_t *__restrict__ codes_out, float *__restrict__ scales_out,
-                                                        int64_t nb, const WireTable tab)
+                                                        int64_t mirror, const WireTable tab)
 {
-    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<pass_threads(K)> * K);
+    const int64_t wg_at = first_element<pass_threads(K), K>(mirror);
+    const int64_t nb = (n + B - 1) / B;
     if (wg_at + tile_elems<pass_threads(K)> * K <= n) {
         flat_body<B, K, U, kOutBf16, kOutWire, kAG, true, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
     } else {
@@ -1443,13 +1495,13 @@ struct WirePair {           // one wire buffer per direction
 
 template <int B, int K>
 __global__ __launch_bounds__(pass_threads(K)) void semi_ring_step_kernel(int P, int t, int64_t n, int64_t shard_elems,
-                                                                  const WirePair in, const WirePair out,
-                                                                  const PartialTable tab)
+                                                                  const WirePair wire, const PartialTable tab)
 {
     constexpr int T = pass_threads(K);
-    const Span sp = workgroup_span<T, K>(n, shard_elems, 0);       // rot = the owner's device number
+    const bool backward = walks_back(2 * n, t);                     // two wires
+    const Span sp = workgroup_span<T, K>(n, shard_elems, 0, backward ? P : 0);     // rot = the owner's device number
     if (!sp.any) return;
-    const int dir = blockIdx.z, h = P / 2;
+    const int dir = backward ? 1 - (int)blockIdx.z : (int)blockIdx.z, h = P / 2;
     const int count = dir == 0 ? P - 1 - h : h;                 // devices in this direction's chain
     if (t >= count) return;                                     // the shorter chain has already arrived
     int dev = sp.rot + (dir == 0 ? h + 1 + t : h - t);          // < 2P
@@ -1459,14 +1511,14 @@ __global__ __launch_bounds__(pass_threads(K)) void semi_ring_step_kernel(int P, 
     const bool full = sp.wg_at + tile_elems<T> * K <= sp.hi;
     if (t == 0) {
         if (full) {
-            quantize_body<B, T, K, true>(x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
+            quantize_body<B, T, K, true>(x, sp.hi, wire.codes[dir], wire.scales[dir], nb, sp.wg_at);
         } else {
-            quantize_body<B, T, K, false>(x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
+            quantize_body<B, T, K, false>(x, sp.hi, wire.codes[dir], wire.scales[dir], nb, sp.wg_at);
         }
     } else if (full) {
-        hop_body<B, T, K, true>(in.codes[dir], in.scales[dir], x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
+        hop_body<B, T, K, true>(wire.codes[dir], wire.scales[dir], x, sp.hi, wire.codes[dir], wire.scales[dir], nb, sp.wg_at);
     } else {
-        hop_body<B, T, K, false>(in.codes[dir], in.scales[dir], x, sp.hi, out.codes[dir], out.scales[dir], nb, sp.wg_at);
+        hop_body<B, T, K, false>(wire.codes[dir], wire.scales[dir], x, sp.hi, wire.codes[dir], wire.scales[dir], nb, sp.wg_at);
     }
 }
 
@@ -1478,7 +1530,7 @@ __global__ __launch_bounds__(pass_threads(K)) void semi_ring_owner_kernel(int P,
                                                                    const PartialTable tab)
 {
     constexpr int T = pass_threads(K);
-    const Span sp = workgroup_span<T, K>(n, shard_elems, 0);
+    const Span sp = workgroup_span<T, K>(n, shard_elems, 0, walks_back(2 * n, P / 2) ? P : 0);
     if (!sp.any) return;
     const uint16_t *own = tab.x[sp.rot >= P ? sp.rot - P : sp.rot];
     const int64_t nb = (sp.hi + B - 1) / B;

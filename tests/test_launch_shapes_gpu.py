@@ -12,6 +12,7 @@ FIVE_PER_CU = 5 * 256 * 4096    # single-launch calls: up to here 256 threads x 
 WIDE_ROUND = 768 * 8192         # single-launch calls: up to here 512 threads x 2 tiles, above 1024 x 1
 PAIRED_FROM = 2560 * 8192       # single-launch chain: above, 256 threads x 4 tiles
 CACHED_OUT = 32 << 20           # single-launch calls: up to here the output stays in the Infinity Cache
+TURN_FROM = 20 << 20            # elements of wire: from here every second launch of a hop-by-hop chain walks back
 ONE_ROUND = 2048 * 2048         # elements: up to here one tile of 256 threads per workgroup, above 512 threads x 2 tiles
 
 
@@ -58,6 +59,26 @@ def test_two_directions_around_one_round_of_workgroups(gpu, oracle, values, n): 
     eq.equarx_reduce_variant_hops([gpu.dev_bf16(p) for p in x], 64, flags, out,
                                   eq.alloc_variant_workspace(flags, 4, n, 64))
     assert (gpu.host_u16(out) == _oracle_variant(oracle, x, 64, flags)).all()
+
+
+@pytest.mark.parametrize("n,P,B", ((TURN_FROM - 1, 4, 256), (TURN_FROM, 3, 32), (TURN_FROM + 5 * 8192 + 3, 4, 512),
+                                   (TURN_FROM + 8 * 8192, 5, 64), (TURN_FROM // 2, 5, 128), (TURN_FROM // 2 + 4099, 4, 64)))
+def test_chains_that_turn(gpu, oracle, long_values, n, P, B):  # noqa: F811
+    x = [np.resize(long_values[i % 3], n + i)[i:].copy() for i in range(P)]
+    dev = [gpu.dev_bf16(p) for p in x]
+    out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    want = oracle.reduce_chain(x, B)
+    if n >= TURN_FROM - 1:
+        eq.equarx_reduce_quantized(dev, B, out, eq.alloc_workspace(P, n, B))
+        assert (gpu.host_u16(out) == want).all()
+        eq.equarx_reduce_quantized_static(dev, B, out)
+        assert (gpu.host_u16(out) == want).all()
+        eq.equarx_reduce_quantized_fused_ends(dev, B, out, eq.alloc_workspace(P, n, B))
+        assert (gpu.host_u16(out) == want).all()
+    flavours = (0, eq.AG_UNQUANTIZED | eq.RING_ORDER, eq.SEMI_LOOP) if n >= TURN_FROM - 1 else ()
+    for flags in (*flavours, eq.SEMI_LOOP | eq.RING_ORDER):
+        eq.equarx_reduce_variant_hops(dev, B, flags, out, eq.alloc_variant_workspace(flags, P, n, B))
+        assert (gpu.host_u16(out) == _oracle_variant(oracle, x, B, flags)).all(), flags
 
 
 @pytest.mark.parametrize("n", (ONE_ROUND // 2, ONE_ROUND // 2 + 3))
