@@ -346,8 +346,8 @@ int equarx_reduce_flat(const void *local_bf16, const int8_t *const *codes, const
  *            the same launch), each of them in ring order one ring step on
  *            all P shards at once; workspace of
  *            equarx_variant_workspace_bytes(flags without EQUARX_RING_ORDER,
- *            P, n, chunks) bytes, 256-byte aligned (two wire buffers, three
- *            for the semi-loop); same bits as the single launch.
+ *            P, n, chunks) bytes, 256-byte aligned; same bits as the single
+ *            launch.
  */
 int equarx_quantize_strided(const void *x_bf16, int64_t n, int32_t chunks,
                             int8_t *codes, float *scales, void *stream);

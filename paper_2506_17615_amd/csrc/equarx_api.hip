@@ -506,6 +506,9 @@ constexpr int64_t kStridedMedium = 32;
 
 inline bool strided_small(int64_t n, int32_t chunks) { return n / ((int64_t)kChunk * chunks) <= kStridedSmall; }
 
+// The first workgroups of a grid, in whole groups of eight, that a launch takes in the opposite order (mirrored_place).
+inline unsigned strided_mirror(unsigned grid, bool backward) { return backward ? grid & ~7u : 0; }
+
 inline unsigned strided_small_grid(int64_t n, int32_t chunks)       // of the per-pass kernels
 {
     return (unsigned)(n / ((int64_t)kChunk * chunks) * wave_layout_wgs<4, 8>);
@@ -551,7 +554,7 @@ void do_quantize_strided(const StridedSource &src, int64_t n, int32_t chunks, in
 }
 
 void do_hop_strided(const int8_t *cin, const float *sin, const StridedSource &src, int64_t n, int32_t chunks, int8_t *cout,
-                    float *sout, LaunchCtx &ctx)
+                    float *sout, LaunchCtx &ctx, bool backward = false)
 {
     if (strided_small(n, chunks)) {
 #define CALL(CC) \
@@ -560,13 +563,16 @@ void do_hop_strided(const int8_t *cin, const float *sin, const StridedSource &sr
 #undef CALL
         return;
     }
-#define CALL(CC) ctx.launch(hop_strided_kernel<CC / kChunkGroups>, strided_grid(n, chunks), kThreads, cin, sin, cout, sout, src)
+    const unsigned grid = strided_grid(n, chunks);
+#define CALL(CC)                                                                                             \
+    ctx.launch(hop_strided_kernel<CC / kChunkGroups>, grid, kThreads, cin, sin, cout, sout, strided_mirror(grid, backward), \
+               src)
     EQUARX_DISPATCH_CHUNKS(chunks, CALL)
 #undef CALL
 }
 
 void do_semi_step_strided(const StridedDirections &dirs, const PartialTable &tab, int P, int per_shard, int64_t n,
-                          int32_t chunks, LaunchCtx &ctx)
+                          int32_t chunks, LaunchCtx &ctx, bool backward)
 {
     if (strided_small(n, chunks)) {
 #define CALL(CC)                                                                                                      \
@@ -575,14 +581,16 @@ void do_semi_step_strided(const StridedDirections &dirs, const PartialTable &tab
 #undef CALL
         return;
     }
+    const unsigned count = strided_grid(n, chunks);
 #define CALL(CC)                                                                                                      \
-    ctx.launch2d(semi_step_strided_kernel<CC / kChunkGroups>, strided_grid(n, chunks), 2u, kThreads, P, per_shard, dirs, tab)
+    ctx.launch(semi_step_strided_kernel<CC / kChunkGroups>, 2 * whole_groups(count), kThreads, P, per_shard, count,    \
+               backward, dirs, tab)
     EQUARX_DISPATCH_CHUNKS(chunks, CALL)
 #undef CALL
 }
 
 void do_owner_strided(const StridedSource &own, const StridedWires &wires, int received, int64_t n, int32_t chunks, bool ag,
-                      uint16_t *out, LaunchCtx &ctx)
+                      uint16_t *out, LaunchCtx &ctx, bool backward)
 {
     if (strided_small(n, chunks)) {
 #define CALL(CC)                                                                                                           \
@@ -597,9 +605,9 @@ void do_owner_strided(const StridedSource &own, const StridedWires &wires, int r
     }
 #define CALL(CC)                                                                                                           \
     do {                                                                                                                   \
-        const unsigned grid = strided_grid(n, chunks);                                                                     \
-        if (ag) ctx.launch(owner_strided_kernel<CC / kChunkGroups, true>, grid, kThreads, received, out, wires, own);      \
-        else ctx.launch(owner_strided_kernel<CC / kChunkGroups, false>, grid, kThreads, received, out, wires, own);        \
+        const unsigned grid = strided_grid(n, chunks), mirror = strided_mirror(grid, backward);                            \
+        if (ag) ctx.launch(owner_strided_kernel<CC / kChunkGroups, true>, grid, kThreads, received, mirror, out, wires, own);  \
+        else ctx.launch(owner_strided_kernel<CC / kChunkGroups, false>, grid, kThreads, received, mirror, out, wires, own);    \
     } while (0)
     EQUARX_DISPATCH_CHUNKS(chunks, CALL)
 #undef CALL
@@ -644,13 +652,13 @@ void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chu
 }
 
 void do_dequantize_strided(const int8_t *codes, const float *scales, int64_t n, int32_t chunks, void *out,
-                           LaunchCtx &ctx)
+                           LaunchCtx &ctx, bool backward = false)
 {
     in_pieces(n, [&](int64_t at, int64_t m) {
         with_pass_shape(m, [&](auto shape) {
             using S = decltype(shape);
             ctx.launch(dequantize_strided_kernel<S::K>, grid_for<S>(m), S::T, codes + at, scales + at / chunks, m, (int)chunks,
-                       static_cast<uint16_t *>(out) + at);
+                       static_cast<uint16_t *>(out) + at, mirrored<S>(m, backward));
         });
     });
 }
@@ -1184,9 +1192,9 @@ int equarx_reduce_quantized_strided(const void *const *partials_bf16, int32_t P,
     const WireBuffers w = carve_workspace(workspace, n, n / chunks);
     do_quantize_strided(one_tensor(partials_bf16[0]), n, chunks, w.c[0], w.s[0], ctx);
     for (int32_t i = 1; i < P; ++i) {
-        do_hop_strided(w.c[(i - 1) & 1], w.s[(i - 1) & 1], one_tensor(partials_bf16[i]), n, chunks, w.c[i & 1], w.s[i & 1], ctx);
+        do_hop_strided(w.c[0], w.s[0], one_tensor(partials_bf16[i]), n, chunks, w.c[0], w.s[0], ctx, walks_back(n, i));
     }
-    do_dequantize_strided(w.c[(P - 1) & 1], w.s[(P - 1) & 1], n, chunks, out_bf16, ctx);
+    do_dequantize_strided(w.c[0], w.s[0], n, chunks, out_bf16, ctx, walks_back(n, P));
     return ctx.status();
 }
 
@@ -1277,19 +1285,19 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
         if (P > 1) {
             do_quantize_strided(at(0), n, chunks, c[0], s[0], ctx);
             for (int32_t i = 1; i + 1 < P; ++i) {
-                do_hop_strided(c[(i - 1) & 1], s[(i - 1) & 1], at(i), n, chunks, c[i & 1], s[i & 1], ctx);
+                do_hop_strided(c[0], s[0], at(i), n, chunks, c[0], s[0], ctx, walks_back(n, i));
             }
-            wires.codes[0] = c[(P - 2) & 1];
-            wires.scales[0] = s[(P - 2) & 1];
+            wires.codes[0] = c[0];
+            wires.scales[0] = s[0];
             received = 1;
         }
-        do_owner_strided(at(P - 1), wires, received, n, chunks, ag, out, ctx);
+        do_owner_strided(at(P - 1), wires, received, n, chunks, ag, out, ctx, walks_back(n, P - 1));
         return ctx.status();
     }
 
     // Semi-loop (Sec. 3.3): the owner is position 0; the chain h+1, h+2, ..., P-1 (na sends) and the chain h, h-1,
     // ..., 1 (nb >= na sends) each advance one device per launch, both in the same launch while both are under way
-    // (grid row = chain), each on a wire buffer of its own that its hops rewrite in place; the owner receives the
+    // (half a grid per chain), each on a wire buffer of its own that its hops rewrite in place; the owner receives the
     // shorter chain's wire first.
     const int32_t h = P / 2, na = P - 1 - h, nb = h;
     for (int32_t t = 0; t < nb; ++t) {
@@ -1297,11 +1305,11 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
         dirs.d[0] = {h + 1 + t, t ? c[0] : nullptr, t ? s[0] : nullptr, c[0], s[0]};
         dirs.d[1] = {h - t, t ? c[1] : nullptr, t ? s[1] : nullptr, c[1], s[1]};
         if (t < na) {
-            do_semi_step_strided(dirs, tab, P, per_shard, n, chunks, ctx);
+            do_semi_step_strided(dirs, tab, P, per_shard, n, chunks, ctx, walks_back(2 * n, t));
         } else if (t == 0) {
             do_quantize_strided(around(h), n, chunks, c[1], s[1], ctx);
         } else {
-            do_hop_strided(c[1], s[1], around(h - t), n, chunks, c[1], s[1], ctx);
+            do_hop_strided(c[1], s[1], around(h - t), n, chunks, c[1], s[1], ctx, walks_back(2 * n, t));
         }
     }
     int received = 0;
@@ -1315,7 +1323,7 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
         wires.scales[received] = s[1];
         ++received;
     }
-    do_owner_strided(around(0), wires, received, n, chunks, ag, out, ctx);
+    do_owner_strided(around(0), wires, received, n, chunks, ag, out, ctx, walks_back(2 * n, nb));
     return ctx.status();
 }
 

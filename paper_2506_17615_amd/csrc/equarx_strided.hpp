@@ -40,6 +40,15 @@ constexpr int kChunkGroups = kThreads / kSliceLanes;       // 8 groups of lanes,
 constexpr int kSlicesPerChunk = kChunk / kSlicePos;        // 4 workgroups per minishard
 static_assert(kThreads == 256, "the strided kernels are laid out for 256-thread workgroups");
 
+// A launch that walks back (walks_back): workgroup b of the first `mirror`, a multiple of eight, takes the place of one
+// in the opposite group of eight.  mirror == 0: it walks forward.
+__device__ __forceinline__ unsigned mirrored_place(unsigned b, unsigned mirror)
+{
+    return b < mirror ? mirror - 8 - (b & ~7u) + (b & 7u) : b;
+}
+
+__host__ __device__ inline unsigned whole_groups(unsigned count) { return (count + 7) & ~7u; }
+
 struct StridedSpot {
     int64_t minishard;  // which minishard the workgroup works on
     int64_t elem;       // first element of the lane in chunk `g` of its minishard
@@ -47,13 +56,14 @@ struct StridedSpot {
     int g;              // chunk group
 };
 
-__device__ __forceinline__ StridedSpot strided_spot(int chunks)
+// at: the workgroup's place in the tensor.
+__device__ __forceinline__ StridedSpot strided_spot(int chunks, unsigned at)
 {
     StridedSpot sp;
     const int l = threadIdx.x % kSliceLanes;
     sp.g = threadIdx.x / kSliceLanes;
-    const int64_t ms = blockIdx.x / kSlicesPerChunk;
-    const int pos = (blockIdx.x % kSlicesPerChunk) * kSlicePos + l * kLaneElems;
+    const int64_t ms = at / kSlicesPerChunk;
+    const int pos = (at % kSlicesPerChunk) * kSlicePos + l * kLaneElems;
     sp.minishard = ms;
     sp.elem = ms * ((int64_t)kChunk * chunks) + (int64_t)sp.g * kChunk + pos;
     sp.scale = ms * kChunk + pos;
@@ -159,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void quantize_strided_kernel(int8_t *__re
                                                                     const StridedSource src)
 {
     __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
-    const StridedSpot sp = strided_spot(R * kChunkGroups);
+    const StridedSpot sp = strided_spot(R * kChunkGroups, blockIdx.x);
     quantize_strided_body<R>(strided_source(src, sp.minishard), codes, scales, sp, red);
 }
 
@@ -223,17 +233,18 @@ __device__ __forceinline__ void hop_strided_body(const int8_t *cin, const float 
 
 template <int R>
 __global__ __launch_bounds__(kThreads) void hop_strided_kernel(const int8_t *cin, const float *sin,
-                                                               int8_t *cout, float *sout, const StridedSource src)
+                                                               int8_t *cout, float *sout, unsigned mirror,
+                                                               const StridedSource src)
 {
     __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
-    const StridedSpot sp = strided_spot(R * kChunkGroups);
+    const StridedSpot sp = strided_spot(R * kChunkGroups, mirrored_place(blockIdx.x, mirror));
     hop_strided_body<R>(cin, sin, strided_source(src, sp.minishard), cout, sout, sp, red);
 }
 
-// One iteration of the semi-loop reduce-scatter (Sec. 3.3) on both of its chains at once: grid row 0 advances the
-// chain that walks up from device h+1, row 1 the one that walks down from device h, each by one device -- the
-// first iteration quantizes the chain's first shard (no incoming wire: cin == nullptr), the later ones are hops on
-// the chain's own wire buffer in place.  The two rows share nothing.
+// One iteration of the semi-loop reduce-scatter (Sec. 3.3) on both of its chains at once: the first half of the grid
+// (`count` workgroups, in whole groups of eight) advances the chain that walks up from device h+1, the second the one that
+// walks down from device h, each by one device -- the first iteration quantizes the chain's first shard (no incoming wire: cin == nullptr), the later ones are hops on
+// the chain's own wire buffer in place.  The two halves share nothing.
 struct StridedDirection {
     int offset;             // as StridedSource::offset
     const int8_t *cin;      // nullptr: this is the chain's first device, it only quantizes its shard
@@ -247,12 +258,16 @@ struct StridedDirections {
 };
 
 template <int R>
-__global__ __launch_bounds__(kThreads) void semi_step_strided_kernel(int P, int per_shard, const StridedDirections dirs,
-                                                                     const PartialTable tab)
+__global__ __launch_bounds__(kThreads) void semi_step_strided_kernel(int P, int per_shard, unsigned count, int backward,
+                                                                     const StridedDirections dirs, const PartialTable tab)
 {
     __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
-    const StridedSpot sp = strided_spot(R * kChunkGroups);
-    const StridedDirection d = blockIdx.y == 0 ? dirs.d[0] : dirs.d[1];
+    const unsigned half = whole_groups(count);
+    const unsigned place = mirrored_place(blockIdx.x, backward ? 2 * half : 0);
+    const unsigned at = place < half ? place : place - half;
+    if (at >= count) return;            // uniform over the workgroup
+    const StridedSpot sp = strided_spot(R * kChunkGroups, at);
+    const StridedDirection d = place < half ? dirs.d[0] : dirs.d[1];
     const int j = (per_shard > 0 ? (int)(sp.minishard / per_shard) : 0) + d.offset;     // < 2P
     const uint16_t *x = tab.x[j >= P ? j - P : j];
     if (d.cin == nullptr) {             // uniform over the workgroup
@@ -273,12 +288,12 @@ struct StridedWires {
 };
 
 template <int R, bool kAG>
-__global__ __launch_bounds__(kThreads) void owner_strided_kernel(int received, uint16_t *out,
+__global__ __launch_bounds__(kThreads) void owner_strided_kernel(int received, unsigned mirror, uint16_t *out,
                                                                  const StridedWires wires, const StridedSource src)
 {
     __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
     constexpr int chunks = R * kChunkGroups;
-    const StridedSpot sp = strided_spot(chunks);
+    const StridedSpot sp = strided_spot(chunks, mirrored_place(blockIdx.x, mirror));
     const uint16_t *own = strided_source(src, sp.minishard);
 
     float acc[R][8];
@@ -742,10 +757,10 @@ __global__ __launch_bounds__(kThreads) void owner_strided_small_kernel(int recei
 template <int K>
 __global__ __launch_bounds__(pass_threads(K)) void dequantize_strided_kernel(const int8_t *__restrict__ codes,
                                                                       const float *__restrict__ scales, int64_t n,
-                                                                      int chunks, uint16_t *__restrict__ out)
+                                                                      int chunks, uint16_t *__restrict__ out, int64_t mirror)
 {
     constexpr int T = pass_threads(K);
-    const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
+    const int64_t wg_at = first_element<T, K>(mirror);
     const int lane_at = threadIdx.x * kLaneElems;
     const int64_t minishard = (int64_t)kChunk * chunks;
 #pragma unroll

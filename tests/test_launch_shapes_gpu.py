@@ -220,6 +220,22 @@ def test_strided_layouts(gpu, oracle, chunks, minishards, P):  # noqa: F811
             assert (gpu.host_u16(out) == want).all(), flags
 
 
+@pytest.mark.parametrize("chunks,minishards,P", ((64, 319, 3), (64, 320, 4), (64, 321, 3), (128, 161, 4), (32, 641, 3),
+                                                 (64, 159, 5), (64, 161, 4), (128, 81, 5)))
+def test_strided_chains_that_turn(gpu, oracle, long_values, chunks, minishards, P):  # noqa: F811
+    n = 1024 * chunks * minishards
+    x = [np.resize(long_values[i % 3], n + i)[i:].copy() for i in range(P)]
+    dev = [gpu.dev_bf16(p) for p in x]
+    out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    if n > TURN_FROM // 2 * 3:
+        eq.equarx_reduce_quantized_strided(dev, chunks, out, eq.alloc_workspace(P, n, chunks))
+        assert (gpu.host_u16(out) == oracle.reduce_chain_strided(x, chunks)).all()
+    for flags in (0, eq.RING_ORDER) if n > TURN_FROM // 2 * 3 else (eq.SEMI_LOOP, eq.SEMI_LOOP | eq.RING_ORDER | eq.AG_UNQUANTIZED):
+        work = eq.alloc_variant_workspace(flags & ~eq.RING_ORDER, P, n, chunks)
+        eq.equarx_reduce_variant_hops_strided(dev, chunks, flags, out.fill_(5.0), work)
+        assert (gpu.host_u16(out) == _oracle_variant_strided(oracle, x, chunks, flags)).all(), flags
+
+
 @pytest.mark.parametrize("chunks,minishards", ((32, 17), (64, 17), (64, 33), (128, 17)))
 @pytest.mark.parametrize("kind", ("sparse", "tiny", "huge"))
 def test_strided_layouts_above_the_small_ones_with_extreme_values(gpu, oracle, chunks, minishards, kind):  # noqa: F811
