@@ -164,8 +164,8 @@ __device__ __forceinline__ void quantize_strided_body(const uint16_t *__restrict
 }
 
 template <int R>
-__global__ __launch_bounds__(kThreads) void quantize_strided_kernel(int8_t *__restrict__ codes,
-                                                                    float *__restrict__ scales,
+__global__ __launch_bounds__(kThreads) void quantize_strided_kernel(Global<int8_t> codes,
+                                                                    Global<float> scales,
                                                                     const StridedSource src)
 {
     __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
@@ -232,8 +232,8 @@ __device__ __forceinline__ void hop_strided_body(const int8_t *cin, const float 
 }
 
 template <int R>
-__global__ __launch_bounds__(kThreads) void hop_strided_kernel(const int8_t *cin, const float *sin,
-                                                               int8_t *cout, float *sout, unsigned mirror,
+__global__ __launch_bounds__(kThreads) void hop_strided_kernel(Global<const int8_t> cin, Global<const float> sin,
+                                                               Global<int8_t> cout, Global<float> sout, unsigned mirror,
                                                                const StridedSource src)
 {
     __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
@@ -288,7 +288,7 @@ struct StridedWires {
 };
 
 template <int R, bool kAG>
-__global__ __launch_bounds__(kThreads) void owner_strided_kernel(int received, unsigned mirror, uint16_t *out,
+__global__ __launch_bounds__(kThreads) void owner_strided_kernel(int received, unsigned mirror, Global<uint16_t> out,
                                                                  const StridedWires wires, const StridedSource src)
 {
     __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
@@ -578,7 +578,7 @@ constexpr int strided_chain_waves(bool semi, bool rs, int V) { return (!semi && 
 // as its owner and the devices k+1, k+2, ... around it.  per_shard == 0: array order everywhere.
 template <int R, int W, int V, bool kSemi, bool kRS, bool kAG>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, strided_chain_waves(kSemi, kRS, V))))
-void chain_strided_kernel(int P, int per_shard, uint16_t *out, const PartialTable tab)
+void chain_strided_kernel(int P, int per_shard, Global<uint16_t> out, const PartialTable tab)
 {
     static_assert(kRS || !kSemi, "the semi-loop is a quantized reduce-scatter");
     __shared__ __align__(16) ChunkMaxRows<W, V> red;
@@ -706,8 +706,8 @@ struct WavePass {
 // kWire: a hop; otherwise the chain's first shard is quantized.  The output wire may be the input wire: the waves of a
 // piece meet at a barrier between their last load and their first store.
 template <int R, bool kWire>
-__global__ __launch_bounds__(kThreads) void pass_strided_small_kernel(const int8_t *cin, const float *sin, int8_t *cout,
-                                                                      float *sout, const StridedSource src)
+__global__ __launch_bounds__(kThreads) void pass_strided_small_kernel(Global<const int8_t> cin, Global<const float> sin, Global<int8_t> cout,
+                                                                      Global<float> sout, const StridedSource src)
 {
     __shared__ __align__(16) ChunkMaxRows<4, 8> red;
     WavePass<R> pass(red);
@@ -733,7 +733,7 @@ __global__ __launch_bounds__(kThreads) void semi_step_strided_small_kernel(int P
 }
 
 template <int R, bool kAG>
-__global__ __launch_bounds__(kThreads) void owner_strided_small_kernel(int received, uint16_t *out,
+__global__ __launch_bounds__(kThreads) void owner_strided_small_kernel(int received, Global<uint16_t> out,
                                                                        const StridedWires wires, const StridedSource src)
 {
     __shared__ __align__(16) ChunkMaxRows<4, 8> red;
@@ -755,9 +755,9 @@ __global__ __launch_bounds__(kThreads) void owner_strided_small_kernel(int recei
 // Dequantize in the strided geometry: element e uses scale (e / (1024*chunks)) * 1024 + e % 1024, so the 8
 // elements of a lane use 8 consecutive scales.  n is a multiple of 1024: 8 elements are inside or outside as a whole.
 template <int K>
-__global__ __launch_bounds__(pass_threads(K)) void dequantize_strided_kernel(const int8_t *__restrict__ codes,
-                                                                      const float *__restrict__ scales, int64_t n,
-                                                                      int chunks, uint16_t *__restrict__ out, int64_t mirror)
+__global__ __launch_bounds__(pass_threads(K)) void dequantize_strided_kernel(Global<const int8_t> codes,
+                                                                      Global<const float> scales, int64_t n,
+                                                                      int chunks, Global<uint16_t> out, int64_t mirror)
 {
     constexpr int T = pass_threads(K);
     const int64_t wg_at = first_element<T, K>(mirror);
