@@ -137,12 +137,15 @@ inline int64_t mirrored(int64_t n, bool backward)
     return backward ? (int64_t)(grid_for<S>(n) & ~7u) * S::kElems : 0;
 }
 
-// The workgroup's first element.
-template <int T, int K>
+// The workgroup's first element.  Launches that never walk back -- one tile per thread, so the message (or the last piece
+// of a longer one) is far below kTurnFrom, and the steps of a ring between devices -- do not ask: their loads begin with
+// this address (MI355X, one device's nine calls in a ring of eight, 27B shape: 38.5 -> 38.3 us).
+template <int T, int K, bool kTurns = true>
 __device__ __forceinline__ int64_t first_element(int64_t mirror)
 {
     constexpr int64_t kSpan = T * K * kLaneElems;
     const int64_t at = blockIdx.x * kSpan;
+    if (!kTurns || K == 1) return at;
     return at < mirror ? mirror - 8 * kSpan - at + 2 * (int64_t)(blockIdx.x & 7u) * kSpan : at;
 }
 
@@ -685,7 +688,7 @@ __global__ __launch_bounds__(pass_threads(K)) void hop_kernel(Global<const int8_
                                                        Global<int8_t> cout, Global<float> sout, int64_t mirror)
 {
     constexpr int T = pass_threads(K);
-    const int64_t wg_at = first_element<T, K>(mirror);
+    const int64_t wg_at = first_element<T, K, !kStream>(mirror);
     const int64_t nb = (n + B - 1) / B;
     if (wg_at + tile_elems<T> * K <= n) {
         hop_body<B, T, K, true, kStream>(cin, sin, x, n, cout, sout, nb, wg_at);
@@ -737,7 +740,7 @@ __global__ __launch_bounds__(pass_threads(K)) void dequantize_kernel(Global<cons
                                                               Global<uint16_t> out, int64_t mirror)
 {
     constexpr int T = pass_threads(K);
-    const int64_t wg_at = first_element<T, K>(mirror);
+    const int64_t wg_at = first_element<T, K, !kStream>(mirror);
     const int64_t nb = (n + B - 1) / B;
     if (wg_at + tile_elems<T> * K <= n) {
         dequantize_body<B, T, K, true, kStream>(codes, scales, n, out, nb, wg_at);
@@ -1484,7 +1487,7 @@ __global__ __launch_bounds__(pass_threads(K)) void flat_kernel(Global<const uint
                                                         Global<int8_t> codes_out, Global<float> scales_out,
                                                         int64_t mirror, const WireTable tab)
 {
-    const int64_t wg_at = first_element<pass_threads(K), K>(mirror);
+    const int64_t wg_at = first_element<pass_threads(K), K, !kStream>(mirror);
     const int64_t nb = (n + B - 1) / B;
     if (wg_at + tile_elems<pass_threads(K)> * K <= n) {
         flat_body<B, K, U, kOutBf16, kOutWire, kAG, true, kStream>(local, tab, R, n, out, codes_out, scales_out, nb, wg_at);
