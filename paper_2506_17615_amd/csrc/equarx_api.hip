@@ -133,20 +133,42 @@ inline ChainGrid chain_grid(int64_t n, int32_t block, int32_t P, bool ring)
 }
 
 // Which single-launch calls the latency-shaped small_kernel takes: messages of up to three workgroups per CU, with
-// enough partials that requesting them together pays, and, for the semi-loop, whose code is twice as long, enough
-// tiles to repay fetching it.  Measured on MI355X, us with the bandwidth kernel -> with small_kernel:
-//     full loop, P =      2             4             8             16      semi-loop, P = 5       8            16 (ring)
-//     20 k            2.1 -> 2.2    2.4 -> 2.4    3.1 -> 2.9    4.6 -> 4.3     2.9 -> 3.2    3.5 -> 3.7     5.4 -> 6.6
-//     160 k           2.2 -> 2.3    2.5 -> 2.5    3.8 -> 3.2    7.8 -> 4.6     3.7 -> 3.6    4.3 -> 4.1     9.2 -> 6.9
-//     600 k           2.4 -> 2.8    3.3 -> 3.3    5.8 -> 4.2   10.6 -> 6.9     4.2 -> 4.2    6.2 -> 5.2    11.3 -> 8.6
-//     1.5 M           2.6 -> 3.5    4.7 -> 4.2    7.4 -> 5.7   12.7 -> 10.0    5.7 -> 5.4    7.4 -> 6.9    13.3 -> 12.3
-//     1.9 M           2.7 -> 3.8    5.0 -> 5.2    7.9 -> 7.0   13.5 -> 12.7    6.1 -> 6.2    8.0 -> 8.2    14.2 -> 15.6
-//     3.0 M           4.2 -> 6.0    6.0 -> 7.0    9.6 -> 9.9   16.5 -> 18.6    7.4 -> 8.2    9.8 -> 11.0   16.9 -> 21.3
+// enough partials that requesting them together pays.  The semi-loop, whose code is twice as long, needs enough tiles to
+// repay fetching it if its chain is long (or its blocks of 512, which keep it to 8 elements per lane).  Measured on MI355X,
+// GPU us per call, bandwidth kernel (256 x 1) / small_kernel with 8 / with 4 elements per lane:
+//     full loop, P = 4     8, block 32          12                 16                 24
+//     4,099    2.17/2.30/2.04  2.86/2.75/2.25  3.57/3.59/2.94     4.37/4.17/3.34     5.85/6.17/5.31
+//     64 k     2.22/2.20/2.13  2.90/2.64/2.44  3.56/3.43/2.97     4.20/3.92/3.37     5.57/6.18/5.55
+//     256 k    2.71/2.68/2.69  5.30/3.18/3.10  7.51/3.86/3.78     9.30/4.50/4.30    14.13/7.29/6.85
+//     344 k    3.06/2.71/2.85  5.58/3.28/3.43  7.88/4.01/4.42     9.92/4.57/5.09    14.42/7.61/7.79
+//     524 k    2.86/2.75/3.13  5.89/3.44/3.88  8.27/4.42/5.02    10.24/5.24/5.88    14.75/8.47/8.51
+//     600 k    3.82/3.18/3.27  6.37/4.12/4.08  8.66/5.82/5.45    10.91/7.01/6.37    15.46/10.12/9.58
+//     1 M      4.36/3.60/3.88  6.89/4.84/4.93  9.21/6.98/6.88    11.59/8.33/8.17    16.45/13.23/12.28
+//     1.57 M   4.77/4.36/4.84  7.56/6.35/6.39 10.16/10.39/9.48   12.77/12.12/11.23  18.08/18.22/17.33
+//     1.9 M    5.11/5.10/5.47  7.95/7.46/7.39 10.76/12.53/11.15  13.43/14.70/13.04  19.05/22.13/20.53
+//     semi-loop, P = 4     5                    8                  16
+//     4,099    2.43/2.73/2.22  2.67/2.89/2.36   3.25/3.42/2.83    5.07/6.10/5.15
+//     64 k     2.47/2.72/2.42  2.70/2.84/2.57   3.26/3.42/3.16    4.83/5.24/4.69
+//     256 k    2.98/3.11/2.98  3.29/3.31/3.17   5.57/3.91/3.73   10.42/6.40/5.64
+//     524 k    3.06/3.27/3.44  4.15/3.48/3.68   6.08/4.24/4.45   10.79/7.46/7.17
+//     1 M      4.52/4.05/4.16  5.10/4.53/4.46   7.12/5.67/5.58   12.09/10.54/9.78
+//     1.57 M   4.86/4.88/5.13  5.55/5.42/5.55   7.67/7.17/6.91   13.10/14.26/12.65
+//     1.9 M    5.24/5.64/5.74  5.92/6.09/6.26   8.03/8.24/7.96   13.71/17.23/14.51
+// (two and three partials 1.93/2.11/2.07 and 2.02/2.20/2.13 at 4,099, 3.17/3.34/4.32 and 4.05/3.96/4.57 at 1.57 M).
 constexpr int64_t kSmallElems = (int64_t)768 * NarrowPass::kElems;
 constexpr int64_t kSmallSemiFrom = (int64_t)32 * NarrowPass::kElems;
 
 inline bool small_chain(int64_t n, int P) { return n <= kSmallElems && P >= 4; }
-inline bool small_semi(int64_t n, int P) { return n <= kSmallElems && n > kSmallSemiFrom && P >= 5; }
+inline bool small_semi(int64_t n, int P, int32_t block)
+{
+    return n <= kSmallElems && P >= 5 && (n > kSmallSemiFrom || (P <= 8 && block <= 256));
+}
+
+// 4 elements per lane (a full loop, blocks of up to 256; the table above): up to one wave of them for each of the 1024
+// SIMDs.  With more, some SIMDs have two waves to the others' one, and 8 per lane even out better; from two waves for each
+// on that no longer decides, and long chains, whose arithmetic it is that counts, are faster with 4 again.
+constexpr int64_t kOneWaveEach = (int64_t)1024 * SmallShape<4>::kElems;
+inline bool small_lanes_of_4(int64_t n, int P) { return n <= kOneWaveEach || (P > 8 && n > 2 * kOneWaveEach); }
 
 // Launch shapes of the bandwidth kernels of the single-launch calls.  What a message of a few million elements pays
 // for is the last round of workgroups, so each shape is used where its rounds come out even:
@@ -250,20 +272,29 @@ void launch_chain_as(const PartialTable &tab, int P, int64_t n, bool rs, bool ag
 #undef EQUARX_CHAIN
 }
 
+template <int B, int E, bool kSemi, bool kRS, bool kAG, bool kWire>
+void launch_small_as(const PartialTable &tab, int P, int64_t n, bool ring, uint16_t *out, int8_t *wire_codes,
+                     float *wire_scales, int64_t c_step, int64_t s_step, LaunchCtx &ctx)
+{
+    const ChainGrid g = chain_grid<SmallShape<E>>(n, B, P, ring);
+    ctx.launch2d(P <= 8    ? small_kernel<B, E, 8, false, kSemi, kRS, kAG, kWire>
+                 : P <= 16 ? small_kernel<B, E, 16, false, kSemi, kRS, kAG, kWire>
+                           : small_kernel<B, E, 16, true, kSemi, kRS, kAG, kWire>,
+                 g.x, g.y, SmallShape<E>::T, P, n, g.shard_elems, out, wire_codes, wire_scales, c_step, s_step, tab);
+}
+
 template <int B, bool kSemi, bool kRS, bool kAG, bool kWire>
 void launch_small(const PartialTable &tab, int P, int64_t n, bool ring, uint16_t *out, int8_t *wire_codes,
                   float *wire_scales, int64_t c_step, int64_t s_step, LaunchCtx &ctx)
 {
-    const ChainGrid g = chain_grid<NarrowPass>(n, B, P, ring);
-    if (P <= 8) {
-        ctx.launch2d(small_kernel<B, 8, false, kSemi, kRS, kAG, kWire>, g.x, g.y, kThreads, P, n, g.shard_elems, out,
-                     wire_codes, wire_scales, c_step, s_step, tab);
-    } else if (P <= 16) {
-        ctx.launch2d(small_kernel<B, 16, false, kSemi, kRS, kAG, kWire>, g.x, g.y, kThreads, P, n, g.shard_elems, out,
-                     wire_codes, wire_scales, c_step, s_step, tab);
+    if constexpr (B > 256) {            // 4 elements per lane would spread a block over two waves
+        launch_small_as<B, 8, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
+    } else if constexpr (kSemi) {
+        launch_small_as<B, 4, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
+    } else if (small_lanes_of_4(n, P)) {
+        launch_small_as<B, 4, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
     } else {
-        ctx.launch2d(small_kernel<B, 16, true, kSemi, kRS, kAG, kWire>, g.x, g.y, kThreads, P, n, g.shard_elems, out,
-                     wire_codes, wire_scales, c_step, s_step, tab);
+        launch_small_as<B, 8, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
     }
 }
 
@@ -291,7 +322,7 @@ void launch_chain(const PartialTable &tab, int P, int64_t n, bool rs, bool ag, b
 template <int B>
 void launch_semi(const PartialTable &tab, int P, int64_t n, bool ag, bool ring, uint16_t *out, LaunchCtx &ctx)
 {
-    if (small_semi(n, P)) {
+    if (small_semi(n, P, B)) {
         if (ag) {
             launch_small<B, true, true, true, false>(tab, P, n, ring, out, nullptr, nullptr, 0, 0, ctx);
         } else {

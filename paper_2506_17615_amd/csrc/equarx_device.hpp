@@ -200,6 +200,16 @@ __device__ __forceinline__ uint32_t group_max_bits(uint32_t m)
 
 // ---------------------------------------------------------------- element codecs
 
+__device__ __forceinline__ void widen_bf16x4(const u32x2 &w, float (&f)[4])
+{
+    const uint32_t d[2] = {w.x, w.y};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        f[2 * i] = __uint_as_float(d[i] << 16);
+        f[2 * i + 1] = __uint_as_float(d[i] & 0xFFFF0000u);
+    }
+}
+
 __device__ __forceinline__ void widen_bf16x8(const u32x4 &w, float (&f)[8])
 {
     const uint32_t d[4] = {w.x, w.y, w.z, w.w};
@@ -482,7 +492,7 @@ __device__ __forceinline__ void block_quotients_ieee(float a, float &scale, floa
 
 // ---------------------------------------------------------------- Q_B on registers
 
-// Quantize the 8 values a lane holds, given that the G lanes of its group hold
+// Quantize the E values a lane holds, given that the G lanes of its group hold
 // one block.  r[i] receives the code of t[i] as a float (an integer in
 // [-127, 127]); `scale` is the block's scale (the same in every lane of the group).
 //
@@ -491,18 +501,18 @@ __device__ __forceinline__ void block_quotients_ieee(float a, float &scale, floa
 // codes as floats and multiply them again set this flag, which adds +0.0
 // (turning -0.0 into +0.0 and changing nothing else); the sign of a zero
 // product would otherwise leak into a sum whose other term is -0.0.
-template <int G, bool kPositiveZero = false>
-__device__ __forceinline__ void quantize_lane_f(const float (&t)[8], float (&r)[8], float &scale)
+template <int G, bool kPositiveZero = false, int E>
+__device__ __forceinline__ void quantize_lane_f(const float (&t)[E], float (&r)[E], float &scale)
 {
     float m = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) m = __builtin_fmaxf(m, __builtin_fabsf(t[i]));
+    for (int i = 0; i < E; ++i) m = __builtin_fmaxf(m, __builtin_fabsf(t[i]));
     const float a = __uint_as_float(group_max_bits<G>(__float_as_uint(m)));
 
     float inv;
     block_quotients(a, scale, inv);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < E; ++i) {
         // |t*inv| <= 127*(1+2^-23): rounds to at most 127, no clamp needed
         r[i] = __builtin_rintf(t[i] * inv);
         if (kPositiveZero) r[i] += 0.0f;
@@ -1257,21 +1267,192 @@ __global__ __launch_bounds__(pass_threads(K)) void tail_ring_kernel(Global<const
 // unconditional -- positions past the last one repeat it and are ignored --
 // because a load behind a condition makes the compiler wait for all
 // outstanding loads where the paths join.
-// What bounds it then is the chain of quantizations, 0.18 us per hop.
+//
+// What bounds it then is the chain of quantizations: a wave or two per SIMD
+// issue some 55 instructions per hop one after the other, with nothing to fill
+// the waits between them.
+// * A step is nested in the one before (small_steps), so that a hop costs one
+//   compare and branch; leaving a loop over the positions cost eight scalar
+//   instructions per hop.  Measured on MI355X, GPU us per call: 16 partials of
+//   344 k elements 4.86 -> 4.34, of 20 k 3.93 -> 3.59; 8 partials of 1 M 5.28 ->
+//   4.81, of 20 k 2.76 -> 2.53.
+// * E = 4 elements per lane in workgroups of a single wave, while the chip has
+//   a SIMD for each (SmallLane): half the arithmetic per hop for one more lane
+//   exchange, and the requests come from more CUs.  After the step above: 16
+//   partials of 172 k 4.06 -> 3.63, of 20 k 3.59 -> 3.05, of 344 k 4.34 -> 4.77
+//   (not taken); 8 of 172 k 3.02 -> 2.93, of 20 k 2.53 -> 2.30.
 //
 // The full loop (kSemi = false) takes position i at step i.  The semi-loop
 // takes the owner at step 0, positions h+1 .. P-1 at steps 1 .. na = P-1-h and
 // positions h .. 1 at the steps after that: at step i > na that is P - i.
-template <int B, int N, bool kMany, bool kSemi, bool kRS, bool kAG, bool kWire, bool kFull>
+
+// What a lane of small_kernel holds: E elements of each tile.
+template <int E>
+struct SmallLane;
+
+template <>
+struct SmallLane<8> {
+    typedef u32x4 Raw;
+    static constexpr int T = kThreads;
+    template <bool kFull>
+    static __device__ __forceinline__ Raw load(const uint16_t *p, int64_t base, int off, int64_t n)
+    {
+        return load_bf16x8(p, base, off, n, kFull);
+    }
+    static __device__ __forceinline__ void widen(const Raw &w, float (&f)[8]) { widen_bf16x8(w, f); }
+    template <bool kFull>
+    static __device__ __forceinline__ void store_codes(int8_t *p, int64_t base, int off, int64_t n, const float (&r)[8])
+    {
+        store_i8x8(p, base, off, n, kFull, pack_codes(r));
+    }
+    template <bool kFull, bool kKeepsHint>
+    static __device__ __forceinline__ void store(uint16_t *out, int64_t base, int off, int64_t n, const float (&v)[8])
+    {
+        store_narrowed_tile<kFull, kKeepsHint>(out, base, off, n, v);
+    }
+};
+
+template <>
+struct SmallLane<4> {
+    typedef u32x2 Raw;
+    static constexpr int T = 64;
+    template <bool kFull>
+    static __device__ __forceinline__ Raw load(const uint16_t *p, int64_t base, int off, int64_t n)
+    {
+        if (kFull) {
+            const Raw *v = reinterpret_cast<const Raw *>(p + base + off);
+            return EQUARX_NT_LOAD_BF16 ? __builtin_nontemporal_load(v) : *v;
+        }
+        // the end of a tensor, as request_end and whole_end
+        const int left = left_of(n, base);
+        const int whole = left & ~1;
+        constexpr int kPolicy = EQUARX_NT_LOAD_BF16 ? kNonTemporal : 0;
+        Raw w = __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b64(bounded(p + base, whole * 2), off * 2, 0, kPolicy));
+        const uint32_t last = __builtin_amdgcn_raw_buffer_load_b16(bounded(p + base, left * 2), whole * 2, 0, 0);
+        if (off == whole) w.x = last;
+        if (off + 2 == whole) w.y = last;
+        return w;
+    }
+    static __device__ __forceinline__ void widen(const Raw &w, float (&f)[4]) { widen_bf16x4(w, f); }
+    template <bool kFull>
+    static __device__ __forceinline__ void store_codes(int8_t *p, int64_t base, int off, int64_t n, const float (&r)[4])
+    {
+        uint32_t b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = __float_as_uint(r[i] + kRoundMagic);
+        const uint32_t w = gather_low_bytes(b[0], b[1], b[2], b[3]);
+        if (kFull) {
+            *reinterpret_cast<uint32_t *>(p + base + off) = w;
+            return;
+        }
+        const int left = left_of(n, base);
+        const int whole = left & ~3;
+        __builtin_amdgcn_raw_buffer_store_b32(w, bounded(p + base, whole), off, 0, 0);
+        const auto end = bounded(p + base, left);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(w >> (8 * i)), end, off == whole ? whole + i : kNowhere, 0, 0);
+        }
+    }
+    template <bool kFull, bool kKeepsHint>
+    static __device__ __forceinline__ void store(uint16_t *out, int64_t base, int off, int64_t n, const float (&v)[4])
+    {
+        Raw w;
+        w.x = narrow_bf16x2(v[0], v[1]);
+        w.y = narrow_bf16x2(v[2], v[3]);
+        if (kFull) {
+            Raw *o = reinterpret_cast<Raw *>(out + base + off);
+            if (EQUARX_NT_STORE_BF16) {
+                __builtin_nontemporal_store(w, o);
+            } else {
+                *o = w;
+            }
+            return;
+        }
+        const int left = left_of(n, base);
+        const int whole = left & ~1;
+        __builtin_amdgcn_raw_buffer_store_b64(w, bounded(out + base, whole * 2), off * 2, 0, EQUARX_NT_STORE_BF16 ? kNonTemporal : 0);
+        const bool holds = off == whole || off + 2 == whole;        // the lane with the last element of an odd length
+        const uint32_t last = off == whole ? w.x : w.y;
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)last, bounded(out + base, left * 2), holds ? whole * 2 : kNowhere, 0, 0);
+    }
+};
+
+template <int E>
+struct SmallShape {
+    static constexpr int T = SmallLane<E>::T;
+    static constexpr int64_t kElems = (int64_t)T * E;
+};
+
+// Where a lane of a small chain is, and where its wire goes (kWire).
+struct SmallPlace {
+    int P, na, off;
+    int64_t wg_at, n;
+    int8_t *wire_codes;
+    float *wire_scales;
+    int64_t c_step, s_step;
+};
+
+// The wire after a quantization: row `row` of the kept wire.
+template <int B, int E, bool kFull>
+__device__ __forceinline__ void store_small_wire(const SmallPlace &at, int row, const float (&r)[E], float s)
+{
+    constexpr int G = B / E;
+    SmallLane<E>::template store_codes<kFull>(at.wire_codes + (int64_t)row * at.c_step, at.wg_at, at.off, at.n, r);
+    if ((threadIdx.x % G) == 0 && (kFull || at.wg_at + at.off < at.n)) {
+        at.wire_scales[(int64_t)row * at.s_step + (at.wg_at + at.off) / B] = s;
+    }
+}
+
+// Step i = base + U of the chain, and within it all that follow: `own` the owner's sum (semi-loop), `t` the running sum.
+template <int B, int E, int N, int U, bool kSemi, bool kRS, bool kAG, bool kWire, bool kFull>
+__device__ __forceinline__ void small_steps(const SmallPlace &at, int base, const typename SmallLane<E>::Raw (&x)[N],
+                                            float (&own)[E], float (&t)[E])
+{
+    if constexpr (U < N) {
+        const int i = base + U;
+        if (i >= at.P) return;                                      // uniform, as every condition here
+        constexpr int G = B / E;
+        float xf[E];
+        SmallLane<E>::widen(x[U], xf);
+        if (U == 0 && i == 0) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) (kSemi ? own : t)[e] = xf[e];
+        } else {
+            if (kSemi && (i == 1 || i == at.na + 1)) {              // a half chain starts
+#pragma unroll
+                for (int e = 0; e < E; ++e) t[e] = xf[e];
+            } else if (kRS) {
+                float r[E], s;
+                quantize_lane_f<G, !kAG>(t, r, s);
+                if (kWire) store_small_wire<B, E, kFull>(at, i - 1, r, s);
+#pragma unroll
+                for (int e = 0; e < E; ++e) t[e] = __builtin_fmaf(r[e], s, xf[e]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < E; ++e) t[e] = t[e] + xf[e];
+            }
+            if (kSemi && (i == at.na || i == at.P - 1)) {           // ... and ends at the owner
+                float r[E], s;
+                quantize_lane_f<G, !kAG>(t, r, s);
+#pragma unroll
+                for (int e = 0; e < E; ++e) own[e] = __builtin_fmaf(r[e], s, own[e]);
+            }
+        }
+        small_steps<B, E, N, U + 1, kSemi, kRS, kAG, kWire, kFull>(at, base, x, own, t);
+    }
+}
+
+template <int B, int E, int N, bool kMany, bool kSemi, bool kRS, bool kAG, bool kWire, bool kFull>
 __device__ __forceinline__ void small_body(const PartialTable &tab, int P, int rot, int64_t n, uint16_t *out,
                                            int8_t *__restrict__ wire_codes, float *__restrict__ wire_scales,
                                            int64_t c_step, int64_t s_step, int64_t wg_at)
 {
-    constexpr int T = kThreads, G = B / kLaneElems;
-    const int lane_at = threadIdx.x * kLaneElems;
+    typedef SmallLane<E> Lane;
     const int h = P / 2, na = kSemi ? P - 1 - h : 0;
-    float t[1][8], own[8];
-    u32x4 x[N][1];
+    const SmallPlace at{P, na, (int)threadIdx.x * E, wg_at, n, wire_codes, wire_scales, c_step, s_step};
+    float t[E], own[E];
+    typename Lane::Raw x[N];
 
     for (int base = 0; base < P; base += N) {        // once, unless kMany
 #pragma unroll
@@ -1286,50 +1467,38 @@ __device__ __forceinline__ void small_body(const PartialTable &tab, int P, int r
                 j = u <= na ? rot + h + u : rot + 2 * P - u;
                 if (j < 0) j = 0;               // u past 2 P: a repeat like any other
             }
-            load_tiles<T, 1, kFull>(tab.x[j], wg_at, n, x[u]);
+            x[u] = Lane::template load<kFull>(tab.x[j], wg_at, at.off, n);
         }
         loads_first();
-#pragma unroll
-        for (int u = 0; u < N; ++u) {
-            const int i = base + u;
-            if (i >= P) break;                                      // uniform, as every condition here
-            if (i == 0) {
-                if (kSemi) {
-                    widen_bf16x8(x[0][0], own);
-                } else {
-                    widen_bf16x8(x[0][0], t[0]);
-                }
-                continue;
-            }
-            if (kSemi && (i == 1 || i == na + 1)) {
-                widen_bf16x8(x[u][0], t[0]);                        // a half chain starts
-            } else {
-                hop_tiles<B, T, 1, kRS, kWire, !kAG, kFull>(t, x[u], wire_codes, wire_scales, c_step, s_step, i - 1, wg_at, n);
-            }
-            if (kSemi && (i == na || i == P - 1)) {                 // ... and ends at the owner
-                float r[8], s;
-                quantize_lane_f<G, !kAG>(t[0], r, s);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) own[e] = __builtin_fmaf(r[e], s, own[e]);
-            }
-        }
+        small_steps<B, E, N, 0, kSemi, kRS, kAG, kWire, kFull>(at, base, x, own, t);
     }
-    finish_tile<B, kAG, kWire, kFull>(kSemi ? own : t[0], out, wire_codes, wire_scales, c_step, s_step, P - 1, wg_at,
-                                      lane_at, n);
+
+    const float (&sum)[E] = kSemi ? own : t;
+    if (!kAG) {
+        Lane::template store<kFull, kWire>(out, wg_at, at.off, n, sum);
+        return;
+    }
+    float r[E], d[E], s;
+    quantize_lane_f<B / E, true>(sum, r, s);        // +0.0 codes: the product below shows the sign of a zero
+    if (kWire) store_small_wire<B, E, kFull>(at, P - 1, r, s);
+#pragma unroll
+    for (int e = 0; e < E; ++e) d[e] = r[e] * s;
+    Lane::template store<kFull, kWire>(out, wg_at, at.off, n, d);
 }
 
-template <int B, int N, bool kMany, bool kSemi, bool kRS, bool kAG, bool kWire>
-__global__ __launch_bounds__(kThreads) void small_kernel(int P, int64_t n, int64_t shard_elems, Global<uint16_t> out,
-                                                         Global<int8_t> wire_codes,
-                                                         Global<float> wire_scales, int64_t c_step,
-                                                         int64_t s_step, const PartialTable tab)
+template <int B, int E, int N, bool kMany, bool kSemi, bool kRS, bool kAG, bool kWire>
+__global__ __launch_bounds__(SmallShape<E>::T) void small_kernel(int P, int64_t n, int64_t shard_elems, Global<uint16_t> out,
+                                                                 Global<int8_t> wire_codes, Global<float> wire_scales,
+                                                                 int64_t c_step, int64_t s_step, const PartialTable tab)
 {
-    const Span sp = workgroup_span<kThreads, 1>(n, shard_elems, kSemi ? 0 : 1);
+    static_assert(B / E <= 64, "a block inside one wave");
+    constexpr int64_t kElems = SmallShape<E>::kElems;
+    const Span sp = workgroup_span<(int)(kElems / kLaneElems), 1>(n, shard_elems, kSemi ? 0 : 1);
     if (!sp.any) return;
-    if (sp.wg_at + tile_elems<kThreads> <= sp.hi) {
-        small_body<B, N, kMany, kSemi, kRS, kAG, kWire, true>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step, s_step, sp.wg_at);
+    if (sp.wg_at + kElems <= sp.hi) {
+        small_body<B, E, N, kMany, kSemi, kRS, kAG, kWire, true>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step, s_step, sp.wg_at);
     } else {
-        small_body<B, N, kMany, kSemi, kRS, kAG, kWire, false>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step, s_step, sp.wg_at);
+        small_body<B, E, N, kMany, kSemi, kRS, kAG, kWire, false>(tab, P, sp.rot, sp.hi, out, wire_codes, wire_scales, c_step, s_step, sp.wg_at);
     }
 }
 

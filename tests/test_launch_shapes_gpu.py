@@ -13,6 +13,7 @@ WIDE_ROUND = 768 * 8192         # single-launch calls: up to here 512 threads x 
 PAIRED_FROM = 2560 * 8192       # single-launch chain: above, 256 threads x 4 tiles
 CACHED_OUT = 32 << 20           # single-launch calls: up to here the output stays in the Infinity Cache
 TURN_FROM = 20 << 20            # elements of wire: from here every second launch of a hop-by-hop chain walks back
+ONE_WAVE_EACH = 1024 * 256      # small single-launch calls: up to here 4 elements per lane, and above twice that for P > 8
 ONE_ROUND = 2048 * 2048         # elements: up to here one tile of 256 threads per workgroup, above 512 threads x 2 tiles
 
 
@@ -103,6 +104,21 @@ def test_single_launch_around_its_shapes(gpu, oracle, n, flags):  # noqa: F811
     x = [gpu.bf16_of(rng.standard_normal(n, dtype=np.float32)) for _ in range(3)]
     B = 64 if flags & eq.RING_ORDER else 256
     assert (gpu.gpu_variant(x, B, flags) == _oracle_variant(oracle, x, B, flags)).all()
+
+
+@pytest.mark.parametrize("n", (1, 2, 3, 255, 257, 4097, 65 * 1024 + 2, ONE_WAVE_EACH - 1, ONE_WAVE_EACH, ONE_WAVE_EACH + 1,
+                               2 * ONE_WAVE_EACH, 2 * ONE_WAVE_EACH + 5))
+@pytest.mark.parametrize("P", (4, 8, 9, 16, 17, 33))
+def test_small_single_launches_by_elements_per_lane(gpu, oracle, values, n, P):  # noqa: F811
+    """Every flavour around the ends of a lane's words, a wave's tile and the lines between the layouts, kept wire included."""
+    x = [values[i % 4][i:i + n] for i in range(P)]
+    for k, flags in enumerate(SINGLE):
+        B = (32, 64, 128, 256, 512)[(n + P + k) % 5]
+        assert (gpu.gpu_variant(x, B, flags) == _oracle_variant(oracle, x, B, flags)).all(), (B, flags)
+    B = (32, 64, 128, 256, 512)[(n + 2 * P) % 5]
+    want, wc, ws = oracle.reduce_chain(x, B, keep_wire=True)
+    got, c, s = gpu.gpu_chain_fused(x, B)
+    assert (got == want).all() and (c == wc).all() and (s.view(np.uint32) == ws.view(np.uint32)).all()
 
 
 @pytest.fixture(scope="module")
