@@ -105,6 +105,56 @@ inline void with_pass_shape(int64_t n, F f)
     }
 }
 
+// Passes whose wire leaves for, or came from, another device run alone on tensors that no cache holds, where other shapes
+// than WidePass stream better.  A quantization: 256 threads x 2 tiles.  A dequantization: 256 x 2 while that is one round
+// on the chip (1792 workgroups, seven per CU), 1024 x 1 for the longest, whose sixteen waves walk one piece together.
+// Measured on MI355X, us, many sets of buffers in turn:
+//     elements     quantize 256 x 1   256 x 2   512 x 2     dequantize 256 x 2   512 x 2   1024 x 1
+//     4.2 M              3.5            3.49      3.60              3.02           3.21      4.18
+//     5.2 M              4.4            3.91      4.03              3.48           3.86      4.15
+//     7.3 M                             5.13      5.22              4.30           5.21      5.30
+//     7.9 M                             5.30      5.43              5.49           5.37      5.45
+//     10.5 M                            6.78      6.98              6.86           6.65      6.93
+//     12.6 M             8.35           7.68      7.92              8.07           7.84      7.89
+//     14.7 M                            8.59      8.77              9.16           8.93      8.69
+//     22 M              12.84          11.83     12.03             12.77          12.29     12.05
+//     44 M              23.98          21.53     21.70             22.90          22.36     21.88
+//     100 M             51.43          45.99     45.99             48.21          47.70     46.58
+// (The hop in between stays with WidePass: 256 x 2 5.02 instead of 5.16 at 5 M, 15.42 instead of 15.22 at 22 M.  In the
+// chains, whose wire the next launch finds in a cache, all of these are within 0.3 us.)
+// A batch of tensors is one such quantization of all their elements together: seven of 2.75 M 11.7 with 256 x 1, 10.9 with
+// 256 x 2, 11.2 with 512 x 2; fifteen of 344 k 4.71, 4.11, 4.55; three of 1.4 M 3.61, 3.77, 3.78.
+constexpr int64_t kOneNarrowPairRound = (int64_t)1792 * Shape<256, 2>::kElems;
+constexpr int64_t kLongDequantize = (int64_t)13 << 20;
+constexpr int64_t kLongestOneTile = (int64_t)1 << 34;       // beyond, one tile per thread is more threads than a grid holds
+
+// Threads of a quantization with K tiles each.
+constexpr int quantize_threads(int K, bool streams) { return streams ? 256 : pass_threads(K); }
+
+template <typename F>
+inline void with_stream_quantize_shape(int64_t n, F f)
+{
+    if (n <= kOneRound) {
+        f(NarrowPass{});
+    } else {
+        f(Shape<quantize_threads(2, true), 2>{});
+    }
+}
+
+template <typename F>
+inline void with_stream_dequantize_shape(int64_t n, F f)
+{
+    if (n <= kOneRound) {
+        f(NarrowPass{});
+    } else if (n <= kOneNarrowPairRound) {
+        f(Shape<256, 2>{});
+    } else if (n < kLongDequantize || n > kLongestOneTile) {
+        f(WidePass{});
+    } else {
+        f(Shape<1024, 1>{});
+    }
+}
+
 // The chains that walk their wire through memory, hop by hop, rewrite ONE wire buffer in place, and from kTurnFrom
 // elements of wire on every second launch takes its tiles in the opposite order.  What bounds a hop is what it moves
 // beyond the L2s (8 x 4 MB, write-back, and the lines stay from one launch to the next; workgroup b runs on XCD b % 8,
@@ -614,11 +664,11 @@ __device__ __forceinline__ void quantize_body(const uint16_t *__restrict__ x, in
 
 // Pass 0 of the chain: quantize a bf16 tensor.
 template <int B, int K, bool kStream = false>
-__global__ __launch_bounds__(pass_threads(K)) void quantize_kernel(Global<const uint16_t> x, int64_t n,
+__global__ __launch_bounds__(quantize_threads(K, kStream)) void quantize_kernel(Global<const uint16_t> x, int64_t n,
                                                             Global<int8_t> codes, Global<float> scales,
                                                             int64_t nb)
 {
-    constexpr int T = pass_threads(K);
+    constexpr int T = quantize_threads(K, kStream);
     const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
     if (wg_at + tile_elems<T> * K <= n) {
         quantize_body<B, T, K, true, kStream>(x, n, codes, scales, nb, wg_at);
@@ -639,9 +689,9 @@ struct QuantizeBatch {
 };
 
 template <int B, int K, bool kStream = false>
-__global__ __launch_bounds__(pass_threads(K)) void quantize_batch_kernel(int64_t n, int64_t nb, const QuantizeBatch tab)
+__global__ __launch_bounds__(quantize_threads(K, kStream)) void quantize_batch_kernel(int64_t n, int64_t nb, const QuantizeBatch tab)
 {
-    constexpr int T = pass_threads(K);
+    constexpr int T = quantize_threads(K, kStream);
     const uint16_t *x = tab.x[blockIdx.y];
     int8_t *codes = tab.codes[blockIdx.y];
     float *scales = tab.scales[blockIdx.y];
@@ -744,12 +794,11 @@ __device__ __forceinline__ void dequantize_body(const int8_t *__restrict__ codes
 }
 
 // Last pass: dequantize the wire to bf16.
-template <int B, int K, bool kStream = false>
-__global__ __launch_bounds__(pass_threads(K)) void dequantize_kernel(Global<const int8_t> codes,
+template <int B, int K, bool kStream = false, int T = pass_threads(K)>
+__global__ __launch_bounds__(T) void dequantize_kernel(Global<const int8_t> codes,
                                                               Global<const float> scales, int64_t n,
                                                               Global<uint16_t> out, int64_t mirror)
 {
-    constexpr int T = pass_threads(K);
     const int64_t wg_at = first_element<T, K, !kStream>(mirror);
     const int64_t nb = (n + B - 1) / B;
     if (wg_at + tile_elems<T> * K <= n) {

@@ -15,10 +15,18 @@ template <int B>
 void launch_quantize(const uint16_t *x, int64_t n, int8_t *codes, float *scales, LaunchCtx &ctx, bool streaming = false)
 {
     in_pieces(n, [&](int64_t at, int64_t m) {
+        if (streaming) {
+            with_stream_quantize_shape(m, [&](auto shape) {
+                using S = decltype(shape);
+                ctx.launch(quantize_kernel<B, S::K, true>, grid_for<S>(m), S::T, x + at, m, codes + at, scales + at / B,
+                           blocks_of(m, B));
+            });
+            return;
+        }
         with_pass_shape(m, [&](auto shape) {
             using S = decltype(shape);
-            ctx.launch(streaming ? quantize_kernel<B, S::K, true> : quantize_kernel<B, S::K, false>, grid_for<S>(m), S::T,
-                       x + at, m, codes + at, scales + at / B, blocks_of(m, B));
+            ctx.launch(quantize_kernel<B, S::K, false>, grid_for<S>(m), S::T, x + at, m, codes + at, scales + at / B,
+                       blocks_of(m, B));
         });
     });
 }
@@ -41,10 +49,18 @@ void launch_dequantize(const int8_t *codes, const float *scales, int64_t n, uint
                        bool streaming = false, bool backward = false)
 {
     in_pieces(n, [&](int64_t at, int64_t m) {
+        if (streaming) {
+            with_stream_dequantize_shape(m, [&](auto shape) {
+                using S = decltype(shape);
+                ctx.launch(dequantize_kernel<B, S::K, true, S::T>, grid_for<S>(m), S::T, codes + at, scales + at / B, m,
+                           out + at, 0);
+            });
+            return;
+        }
         with_pass_shape(m, [&](auto shape) {
             using S = decltype(shape);
-            ctx.launch(streaming ? dequantize_kernel<B, S::K, true> : dequantize_kernel<B, S::K, false>, grid_for<S>(m), S::T,
-                       codes + at, scales + at / B, m, out + at, mirrored<S>(m, backward));
+            ctx.launch(dequantize_kernel<B, S::K, false>, grid_for<S>(m), S::T, codes + at, scales + at / B, m, out + at,
+                       mirrored<S>(m, backward));
         });
     });
 }

@@ -14,6 +14,8 @@ PAIRED_FROM = 2560 * 8192       # single-launch chain: above, 256 threads x 4 ti
 CACHED_OUT = 32 << 20           # single-launch calls: up to here the output stays in the Infinity Cache
 TURN_FROM = 20 << 20            # elements of wire: from here every second launch of a hop-by-hop chain walks back
 ONE_WAVE_EACH = 1024 * 256      # small single-launch calls: up to here 4 elements per lane, and above twice that for P > 8
+PAIR_ROUND = 1792 * 4096        # a dequantization of a wire that arrived: up to here 256 threads x 2 tiles
+LONG_DEQUANTIZE = 13 << 20      # ... and from here 1024 x 1
 ONE_ROUND = 2048 * 2048         # elements: up to here one tile of 256 threads per workgroup, above 512 threads x 2 tiles
 
 
@@ -91,6 +93,22 @@ def test_batch_around_one_round_of_workgroups(gpu, oracle, values, n):  # noqa: 
     for p, c, s in zip(x, codes, scales):
         wc, ws = oracle.quantize_bf16(p, 128)
         assert (c.cpu().numpy() == wc).all() and (_bits(s) == ws.view(np.uint32)).all()
+
+
+@pytest.mark.parametrize("n", (PAIR_ROUND, PAIR_ROUND + 1, PAIR_ROUND + 4099, LONG_DEQUANTIZE - 1, LONG_DEQUANTIZE,
+                               LONG_DEQUANTIZE + 8192 * 3 + 7))
+@pytest.mark.parametrize("B", (32, 256, 512))
+def test_steps_of_a_ring_around_their_shapes(gpu, oracle, long_values, n, B):  # noqa: F811
+    x, nb = long_values[0][:n], eq.num_blocks(n, B)
+    codes = torch.full((n + 16,), 77, dtype=torch.int8, device="cuda")
+    scales = torch.full((nb + 4,), 7.0, dtype=torch.float32, device="cuda")
+    out = torch.full((n + 8,), 3.0, dtype=torch.bfloat16, device="cuda")
+    eq.equarx_quantize(gpu.dev_bf16(x), B, codes[:n], scales[:nb])
+    wc, ws = oracle.quantize_bf16(x, B)
+    assert (codes[:n].cpu().numpy() == wc).all() and (_bits(scales[:nb]) == ws.view(np.uint32)).all()
+    eq.equarx_dequantize(codes[:n], scales[:nb], B, out[:n])
+    assert (gpu.host_u16(out[:n]) == oracle.dequantize_bf16(wc, ws, B)).all()
+    assert (codes[n:] == 77).all() and (scales[nb:] == 7.0).all() and (out[n:] == 3.0).all()
 
 
 SINGLE = (0, eq.RING_ORDER, eq.AG_UNQUANTIZED, eq.RS_UNQUANTIZED | eq.RING_ORDER, eq.SEMI_LOOP,
