@@ -790,7 +790,7 @@ int equarx_quantize_batch(const void *const *x_bf16, int8_t *const *codes, float
             tab.scales[i] += kPieceElems / block;
         }
 #define CALL(BB)                                                                                                  \
-    with_stream_quantize_shape(count * m, [&](auto shape) {                                                       \
+    with_pass_shape(count * m, [&](auto shape) {                                                                  \
         using S = decltype(shape);                                                                                \
         ctx.launch2d(quantize_batch_kernel<BB, S::K, kWireLeavesTheDevice>, grid_for<S>(m), (unsigned)count,    \
                      S::T, m, blocks_of(m, BB), tab);                                                             \

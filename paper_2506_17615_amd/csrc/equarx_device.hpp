@@ -105,41 +105,28 @@ inline void with_pass_shape(int64_t n, F f)
     }
 }
 
-// Passes whose wire leaves for, or came from, another device run alone on tensors that no cache holds, where other shapes
-// than WidePass stream better.  A quantization: 256 threads x 2 tiles.  A dequantization: 256 x 2 while that is one round
-// on the chip (1792 workgroups, seven per CU), 1024 x 1 for the longest, whose sixteen waves walk one piece together.
-// Measured on MI355X, us, many sets of buffers in turn:
-//     elements     quantize 256 x 1   256 x 2   512 x 2     dequantize 256 x 2   512 x 2   1024 x 1
-//     4.2 M              3.5            3.49      3.60              3.02           3.21      4.18
-//     5.2 M              4.4            3.91      4.03              3.48           3.86      4.15
-//     7.3 M                             5.13      5.22              4.30           5.21      5.30
-//     7.9 M                             5.30      5.43              5.49           5.37      5.45
-//     10.5 M                            6.78      6.98              6.86           6.65      6.93
-//     12.6 M             8.35           7.68      7.92              8.07           7.84      7.89
-//     14.7 M                            8.59      8.77              9.16           8.93      8.69
-//     22 M              12.84          11.83     12.03             12.77          12.29     12.05
-//     44 M              23.98          21.53     21.70             22.90          22.36     21.88
-//     100 M             51.43          45.99     45.99             48.21          47.70     46.58
-// (The hop in between stays with WidePass: 256 x 2 5.02 instead of 5.16 at 5 M, 15.42 instead of 15.22 at 22 M.  In the
-// chains, whose wire the next launch finds in a cache, all of these are within 0.3 us.)
-// A batch of tensors is one such quantization of all their elements together: seven of 2.75 M 11.7 with 256 x 1, 10.9 with
-// 256 x 2, 11.2 with 512 x 2; fifteen of 344 k 4.71, 4.11, 4.55; three of 1.4 M 3.61, 3.77, 3.78.
+// A dequantization of what an all-gather brought runs alone on a tensor that no cache holds, where other shapes than
+// WidePass stream better: 256 threads x 2 tiles while that is one round on the chip (1792 workgroups, seven per CU),
+// 1024 x 1 for the longest, whose sixteen waves walk one piece together.  Measured on MI355X, us, block 256, many sets of
+// buffers in turn:
+//     elements     256 x 2   512 x 2   1024 x 1
+//     4.2 M          3.02      3.21      4.18
+//     5.2 M          3.48      3.86      4.15
+//     7.3 M          4.30      5.21      5.30
+//     7.9 M          5.49      5.37      5.45
+//     10.5 M         6.86      6.65      6.93
+//     12.6 M         8.07      7.84      7.89
+//     14.7 M         9.16      8.93      8.69
+//     22 M          12.74     12.30     12.04
+//     88 M          43.06     42.28     41.66     (block 32: 43.65, 42.83, 41.72)
+//     200 M         95.06     94.20     91.21     (block 32: 96.93, 94.67, 92.32)
+// The other steps of a device stay with WidePass: with 256 x 2 a quantization gains up to 3 % below 22 M and loses 2 %
+// above with small blocks, a batch of them loses more (seven of 16.8 M and their flat reduce together 84.9 -> 88.8), the
+// hop takes 15.42 instead of 15.22 at 22 M.  In the chains, whose wire the next launch finds in a cache, all of these
+// are within 0.3 us.
 constexpr int64_t kOneNarrowPairRound = (int64_t)1792 * Shape<256, 2>::kElems;
 constexpr int64_t kLongDequantize = (int64_t)13 << 20;
 constexpr int64_t kLongestOneTile = (int64_t)1 << 34;       // beyond, one tile per thread is more threads than a grid holds
-
-// Threads of a quantization with K tiles each.
-constexpr int quantize_threads(int K, bool streams) { return streams ? 256 : pass_threads(K); }
-
-template <typename F>
-inline void with_stream_quantize_shape(int64_t n, F f)
-{
-    if (n <= kOneRound) {
-        f(NarrowPass{});
-    } else {
-        f(Shape<quantize_threads(2, true), 2>{});
-    }
-}
 
 template <typename F>
 inline void with_stream_dequantize_shape(int64_t n, F f)
@@ -664,11 +651,11 @@ __device__ __forceinline__ void quantize_body(const uint16_t *__restrict__ x, in
 
 // Pass 0 of the chain: quantize a bf16 tensor.
 template <int B, int K, bool kStream = false>
-__global__ __launch_bounds__(quantize_threads(K, kStream)) void quantize_kernel(Global<const uint16_t> x, int64_t n,
+__global__ __launch_bounds__(pass_threads(K)) void quantize_kernel(Global<const uint16_t> x, int64_t n,
                                                             Global<int8_t> codes, Global<float> scales,
                                                             int64_t nb)
 {
-    constexpr int T = quantize_threads(K, kStream);
+    constexpr int T = pass_threads(K);
     const int64_t wg_at = (int64_t)blockIdx.x * (tile_elems<T> * K);
     if (wg_at + tile_elems<T> * K <= n) {
         quantize_body<B, T, K, true, kStream>(x, n, codes, scales, nb, wg_at);
@@ -689,9 +676,9 @@ struct QuantizeBatch {
 };
 
 template <int B, int K, bool kStream = false>
-__global__ __launch_bounds__(quantize_threads(K, kStream)) void quantize_batch_kernel(int64_t n, int64_t nb, const QuantizeBatch tab)
+__global__ __launch_bounds__(pass_threads(K)) void quantize_batch_kernel(int64_t n, int64_t nb, const QuantizeBatch tab)
 {
-    constexpr int T = quantize_threads(K, kStream);
+    constexpr int T = pass_threads(K);
     const uint16_t *x = tab.x[blockIdx.y];
     int8_t *codes = tab.codes[blockIdx.y];
     float *scales = tab.scales[blockIdx.y];

@@ -15,18 +15,10 @@ template <int B>
 void launch_quantize(const uint16_t *x, int64_t n, int8_t *codes, float *scales, LaunchCtx &ctx, bool streaming = false)
 {
     in_pieces(n, [&](int64_t at, int64_t m) {
-        if (streaming) {
-            with_stream_quantize_shape(m, [&](auto shape) {
-                using S = decltype(shape);
-                ctx.launch(quantize_kernel<B, S::K, true>, grid_for<S>(m), S::T, x + at, m, codes + at, scales + at / B,
-                           blocks_of(m, B));
-            });
-            return;
-        }
         with_pass_shape(m, [&](auto shape) {
             using S = decltype(shape);
-            ctx.launch(quantize_kernel<B, S::K, false>, grid_for<S>(m), S::T, x + at, m, codes + at, scales + at / B,
-                       blocks_of(m, B));
+            ctx.launch(streaming ? quantize_kernel<B, S::K, true> : quantize_kernel<B, S::K, false>, grid_for<S>(m), S::T,
+                       x + at, m, codes + at, scales + at / B, blocks_of(m, B));
         });
     });
 }
