@@ -107,6 +107,7 @@ void launch_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, int8_t
     });
 }
 
+static_assert(kMostElems<Shape<1024, 1>> / 8192 * 1024 <= kGridThreads && kMostElems<WidePass> >= kPieceElems, "grid limits");
 static_assert(kMaxPartials == EQUARX_MAX_PARTIALS && kMaxBatch == EQUARX_MAX_PARTIALS, "header and device limits differ");
 
 // Shape of a chain launch: the whole tensor in array order, or (ring layout) one grid row per shard.
@@ -229,7 +230,7 @@ void with_chain_shape(int64_t n, int P, bool keeps_wire, F f)
         f(Shape<256, 2>{});
     } else if (n <= kOneWideRound && (!keeps_wire || P <= 6)) {
         f(Shape<512, 2>{});
-    } else if (n <= kPairedFrom || (n < kPieceElems && few_partials(n, P, keeps_wire))) {
+    } else if (n <= kPairedFrom || (n <= kMostElems<Shape<1024, 1>> && few_partials(n, P, keeps_wire))) {
         f(Shape<1024, 1>{});
     } else {
         f(Shape<256, 4>{});
@@ -243,7 +244,7 @@ void with_semi_shape(int64_t n, F f)
         f(Shape<256, 1>{});
     } else if (n <= kFivePerCU) {
         f(Shape<256, 2>{});
-    } else if (n <= kOneWideRound || n >= kPieceElems) {        // longer, 1024 x 1 has more threads than a grid holds
+    } else if (n <= kOneWideRound || n > kMostElems<Shape<1024, 1>>) {
         f(Shape<512, 2>{});
     } else {
         f(Shape<1024, 1>{});

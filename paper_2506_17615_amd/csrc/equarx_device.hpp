@@ -62,6 +62,10 @@ struct Shape {
 template <int T>
 constexpr int tile_elems = T * kLaneElems;
 
+// The most elements a launch of that shape takes: a dimension of a grid holds fewer than 2^32 threads.
+template <typename S>
+constexpr int64_t kMostElems = (int64_t)(0xffffffffu / S::T) * S::kElems;
+
 // Workgroups of a launch of that shape over n elements.
 template <typename S>
 inline unsigned grid_for(int64_t n)
@@ -120,13 +124,13 @@ inline void with_pass_shape(int64_t n, F f)
 //     22 M          12.74     12.30     12.04
 //     88 M          43.06     42.28     41.66     (block 32: 43.65, 42.83, 41.72)
 //     200 M         95.06     94.20     91.21     (block 32: 96.93, 94.67, 92.32)
+//     34.4 G          --      16858     15933     (block 32: 17794, 16989)
 // The other steps of a device stay with WidePass: with 256 x 2 a quantization gains up to 3 % below 22 M and loses 2 %
 // above with small blocks, a batch of them loses more (seven of 16.8 M and their flat reduce together 84.9 -> 88.8), the
 // hop takes 15.42 instead of 15.22 at 22 M.  In the chains, whose wire the next launch finds in a cache, all of these
 // are within 0.3 us.
 constexpr int64_t kOneNarrowPairRound = (int64_t)1792 * Shape<256, 2>::kElems;
 constexpr int64_t kLongDequantize = (int64_t)13 << 20;
-constexpr int64_t kLongestOneTile = (int64_t)1 << 34;       // beyond, one tile per thread is more threads than a grid holds
 
 template <typename F>
 inline void with_stream_dequantize_shape(int64_t n, F f)
@@ -135,7 +139,7 @@ inline void with_stream_dequantize_shape(int64_t n, F f)
         f(NarrowPass{});
     } else if (n <= kOneNarrowPairRound) {
         f(Shape<256, 2>{});
-    } else if (n < kLongDequantize || n > kLongestOneTile) {
+    } else if (n < kLongDequantize || n > kMostElems<Shape<1024, 1>>) {
         f(WidePass{});
     } else {
         f(Shape<1024, 1>{});

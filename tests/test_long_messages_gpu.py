@@ -86,6 +86,21 @@ def test_received_wires_and_chains(gpu, oracle):  # noqa: F811
     m.holds(lambda v: oracle.reduce_stages([v] * 2, B, True, False), out=out)
 
 
+@pytest.mark.parametrize("n", ((1 << 35) - 8192, (1 << 35) - 4096))
+def test_around_the_last_length_of_1024_threads_by_one_tile(gpu, oracle, n):  # noqa: F811
+    """The shape of few partials, of the semi-loop and of a long dequantization, as far as a grid holds its threads, and
+    the first length beyond."""
+    m, B = _Message(gpu, n), 512
+    c, s, out = m.codes, m.buffer(torch.float32, n // B), m.buffer(torch.bfloat16).fill_(7.0)
+    eq.equarx_quantize(m.x, B, c, s)
+    eq.equarx_dequantize(c, s, B, out)
+    m.holds(lambda v: oracle.dequantize_bf16(*oracle.quantize_bf16(v, B), B), out=out)
+    eq.equarx_reduce_fused([m.x] * 2, B, out.fill_(7.0))
+    m.holds(lambda v: oracle.reduce_chain([v] * 2, B), out=out)
+    eq.equarx_reduce_variant([m.x] * 2, B, eq.SEMI_LOOP, out.fill_(7.0))
+    m.holds(lambda v: oracle.reduce_semi_loop([v] * 2, B), out=out)
+
+
 def test_semi_loop_in_one_launch(gpu, oracle):  # noqa: F811
     """In place, all partials one tensor: taken as far as one launch goes, and refused beyond."""
     m = _Message(gpu, LONG)
