@@ -438,7 +438,8 @@ inline int fill_table(const void *const *partials_bf16, int32_t P, int64_t n, Al
 }
 
 // The two wire buffers at the front of a workspace: codes, then scales, each part rounded up to the workspace alignment.
-// A chain rewrites one of them in place; the two chains of a semi-loop take one each.
+// A chain rewrites one of them in place (a strided one may end in the other, ends_beside); the two chains of a semi-loop
+// take one each.
 struct WireBuffers {
     int8_t *c[2];
     float *s[2];
@@ -545,6 +546,26 @@ inline unsigned strided_small_grid(int64_t n, int32_t chunks)       // of the pe
 {
     return (unsigned)(n / ((int64_t)kChunk * chunks) * wave_layout_wgs<4, 8>);
 }
+
+// Short and long strided chains end beside the wire that their last hop reads, not over it.  The dequantization that follows
+// takes consecutive elements to a workgroup where a hop takes 256 positions of a minishard, so a tile is on another XCD
+// there than it was in the hop, and what it reads is found slower if the hop's L2 still holds the line: it keeps one that
+// was read and rewritten in place and not one that was only written.  In between the wire that need not be written anew
+// weighs more, and above, where the L2s no longer hold it, the order of the last launches does (walks_back).  Measured on
+// MI355X, us per chain, over it -> beside it:
+//     chunks, elements      P = 2            3               4               8
+//     32, 2.1 M          12.1 -> 10.6    16.4 -> 14.5    20.7 -> 18.8    37.5 -> 35.0
+//     64, 2.1 M          12.7 -> 11.5    17.4 -> 15.9    22.1 -> 20.6    40.9 -> 38.7
+//     32, 3.2 M          14.0 -> 13.7    19.1 -> 18.8    24.0 -> 23.6    43.8 -> 43.5
+//     32, 3.6 M          14.3 -> 14.7    19.5 -> 19.8    24.6 -> 24.8    44.8 -> 45.1
+//     64, 5.0 M          17.5 -> 17.9    24.0 -> 24.4    30.6 -> 31.0    56.9 -> 57.5
+//     128, 8.4 M         23.0 -> 23.1    30.7 -> 31.0    38.6 -> 38.6    69.1 -> 69.5
+//     32, 9.6 M          24.9 -> 24.4    33.3 -> 32.5    41.7 -> 41.1    75.0 -> 74.8
+//     64, 12.6 M         30.3 -> 28.0    39.7 -> 37.6    49.1 -> 46.6    86.7 -> 84.8
+//     128, 16.8 M        37.8 -> 34.6    49.9 -> 46.8    61.4 -> 58.3   109.3 -> 106.2
+//     64, 28.0 M         53.6 -> 52.3    70.7 -> 70.7    90.0 -> 89.6   160.8 -> 161.7
+//     64, 33.6 M         61.3 -> 62.6    83.0 -> 83.8   103.3 -> 104.0  186.7 -> 187.5
+inline bool ends_beside(int64_t n) { return n <= (int64_t)3 << 20 || (n >= (int64_t)9 << 20 && n <= (int64_t)28 << 20); }
 
 // One tensor as the source of a per-pass strided kernel.
 inline StridedSource one_tensor(const void *x)
@@ -1223,10 +1244,12 @@ int equarx_reduce_quantized_strided(const void *const *partials_bf16, int32_t P,
     if (int st = mem.check()) return st;
     const WireBuffers w = carve_workspace(workspace, n, n / chunks);
     do_quantize_strided(one_tensor(partials_bf16[0]), n, chunks, w.c[0], w.s[0], ctx);
+    const int last = P > 1 && ends_beside(n);     // the buffer of the last wire
     for (int32_t i = 1; i < P; ++i) {
-        do_hop_strided(w.c[0], w.s[0], one_tensor(partials_bf16[i]), n, chunks, w.c[0], w.s[0], ctx, walks_back(n, i));
+        const int to = i + 1 < P ? 0 : last;
+        do_hop_strided(w.c[0], w.s[0], one_tensor(partials_bf16[i]), n, chunks, w.c[to], w.s[to], ctx, walks_back(n, i));
     }
-    do_dequantize_strided(w.c[0], w.s[0], n, chunks, out_bf16, ctx, walks_back(n, P));
+    do_dequantize_strided(w.c[last], w.s[last], n, chunks, out_bf16, ctx, walks_back(n, P));
     return ctx.status();
 }
 

@@ -270,6 +270,25 @@ def test_strided_chains_that_turn(gpu, oracle, long_values, chunks, minishards, 
         assert (gpu.host_u16(out) == _oracle_variant_strided(oracle, x, chunks, flags)).all(), flags
 
 
+@pytest.mark.parametrize("chunks,minishards,P,beside", ((32, 3, 2, True), (32, 96, 3, True), (32, 97, 2, False),
+                                                        (64, 143, 3, False), (64, 144, 2, True), (64, 448, 3, True),
+                                                        (64, 449, 2, False), (128, 20, 1, False)))
+def test_where_the_last_wire_of_a_strided_chain_is(gpu, oracle, long_values, chunks, minishards, P, beside):  # noqa: F811
+    """In the workspace's second buffer, up to 3 Mi elements and from 9 to 28 Mi."""
+    n = 1024 * chunks * minishards
+    x = [np.resize(long_values[i], n) for i in range(P)]
+    work, out = eq.alloc_workspace(P, n, chunks).fill_(0x55), torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    eq.equarx_reduce_quantized_strided([gpu.dev_bf16(p) for p in x], chunks, out, work)
+    assert (gpu.host_u16(out) == oracle.reduce_chain_strided(x, chunks)).all()
+    codes, scales = work[work.numel() // 2 if beside else 0:][:n].view(torch.int8), n // chunks
+    scales = work[(work.numel() // 2 if beside else 0) + n:][:4 * scales].view(torch.float32)
+    got = torch.empty_like(out)
+    eq.equarx_dequantize_strided(codes, scales, chunks, got)
+    assert torch.equal(got, out)
+    if not beside:
+        assert (work[work.numel() // 2:] == 0x55).all()
+
+
 @pytest.mark.parametrize("chunks,minishards", ((32, 17), (64, 17), (64, 33), (128, 17)))
 @pytest.mark.parametrize("kind", ("sparse", "tiny", "huge"))
 def test_strided_layouts_above_the_small_ones_with_extreme_values(gpu, oracle, chunks, minishards, kind):  # noqa: F811
