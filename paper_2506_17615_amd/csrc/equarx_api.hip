@@ -77,11 +77,23 @@ void launch_fused_ends(const PartialTable &tab, int P, int64_t n, int8_t *c, flo
     launch_tail<B>(c, s, tab.x[P - 1], n, out, ctx, true, walks_back(n, P - 2));
 }
 
-// Workgroups per shard of a launch in the ring layout, one grid row per shard (wire_elems: see walks_back).
-template <typename S>
-inline unsigned ring_grid(int64_t shard_elems, int64_t wire_elems)
+// f(shape, whether every second launch walks back) for the launches over `work_elems` elements in the ring layout, one
+// grid row per shard, whose wires are of `wire_elems` (see walks_back).
+template <typename F>
+void with_ring_shape(int64_t work_elems, int64_t wire_elems, F f)
 {
-    return wire_elems >= kTurnFrom ? (unsigned)ring_groups<S>(shard_elems) : grid_for<S>(shard_elems);
+    if (wire_elems >= kTurnFrom) {
+        f(WidePass{}, std::true_type{});
+    } else {
+        with_pass_shape(work_elems, [&](auto shape) { f(shape, std::false_type{}); });
+    }
+}
+
+// Workgroups per row.
+template <typename S, bool kTurns>
+inline unsigned ring_grid(int64_t shard_elems)
+{
+    return kTurns ? (unsigned)ring_groups<S>(shard_elems) : grid_for<S>(shard_elems);
 }
 
 // Full loop in ring order, hop by hop: P launches, each over all P shards (one grid row per shard).
@@ -92,17 +104,18 @@ void launch_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, int8_t
     const int64_t nb = blocks_of(n, B);
     const int64_t shard_elems = (nb + P - 1) / P * B;       // ceil(nb / P) blocks per shard, as the single launch
     const unsigned gy = (unsigned)P;
-    with_pass_shape(n, [&](auto shape) {
+    with_ring_shape(n, n, [&](auto shape, auto turns) {
         using S = decltype(shape);
-        const unsigned gx = ring_grid<S>(shard_elems, n);
+        constexpr bool kTurns = decltype(turns)::value;
+        const unsigned gx = ring_grid<S, kTurns>(shard_elems);
         ctx.launch2d(quantize_ring_kernel<B, S::K>, gx, gy, S::T, P, n, shard_elems, c, s, tab);
         for (int i = 1; i + 1 < P; ++i) {
-            ctx.launch2d(hop_ring_kernel<B, S::K>, gx, gy, S::T, c, s, P, i, n, shard_elems, c, s, tab);
+            ctx.launch2d(hop_ring_kernel<B, S::K, kTurns>, gx, gy, S::T, c, s, P, i, n, shard_elems, c, s, tab);
         }
         if (ag) {
-            ctx.launch2d(tail_ring_kernel<B, S::K, true>, gx, gy, S::T, c, s, P, P - 1, n, shard_elems, out, tab);
+            ctx.launch2d(tail_ring_kernel<B, S::K, true, kTurns>, gx, gy, S::T, c, s, P, P - 1, n, shard_elems, out, tab);
         } else {
-            ctx.launch2d(tail_ring_kernel<B, S::K, false>, gx, gy, S::T, c, s, P, P - 1, n, shard_elems, out, tab);
+            ctx.launch2d(tail_ring_kernel<B, S::K, false, kTurns>, gx, gy, S::T, c, s, P, P - 1, n, shard_elems, out, tab);
         }
     });
 }
@@ -460,6 +473,18 @@ inline WireBuffers carve_workspace(void *workspace, int64_t n, int64_t scales_co
 
 // Semi-loop in ring order, hop by hop: h = P/2 launches in which both chains of every shard advance one device
 // (grid row = shard, grid layer = direction), then the owners' launch.  Direction d rewrites wire buffer d in place.
+//
+// The owners' launch takes the steps' shape, and a layer's workgroups are a multiple of eight, so that a tile is on the
+// same XCD in either direction and in every launch: that XCD's L2 may hold the wire, and another one has to wait for it.
+// Measured on MI355X, us per call, block 64, with the owners' own shape and rows without padding -> as it is:
+//     elements     P = 2             3               4               5               8
+//     1 M       6.71 ->  6.17    6.83 ->  6.54  10.31 ->  9.63  10.44 -> 10.10  16.58 -> 16.52
+//     2 M       7.89 ->  7.37    8.38 ->  8.20  12.42 -> 11.83  13.22 -> 12.72  20.91 -> 20.84
+//     3 M       9.97 ->  8.21   11.87 ->  9.97  16.11 -> 14.26  17.60 -> 16.15  26.97 -> 25.12
+//     4 M      11.14 ->  9.06   14.25 -> 11.47  19.50 -> 15.97  21.49 -> 19.30  33.08 -> 29.72
+//     6 M      14.01 -> 11.24   17.02 -> 14.90  20.47 -> 20.29  27.13 -> 24.19  38.45 -> 38.08
+//     8 M      17.32 -> 13.60   21.99 -> 18.53  29.66 -> 25.56  33.13 -> 29.31  47.27 -> 47.02
+// Rows of a single workgroup are padded for an odd P only: 4096 elements, P = 5 6.33 -> 5.59, but P = 4 5.82 -> 6.22.
 template <int B>
 void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, const WireBuffers &w, uint16_t *out,
                            LaunchCtx &ctx)
@@ -469,13 +494,6 @@ void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, c
     const unsigned gy = (unsigned)P;
     const int h = P / 2, count[2] = {P - 1 - h, h};
     const WirePair wire = {{w.c[0], w.c[1]}, {w.s[0], w.s[1]}};
-    for (int t = 0; t < h; ++t) {
-        with_pass_shape(2 * n, [&](auto shape) {        // two shards' worth of work per shard: one per direction
-            using S = decltype(shape);
-            ctx.launch3d(semi_ring_step_kernel<B, S::K>, ring_grid<S>(shard_elems, 2 * n), gy, 2u, S::T, P, t, n, shard_elems,
-                         wire, tab);
-        });
-    }
     WireTable wires;
     for (int r = 0; r < kMaxPartials; ++r) {
         wires.codes[r] = nullptr;
@@ -488,20 +506,25 @@ void launch_semi_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, c
         wires.scales[received] = w.s[d];
         ++received;
     }
-    with_flat_shape(n, 2, [&](auto shape, auto batch) {
+    // two shards' worth of work per shard: one per direction.  With one step no wire is rewritten, and nothing turns (P = 2,
+    // 21 M elements 32.9 -> 32.6 us, 42 M 61.1 -> 60.3).
+    with_ring_shape(2 * n, h > 1 ? 2 * n : 0, [&](auto shape, auto turns) {
         using S = decltype(shape);
-        constexpr int U = decltype(batch)::value;
-        const unsigned gx = ring_grid<S>(shard_elems, 2 * n);
-        if constexpr (U <= 2) {
-            if (ag) {
-                ctx.launch2d(semi_ring_owner_kernel<B, S::K, U, true>, gx, gy, S::T, P, n, shard_elems, received, out, wires, tab);
-            } else {
-                ctx.launch2d(semi_ring_owner_kernel<B, S::K, U, false>, gx, gy, S::T, P, n, shard_elems, received, out, wires, tab);
-            }
+        constexpr bool kTurns = decltype(turns)::value;
+        constexpr int U = S::K == 1 ? 2 : 1;            // received wires to request at a time, as with_flat_shape
+        unsigned gx = ring_grid<S, kTurns>(shard_elems);
+        const unsigned unit = P & 1 ? 8 : P & 2 ? 4 : P & 4 ? 2 : 1;        // P rows of a multiple of this are one of eight
+        if (gx > 1 || (P & 1) != 0) gx = (gx + unit - 1) & ~(unit - 1);
+        for (int t = 0; t < h; ++t) {
+            ctx.launch3d(semi_ring_step_kernel<B, S::K, kTurns>, gx, gy, 2u, S::T, P, t, n, shard_elems, wire, tab);
+        }
+        if (ag) {
+            ctx.launch2d(semi_ring_owner_kernel<B, S::K, U, true, kTurns>, gx, gy, S::T, P, n, shard_elems, received, out, wires, tab);
+        } else {
+            ctx.launch2d(semi_ring_owner_kernel<B, S::K, U, false, kTurns>, gx, gy, S::T, P, n, shard_elems, received, out, wires, tab);
         }
     });
 }
-
 
 // ---- strided (Sec. 3.2) geometry ----
 

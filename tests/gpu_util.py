@@ -131,3 +131,27 @@ def gpu_variant(partials_u16, B, flags):
     eq.equarx_reduce_variant(parts, B, flags, out)
     torch.cuda.synchronize()
     return host_u16(out)
+
+
+def launches(call):
+    """The (grid, block) of every kernel that call() launches, in order: captured into a graph that is never run."""
+    import ctypes
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+
+    class Params(ctypes.Structure):     # hipKernelNodeParams
+        _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                    ("grid", ctypes.c_uint32 * 3), ("params", ctypes.c_void_p), ("shared", ctypes.c_uint32)]
+
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    raw, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0
+    nodes, found = (ctypes.c_void_p * count.value)(), []
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(count)) == 0
+    for node in nodes:
+        p = Params()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        found.append((tuple(p.grid), tuple(p.block)))
+    return found

@@ -65,7 +65,8 @@ def test_two_directions_around_one_round_of_workgroups(gpu, oracle, values, n): 
 
 
 @pytest.mark.parametrize("n,P,B", ((TURN_FROM - 1, 4, 256), (TURN_FROM, 3, 32), (TURN_FROM + 5 * 8192 + 3, 4, 512),
-                                   (TURN_FROM + 8 * 8192, 5, 64), (TURN_FROM // 2, 5, 128), (TURN_FROM // 2 + 4099, 4, 64)))
+                                   (TURN_FROM + 8 * 8192, 5, 64), (TURN_FROM // 2, 5, 128), (TURN_FROM // 2 + 4099, 4, 64),
+                                   (TURN_FROM - 3, 2, 64), (TURN_FROM + 4097, 2, 128)))
 def test_chains_that_turn(gpu, oracle, long_values, n, P, B):  # noqa: F811
     x = [np.resize(long_values[i % 3], n + i)[i:].copy() for i in range(P)]
     dev = [gpu.dev_bf16(p) for p in x]
@@ -82,6 +83,24 @@ def test_chains_that_turn(gpu, oracle, long_values, n, P, B):  # noqa: F811
     for flags in (*flavours, eq.SEMI_LOOP | eq.RING_ORDER):
         eq.equarx_reduce_variant_hops(dev, B, flags, out, eq.alloc_variant_workspace(flags, P, n, B))
         assert (gpu.host_u16(out) == _oracle_variant(oracle, x, B, flags)).all(), flags
+
+
+@pytest.mark.parametrize("n", (4099, ONE_ROUND // 2 - 5, ONE_ROUND // 2 + 1, ONE_ROUND + 9, TURN_FROM // 2 + 4099))
+@pytest.mark.parametrize("P", (1, 2, 3, 4, 6, 8))
+def test_a_tile_of_the_two_directions_stays_on_its_xcd(gpu, oracle, values, n, P):  # noqa: F811
+    """Workgroup b runs on XCD b % 8: every launch has the same rows of the same workgroups, and a direction's are a
+    multiple of eight (unless a row is a single one, and P even)."""
+    flags = eq.SEMI_LOOP | eq.RING_ORDER
+    x = [np.resize(values[i % 4], n + i)[i:].copy() for i in range(P)]
+    dev, work = [gpu.dev_bf16(p) for p in x], eq.alloc_variant_workspace(flags, P, n, 64)
+    out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    call = lambda: eq.equarx_reduce_variant_hops(dev, 64, flags, out, work)       # noqa: E731
+    call()
+    assert (gpu.host_u16(out) == _oracle_variant(oracle, x, 64, flags)).all()
+    made = gpu.launches(call)
+    assert len(made) == P // 2 + 1 and [g[2] for g, _ in made] == [2] * (P // 2) + [1]
+    (x, y), = {g[:2] for g, _ in made}
+    assert len({b for _, b in made}) == 1 and (x * y % 8 == 0 or (x == 1 and P % 2 == 0))
 
 
 @pytest.mark.parametrize("n", (ONE_ROUND // 2, ONE_ROUND // 2 + 3))
