@@ -96,11 +96,37 @@ inline unsigned ring_grid(int64_t shard_elems)
     return kTurns ? (unsigned)ring_groups<S>(shard_elems) : grid_for<S>(shard_elems);
 }
 
-// Full loop in ring order, hop by hop: P launches, each over all P shards (one grid row per shard).
-template <int B>
-void launch_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, int8_t *c, float *s, uint16_t *out,
-                      LaunchCtx &ctx)
+// The two wire buffers at the front of a workspace: codes, then scales, each part rounded up to the workspace alignment.
+// A chain rewrites one of them in place, but a strided one may end in the other (ends_beside), and a short one in ring order
+// takes them in turn; the two chains of a semi-loop take one each.
+struct WireBuffers {
+    int8_t *c[2];
+    float *s[2];
+};
+
+inline WireBuffers carve_workspace(void *workspace, int64_t n, int64_t scales_count)
 {
+    const size_t codes = round_up((size_t)n, kWorkspaceAlign);
+    const size_t scales = round_up((size_t)scales_count * sizeof(float), kWorkspaceAlign);
+    char *w = static_cast<char *>(workspace);
+    WireBuffers b;
+    for (int i = 0; i < 2; ++i) {
+        b.c[i] = reinterpret_cast<int8_t *>(w + (size_t)i * (codes + scales));
+        b.s[i] = reinterpret_cast<float *>(w + (size_t)i * (codes + scales) + codes);
+    }
+    return b;
+}
+
+// Full loop in ring order, hop by hop: P launches, each over all P shards (one grid row per shard).  Up to kOneRound
+// elements two wire buffers take turns, which in this layout is a little faster there than one that is rewritten in place
+// (MI355X, us per call, P = 3, 4, 5 and 8, in place -> in turn: 2 M elements of block 256 10.26 -> 9.91, 13.37 -> 13.25,
+// 17.11 -> 17.00, 26.87 -> 26.84; 4 M of block 64 13.36 -> 12.98, 17.92 -> 17.59, 22.17 -> 21.72, 36.45 -> 36.00; 4.4 M
+// 14.51 -> 14.44, 19.25 -> 19.33, 23.98 -> 23.98, 38.65 -> 38.46; 8 M 20.02 -> 20.10, 26.54 -> 26.82, 32.77 -> 34.01,
+// 53.70 -> 54.35).
+template <int B>
+void launch_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, const WireBuffers &w, uint16_t *out, LaunchCtx &ctx)
+{
+    const int other = n <= kOneRound ? 1 : 0;
     const int64_t nb = blocks_of(n, B);
     const int64_t shard_elems = (nb + P - 1) / P * B;       // ceil(nb / P) blocks per shard, as the single launch
     const unsigned gy = (unsigned)P;
@@ -108,15 +134,15 @@ void launch_ring_hops(const PartialTable &tab, int P, int64_t n, bool ag, int8_t
         using S = decltype(shape);
         constexpr bool kTurns = decltype(turns)::value;
         const unsigned gx = ring_grid<S, kTurns>(shard_elems);
-        ctx.launch2d(quantize_ring_kernel<B, S::K>, gx, gy, S::T, P, n, shard_elems, c, s, tab);
+        ctx.launch2d(quantize_ring_kernel<B, S::K>, gx, gy, S::T, P, n, shard_elems, w.c[0], w.s[0], tab);
         for (int i = 1; i + 1 < P; ++i) {
-            ctx.launch2d(hop_ring_kernel<B, S::K, kTurns>, gx, gy, S::T, c, s, P, i, n, shard_elems, c, s, tab);
+            const int from = (i - 1) & other, to = i & other;
+            ctx.launch2d(hop_ring_kernel<B, S::K, kTurns>, gx, gy, S::T, w.c[from], w.s[from], P, i, n, shard_elems, w.c[to],
+                         w.s[to], tab);
         }
-        if (ag) {
-            ctx.launch2d(tail_ring_kernel<B, S::K, true, kTurns>, gx, gy, S::T, c, s, P, P - 1, n, shard_elems, out, tab);
-        } else {
-            ctx.launch2d(tail_ring_kernel<B, S::K, false, kTurns>, gx, gy, S::T, c, s, P, P - 1, n, shard_elems, out, tab);
-        }
+        const int last = (P - 2) & other;
+        ctx.launch2d(ag ? tail_ring_kernel<B, S::K, true, kTurns> : tail_ring_kernel<B, S::K, false, kTurns>, gx, gy, S::T,
+                     w.c[last], w.s[last], P, P - 1, n, shard_elems, out, tab);
     });
 }
 
@@ -448,27 +474,6 @@ inline int fill_table(const void *const *partials_bf16, int32_t P, int64_t n, Al
     for (int32_t i = 0; i < P; ++i) tab.x[i] = static_cast<const uint16_t *>(partials_bf16[i]);
     for (int32_t i = P; i < kMaxPartials; ++i) tab.x[i] = tab.x[i - P];     // small_kernel reads on around the ring
     return EQUARX_OK;
-}
-
-// The two wire buffers at the front of a workspace: codes, then scales, each part rounded up to the workspace alignment.
-// A chain rewrites one of them in place (a strided one may end in the other, ends_beside); the two chains of a semi-loop
-// take one each.
-struct WireBuffers {
-    int8_t *c[2];
-    float *s[2];
-};
-
-inline WireBuffers carve_workspace(void *workspace, int64_t n, int64_t scales_count)
-{
-    const size_t codes = round_up((size_t)n, kWorkspaceAlign);
-    const size_t scales = round_up((size_t)scales_count * sizeof(float), kWorkspaceAlign);
-    char *w = static_cast<char *>(workspace);
-    WireBuffers b;
-    for (int i = 0; i < 2; ++i) {
-        b.c[i] = reinterpret_cast<int8_t *>(w + (size_t)i * (codes + scales));
-        b.s[i] = reinterpret_cast<float *>(w + (size_t)i * (codes + scales) + codes);
-    }
-    return b;
 }
 
 // Semi-loop in ring order, hop by hop: h = P/2 launches in which both chains of every shard advance one device
@@ -1117,7 +1122,7 @@ int equarx_reduce_variant_hops(const void *const *partials_bf16, int32_t P, int6
             return ctx.status();
         }
         if (ring) {         // every launch is one ring step on all P shards: grid row k takes device k+1+step's partial
-#define CALL(BB) launch_ring_hops<BB>(tab, P, n, ag, c, s, out, ctx)
+#define CALL(BB) launch_ring_hops<BB>(tab, P, n, ag, w, out, ctx)
             EQUARX_DISPATCH_BLOCK(block, CALL)
 #undef CALL
             return ctx.status();

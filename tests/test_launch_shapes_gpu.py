@@ -85,6 +85,17 @@ def test_chains_that_turn(gpu, oracle, long_values, n, P, B):  # noqa: F811
         assert (gpu.host_u16(out) == _oracle_variant(oracle, x, B, flags)).all(), flags
 
 
+@pytest.mark.parametrize("n,P", ((4099, 2), (4099, 5), (ONE_ROUND - 3, 4), (ONE_ROUND, 3), (ONE_ROUND + 1, 4)))
+@pytest.mark.parametrize("flags", (eq.RING_ORDER, eq.RING_ORDER | eq.AG_UNQUANTIZED))
+def test_short_chains_in_ring_order_take_their_buffers_in_turn(gpu, oracle, values, n, P, flags):  # noqa: F811
+    x = [np.resize(values[i % 4], n + i)[i:].copy() for i in range(P)]
+    work, out = eq.alloc_variant_workspace(flags, P, n, 64).fill_(0x55), torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    eq.equarx_reduce_variant_hops([gpu.dev_bf16(p) for p in x], 64, flags, out, work)
+    assert (gpu.host_u16(out) == _oracle_variant(oracle, x, 64, flags)).all()
+    second = work[work.numel() // 2:]
+    assert bool((second[:n] != 0x55).any()) == (P > 2 and n <= ONE_ROUND)
+
+
 @pytest.mark.parametrize("n", (4099, ONE_ROUND // 2 - 5, ONE_ROUND // 2 + 1, ONE_ROUND + 9, TURN_FROM // 2 + 4099))
 @pytest.mark.parametrize("P", (1, 2, 3, 4, 6, 8))
 def test_a_tile_of_the_two_directions_stays_on_its_xcd(gpu, oracle, values, n, P):  # noqa: F811
