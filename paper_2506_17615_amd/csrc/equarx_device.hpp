@@ -1316,14 +1316,19 @@ __global__ __launch_bounds__(pass_threads(K)) void tail_ring_kernel(Global<const
 // the waits between them.
 // * A step is nested in the one before (small_steps), so that a hop costs one
 //   compare and branch; leaving a loop over the positions cost eight scalar
-//   instructions per hop.  Measured on MI355X, GPU us per call: 16 partials of
-//   344 k elements 4.86 -> 4.34, of 20 k 3.93 -> 3.59; 8 partials of 1 M 5.28 ->
-//   4.81, of 20 k 2.76 -> 2.53.
+//   instructions per hop.  And there is no loop around the steps unless kMany:
+//   in one, the first step asks at run time whether it is the first.  Measured
+//   on MI355X, GPU us per call (captured calls one after the other, inputs
+//   cold), loop over positions -> nested in a loop -> as it is, 8 elements per
+//   lane: 16 partials of 344 k elements, block 128, 4.90 -> 4.90 -> 4.77, of
+//   600 k 7.13 -> 7.32 -> 7.11; 8 partials, block 256, of 4 k 3.08 -> 3.07 ->
+//   2.96, of 600 k 4.60 -> 4.84 -> 4.66; 4 partials of 344 k 2.93 -> 2.97 ->
+//   2.83, of 600 k 3.57 -> 3.61 -> 3.48.
 // * E = 4 elements per lane in workgroups of a single wave, while the chip has
 //   a SIMD for each (SmallLane): half the arithmetic per hop for one more lane
 //   exchange, and the requests come from more CUs.  After the step above: 16
-//   partials of 172 k 4.06 -> 3.63, of 20 k 3.59 -> 3.05, of 344 k 4.34 -> 4.77
-//   (not taken); 8 of 172 k 3.02 -> 2.93, of 20 k 2.53 -> 2.30.
+//   partials of 4 k 3.99 -> 3.41, of 66 k 4.22 -> 3.66, of 344 k 4.77 -> 5.21
+//   (not taken); 8 of 4 k 2.96 -> 2.63, of 66 k 3.14 -> 2.93.
 //
 // The full loop (kSemi = false) takes position i at step i.  The semi-loop
 // takes the owner at step 0, positions h+1 .. P-1 at steps 1 .. na = P-1-h and
@@ -1497,7 +1502,7 @@ __device__ __forceinline__ void small_body(const PartialTable &tab, int P, int r
     float t[E], own[E];
     typename Lane::Raw x[N];
 
-    for (int base = 0; base < P; base += N) {        // once, unless kMany
+    for (int base = 0; base < (kMany ? P : 1); base += N) {
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             // The table repeats after P entries, so a position may run past P (rot <= P <= N, unless kMany).
