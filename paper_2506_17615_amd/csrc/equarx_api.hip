@@ -175,26 +175,37 @@ inline ChainGrid chain_grid(int64_t n, int32_t block, int32_t P, bool ring)
 // Which single-launch calls the latency-shaped small_kernel takes: messages of up to three workgroups per CU, with
 // enough partials that requesting them together pays.  The semi-loop, whose code is twice as long, needs enough tiles to
 // repay fetching it if its chain is long (or its blocks of 512, which keep it to 8 elements per lane).  Measured on MI355X,
-// GPU us per call, bandwidth kernel (256 x 1) / small_kernel with 8 / with 4 elements per lane:
-//     full loop, P = 4     8, block 32          12                 16                 24
-//     4,099    2.17/2.30/2.04  2.86/2.75/2.25  3.57/3.59/2.94     4.37/4.17/3.34     5.85/6.17/5.31
-//     64 k     2.22/2.20/2.13  2.90/2.64/2.44  3.56/3.43/2.97     4.20/3.92/3.37     5.57/6.18/5.55
-//     256 k    2.71/2.68/2.69  5.30/3.18/3.10  7.51/3.86/3.78     9.30/4.50/4.30    14.13/7.29/6.85
-//     344 k    3.06/2.71/2.85  5.58/3.28/3.43  7.88/4.01/4.42     9.92/4.57/5.09    14.42/7.61/7.79
-//     524 k    2.86/2.75/3.13  5.89/3.44/3.88  8.27/4.42/5.02    10.24/5.24/5.88    14.75/8.47/8.51
-//     600 k    3.82/3.18/3.27  6.37/4.12/4.08  8.66/5.82/5.45    10.91/7.01/6.37    15.46/10.12/9.58
-//     1 M      4.36/3.60/3.88  6.89/4.84/4.93  9.21/6.98/6.88    11.59/8.33/8.17    16.45/13.23/12.28
-//     1.57 M   4.77/4.36/4.84  7.56/6.35/6.39 10.16/10.39/9.48   12.77/12.12/11.23  18.08/18.22/17.33
-//     1.9 M    5.11/5.10/5.47  7.95/7.46/7.39 10.76/12.53/11.15  13.43/14.70/13.04  19.05/22.13/20.53
-//     semi-loop, P = 4     5                    8                  16
-//     4,099    2.43/2.73/2.22  2.67/2.89/2.36   3.25/3.42/2.83    5.07/6.10/5.15
-//     64 k     2.47/2.72/2.42  2.70/2.84/2.57   3.26/3.42/3.16    4.83/5.24/4.69
-//     256 k    2.98/3.11/2.98  3.29/3.31/3.17   5.57/3.91/3.73   10.42/6.40/5.64
-//     524 k    3.06/3.27/3.44  4.15/3.48/3.68   6.08/4.24/4.45   10.79/7.46/7.17
-//     1 M      4.52/4.05/4.16  5.10/4.53/4.46   7.12/5.67/5.58   12.09/10.54/9.78
-//     1.57 M   4.86/4.88/5.13  5.55/5.42/5.55   7.67/7.17/6.91   13.10/14.26/12.65
-//     1.9 M    5.24/5.64/5.74  5.92/6.09/6.26   8.03/8.24/7.96   13.71/17.23/14.51
-// (two and three partials 1.93/2.11/2.07 and 2.02/2.20/2.13 at 4,099, 3.17/3.34/4.32 and 4.05/3.96/4.57 at 1.57 M).
+// GPU us per call (captured calls one after the other, inputs cold, block 256), bandwidth kernel (256 x 1) / small_kernel with
+// 8 / with 4 elements per lane, full loop:
+//                        P = 2                 4                 8                12                16                24                32
+//     4,099     1.86/1.99/2.00    2.16/2.13/2.01    2.86/2.66/2.43    3.63/3.51/2.99    4.36/4.08/3.42    5.90/6.36/5.55    7.46/7.49/6.54
+//     66 k      2.11/2.11/2.12    2.60/2.39/2.39    4.05/3.04/2.89    6.62/3.84/3.37    8.89/4.38/3.82   12.96/7.12/6.28   17.01/8.23/7.20
+//     262 k     2.74/2.46/2.57    3.86/2.70/2.76    5.94/3.34/3.43    8.00/4.06/4.18    9.95/4.66/4.80   14.05/7.72/7.20   18.20/9.11/8.68
+//     344 k     2.81/2.45/2.64    4.01/2.76/2.95    6.16/3.52/3.76    8.06/4.30/4.67   10.14/4.85/5.59   14.31/8.20/8.72   18.23/9.55/9.66
+//     524 k     3.01/2.61/2.94    4.22/3.01/3.25    6.49/4.09/4.36    8.70/4.96/5.44   11.01/5.74/6.64   15.38/9.06/9.40  20.05/11.14/10.65
+//     600 k     3.22/3.04/3.02    4.40/3.45/3.37    6.75/4.60/4.54    8.98/6.24/5.76   11.20/7.35/7.02  15.60/10.91/10.48  20.12/12.18/12.31
+//     786 k     3.24/3.20/3.41    4.50/3.58/3.74    6.78/4.87/5.01    9.13/6.78/6.67   11.39/7.64/7.88  16.11/11.26/11.49  20.69/12.66/13.56
+//     800 k     3.27/3.23/3.27    4.56/3.58/3.75    6.89/4.89/5.07    9.11/6.73/6.93   11.48/7.65/8.20  16.24/11.39/12.38  20.75/12.65/15.15
+//     1.05 M    3.35/3.49/3.70    4.71/3.85/4.12    7.13/5.54/5.95    9.61/7.45/7.80   11.91/8.28/9.39  16.74/13.11/13.90  21.47/15.81/16.86
+//     1.07 M    3.41/3.77/3.85    4.78/4.17/4.24    7.23/5.98/6.02    9.62/8.61/8.16   12.06/9.89/9.71  16.93/15.84/14.57  21.93/19.53/17.78
+//     1.31 M    3.56/4.10/4.18    5.06/4.50/4.70    7.74/6.36/6.49   10.26/9.39/8.90  12.78/10.33/10.68  18.27/16.64/16.14  23.21/20.17/19.16
+//     1.34 M    3.67/4.02/4.33    5.15/4.53/4.76    7.76/6.33/6.59   10.28/9.18/9.22  12.74/10.24/11.15  18.00/16.45/17.00  23.35/20.32/20.19
+//     1.57 M    3.79/4.21/4.62    5.27/4.82/5.05    8.10/7.08/7.28  10.85/11.08/10.34  13.54/12.49/12.54  19.00/18.56/18.95  24.46/23.62/23.27
+// semi-loop:
+//                        P = 4                 5                 8                12                16                17                24
+//     4,099     2.45/2.45/2.31    2.69/2.68/2.49    3.31/3.37/3.03    4.20/4.62/4.08    5.16/5.51/4.83    5.38/7.71/6.67    7.02/8.73/7.81
+//     66 k      2.89/2.70/2.70    3.13/2.98/2.90    4.46/3.76/3.48    7.13/4.99/4.48    9.45/5.92/5.26   10.07/7.52/6.77   13.74/8.87/7.96
+//     262 k     4.10/3.12/3.38    4.63/3.25/3.32    6.21/4.12/4.01    8.37/5.27/5.03   10.50/6.26/5.73   11.00/7.35/6.90   14.78/8.60/8.01
+//     344 k     4.20/3.10/3.30    4.72/3.32/3.51    6.36/4.24/4.29    8.50/5.48/5.80   10.70/6.38/6.81   11.21/7.37/7.85   15.12/8.87/9.31
+//     524 k     4.42/3.32/3.61    5.02/3.68/3.86    6.84/4.77/4.87    9.10/6.20/6.25   11.62/7.55/7.46   12.20/8.16/8.69   16.19/9.53/9.83
+//     600 k     4.41/3.90/3.77    5.02/4.11/3.99    6.85/5.34/5.09    9.11/7.32/6.87   11.65/8.71/8.33  12.19/10.20/9.91  16.32/11.61/11.42
+//     786 k     4.56/4.00/4.10    5.20/4.38/4.37    7.02/5.58/5.50    9.57/7.79/7.44   11.97/8.87/8.62  12.59/10.39/10.19  16.93/11.85/11.75
+//     800 k     4.59/3.91/4.14    5.22/4.35/4.43    7.06/5.62/5.58    9.54/7.72/7.90   11.92/8.88/9.31  12.49/10.37/11.06  16.84/11.89/12.98
+//     1.05 M    4.81/4.22/4.52    5.42/4.56/4.77    7.43/6.24/6.36    9.89/8.40/8.43  12.37/9.79/10.11  12.96/11.16/12.18  17.43/12.84/14.58
+//     1.07 M    4.84/4.49/4.59    5.46/4.94/4.89    7.55/6.65/6.49    9.95/9.56/9.07  12.50/10.92/10.79  13.12/13.04/13.28  17.68/15.16/16.03
+//     1.31 M    5.15/4.90/5.00    5.71/5.22/5.24    7.96/7.05/6.90  10.52/10.19/9.59  13.20/11.73/11.45  13.86/13.87/13.99  18.80/16.65/16.76
+//     1.34 M    5.25/4.93/5.14    5.91/5.21/5.32    8.02/7.12/7.04  10.57/10.05/10.18  13.20/11.63/12.13  13.88/13.88/15.05  18.60/16.61/17.89
+//     1.57 M    5.38/5.06/5.35    6.01/5.55/5.65    8.30/7.78/7.61  11.06/11.92/10.94  13.92/13.77/13.35  14.58/15.52/15.98  19.51/19.43/18.90
 constexpr int64_t kSmallElems = (int64_t)768 * NarrowPass::kElems;
 constexpr int64_t kSmallSemiFrom = (int64_t)32 * NarrowPass::kElems;
 
@@ -204,11 +215,21 @@ inline bool small_semi(int64_t n, int P, int32_t block)
     return n <= kSmallElems && P >= 5 && (n > kSmallSemiFrom || (P <= 8 && block <= 256));
 }
 
-// 4 elements per lane (a full loop, blocks of up to 256; the table above): up to one wave of them for each of the 1024
-// SIMDs.  With more, some SIMDs have two waves to the others' one, and 8 per lane even out better; from two waves for each
-// on that no longer decides, and long chains, whose arithmetic it is that counts, are faster with 4 again.
+// 4 elements per lane instead of 8 (blocks of up to 256): half the arithmetic per hop, twice the waves.  What a message takes
+// goes by how many waves its fullest SIMD has (MI355X has 1024), and 8 per lane come in workgroups of four, one per SIMD of
+// a CU, so that a SIMD has half of the next even number of the waves that it would have with 4: an odd number of those is
+// where 4 wins, an even one where 8 does, as the table shows at 524 k | 600 k, 786 k | 800 k and 1.05 | 1.07 M.  Chains of up
+// to 8, which wait for memory more than for arithmetic, gain too little from 4 beyond the first wave.  The semi-loop of up
+// to 16, whose steps are longer, does not mind an even number.  (Full loops of more than 24 in three waves, and what a sixth
+// wave takes, are as measured.)
 constexpr int64_t kOneWaveEach = (int64_t)1024 * SmallShape<4>::kElems;
-inline bool small_lanes_of_4(int64_t n, int P) { return n <= kOneWaveEach || (P > 8 && n > 2 * kOneWaveEach); }
+constexpr bool small_lanes_of_4(int64_t n, int P, bool semi)
+{
+    const int64_t waves = (n + kOneWaveEach - 1) / kOneWaveEach;        // 1 .. 6
+    if (waves == 1 || (semi && P <= 16)) return true;
+    if (semi) return waves % 2 == 1 || (waves != 4 && P > 24);
+    return P > 8 && (waves == 5 || (waves == 3 && P <= 24) || (waves == 6 && (P <= 14 || P > 24)));
+}
 
 // Launch shapes of the bandwidth kernels of the single-launch calls.  What a message of a few million elements pays
 // for is the last round of workgroups, so each shape is used where its rounds come out even:
@@ -329,9 +350,7 @@ void launch_small(const PartialTable &tab, int P, int64_t n, bool ring, uint16_t
 {
     if constexpr (B > 256) {            // 4 elements per lane would spread a block over two waves
         launch_small_as<B, 8, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
-    } else if constexpr (kSemi) {
-        launch_small_as<B, 4, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
-    } else if (small_lanes_of_4(n, P)) {
+    } else if (small_lanes_of_4(n, P, kSemi)) {
         launch_small_as<B, 4, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
     } else {
         launch_small_as<B, 8, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);

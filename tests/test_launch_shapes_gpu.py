@@ -13,7 +13,7 @@ WIDE_ROUND = 768 * 8192         # single-launch calls: up to here 512 threads x 
 PAIRED_FROM = 2560 * 8192       # single-launch chain: above, 256 threads x 4 tiles
 CACHED_OUT = 32 << 20           # single-launch calls: up to here the output stays in the Infinity Cache
 TURN_FROM = 20 << 20            # elements of wire: from here every second launch of a hop-by-hop chain walks back
-ONE_WAVE_EACH = 1024 * 256      # small single-launch calls: up to here 4 elements per lane, and above twice that for P > 8
+ONE_WAVE_EACH = 1024 * 256      # small single-launch calls: up to here 4 elements per lane, and above by waves per SIMD
 PAIR_ROUND = 1792 * 4096        # a dequantization of a wire that arrived: up to here 256 threads x 2 tiles
 LONG_DEQUANTIZE = 13 << 20      # ... and from here 1024 x 1
 ONE_ROUND = 2048 * 2048         # elements: up to here one tile of 256 threads per workgroup, above 512 threads x 2 tiles
@@ -152,6 +152,19 @@ def test_single_launch_around_its_shapes(gpu, oracle, n, flags):  # noqa: F811
     x = [gpu.bf16_of(rng.standard_normal(n, dtype=np.float32)) for _ in range(3)]
     B = 64 if flags & eq.RING_ORDER else 256
     assert (gpu.gpu_variant(x, B, flags) == _oracle_variant(oracle, x, B, flags)).all()
+
+
+@pytest.mark.parametrize("flags,P,lanes", ((0, 4, "488888"), (0, 8, "488888"), (0, 9, "484844"), (0, 14, "484844"), (0, 15, "484848"),
+                                           (0, 24, "484848"), (0, 25, "488844"), (eq.RING_ORDER, 12, "484844"),
+                                           (eq.SEMI_LOOP, 5, "444444"), (eq.SEMI_LOOP, 16, "444444"),
+                                           (eq.SEMI_LOOP, 17, "484848"), (eq.SEMI_LOOP, 25, "444844")))
+def test_elements_per_lane_by_waves_per_simd(gpu, flags, P, lanes):  # noqa: F811
+    """Of small single launches of 1 to 6 waves of 4 elements per lane for each SIMD, at both ends of each."""
+    x, out = (torch.zeros(6 * ONE_WAVE_EACH, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    for waves, lane in enumerate(lanes, 1):
+        for n in ((waves - 1) * ONE_WAVE_EACH + 1 if waves > 1 else 70000, waves * ONE_WAVE_EACH):
+            made, = gpu.launches(lambda: eq.equarx_reduce_variant([x[:n]] * P, 256, flags, out[:n]))
+            assert made[1] == ((64, 1, 1) if lane == "4" else (256, 1, 1)), (n, made)
 
 
 @pytest.mark.parametrize("n", (1, 2, 3, 255, 257, 4097, 65 * 1024 + 2, ONE_WAVE_EACH - 1, ONE_WAVE_EACH, ONE_WAVE_EACH + 1,
