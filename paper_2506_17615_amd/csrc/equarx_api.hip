@@ -220,15 +220,30 @@ inline bool small_semi(int64_t n, int P, int32_t block)
 // a CU, so that a SIMD has half of the next even number of the waves that it would have with 4: an odd number of those is
 // where 4 wins, an even one where 8 does, as the table shows at 524 k | 600 k, 786 k | 800 k and 1.05 | 1.07 M.  Chains of up
 // to 8, which wait for memory more than for arithmetic, gain too little from 4 beyond the first wave.  The semi-loop of up
-// to 16, whose steps are longer, does not mind an even number.  (Full loops of more than 24 in three waves, and what a sixth
-// wave takes, are as measured.)
+// to 16, whose steps are longer, does not mind an even number; with more, whose partials come in two requests, three waves are
+// the most that pays.  (Full loops of more than 24 in three waves, and of up to 14 in six, are as measured.)
+//
+// on_lines: all partials begin on a 128-byte line.  Those of one tensor that was cut into pieces may not, and then the 512
+// bytes that a workgroup of one wave reads of each are five lines for four, the 4 KB of one of four waves 33 for 32.  us, 8 /
+// 4 elements per lane, on lines and 16 bytes off them: full loop, P = 12, block 256, 655 k 6.41/5.89 and 6.58/6.33, 1.31 M
+// 9.21/8.83 and 9.35/9.88; P = 16, block 64, 786 k 7.29/7.14 and 7.51/7.79, 1.18 M 9.65/9.31 and 9.85/10.68; P = 24, block 256,
+// 786 k 11.41/11.50 and 11.54/12.80; semi-loop, P = 8, block 64, 786 k 5.53/5.18 and 5.61/5.64, 1.05 M 6.05/5.92 and 6.11/6.75;
+// P = 16, block 256, 786 k 8.93/8.66 and 9.07/9.33, 1.57 M 12.62/13.07 and 12.88/14.49.
 constexpr int64_t kOneWaveEach = (int64_t)1024 * SmallShape<4>::kElems;
-constexpr bool small_lanes_of_4(int64_t n, int P, bool semi)
+constexpr bool small_lanes_of_4(int64_t n, int P, bool semi, bool on_lines)
 {
     const int64_t waves = (n + kOneWaveEach - 1) / kOneWaveEach;        // 1 .. 6
-    if (waves == 1 || (semi && P <= 16)) return true;
-    if (semi) return waves % 2 == 1 || (waves != 4 && P > 24);
-    return P > 8 && (waves == 5 || (waves == 3 && P <= 24) || (waves == 6 && (P <= 14 || P > 24)));
+    if (waves == 1) return true;
+    if (semi) return waves == 3 || (P <= 16 && on_lines);
+    if (!on_lines) return P > 8 && P <= 12 && waves == 3;
+    return P > 8 && (waves == 5 || (waves == 3 && P <= 24) || (waves == 6 && P <= 14));
+}
+
+inline bool on_lines(const PartialTable &tab, int P)
+{
+    uintptr_t bits = 0;
+    for (int i = 0; i < P; ++i) bits |= reinterpret_cast<uintptr_t>(tab.x[i]);
+    return bits % 128 == 0;
 }
 
 // Launch shapes of the bandwidth kernels of the single-launch calls.  What a message of a few million elements pays
@@ -350,7 +365,7 @@ void launch_small(const PartialTable &tab, int P, int64_t n, bool ring, uint16_t
 {
     if constexpr (B > 256) {            // 4 elements per lane would spread a block over two waves
         launch_small_as<B, 8, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
-    } else if (small_lanes_of_4(n, P, kSemi)) {
+    } else if (small_lanes_of_4(n, P, kSemi, on_lines(tab, P))) {
         launch_small_as<B, 4, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
     } else {
         launch_small_as<B, 8, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);

@@ -155,16 +155,20 @@ def test_single_launch_around_its_shapes(gpu, oracle, n, flags):  # noqa: F811
 
 
 @pytest.mark.parametrize("flags,P,lanes", ((0, 4, "488888"), (0, 8, "488888"), (0, 9, "484844"), (0, 14, "484844"), (0, 15, "484848"),
-                                           (0, 24, "484848"), (0, 25, "488844"), (eq.RING_ORDER, 12, "484844"),
+                                           (0, 24, "484848"), (0, 25, "488848"), (eq.RING_ORDER, 12, "484844"),
                                            (eq.SEMI_LOOP, 5, "444444"), (eq.SEMI_LOOP, 16, "444444"),
-                                           (eq.SEMI_LOOP, 17, "484848"), (eq.SEMI_LOOP, 25, "444844")))
+                                           (eq.SEMI_LOOP, 17, "484888"), (eq.SEMI_LOOP, 25, "484888")))
 def test_elements_per_lane_by_waves_per_simd(gpu, flags, P, lanes):  # noqa: F811
-    """Of small single launches of 1 to 6 waves of 4 elements per lane for each SIMD, at both ends of each."""
-    x, out = (torch.zeros(6 * ONE_WAVE_EACH, dtype=torch.bfloat16, device="cuda") for _ in range(2))
-    for waves, lane in enumerate(lanes, 1):
-        for n in ((waves - 1) * ONE_WAVE_EACH + 1 if waves > 1 else 70000, waves * ONE_WAVE_EACH):
-            made, = gpu.launches(lambda: eq.equarx_reduce_variant([x[:n]] * P, 256, flags, out[:n]))
-            assert made[1] == ((64, 1, 1) if lane == "4" else (256, 1, 1)), (n, made)
+    """Of small single launches of 1 to 6 waves of 4 elements per lane for each SIMD, at both ends of each; the last partial on
+    a 128-byte line and 16 bytes off one."""
+    x, out = (torch.zeros(6 * ONE_WAVE_EACH + 8, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    off_lines = "484888" if flags & eq.SEMI_LOOP or 8 < P <= 12 else "488888"
+    for at, by_waves in ((0, lanes), (8, off_lines)):
+        for waves, lane in enumerate(by_waves, 1):
+            for n in ((waves - 1) * ONE_WAVE_EACH + 1 if waves > 1 else 70000, waves * ONE_WAVE_EACH):
+                parts = [x[:n]] * (P - 1) + [x[at:at + n]]
+                made, = gpu.launches(lambda: eq.equarx_reduce_variant(parts, 256, flags, out[:n]))
+                assert made[1] == ((64, 1, 1) if lane == "4" else (256, 1, 1)), (at, n, made)
 
 
 @pytest.mark.parametrize("n", (1, 2, 3, 255, 257, 4097, 65 * 1024 + 2, ONE_WAVE_EACH - 1, ONE_WAVE_EACH, ONE_WAVE_EACH + 1,
@@ -173,9 +177,15 @@ def test_elements_per_lane_by_waves_per_simd(gpu, flags, P, lanes):  # noqa: F81
 def test_small_single_launches_by_elements_per_lane(gpu, oracle, values, n, P):  # noqa: F811
     """Every flavour around the ends of a lane's words, a wave's tile and the lines between the layouts, kept wire included."""
     x = [values[i % 4][i:i + n] for i in range(P)]
+    one = gpu.dev_bf16(np.concatenate([np.concatenate([v, np.zeros(-n % 8 + 8, v.dtype)]) for v in x]))
+    off_lines = [one[i * (n + -n % 8 + 8):][:n] for i in range(P)]
     for k, flags in enumerate(SINGLE):
         B = (32, 64, 128, 256, 512)[(n + P + k) % 5]
-        assert (gpu.gpu_variant(x, B, flags) == _oracle_variant(oracle, x, B, flags)).all(), (B, flags)
+        want = _oracle_variant(oracle, x, B, flags)
+        assert (gpu.gpu_variant(x, B, flags) == want).all(), (B, flags)
+        out = torch.full((n,), 7.0, dtype=torch.bfloat16, device="cuda")
+        eq.equarx_reduce_variant(off_lines, B, flags, out)
+        assert (gpu.host_u16(out) == want).all(), (B, flags)
     B = (32, 64, 128, 256, 512)[(n + 2 * P) % 5]
     want, wc, ws = oracle.reduce_chain(x, B, keep_wire=True)
     got, c, s = gpu.gpu_chain_fused(x, B)
