@@ -71,18 +71,27 @@ def test_chains_that_turn(gpu, oracle, long_values, n, P, B):  # noqa: F811
     x = [np.resize(long_values[i % 3], n + i)[i:].copy() for i in range(P)]
     dev = [gpu.dev_bf16(p) for p in x]
     out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
-    want = oracle.reduce_chain(x, B)
-    if n >= TURN_FROM - 1:
-        eq.equarx_reduce_quantized(dev, B, out, eq.alloc_workspace(P, n, B))
+    flavours = (eq.SEMI_LOOP | eq.RING_ORDER,)
+    if n >= TURN_FROM - 3:
+        want = oracle.reduce_chain(x, B)
+        eq.equarx_reduce_quantized(dev, B, out.fill_(5.0), eq.alloc_workspace(P, n, B))
         assert (gpu.host_u16(out) == want).all()
-        eq.equarx_reduce_quantized_static(dev, B, out)
+        eq.equarx_reduce_quantized_static(dev, B, out.fill_(5.0))
         assert (gpu.host_u16(out) == want).all()
-        eq.equarx_reduce_quantized_fused_ends(dev, B, out, eq.alloc_workspace(P, n, B))
+        eq.equarx_reduce_quantized_fused_ends(dev, B, out.fill_(5.0), eq.alloc_workspace(P, n, B))
         assert (gpu.host_u16(out) == want).all()
-    flavours = (0, eq.AG_UNQUANTIZED | eq.RING_ORDER, eq.SEMI_LOOP) if n >= TURN_FROM - 1 else ()
-    for flags in (*flavours, eq.SEMI_LOOP | eq.RING_ORDER):
-        eq.equarx_reduce_variant_hops(dev, B, flags, out, eq.alloc_variant_workspace(flags, P, n, B))
+        flavours += (0, eq.AG_UNQUANTIZED, eq.RING_ORDER, eq.RING_ORDER | eq.AG_UNQUANTIZED, eq.SEMI_LOOP)
+    for flags in flavours:
+        eq.equarx_reduce_variant_hops(dev, B, flags, out.fill_(5.0), eq.alloc_variant_workspace(flags, P, n, B))
         assert (gpu.host_u16(out) == _oracle_variant(oracle, x, B, flags)).all(), flags
+
+
+@pytest.mark.parametrize("n,B", ((TURN_FROM + 8 * 8192, 32), (TURN_FROM + 4097, 128)))
+def test_a_kept_wire_does_not_turn(gpu, oracle, long_values, n, B):  # noqa: F811
+    x = [np.resize(long_values[i], n + i)[i:].copy() for i in range(3)]
+    want, wc, ws = oracle.reduce_chain(x, B, keep_wire=True)
+    got, c, s, _ = gpu.gpu_chain(x, B)
+    assert (got == want).all() and (c == wc).all() and (s.view(np.uint32) == ws.view(np.uint32)).all()
 
 
 @pytest.mark.parametrize("n,P", ((4099, 2), (4099, 5), (ONE_ROUND - 3, 4), (ONE_ROUND, 3), (ONE_ROUND + 1, 4)))
