@@ -144,7 +144,10 @@ int equarx_reduce_stage(const int8_t *codes_in, const float *scales_in, const vo
  *   workspace       device, at least equarx_workspace_bytes(P, n, block)
  *                   bytes, 256-byte aligned; holds the wire, which the hops
  *                   rewrite in place (its contents after the call are
- *                   unspecified).  Not needed (may be NULL) when both wire_*
+ *                   unspecified, and so is how much of it a call uses: the
+ *                   sizes that the calls of this header ask for are fixed, as
+ *                   callers may keep them, and have room for two wires, though
+ *                   most calls use one).  Not needed (may be NULL) when both wire_*
  *                   are given.
  *   wire_codes      NULL, or device int8 [P][equarx_wire_row_codes(n)]:
  *                   receives the codes on the wire after every quantization
@@ -273,7 +276,8 @@ int equarx_reduce_variant(const void *const *partials_bf16, int32_t P, int64_t n
  *           of every shard advance one device per launch, as both directions
  *           of a ring do -- then the owners' launch: P/2 + 1 launches.
  *   workspace  equarx_variant_workspace_bytes(flags, P, n, block) bytes, 256-byte
- *           aligned (more for the semi-loop, and more again in ring order).
+ *           aligned: room for two wires in the full loop, three in the semi-loop
+ *           and four there in ring order.
  * Other arguments as for equarx_reduce_quantized (out_bf16 may be a partial).
  */
 int equarx_reduce_variant_hops(const void *const *partials_bf16, int32_t P, int64_t n, int32_t block,
