@@ -7,10 +7,11 @@ Prints ONE JSON line:
 
   value      effective input GB/s (bf16 bytes reduced per second): 2*P*n / (mean wall-clock time of a step over
              the K timed steps, between two device synchronisations).  Inputs are COLD (two resident input sets
-             used in turn, more than the 256 MB Infinity Cache); the wire is WARM (each hop reads what the launch
-             before it wrote, which that cache still holds).
+             used in turn, more than the 256 MB Infinity Cache); the wire is WARM (each hop rewrites in place what the
+             launch before it wrote, most of which the L2s still hold).
   roofline   the dominant kernel (the hop), its duration measured with HIP events recorded on the stream around
-             runs of hops inside the real call.  `achieved`/`frac` are the warm-wire figures of the timed chain;
+             runs of hops inside the real call.  `achieved`/`frac` are the warm-wire figures of the timed chain, by the
+             schedule's bytes: wire bytes that the L2s serve are among them, so they are no HBM rate;
              `cold_wire` holds the same kernel's figures when every wire it reads was written several launches
              earlier (independent chains interleaved pass by pass), which is what a wire arriving from another
              device looks like.
@@ -422,12 +423,11 @@ def main() -> int:
         kernel_ms = launches_timed = traffic_only_ms = copy_gbps = None
         if everything and P > 1:
             kernel_ms, launches_timed = per_launch_ms(calls["hop"], 1, P - 1)
-            if n % B == 0:      # calibration: the hops' loads and stores without their arithmetic, same ping-pong, same cadence
-                codes = [torch.empty(n, dtype=torch.int8, device="cuda") for _ in range(2)]
-                scales = [torch.empty(nb, dtype=torch.float32, device="cuda") for _ in range(2)]
+            if n % B == 0:      # calibration: the hops' loads and stores without their arithmetic, same wire in place, same order
+                codes = torch.empty(n, dtype=torch.int8, device="cuda")
+                scales = torch.empty(nb, dtype=torch.float32, device="cuda")
                 traffic_only_ms, _ = per_launch_ms(
-                    lambda k: eq.equarx_calib_hop_traffic(sets[k % S], B, codes[0], scales[0], codes[1], scales[1]),
-                    0, P - 1)
+                    lambda k: eq.equarx_calib_hop_traffic(sets[k % S], B, codes, scales, codes, scales), 0, P - 1)
                 del codes, scales
         elif everything:
             kernel_ms, launches_timed = per_launch_ms(calls["hop"], 0, 1)
@@ -443,7 +443,9 @@ def main() -> int:
                 b.record(stream)
             torch.cuda.synchronize()
             empty_us = statistics.median(a.elapsed_time(b) for a, b in ev) * 1e3 / 256
-        if empty_us:        # what the launches alone cost each schedule, and the time no such schedule can beat
+        # what the launches alone cost each schedule, and its bytes at HBM's peak on top: an estimate, which a chain whose
+        # wire stays in the L2s, or whose inputs partly sit in the Infinity Cache, can beat
+        if empty_us:
             launches = {"hop": P + 1, "ends": max(P - 1, 1), "fused": 1}
             for name, info in infos.items():
                 floor_us = launches[name] * empty_us
@@ -538,7 +540,9 @@ def main() -> int:
             "achieved": round(achieved, 1), "frac": round(achieved / HBM_PEAK_GBPS, 4),
             "avg_launch_us": round(kernel_ms * 1e3, 3), "launches_timed": launches_timed,
             "measured": "HIP events on the stream around runs of this kernel inside the timed entry point; inputs cold, "
-                        "wire warm (written by the previous launch, still in the 256 MB Infinity Cache)",
+                        "wire warm (rewritten in place by the previous launch; most of it is still in the L2s)",
+            "bytes_are": "the schedule's own: wire bytes that the L2s serve count like those of HBM, so achieved / peak is no "
+                         "utilisation of HBM and can exceed what a copy reaches (cold_wire: nothing of the wire is cached)",
         })
     if args.schedule != "fused":
         traffic = read_traffic(hip_build.source_digest()) if (w.name, B) == ("c3_gemma3_27b", 256) else None

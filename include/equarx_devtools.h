@@ -28,12 +28,14 @@ int equarx_calib_empty_launches(int32_t count, int32_t workgroups, void *stream)
 
 /* The chain's hops as memory traffic only: P-1 launches of a kernel with
  * exactly the loads and stores of equarx_reduce_stage (same tiling, same
- * access widths, the same ping-pong between two wire buffers, partial i read by
- * launch i) whose only computation is an XOR -- the time the memory system
- * alone needs for a hop, which the benchmark sets beside the hop kernel's.
- * n must be a multiple of block.  (codes0, scales0) is the input of launch 1,
- * which writes (codes1, scales1); launch 2 reads those and writes buffer 0,
- * and so on.  Per launch and per 8 consecutive elements (the partial as four
+ * access widths, partial i read by launch i) whose only computation is an XOR --
+ * the time the memory system alone needs for a hop, which the benchmark sets
+ * beside the hop kernel's.  n must be a multiple of block.  (codes0, scales0)
+ * is the input of launch 1, which writes (codes1, scales1); launch 2 reads those
+ * and writes buffer 0, and so on.  Both of wire 1 may BE those of wire 0: then
+ * every launch rewrites it in place and takes its tiles in the order in which
+ * the chain's hop of that number takes them, as in equarx_reduce_quantized.
+ * Per launch and per 8 consecutive elements (the partial as four
  * little-endian 32-bit words X0..X3, the codes read as two words C0, C1):
  * codes written = (X0^X2^C0, X1^X3^C1); scales written = scales read. */
 int equarx_calib_hop_traffic(const void *const *partials_bf16, int32_t P, int64_t n, int32_t block,

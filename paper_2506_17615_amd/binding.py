@@ -532,7 +532,8 @@ def equarx_calib_empty_launches(count: int, workgroups: int) -> None:
 
 
 def equarx_calib_hop_traffic(partials, block: int, codes0, scales0, codes1, scales1) -> None:
-    """The chain's P-1 hops as memory traffic only (XOR of what each launch read), ping-pong between two wires."""
+    """The chain's P-1 hops as memory traffic only (XOR of what each launch read), ping-pong between two wires, or, if
+    wire 1 is wire 0, rewriting it in place in the chain's order of tiles."""
     P = len(partials)
     n = partials[0].numel() if P else 0
     nb = num_blocks(n, block) if block in BLOCK_SIZES else 0

@@ -60,10 +60,13 @@ int equarx_calib_hop_traffic(const void *const *partials_bf16, int32_t P, int64_
         if (misaligned(partials_bf16[i], kAlign)) return EQUARX_MISALIGNED;
         mem.reads(partials_bf16[i], (size_t)n * 2);
     }
+    const bool in_place = codes1 == codes0 && scales1 == scales0;
     mem.writes(codes0, (size_t)n);
     mem.writes(scales0, scale_bytes);
-    mem.writes(codes1, (size_t)n);
-    mem.writes(scales1, scale_bytes);
+    if (!in_place) {
+        mem.writes(codes1, (size_t)n);
+        mem.writes(scales1, scale_bytes);
+    }
     if (int st = mem.check()) return st;
     const int64_t lanes = n / kLaneElems;
     u32x2 *c[2] = {reinterpret_cast<u32x2 *>(codes0), reinterpret_cast<u32x2 *>(codes1)};
@@ -73,9 +76,9 @@ int equarx_calib_hop_traffic(const void *const *partials_bf16, int32_t P, int64_
         for (int32_t i = 1; i < P; ++i) {                                                                          \
             with_pass_shape(n, [&](auto shape) {                                                                   \
                 using S = decltype(shape);                                                                         \
-                ctx.launch(hop_traffic_kernel<BB, S::K>, grid_for<S>(n), S::T,                               \
+                ctx.launch(hop_traffic_kernel<BB, S::K>, grid_for<S>(n), S::T,                                     \
                            reinterpret_cast<const u32x4 *>(partials_bf16[i]), c[(i - 1) & 1], s[(i - 1) & 1],      \
-                           lanes, c[i & 1], s[i & 1]);                                                             \
+                           lanes, c[i & 1], s[i & 1], mirrored<S>(n, in_place && walks_back(n, i)));               \
             });                                                                                                    \
         }                                                                                                          \
         break;

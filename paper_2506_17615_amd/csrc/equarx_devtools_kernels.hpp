@@ -89,15 +89,16 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(const u32x4 *__restrict_
 // Calibration: the hop's memory traffic without its arithmetic.  Same loads
 // and stores per lane as hop_kernel (16 bytes of bf16, 8 bytes of codes, the
 // group's scale in; 8 bytes of codes and the group leader's scale out), the
-// same tiling; the "result" is an XOR of what was read.
+// same tiling and order of tiles (mirror: see mirrored); the "result" is an
+// XOR of what was read.  The output wire may be the input wire, as hop_kernel's.
 template <int B, int K>
 __global__ __launch_bounds__(pass_threads(K)) void hop_traffic_kernel(const u32x4 *__restrict__ x, const u32x2 *cin,
                                                                const float *sin, int64_t lanes, u32x2 *cout,
-                                                               float *sout)
+                                                               float *sout, int64_t mirror)
 {
     constexpr int T = pass_threads(K);
     constexpr int G = B / kLaneElems;
-    const int64_t at = (int64_t)blockIdx.x * (T * K) + threadIdx.x;
+    const int64_t at = first_element<T, K>(mirror) / kLaneElems + threadIdx.x;
     u32x4 xv[K];
     u32x2 cv[K];
     float sv[K];

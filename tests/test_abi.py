@@ -347,6 +347,7 @@ def test_overlapping_buffers_are_rejected_before_launch(lib):
     C0, C1 = A + 0x300000, A + 0x400000
     assert ht(ok4, 4, n, blk, C0, C0 + 0x1000, C0 + 2048, C1 + 0x1000, None) == BAD
     assert ht(ok4, 4, n, blk, C0, C0 + 0x1000, C1, C0 + 0x1000 + 16, None) == BAD
+    assert ht(ok4, 4, n, blk, C0, C0 + 0x1000, C1, C0 + 0x1000, None) == BAD        # in place is codes and scales both
     assert ht(ok4, 4, n, blk, A + 0x20000 + 4096, C0 + 0x1000, C1, C1 + 0x1000, None) == BAD
 
 

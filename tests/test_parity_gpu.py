@@ -303,16 +303,21 @@ def test_calibration_copy(gpu):
 @pytest.mark.parametrize("B", (32, 256, 512))
 def test_calibration_hop_traffic(gpu, B):
     """The memory-only stand-in for the chain's hops writes the documented XOR of what it read (so it really
-    reads all of it), launch after launch, ping-pong between the two wires."""
+    reads all of it), launch after launch, ping-pong between the two wires or in place, in turn for a long wire."""
     n = B * 4 * 53 + 2048 * 6          # several workgroups and a ragged last one
-    n -= n % B
+    _hop_traffic(B, n - n % B, False)
+    _hop_traffic(B, n - n % B, True)
+    _hop_traffic(B, (20 << 20) + 8192 * 3 + B, True)
+
+
+def _hop_traffic(B, n, in_place):
     rng = _rng(B)
     P = 4
     xs = [torch.from_numpy(rng.integers(0, 1 << 16, n, dtype=np.int64).astype(np.uint16).view(np.int16)).cuda()
           .view(torch.bfloat16) for _ in range(P)]
     c0 = torch.from_numpy(rng.integers(-128, 128, n, dtype=np.int64).astype(np.int8)).cuda()
     s0 = torch.from_numpy(rng.standard_normal(n // B).astype(np.float32)).cuda()
-    c1, s1 = torch.zeros_like(c0), torch.zeros_like(s0)
+    c1, s1 = (c0, s0) if in_place else (torch.zeros_like(c0), torch.zeros_like(s0))
     cw = c0.cpu().numpy().view(np.uint32).reshape(-1, 2)
     s_first = s0.clone()
     eq.equarx_calib_hop_traffic(xs, B, c0, s0, c1, s1)
