@@ -1316,7 +1316,9 @@ __global__ __launch_bounds__(pass_threads(K)) void tail_ring_kernel(Global<const
 // the waits between them.
 // * A step is nested in the one before (small_steps), so that a hop costs one
 //   compare and branch; leaving a loop over the positions cost eight scalar
-//   instructions per hop.  And there is no loop around the steps unless kMany:
+//   instructions per hop.  And there is no loop around the steps unless kMany
+//   (or 9 to 16 partials keep their wire, which are faster in one: 16 of 262 k,
+//   block 256, 6.84 -> 6.23, of 524 k 8.86 -> 8.39; 12 of 262 k 5.67 -> 5.31):
 //   in one, the first step asks at run time whether it is the first.  Measured
 //   on MI355X, GPU us per call (captured calls one after the other, inputs
 //   cold), loop over positions -> nested in a loop -> as it is, 8 elements per
@@ -1502,7 +1504,7 @@ __device__ __forceinline__ void small_body(const PartialTable &tab, int P, int r
     float t[E], own[E];
     typename Lane::Raw x[N];
 
-    for (int base = 0; base < (kMany ? P : 1); base += N) {
+    for (int base = 0; base < (kMany || (kWire && N == 16) ? P : 1); base += N) {
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             // The table repeats after P entries, so a position may run past P (rot <= P <= N, unless kMany).

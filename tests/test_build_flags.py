@@ -72,12 +72,12 @@ def test_the_tiles_of_a_thread_at_the_end_are_requested_together(device_asm):
 
 def test_the_small_kernel_takes_its_partials_without_a_loop(device_asm):
     """All partials of a call are one request unless there are more than 16: no loop, whose every step would ask whether it
-    is the first."""
-    bodies = re.findall(r"^(_ZN6equarx\d+small_kernelILi\d+ELi[48]ELi(?:8|16)ELb([01])E\S*):(.*?)^\.Lfunc_end",
+    is the first; or unless 9 to 16 keep their wire, which is faster in one."""
+    bodies = re.findall(r"^(_ZN6equarx\d+small_kernelILi\d+ELi[48]ELi(8|16)ELb([01])E(?:Lb[01]E){3}Lb([01])E\S*):(.*?)^\.Lfunc_end",
                         device_asm["equarx_api.hip"], flags=re.M | re.S)
-    assert {many for _, many, _ in bodies} == {"0", "1"}
-    for name, many, body in bodies:
-        assert ("Loop Header" in body) == (many == "1"), name
+    assert {many for _, _, many, _, _ in bodies} == {"0", "1"}
+    for name, count, many, wire, body in bodies:
+        assert ("Loop Header" in body) == (many == "1" or (count, wire) == ("16", "1")), name
 
 
 def test_the_loop_of_the_128_chunk_chain_keeps_its_alignment(device_asm):
