@@ -221,7 +221,9 @@ inline bool small_semi(int64_t n, int P, int32_t block)
 // where 4 wins, an even one where 8 does, as the table shows at 524 k | 600 k, 786 k | 800 k and 1.05 | 1.07 M.  Chains of up
 // to 8, which wait for memory more than for arithmetic, gain too little from 4 beyond the first wave.  The semi-loop of up
 // to 16, whose steps are longer, does not mind an even number; with more, whose partials come in two requests, three waves are
-// the most that pays.  (Full loops of more than 24 in three waves, and of up to 14 in six, are as measured.)
+// the most that pays.  (Full loops of more than 24 in three waves, and of up to 14 in six, are as measured.)  In ring order a
+// shard's last workgroup is one of each shard's, so both layouts' workgroups are counted (us, semi-loop of 524 k, block 256, 8
+// against 4: P = 17 9.88/8.70, P = 24 11.68/10.10, where 8 per lane have 272 and 264 workgroups and not 256).
 //
 // on_lines: all partials begin on a 128-byte line.  Those of one tensor that was cut into pieces may not, and then the 512
 // bytes that a workgroup of one wave reads of each are five lines for four, the 4 KB of one of four waves 33 for 32.  us, 8 /
@@ -230,13 +232,17 @@ inline bool small_semi(int64_t n, int P, int32_t block)
 // 786 k 11.41/11.50 and 11.54/12.80; semi-loop, P = 8, block 64, 786 k 5.53/5.18 and 5.61/5.64, 1.05 M 6.05/5.92 and 6.11/6.75;
 // P = 16, block 256, 786 k 8.93/8.66 and 9.07/9.33, 1.57 M 12.62/13.07 and 12.88/14.49.
 constexpr int64_t kOneWaveEach = (int64_t)1024 * SmallShape<4>::kElems;
-constexpr bool small_lanes_of_4(int64_t n, int P, bool semi, bool on_lines)
+inline bool small_lanes_of_4(int64_t n, int32_t block, int P, bool ring, bool semi, bool keeps_wire, bool on_lines)
 {
-    const int64_t waves = (n + kOneWaveEach - 1) / kOneWaveEach;        // 1 .. 6
-    if (waves == 1) return true;
-    if (semi) return waves == 3 || (P <= 16 && on_lines);
-    if (!on_lines) return P > 8 && P <= 12 && waves == 3;
-    return P > 8 && (waves == 5 || (waves == 3 && P <= 24) || (waves == 6 && P <= 14));
+    if (n <= kOneWaveEach) return true;
+    if (!semi && P <= 8) return false;
+    if (semi && P <= 16 && on_lines) return true;
+    const ChainGrid g4 = chain_grid<SmallShape<4>>(n, block, P, ring), g8 = chain_grid<SmallShape<8>>(n, block, P, ring);
+    const unsigned wgs = g4.x * g4.y, waves = (wgs + 1023) / 1024;      // 2 .. 6, or a little more
+    const bool fewer = waves < (g8.x * g8.y + 255) / 256 * 2;           // in array order: an odd number
+    if (semi) return fewer && waves == 3 && (P <= 16 || on_lines || wgs <= 2560);       // off lines: half a wave at most
+    if (!on_lines) return fewer && waves == 3 && P <= 12;
+    return (fewer && (waves == 5 || (waves == 3 && P <= 24))) || (waves == 6 && P <= 14 && !keeps_wire);
 }
 
 inline bool on_lines(const PartialTable &tab, int P)
@@ -365,7 +371,7 @@ void launch_small(const PartialTable &tab, int P, int64_t n, bool ring, uint16_t
 {
     if constexpr (B > 256) {            // 4 elements per lane would spread a block over two waves
         launch_small_as<B, 8, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
-    } else if (small_lanes_of_4(n, P, kSemi, on_lines(tab, P))) {
+    } else if (small_lanes_of_4(n, B, P, ring, kSemi, kWire, on_lines(tab, P))) {
         launch_small_as<B, 4, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
     } else {
         launch_small_as<B, 8, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);

@@ -164,7 +164,7 @@ def test_single_launch_around_its_shapes(gpu, oracle, n, flags):  # noqa: F811
 
 
 @pytest.mark.parametrize("flags,P,lanes", ((0, 4, "488888"), (0, 8, "488888"), (0, 9, "484844"), (0, 14, "484844"), (0, 15, "484848"),
-                                           (0, 24, "484848"), (0, 25, "488848"), (eq.RING_ORDER, 12, "484844"),
+                                           (0, 24, "484848"), (0, 25, "488848"), (eq.AG_UNQUANTIZED, 12, "484844"),
                                            (eq.SEMI_LOOP, 5, "444444"), (eq.SEMI_LOOP, 16, "444444"),
                                            (eq.SEMI_LOOP, 17, "484888"), (eq.SEMI_LOOP, 25, "484888")))
 def test_elements_per_lane_by_waves_per_simd(gpu, flags, P, lanes):  # noqa: F811
@@ -174,10 +174,27 @@ def test_elements_per_lane_by_waves_per_simd(gpu, flags, P, lanes):  # noqa: F81
     off_lines = "484888" if flags & eq.SEMI_LOOP or 8 < P <= 12 else "488888"
     for at, by_waves in ((0, lanes), (8, off_lines)):
         for waves, lane in enumerate(by_waves, 1):
-            for n in ((waves - 1) * ONE_WAVE_EACH + 1 if waves > 1 else 70000, waves * ONE_WAVE_EACH):
+            half = waves == 3 and at and P > 16         # of the third wave, at most
+            for n in ((waves - 1) * ONE_WAVE_EACH + 1 if waves > 1 else 70000, waves * ONE_WAVE_EACH - half * ONE_WAVE_EACH // 2):
                 parts = [x[:n]] * (P - 1) + [x[at:at + n]]
                 made, = gpu.launches(lambda: eq.equarx_reduce_variant(parts, 256, flags, out[:n]))
                 assert made[1] == ((64, 1, 1) if lane == "4" else (256, 1, 1)), (at, n, made)
+
+
+@pytest.mark.parametrize("flags,P,n,lane", ((eq.SEMI_LOOP, 24, 2 * ONE_WAVE_EACH, 8),
+                                            (eq.SEMI_LOOP | eq.RING_ORDER, 24, 2 * ONE_WAVE_EACH, 4),
+                                            (eq.SEMI_LOOP | eq.RING_ORDER, 17, 2 * ONE_WAVE_EACH, 4),
+                                            (eq.SEMI_LOOP | eq.RING_ORDER, 16, 2 * ONE_WAVE_EACH, 4),
+                                            (eq.RING_ORDER, 12, 2 * ONE_WAVE_EACH, 4), (0, 12, 2 * ONE_WAVE_EACH, 8),
+                                            (eq.RING_ORDER, 17, 3 * ONE_WAVE_EACH, 8), (0, 17, 3 * ONE_WAVE_EACH, 4)))
+def test_elements_per_lane_of_shards(gpu, oracle, values, flags, P, n, lane):  # noqa: F811
+    """Twelve and more shards whose last workgroups make the layouts' rounds different ones from the whole message's."""
+    x = [values[i % 4][:n] for i in range(P)]
+    dev, out = [gpu.dev_bf16(p) for p in x], torch.full((n,), 7.0, dtype=torch.bfloat16, device="cuda")
+    made, = gpu.launches(lambda: eq.equarx_reduce_variant(dev, 256, flags, out))
+    assert made[1] == ((64, 1, 1) if lane == 4 else (256, 1, 1)), made
+    eq.equarx_reduce_variant(dev, 256, flags, out)
+    assert (gpu.host_u16(out) == _oracle_variant(oracle, x, 256, flags)).all()
 
 
 @pytest.mark.parametrize("n", (1, 2, 3, 255, 257, 4097, 65 * 1024 + 2, ONE_WAVE_EACH - 1, ONE_WAVE_EACH, ONE_WAVE_EACH + 1,
