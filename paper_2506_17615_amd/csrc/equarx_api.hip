@@ -215,6 +215,14 @@ inline bool small_semi(int64_t n, int P, int32_t block)
     return n <= kSmallElems && P >= 5 && (n > kSmallSemiFrom || (P <= 8 && block <= 256));
 }
 
+// Do all partials begin on a 128-byte line?
+inline bool on_lines(const PartialTable &tab, int P)
+{
+    uintptr_t bits = 0;
+    for (int i = 0; i < P; ++i) bits |= reinterpret_cast<uintptr_t>(tab.x[i]);
+    return bits % 128 == 0;
+}
+
 // 4 elements per lane instead of 8 (blocks of up to 256): half the arithmetic per hop, twice the waves.  What a message takes
 // goes by how many waves its fullest SIMD has (MI355X has 1024), and 8 per lane come in workgroups of four, one per SIMD of
 // a CU, so that a SIMD has half of the next even number of the waves that it would have with 4: an odd number of those is
@@ -225,31 +233,25 @@ inline bool small_semi(int64_t n, int P, int32_t block)
 // shard's last workgroup is one of each shard's, so both layouts' workgroups are counted (us, semi-loop of 524 k, block 256, 8
 // against 4: P = 17 9.88/8.70, P = 24 11.68/10.10, where 8 per lane have 272 and 264 workgroups and not 256).
 //
-// on_lines: all partials begin on a 128-byte line.  Those of one tensor that was cut into pieces may not, and then the 512
+// The partials begin on 128-byte lines (on_lines).  Those of one tensor that was cut into pieces may not, and then the 512
 // bytes that a workgroup of one wave reads of each are five lines for four, the 4 KB of one of four waves 33 for 32.  us, 8 /
 // 4 elements per lane, on lines and 16 bytes off them: full loop, P = 12, block 256, 655 k 6.41/5.89 and 6.58/6.33, 1.31 M
 // 9.21/8.83 and 9.35/9.88; P = 16, block 64, 786 k 7.29/7.14 and 7.51/7.79, 1.18 M 9.65/9.31 and 9.85/10.68; P = 24, block 256,
 // 786 k 11.41/11.50 and 11.54/12.80; semi-loop, P = 8, block 64, 786 k 5.53/5.18 and 5.61/5.64, 1.05 M 6.05/5.92 and 6.11/6.75;
 // P = 16, block 256, 786 k 8.93/8.66 and 9.07/9.33, 1.57 M 12.62/13.07 and 12.88/14.49.
 constexpr int64_t kOneWaveEach = (int64_t)1024 * SmallShape<4>::kElems;
-inline bool small_lanes_of_4(int64_t n, int32_t block, int P, bool ring, bool semi, bool keeps_wire, bool on_lines)
+inline bool small_lanes_of_4(const PartialTable &tab, int64_t n, int32_t block, int P, bool ring, bool semi, bool keeps_wire)
 {
     if (n <= kOneWaveEach) return true;
     if (!semi && P <= 8) return false;
-    if (semi && P <= 16 && on_lines) return true;
+    const bool lines = on_lines(tab, P);
+    if (semi && P <= 16 && lines) return true;
     const ChainGrid g4 = chain_grid<SmallShape<4>>(n, block, P, ring), g8 = chain_grid<SmallShape<8>>(n, block, P, ring);
     const unsigned wgs = g4.x * g4.y, waves = (wgs + 1023) / 1024;      // 2 .. 6, or a little more
     const bool fewer = waves < (g8.x * g8.y + 255) / 256 * 2;           // in array order: an odd number
-    if (semi) return fewer && waves == 3 && (P <= 16 || on_lines || wgs <= 2560);       // off lines: half a wave at most
-    if (!on_lines) return fewer && waves == 3 && P <= 12;
+    if (semi) return fewer && waves == 3 && (P <= 16 || lines || wgs <= 2560);       // off lines: half a wave at most
+    if (!lines) return fewer && waves == 3 && P <= 12;
     return (fewer && (waves == 5 || (waves == 3 && P <= 24))) || (waves == 6 && P <= 14 && !keeps_wire);
-}
-
-inline bool on_lines(const PartialTable &tab, int P)
-{
-    uintptr_t bits = 0;
-    for (int i = 0; i < P; ++i) bits |= reinterpret_cast<uintptr_t>(tab.x[i]);
-    return bits % 128 == 0;
 }
 
 // Launch shapes of the bandwidth kernels of the single-launch calls.  What a message of a few million elements pays
@@ -371,7 +373,7 @@ void launch_small(const PartialTable &tab, int P, int64_t n, bool ring, uint16_t
 {
     if constexpr (B > 256) {            // 4 elements per lane would spread a block over two waves
         launch_small_as<B, 8, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
-    } else if (small_lanes_of_4(n, B, P, ring, kSemi, kWire, on_lines(tab, P))) {
+    } else if (small_lanes_of_4(tab, n, B, P, ring, kSemi, kWire)) {
         launch_small_as<B, 4, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
     } else {
         launch_small_as<B, 8, kSemi, kRS, kAG, kWire>(tab, P, n, ring, out, wire_codes, wire_scales, c_step, s_step, ctx);
