@@ -619,10 +619,10 @@ inline unsigned strided_small_grid(int64_t n, int32_t chunks)       // of the pe
 
 // Short and long strided chains end beside the wire that their last hop reads, not over it.  The dequantization that follows
 // takes consecutive elements to a workgroup where a hop takes 256 positions of a minishard, so a tile is on another XCD
-// there than it was in the hop, and what it reads is found slower if the hop's L2 still holds the line: it keeps one that
-// was read and rewritten in place and not one that was only written.  In between the wire that need not be written anew
-// weighs more, and above, where the L2s no longer hold it, the order of the last launches does (walks_back).  Measured on
-// MI355X, us per chain, over it -> beside it:
+// there than it was in the hop, and what it reads is found slower if the hop's L2 still holds the line, which, going by
+// these times, it does more often if the line was read and rewritten in place than if it was only written.  In between the
+// wire that need not be written anew weighs more, and above, where the L2s no longer hold it, the order of the last launches
+// does (walks_back).  Measured on MI355X, us per chain, over it -> beside it:
 //     chunks, elements      P = 2            3               4               8
 //     32, 2.1 M          12.1 -> 10.6    16.4 -> 14.5    20.7 -> 18.8    37.5 -> 35.0
 //     64, 2.1 M          12.7 -> 11.5    17.4 -> 15.9    22.1 -> 20.6    40.9 -> 38.7
