@@ -551,7 +551,8 @@ def main() -> int:
             "traffic_source": ("profiles/hop_kernel_c3_traffic.txt: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE per dispatch, "
                                "each scaled by the same counter's reading for a copy of known size; a committed profile "
                                "of this library build, not measured by this run") if traffic else None,
-            "traffic_level": "bytes between L2 and the memory fabric (Infinity Cache + HBM together; not DRAM bytes)",
+            "traffic_level": "bytes between L2 and the memory fabric (Infinity Cache + HBM together; not DRAM bytes), from a run that "
+                             "serialises the launches and empties the L2s between them: in the timed chain part of the wire stays there",
             "same_traffic_no_arithmetic_us": round(traffic_only_ms * 1e3, 3) if traffic_only_ms else None,
             "cold_wire": ({"avg_launch_us": cold["hop_kernel_us"],
                            "achieved": round(hop_bytes(n, B) / (cold["hop_kernel_us"] * 1e-6) / 1e9, 1),
