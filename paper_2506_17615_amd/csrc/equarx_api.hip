@@ -97,8 +97,8 @@ inline unsigned ring_grid(int64_t shard_elems)
 }
 
 // The two wire buffers at the front of a workspace: codes, then scales, each part rounded up to the workspace alignment.
-// A chain rewrites one of them in place, but a strided one may end in the other (ends_beside), and a short one in ring order
-// takes them in turn; the two chains of a semi-loop take one each.
+// A chain rewrites one of them in place, but a short one in ring order takes them in turn; the two chains of a semi-loop take
+// one each.
 struct WireBuffers {
     int8_t *c[2];
     float *s[2];
@@ -582,11 +582,6 @@ inline int check_strided(int64_t n, int32_t chunks)
     return EQUARX_OK;
 }
 
-inline unsigned strided_grid(int64_t n, int32_t chunks)
-{
-    return (unsigned)(n / ((int64_t)kChunk * chunks) * kSlicesPerChunk);
-}
-
 #define EQUARX_DISPATCH_CHUNKS(chunks, CALL) \
     switch (chunks) {                        \
         case 32: CALL(32); break;            \
@@ -595,145 +590,149 @@ inline unsigned strided_grid(int64_t n, int32_t chunks)
         default: break;                      \
     }
 
-// Messages of up to this many minishards take the small layouts of equarx_strided.hpp, whose waves have a quarter or an
-// eighth of the work: with more minishards than that every CU is busy, and the larger layouts do less work in all.
-// Measured on MI355X, us, large -> small layout, by minishards of 64 chunks:
-//                            1               4               16              32
-//     chain, P = 8       10.6 -> 5.6     12.1 -> 7.3     12.9 -> 8.7     13.5 -> 14.4
-//     hops, P = 4        14.9 -> 12.9    16.7 -> 14.4    19.3 -> 16.6    21.5 -> 21.2
-//     semi-loop, P = 6   14.7 -> 12.0    16.9 -> 14.2    18.8 -> 17.4    20.8 -> 23.5
-// (32 chunks, 16 minishards: chain 10.0 -> 7.1, hops 16.8 -> 14.4; 128 chunks: 14.5 -> 14.3, 25.6 -> 20.6).
+inline int64_t minishards_of(int64_t n, int32_t chunks) { return n / ((int64_t)kChunk * chunks); }
+
+// Messages of up to this many minishards have layouts whose waves have a quarter or an eighth of the work: with more than
+// that every CU is busy, and the larger layouts do less work in all.  Single-launch chain, P = 8, 64 chunks, MI355X, us,
+// larger -> small layout: 1 minishard 10.6 -> 5.6, 4 12.1 -> 7.3, 16 12.9 -> 8.7, 32 13.5 -> 14.4; 16 of 32 chunks 10.0 -> 7.1.
 constexpr int64_t kStridedSmall = 16;
 // Between the two, for 64 chunks: half the work per wave (chain, 24 minishards 13.3 -> 10.1, 32 13.5 -> 10.9, 48 14.7 -> 15.3).
 constexpr int64_t kStridedMedium = 32;
 
-inline bool strided_small(int64_t n, int32_t chunks) { return n / ((int64_t)kChunk * chunks) <= kStridedSmall; }
+// f(layout) with the layout of the per-pass kernels: 16 lanes across a slice, where a code piece is a whole line and a thread
+// has 2, 4 or 8 rows.  8 lanes for few minishards of 64 and 128 chunks, which otherwise leave CUs idle.  32 for many of 32
+// chunks, and of 64 if the workgroups that gives are a whole number per CU (256), or over half of the next: every workgroup
+// is resident, so the slowest CU counts.  Measured on MI355X, us (GPU time of captured calls), hop-by-hop chain of P = 8 and
+// semi-loop in ring order of P = 8, 8 / 16 / 32 lanes:
+//     minishards       32 chunks                                   64                                          128
+//     1        19.4/18.0/20.4   12.3/11.1/13.1     20.5/20.3/27.2   13.3/13.4/17.1     26.6/29.3/39.4   16.7/18.4/24.4
+//     8        21.8/22.0/23.3   13.8/14.0/14.8     23.1/24.4/29.7   15.0/15.8/18.8     27.9/31.2/41.5   18.5/20.5/26.8
+//     16       22.2/22.8/24.0   14.8/14.7/15.6     24.3/25.1/30.5   17.2/17.3/20.2     30.5/33.0/43.6   22.3/22.9/29.2
+//     24       24.8/23.4/24.6   16.9/15.7/16.3     29.2/26.8/32.0   20.4/19.5/21.3     38.8/36.3/46.5   28.2/26.9/31.1
+//     64       29.2/27.9/27.8   22.0/20.4/20.5     37.7/36.4/37.4   32.3/29.0/29.5     62.6/52.8/59.5   53.5/45.0/47.4
+//     128      38.9/35.3/36.1   33.7/28.8/27.8     61.6/52.7/52.2   53.5/45.4/43.8      111/92.9/97.0   98.0/87.1/87.6
+//     160           40.1/41.7        33.2/32.4          62.9/64.2        55.1/53.5           112/122          107/111
+//     192           44.0/43.9        37.8/35.8          73.1/70.7        64.9/62.6           133/140          129/129
+//     256           53.5/52.0        46.6/44.1          93.2/90.0        87.6/84.3           170/176          169/168
+//     272           57.0/57.1        50.3/48.8          99.0/99.9        92.6/92.4           178/193          180/182
+//     320           63.5/61.7        58.2/54.0         112.3/108.8      107.8/106.2
+//     400           77.4/76.8        71.0/69.0         135.5/138.4      133.9/135.1
+//     544           97.3/97.2        91.7/93.7         176.7/177.8      178.3/176.6
+// What they replace (32 lanes, every value computed twice, and up to 16 minishards the chain's layout, which is 8 lanes) took
+// 22.8, 27.5, 30.6 | 37.5, 44.7, 65.3 | 81.7, 98.2, 117.7 us for 1, 8, 16 | 24, 64, 128 | 192, 256, 320 minishards of 64 chunks.
+// f(layout) with the layout of the per-pass kernels.
+template <typename F>
+inline void with_slices(int64_t n, int32_t chunks, F f)
+{
+    const int64_t ms = minishards_of(n, chunks);
+    switch (chunks) {
+        case 32:
+            if (ms < 192) f(Slices<32, 16>{});
+            else f(Slices<32, 32>{});
+            break;
+        case 64:
+            if (ms <= kStridedSmall) f(Slices<64, 8>{});
+            else if (ms < 128 || (4 * ms - 1) % 256 < 128) f(Slices<64, 16>{});
+            else f(Slices<64, 32>{});
+            break;
+        case 128:
+            if (ms <= kStridedSmall) f(Slices<128, 8>{});
+            else f(Slices<128, 16>{});
+            break;
+        default: break;
+    }
+}
+
+template <typename S>
+inline unsigned strided_grid(int64_t n) { return (unsigned)(minishards_of(n, S::kChunks) * S::kParts); }
+
+// The places of a launch that go to the XCDs by whole minishards (minishard_part).
+template <typename S>
+inline unsigned strided_owned(int64_t n) { return owned_places<S::kChunks, S::kParts>(minishards_of(n, S::kChunks)); }
 
 // The first workgroups of a grid, in whole groups of eight, that a launch takes in the opposite order (mirrored_place).
 inline unsigned strided_mirror(unsigned grid, bool backward) { return backward ? grid & ~7u : 0; }
 
-inline unsigned strided_small_grid(int64_t n, int32_t chunks)       // of the per-pass kernels
+// A strided chain rewrites one wire in place to its end: the dequantization takes every tile on the XCD that wrote it, and
+// finds it in that L2.  A last hop that writes beside the wire it reads costs (MI355X, us, P = 2, 3, 4 and 8, in place ->
+// beside) 8.8 -> 8.8, 12.0 -> 11.9, 15.1 -> 15.3, 28.0 -> 28.3 at 2.1 M elements of 32 chunks, 21.4 -> 22.6, 29.6 -> 30.9, 36.9 -> 38.2,
+// 68.7 -> 70.6 at 12.6 M of 64, 34.2 -> 38.7, 46.7 -> 52.0, 59.5 -> 64.5, 111.3 -> 116.5 at 22 M.  Up to 3 Mi elements and from 9 to 28
+// Mi it is the workspace's second buffer, as where a chain of that length leaves its last wire: one is as good as the other.
+inline int strided_chain_buffer(int64_t n, int P)
 {
-    return (unsigned)(n / ((int64_t)kChunk * chunks) * wave_layout_wgs<4, 8>);
+    return P > 1 && (n <= (int64_t)3 << 20 || (n >= (int64_t)9 << 20 && n <= (int64_t)28 << 20)) ? 1 : 0;
 }
 
-// Short and long strided chains end beside the wire that their last hop reads, not over it.  The dequantization that follows
-// takes consecutive elements to a workgroup where a hop takes 256 positions of a minishard, so a tile is on another XCD
-// there than it was in the hop, and what it reads is found slower if the hop's L2 still holds the line, which, going by
-// these times, it does more often if the line was read and rewritten in place than if it was only written.  In between the
-// wire that need not be written anew weighs more, and above, where the L2s no longer hold it, the order of the last launches
-// does (walks_back).  Measured on MI355X, us per chain, over it -> beside it:
-//     chunks, elements      P = 2            3               4               8
-//     32, 2.1 M          12.1 -> 10.6    16.4 -> 14.5    20.7 -> 18.8    37.5 -> 35.0
-//     64, 2.1 M          12.7 -> 11.5    17.4 -> 15.9    22.1 -> 20.6    40.9 -> 38.7
-//     32, 3.2 M          14.0 -> 13.7    19.1 -> 18.8    24.0 -> 23.6    43.8 -> 43.5
-//     32, 3.6 M          14.3 -> 14.7    19.5 -> 19.8    24.6 -> 24.8    44.8 -> 45.1
-//     64, 5.0 M          17.5 -> 17.9    24.0 -> 24.4    30.6 -> 31.0    56.9 -> 57.5
-//     128, 8.4 M         23.0 -> 23.1    30.7 -> 31.0    38.6 -> 38.6    69.1 -> 69.5
-//     32, 9.6 M          24.9 -> 24.4    33.3 -> 32.5    41.7 -> 41.1    75.0 -> 74.8
-//     64, 12.6 M         30.3 -> 28.0    39.7 -> 37.6    49.1 -> 46.6    86.7 -> 84.8
-//     128, 16.8 M        37.8 -> 34.6    49.9 -> 46.8    61.4 -> 58.3   109.3 -> 106.2
-//     64, 28.0 M         53.6 -> 52.3    70.7 -> 70.7    90.0 -> 89.6   160.8 -> 161.7
-//     64, 33.6 M         61.3 -> 62.6    83.0 -> 83.8   103.3 -> 104.0  186.7 -> 187.5
-inline bool ends_beside(int64_t n) { return n <= (int64_t)3 << 20 || (n >= (int64_t)9 << 20 && n <= (int64_t)28 << 20); }
+// What a per-pass strided kernel reads of bf16: partial `offset` of a table, or in the ring layout (per_shard minishards
+// per shard) the partial of device (k + offset) mod P for every shard k at once.
+struct StridedSource {
+    const PartialTable &tab;
+    int P, per_shard, offset;
+};
 
-// One tensor as the source of a per-pass strided kernel.
-inline StridedSource one_tensor(const void *x)
-{
-    StridedSource src;
-    for (int i = 0; i < kMaxPartials; ++i) src.tab.x[i] = nullptr;
-    src.tab.x[0] = static_cast<const uint16_t *>(x);
-    src.P = 1;
-    src.per_shard = 0;
-    src.offset = 0;
-    return src;
-}
+inline Global<const uint16_t> one_tensor(const void *x) { return static_cast<const uint16_t *>(x); }
 
-// Partial `offset` of a chain (per_shard == 0), or in the ring layout the partial of device (k + offset) mod P for
-// every shard k at once (per_shard minishards per shard).
-inline StridedSource chain_source(const PartialTable &tab, int P, int per_shard, int offset)
-{
-    StridedSource src;
-    src.tab = tab;
-    src.P = P;
-    src.per_shard = per_shard;
-    src.offset = offset;
-    return src;
-}
+inline int ring_word(int P, int offset, int second = 0) { return P | offset << 8 | second << 16; }
 
-void do_quantize_strided(const StridedSource &src, int64_t n, int32_t chunks, int8_t *codes, float *scales, LaunchCtx &ctx)
+// f(the source as a kernel takes it): see strided_source.
+template <typename F>
+inline void with_source(const StridedSource &src, F f)
 {
-    if (strided_small(n, chunks)) {
-#define CALL(CC)                                                                                                        \
-    ctx.launch(pass_strided_small_kernel<CC / 32, false>, strided_small_grid(n, chunks), kThreads, nullptr, nullptr, codes, \
-               scales, src)
-        EQUARX_DISPATCH_CHUNKS(chunks, CALL)
-#undef CALL
-        return;
+    if (src.per_shard == 0) {
+        f(Global<const uint16_t>(src.tab.x[src.offset]));
+    } else {
+        f(src.per_shard, ring_word(src.P, src.offset), src.tab);
     }
-#define CALL(CC) ctx.launch(quantize_strided_kernel<CC / kChunkGroups>, strided_grid(n, chunks), kThreads, codes, scales, src)
-    EQUARX_DISPATCH_CHUNKS(chunks, CALL)
-#undef CALL
 }
 
-void do_hop_strided(const int8_t *cin, const float *sin, const StridedSource &src, int64_t n, int32_t chunks, int8_t *cout,
-                    float *sout, LaunchCtx &ctx, bool backward = false)
+template <typename... Source>
+void do_quantize_strided(int64_t n, int32_t chunks, int8_t *codes, float *scales, LaunchCtx &ctx, Source... src)
 {
-    if (strided_small(n, chunks)) {
-#define CALL(CC) \
-    ctx.launch(pass_strided_small_kernel<CC / 32, true>, strided_small_grid(n, chunks), kThreads, cin, sin, cout, sout, src)
-        EQUARX_DISPATCH_CHUNKS(chunks, CALL)
-#undef CALL
-        return;
-    }
-    const unsigned grid = strided_grid(n, chunks);
-#define CALL(CC)                                                                                             \
-    ctx.launch(hop_strided_kernel<CC / kChunkGroups>, grid, kThreads, cin, sin, cout, sout, strided_mirror(grid, backward), \
-               src)
-    EQUARX_DISPATCH_CHUNKS(chunks, CALL)
-#undef CALL
+    with_slices(n, chunks, [&](auto slices) {
+        using S = decltype(slices);
+        ctx.launch(quantize_strided_kernel<S, Source...>, strided_grid<S>(n), kThreads, codes, scales, strided_owned<S>(n), src...);
+    });
 }
 
-void do_semi_step_strided(const StridedDirections &dirs, const PartialTable &tab, int P, int per_shard, int64_t n,
+template <typename... Source>
+void do_hop_strided(const int8_t *cin, const float *sin, int64_t n, int32_t chunks, int8_t *cout, float *sout, LaunchCtx &ctx,
+                    bool backward, Source... src)
+{
+    with_slices(n, chunks, [&](auto slices) {
+        using S = decltype(slices);
+        const unsigned grid = strided_grid<S>(n);
+        ctx.launch(hop_strided_kernel<S, Source...>, grid, kThreads, cin, sin, cout, sout, strided_mirror(grid, backward),
+                   strided_owned<S>(n), src...);
+    });
+}
+
+// Step t of the semi-loop's two chains, the first device of one at `up` and of the other at `down` from the owner.
+void do_semi_step_strided(const WireBuffers &w, const PartialTable &tab, int P, int per_shard, int up, int down, bool first, int64_t n,
                           int32_t chunks, LaunchCtx &ctx, bool backward)
 {
-    if (strided_small(n, chunks)) {
-#define CALL(CC)                                                                                                      \
-    ctx.launch2d(semi_step_strided_small_kernel<CC / 32>, strided_small_grid(n, chunks), 2u, kThreads, P, per_shard, dirs, tab)
-        EQUARX_DISPATCH_CHUNKS(chunks, CALL)
-#undef CALL
-        return;
-    }
-    const unsigned count = strided_grid(n, chunks);
-#define CALL(CC)                                                                                                      \
-    ctx.launch(semi_step_strided_kernel<CC / kChunkGroups>, 2 * whole_groups(count), kThreads, P, per_shard, count,    \
-               backward, dirs, tab)
-    EQUARX_DISPATCH_CHUNKS(chunks, CALL)
-#undef CALL
+    with_slices(n, chunks, [&](auto slices) {
+        using S = decltype(slices);
+        const unsigned count = strided_grid<S>(n);
+        ctx.launch(semi_step_strided_kernel<S>, 2 * whole_groups(count), kThreads, w.c[0], w.s[0], w.c[1], w.s[1], per_shard,
+                   ring_word(P, up, down), count, strided_owned<S>(n), backward, first, tab);
+    });
 }
 
-void do_owner_strided(const StridedSource &own, const StridedWires &wires, int received, int64_t n, int32_t chunks, bool ag,
-                      uint16_t *out, LaunchCtx &ctx, bool backward)
+// The wires that the owner received; nullptr: none.
+struct StridedWires {
+    const int8_t *codes[2];
+    const float *scales[2];
+};
+
+template <bool kAG, typename... Source>
+void do_owner_strided(const StridedWires &in, int64_t n, int32_t chunks, uint16_t *out, LaunchCtx &ctx, bool backward, Source... src)
 {
-    if (strided_small(n, chunks)) {
-#define CALL(CC)                                                                                                           \
-    do {                                                                                                                   \
-        const unsigned grid = strided_small_grid(n, chunks);                                                               \
-        if (ag) ctx.launch(owner_strided_small_kernel<CC / 32, true>, grid, kThreads, received, out, wires, own);          \
-        else ctx.launch(owner_strided_small_kernel<CC / 32, false>, grid, kThreads, received, out, wires, own);            \
-    } while (0)
-        EQUARX_DISPATCH_CHUNKS(chunks, CALL)
-#undef CALL
-        return;
-    }
-#define CALL(CC)                                                                                                           \
-    do {                                                                                                                   \
-        const unsigned grid = strided_grid(n, chunks), mirror = strided_mirror(grid, backward);                            \
-        if (ag) ctx.launch(owner_strided_kernel<CC / kChunkGroups, true>, grid, kThreads, received, mirror, out, wires, own);  \
-        else ctx.launch(owner_strided_kernel<CC / kChunkGroups, false>, grid, kThreads, received, mirror, out, wires, own);    \
-    } while (0)
-    EQUARX_DISPATCH_CHUNKS(chunks, CALL)
-#undef CALL
+    with_slices(n, chunks, [&](auto slices) {
+        using S = decltype(slices);
+        const unsigned grid = strided_grid<S>(n);
+        ctx.launch(owner_strided_kernel<S, kAG, Source...>, grid, kThreads, out, in.codes[0], in.scales[0], in.codes[1],
+                   in.scales[1], strided_mirror(grid, backward), strided_owned<S>(n), src...);
+    });
 }
 
 // The single-launch chain and its flavours: chunks = 8 * W * R (see chain_strided_kernel).
@@ -755,7 +754,7 @@ void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chu
 {
     const int64_t ms = n / ((int64_t)kChunk * chunks);
     const int per_shard = ring ? (int)((ms + P - 1) / P) : 0;
-    const bool small = strided_small(n, chunks);
+    const bool small = ms <= kStridedSmall;
     switch (chunks) {
         case 32:
             if (small) launch_chain_strided_as<1, 4, 4>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
@@ -774,15 +773,46 @@ void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chu
     }
 }
 
+template <int kChunks, int T, int K>
+void launch_dequantize_strided(const int8_t *codes, const float *scales, int64_t minishards, uint16_t *out,
+                               LaunchCtx &ctx, bool backward)
+{
+    constexpr int kParts = kChunk * kChunks / (tile_elems<T> * K);
+    const unsigned grid = (unsigned)(minishards * kParts);
+    ctx.launch(dequantize_strided_kernel<kChunks, T, K>, grid, T, codes, scales, out, strided_mirror(grid, backward),
+               owned_places<kChunks, kParts>(minishards));
+}
+
+// 256 threads x 4 tiles, where a lane reads its scales once for 32 elements; 2 while that leaves CUs without work.  Measured on
+// MI355X, us, wires and outputs in turn, 256 x 1 / 256 x 2 / 256 x 4 / 512 x 2 (one instance for every number of chunks, which
+// divided by it per lane, and each load behind a condition: 256 x 1 up to 4 Mi, 512 x 2 above):
+//     elements, chunks
+//     1.0 M, 64      2.35/2.48/2.45/2.45   (2.41)
+//     3.1 M, 64      2.95/2.78/2.91/2.90   (3.09)
+//     5.2 M, 32      4.27/3.71/3.54/3.76   (4.18)
+//     5.2 M, 64      4.42/3.56/3.52/3.61   (4.61)
+//     6.3 M, 64      5.33/4.90/4.18/4.71   (5.50)
+//     8.4 M, 64      6.76/6.32/5.19/6.15   (7.35)
+//     14.7 M, 64     11.0/9.77/9.32/9.89   (11.4)
+//     22 M, 64       14.7/13.5/13.0/13.4   (15.2)
+//     22 M, 128      13.2/13.6/13.1/13.4   (14.2)
+//     62.9 M, 32     36.9/32.6/32.3/33.0   (37.5)
+constexpr int64_t kTwoTileDequantize = (int64_t)5 << 20;
+
 void do_dequantize_strided(const int8_t *codes, const float *scales, int64_t n, int32_t chunks, void *out,
                            LaunchCtx &ctx, bool backward = false)
 {
     in_pieces(n, [&](int64_t at, int64_t m) {
-        with_pass_shape(m, [&](auto shape) {
-            using S = decltype(shape);
-            ctx.launch(dequantize_strided_kernel<S::K>, grid_for<S>(m), S::T, codes + at, scales + at / chunks, m, (int)chunks,
-                       static_cast<uint16_t *>(out) + at, mirrored<S>(m, backward));
-        });
+        uint16_t *o = static_cast<uint16_t *>(out) + at;
+        const int64_t minishards = m / ((int64_t)kChunk * chunks);
+#define CALL(CC)                                                                                                            \
+    do {                                                                                                                    \
+        const float *sc = scales + at / CC;                                                                                 \
+        if (m <= kTwoTileDequantize) launch_dequantize_strided<CC, 256, 2>(codes + at, sc, minishards, o, ctx, backward);     \
+        else launch_dequantize_strided<CC, 256, 4>(codes + at, sc, minishards, o, ctx, backward);                            \
+    } while (0)
+        EQUARX_DISPATCH_CHUNKS(chunks, CALL)
+#undef CALL
     });
 }
 
@@ -1258,7 +1288,7 @@ int equarx_quantize_strided(const void *x_bf16, int64_t n, int32_t chunks, int8_
     mem.writes(codes, (size_t)n);
     mem.writes(scales, (size_t)(n / chunks) * sizeof(float));
     if (int st = mem.check()) return st;
-    do_quantize_strided(one_tensor(x_bf16), n, chunks, codes, scales, ctx);
+    do_quantize_strided(n, chunks, codes, scales, ctx, one_tensor(x_bf16));
     return ctx.status();
 }
 
@@ -1290,7 +1320,7 @@ int equarx_reduce_stage_strided(const int8_t *codes_in, const float *scales_in, 
         misaligned(codes_out, kAlign) || misaligned(scales_out, kAlign))
         return EQUARX_MISALIGNED;
     if (int st = check_hop_memory(codes_in, scales_in, local_bf16, n, n / chunks, codes_out, scales_out)) return st;
-    do_hop_strided(codes_in, scales_in, one_tensor(local_bf16), n, chunks, codes_out, scales_out, ctx);
+    do_hop_strided(codes_in, scales_in, n, chunks, codes_out, scales_out, ctx, false, one_tensor(local_bf16));
     return ctx.status();
 }
 
@@ -1313,13 +1343,14 @@ int equarx_reduce_quantized_strided(const void *const *partials_bf16, int32_t P,
     mem.writes(workspace, need);
     if (int st = mem.check()) return st;
     const WireBuffers w = carve_workspace(workspace, n, n / chunks);
-    do_quantize_strided(one_tensor(partials_bf16[0]), n, chunks, w.c[0], w.s[0], ctx);
-    const int last = P > 1 && ends_beside(n);     // the buffer of the last wire
+    const int at = strided_chain_buffer(n, P);
+    int8_t *const c = w.c[at];
+    float *const sc = w.s[at];
+    do_quantize_strided(n, chunks, c, sc, ctx, one_tensor(partials_bf16[0]));
     for (int32_t i = 1; i < P; ++i) {
-        const int to = i + 1 < P ? 0 : last;
-        do_hop_strided(w.c[0], w.s[0], one_tensor(partials_bf16[i]), n, chunks, w.c[to], w.s[to], ctx, walks_back(n, i));
+        do_hop_strided(c, sc, n, chunks, c, sc, ctx, walks_back(n, i), one_tensor(partials_bf16[i]));
     }
-    do_dequantize_strided(w.c[last], w.s[last], n, chunks, out_bf16, ctx, walks_back(n, P));
+    do_dequantize_strided(c, sc, n, chunks, out_bf16, ctx, walks_back(n, P));
     return ctx.status();
 }
 
@@ -1391,8 +1422,6 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
     if (int st = mem.check()) return st;
 
     const WireBuffers w = carve_workspace(workspace, n, n / chunks);
-    int8_t *const c[2] = {w.c[0], w.c[1]};
-    float *const s[2] = {w.s[0], w.s[1]};
     uint16_t *out = static_cast<uint16_t *>(out_bf16);
     StridedWires wires = {{nullptr, nullptr}, {nullptr, nullptr}};
     // Ring layout: shards of ceil(M / P) whole minishards; every launch is one ring step on all P shards at once,
@@ -1400,23 +1429,30 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
     const int64_t minishards = n / ((int64_t)kChunk * chunks);
     const int per_shard = ring ? (int)((minishards + P - 1) / P) : 0;
     // position i of the full loop: a ring starts shard k's chain at device k+1 and ends it on device k
-    const auto at = [&](int i) { return chain_source(tab, P, per_shard, ring ? (i + 1) % P : i); };
+    const auto at = [&](int i) { return StridedSource{tab, P, per_shard, ring ? (i + 1) % P : i}; };
     // position i of the semi-loop counts from its owner: device k in a ring, partial 0 otherwise
-    const auto around = [&](int i) { return chain_source(tab, P, per_shard, i); };
+    const auto around = [&](int i) { return StridedSource{tab, P, per_shard, i}; };
+    const auto quantize = [&](const StridedSource &from, int to) {
+        with_source(from, [&](auto... src) { do_quantize_strided(n, chunks, w.c[to], w.s[to], ctx, src...); });
+    };
+    const auto hop = [&](const StridedSource &from, int on, bool backward) {
+        with_source(from, [&](auto... src) { do_hop_strided(w.c[on], w.s[on], n, chunks, w.c[on], w.s[on], ctx, backward, src...); });
+    };
+    const auto finish = [&](const StridedSource &own, bool backward) {
+        with_source(own, [&](auto... src) {
+            if (ag) do_owner_strided<true>(wires, n, chunks, out, ctx, backward, src...);
+            else do_owner_strided<false>(wires, n, chunks, out, ctx, backward, src...);
+        });
+    };
 
     if (!semi) {
         // Q_B(x_0), hops 1 .. P-2, then the device holding x_(P-1) adds the last wire and feeds the all-gather
-        int received = 0;
         if (P > 1) {
-            do_quantize_strided(at(0), n, chunks, c[0], s[0], ctx);
-            for (int32_t i = 1; i + 1 < P; ++i) {
-                do_hop_strided(c[0], s[0], at(i), n, chunks, c[0], s[0], ctx, walks_back(n, i));
-            }
-            wires.codes[0] = c[0];
-            wires.scales[0] = s[0];
-            received = 1;
+            quantize(at(0), 0);
+            for (int32_t i = 1; i + 1 < P; ++i) hop(at(i), 0, walks_back(n, i));
+            wires = {{w.c[0], nullptr}, {w.s[0], nullptr}};
         }
-        do_owner_strided(at(P - 1), wires, received, n, chunks, ag, out, ctx, walks_back(n, P - 1));
+        finish(at(P - 1), walks_back(n, P - 1));
         return ctx.status();
     }
 
@@ -1426,29 +1462,21 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
     // shorter chain's wire first.
     const int32_t h = P / 2, na = P - 1 - h, nb = h;
     for (int32_t t = 0; t < nb; ++t) {
-        StridedDirections dirs;
-        dirs.d[0] = {h + 1 + t, t ? c[0] : nullptr, t ? s[0] : nullptr, c[0], s[0]};
-        dirs.d[1] = {h - t, t ? c[1] : nullptr, t ? s[1] : nullptr, c[1], s[1]};
+        const bool backward = walks_back(2 * n, t);
         if (t < na) {
-            do_semi_step_strided(dirs, tab, P, per_shard, n, chunks, ctx, walks_back(2 * n, t));
+            do_semi_step_strided(w, tab, P, per_shard, h + 1 + t, h - t, t == 0, n, chunks, ctx, backward);
         } else if (t == 0) {
-            do_quantize_strided(around(h), n, chunks, c[1], s[1], ctx);
+            quantize(around(h), 1);
         } else {
-            do_hop_strided(c[1], s[1], around(h - t), n, chunks, c[1], s[1], ctx, walks_back(2 * n, t));
+            hop(around(h - t), 1, backward);
         }
     }
-    int received = 0;
     if (na > 0) {
-        wires.codes[received] = c[0];
-        wires.scales[received] = s[0];
-        ++received;
+        wires = {{w.c[0], w.c[1]}, {w.s[0], w.s[1]}};
+    } else if (nb > 0) {
+        wires = {{w.c[1], nullptr}, {w.s[1], nullptr}};
     }
-    if (nb > 0) {
-        wires.codes[received] = c[1];
-        wires.scales[received] = s[1];
-        ++received;
-    }
-    do_owner_strided(around(0), wires, received, n, chunks, ag, out, ctx, walks_back(2 * n, nb));
+    finish(around(0), walks_back(2 * n, nb));
     return ctx.status();
 }
 

@@ -9,16 +9,18 @@
 // no reduction over neighbouring elements (a lane keeps its own 8 positions),
 // but one ACROSS the chunks of a minishard.
 //
-// Decomposition of the per-pass kernels (quantize, hop: codes go to memory, and
-// 8-byte code pieces want 16 lanes or more side by side to fill a 128-byte
-// line; the single-launch chain further down writes no codes and uses a
-// layout without LDS): a workgroup of 256 threads takes one slice of 256 positions of
-// one minishard.  Thread (g, l), g = 0..7, l = 0..31, owns positions 8l..8l+7
-// of the slice in chunks g, g+8, g+16, ...; it keeps the raw inputs of its
-// chunks/8 chunks in registers, so global memory is read once.  The 8 partial
-// maxima per position meet in LDS (8 KiB), every thread derives the scales of
-// its 8 positions, recomputes its values from the registers, scales, rounds
-// and stores.  Loads of a half-wave cover 512 contiguous bytes.
+// Decomposition of the per-pass kernels (quantize, hop, owner): a workgroup of 256 threads takes one slice of 8 L
+// positions of one minishard, L = 8, 16 or 32 lanes across it.  Thread (g, l) owns positions 8l..8l+7 of the slice in
+// chunks g, g + 256/L, ...; its sums stay in registers, so memory is read once and nothing is computed twice.  The
+// 256/L partial maxima per position meet in LDS (8 KiB), thread t turns those of position t into the two quotients, and
+// every thread reads the quotients of its 8 positions back.  A row of L lanes covers 16 L contiguous bytes of bf16 and
+// 8 L of codes.  (The single-launch chain further down writes no codes and uses a layout without LDS.)
+//
+// What bounds a pass is memory, but with all its workgroups resident at once they read together and then compute
+// together, so arithmetic that memory does not cover is paid for.  Measured on MI355X, us per launch of a hop of 64 chunks,
+// 22 M elements inside the hop-by-hop chain: 14.3 with each thread deriving the quotients of its 8 positions and computing
+// its values twice (673 vector instructions at 8 rows), 13.7 as it is but with 64-bit addresses per row and the tensor's
+// address looked up in a table (482), 13.2 as it is (430); the contiguous hop takes 12.3.
 #pragma once
 
 #include "equarx_device.hpp"
@@ -26,19 +28,18 @@
 namespace equarx {
 
 constexpr int kChunk = 1024;                               // elements per chunk (8 x 128)
-// Measured at the 27B-shaped size: 32 lanes per slice is best overall (16: within 2 % for 64 and 128 chunks, 8 %
-// slower for 32; 64: 3 % slower for 32, 30 % slower for 128).  Capping the waves per SIMD at 2 or 3, or dropping
-// the first of the two barriers (a kernel takes the maximum once), changes nothing beyond 2 %; the 8 x 8 in-wave
-// layout of the single-launch chain makes these kernels 5-8 % slower (64-byte code pieces); workgroups of 512 or 1024
-// threads with 1 or 2 KiB runs per chunk are no faster for 64 chunks and 4-100 % slower otherwise.
-#ifndef EQUARX_STRIDED_SLICE_LANES
-#define EQUARX_STRIDED_SLICE_LANES 32
-#endif
-constexpr int kSliceLanes = EQUARX_STRIDED_SLICE_LANES;    // lanes across a slice of a chunk
-constexpr int kSlicePos = kSliceLanes * kLaneElems;        // 256 positions per workgroup
-constexpr int kChunkGroups = kThreads / kSliceLanes;       // 8 groups of lanes, each walking every 8th chunk
-constexpr int kSlicesPerChunk = kChunk / kSlicePos;        // 4 workgroups per minishard
-static_assert(kThreads == 256, "the strided kernels are laid out for 256-thread workgroups");
+
+// Layout of a per-pass kernel for minishards of kChunks chunks: L lanes across a slice of a chunk.
+template <int kChunks_, int L_>
+struct Slices {
+    static constexpr int kChunks = kChunks_, L = L_;
+    static constexpr int kPos = L * kLaneElems;             // positions of a slice, which is a workgroup's
+    static constexpr int kGroups = kThreads / L;            // groups of lanes, each walking every kGroups'th chunk
+    static constexpr int R = kChunks / kGroups;             // chunks per thread
+    static constexpr int kParts = kChunk / kPos;            // workgroups per minishard
+    static constexpr int kRow = kGroups * kChunk;           // elements from a lane's chunk to its next
+    static_assert(R >= 1 && kPos <= kThreads, "layout");
+};
 
 // A launch that walks back (walks_back): workgroup b of the first `mirror`, a multiple of eight, takes the place of one
 // in the opposite group of eight.  mirror == 0: it walks forward.
@@ -49,69 +50,162 @@ __device__ __forceinline__ unsigned mirrored_place(unsigned b, unsigned mirror)
 
 __host__ __device__ inline unsigned whole_groups(unsigned count) { return (count + 7) & ~7u; }
 
+// Which minishard, and which of its kParts equal parts, the workgroup at place `at` of a launch takes.  The first places
+// go to the XCDs in runs of 2^18 elements, whole minishards, the parts of each one after the other; those that follow,
+// fewer than 8 runs, count the parts of one minishard after another.  `owned`: the number of the first, a multiple of 8
+// kParts runs, and the logarithm of the run's minishards in its low two bits.
+//
+// So a minishard is on one XCD in every launch, also in the dequantization, which takes consecutive elements: each finds
+// the wire in the L2 that holds it.  With the parts of a minishard on four XCDs the dequantization did not.  Runs, because
+// what an XCD touches then differs in all the lower address bits: with minishard m on XCD m % 8 the L2s keep less of the
+// wire, as if 256 KiB of address chose the place in them.  Measured on MI355X, P = 8, hop by hop, us with the parts on four
+// XCDs / minishard m on XCD m % 8 / runs of 2^17 / of 2^18 elements (the four kernels otherwise the same): 64 chunks, 16.8 M
+// elements 97.8 / 103.8 / 103.9 / 93.1; 22 M 127.7 / 127.4 / 125.1 / 122.8; 32 chunks, 16.8 M (after the steps above) runs of
+// 2^17 101.7, of 2^18 91.1.  A contiguous eighth of the tensor to an XCD is as good in the hops and worse without any (P = 2,
+// 35.7 M: 51.3, runs 50.9, four XCDs 49.2).
+struct MinishardPart {
+    unsigned minishard;
+    int part;
+};
+
+template <int kParts>
+__device__ __forceinline__ MinishardPart minishard_part(unsigned at, unsigned owned)
+{
+    static_assert(kParts >= 4, "two bits to spare");
+    const unsigned run = owned & 3u;
+    if (at >= (owned & ~3u)) return MinishardPart{at / kParts, (int)(at % kParts)};
+    const unsigned in_xcd = at / 8, in_run = in_xcd & ((kParts << run) - 1), group = in_xcd / kParts >> run;
+    return MinishardPart{(group * 8 + at % 8 << run) + in_run / kParts, (int)(in_run % kParts)};
+}
+
+template <int kChunks, int kParts>
+inline unsigned owned_places(int64_t minishards)
+{
+    int run = kChunks == 32 ? 3 : kChunks == 64 ? 2 : 1;
+    while (run > 0 && minishards < (int64_t)8 << run) --run;
+    return ((unsigned)(minishards >> (3 + run) << (3 + run)) * kParts) | run;
+}
+
 struct StridedSpot {
-    int64_t minishard;  // which minishard the workgroup works on
-    int64_t elem;       // first element of the lane in chunk `g` of its minishard
-    int64_t scale;      // index of the lane's first scale
-    int g;              // chunk group
+    unsigned minishard; // which minishard the workgroup works on
+    int64_t elem;       // first element of the slice in the first chunk of its minishard
+    int64_t scale;      // index of the slice's first scale
+    int at, pos;        // the lane's first element, from there, in the first of its chunks; its first position
 };
 
 // at: the workgroup's place in the tensor.
-__device__ __forceinline__ StridedSpot strided_spot(int chunks, unsigned at)
+template <typename S>
+__device__ __forceinline__ StridedSpot strided_spot(unsigned at, unsigned owned)
 {
     StridedSpot sp;
-    const int l = threadIdx.x % kSliceLanes;
-    sp.g = threadIdx.x / kSliceLanes;
-    const int64_t ms = at / kSlicesPerChunk;
-    const int pos = (at % kSlicesPerChunk) * kSlicePos + l * kLaneElems;
-    sp.minishard = ms;
-    sp.elem = ms * ((int64_t)kChunk * chunks) + (int64_t)sp.g * kChunk + pos;
-    sp.scale = ms * kChunk + pos;
+    const MinishardPart slice = minishard_part<S::kParts>(at, owned);
+    sp.minishard = slice.minishard;
+    sp.elem = (int64_t)slice.minishard * (kChunk * S::kChunks) + slice.part * S::kPos;
+    sp.scale = (int64_t)slice.minishard * kChunk + slice.part * S::kPos;
+    sp.pos = threadIdx.x % S::L * kLaneElems;
+    sp.at = threadIdx.x / S::L * kChunk + sp.pos;
     return sp;
 }
 
-// The bf16 tensor a per-pass kernel reads.  Array order (per_shard == 0): partial `offset` for every workgroup.
-// Ring layout (Sec. 3; per_shard > 0): the tensor is cut into shards of per_shard minishards, shard k ends on device
-// k, and a launch is one ring step on every shard at once -- the workgroups of shard k read the partial of device
-// (k + offset) mod P.  0 <= offset < P.
-struct StridedSource {
-    PartialTable tab;
-    int P;
-    int per_shard;
-    int offset;
-};
+// A lane's access in row r, kRow elements further on in every row: a buffer descriptor that begins where the workgroup
+// does, the lane's offset and, in a scalar register, the row's, so that no row costs vector instructions.  The 16-byte
+// store has its row in the descriptor: the compiler takes an offset in a scalar register for a reason to let the next
+// instruction overwrite what the store is still reading, and on MI355X it does overwrite it (words of the output held later
+// values, now and then, with two workgroups on a CU).
+constexpr int kMinishardEnd = kChunk * 128 * 2;     // bytes from there that no descriptor has to reach past
 
-__device__ __forceinline__ const uint16_t *strided_source(const StridedSource &src, int64_t minishard)
+template <int kRow>
+__device__ __forceinline__ u32x4 load_row_bf16x8(const uint16_t *base, int at, int r)
 {
-    const int j = (src.per_shard > 0 ? (int)(minishard / src.per_shard) : 0) + src.offset;     // < 2P
-    return src.tab.x[j >= src.P ? j - src.P : j];
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(bounded(base, kMinishardEnd), at * 2, r * kRow * 2, kNonTemporal));
 }
 
-// Max over the 8 chunk groups for each of the lane's 8 positions, through LDS.
-// m: bit patterns of non-negative floats.  Every thread of the workgroup calls this.
-__device__ __forceinline__ void across_chunks_max(uint32_t (&m)[8], uint32_t (*red)[kSlicePos])
+template <int kRow>
+__device__ __forceinline__ u32x2 load_row_i8x8(const int8_t *base, int at, int r)
 {
-    const int l = threadIdx.x % kSliceLanes;
-    const int g = threadIdx.x / kSliceLanes;
-    __syncthreads();                                        // the previous round's readers are done
-    u32x4 *row = reinterpret_cast<u32x4 *>(&red[g][l * kLaneElems]);
-    row[0] = u32x4{m[0], m[1], m[2], m[3]};
-    row[1] = u32x4{m[4], m[5], m[6], m[7]};
-    __syncthreads();
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(bounded(base, kMinishardEnd), at, r * kRow, 0));
+}
+
+template <int kRow>
+__device__ __forceinline__ void store_row_i8x8(int8_t *base, int at, int r, const u32x2 &w)
+{
+    __builtin_amdgcn_raw_buffer_store_b64(w, bounded(base, kMinishardEnd), at, r * kRow, 0);
+}
+
+template <int kRow>
+__device__ __forceinline__ void store_row_bf16x8(uint16_t *base, int at, int r, const float (&v)[8])
+{
+    u32x4 w;
+    w.x = narrow_bf16x2(v[0], v[1]);
+    w.y = narrow_bf16x2(v[2], v[3]);
+    w.z = narrow_bf16x2(v[4], v[5]);
+    w.w = narrow_bf16x2(v[6], v[7]);
+    __builtin_amdgcn_raw_buffer_store_b128(w, bounded(base + r * kRow, kMinishardEnd), at * 2, 0, kNonTemporal);
+}
+
+// The bf16 tensor a per-pass kernel reads, as its last parameters: one tensor, in array order; or in the ring layout
+// (Sec. 3), where the tensor is cut into shards of per_shard minishards, shard k ends on device k and a launch is one
+// ring step on every shard at once, the partial of device (k + offset) mod P for the workgroups of shard k, 0 <= offset < P.
+// `ring`: P, and the offset from bit 8 on.  One tensor's address is in scalar registers when a wave starts; a table has to
+// be asked first.
+__device__ __forceinline__ const uint16_t *strided_source(unsigned, Global<const uint16_t> x) { return x; }
+
+__device__ __forceinline__ const uint16_t *strided_source(unsigned minishard, int per_shard, int ring, const PartialTable &tab)
+{
+    const int P = ring & 255;
+    const int j = (per_shard > 0 ? (int)(minishard / (unsigned)per_shard) : 0) + (ring >> 8 & 255);     // < 2P
+    return tab.x[j >= P ? j - P : j];
+}
+
+// The quotients of a slice's positions, through LDS: each group leaves its 8 maxima per lane, then thread t works on
+// position t alone and hands the quotients back.
+template <typename S>
+struct SliceQuotients {
+    float part[S::kGroups][S::kPos];
+    float inv[S::kPos];
+    float scale[S::kPos];
+};
+
+__device__ __forceinline__ void read_eight(const float *p, float (&v)[8])
+{
+    const u32x4 *w = reinterpret_cast<const u32x4 *>(p);
+    const u32x4 a = w[0], b = w[1];
 #pragma unroll
-    for (int h = 0; h < kChunkGroups; ++h) {
-        const u32x4 *other = reinterpret_cast<const u32x4 *>(&red[h][l * kLaneElems]);
-        const u32x4 a = other[0], b = other[1];
-        m[0] = umax(m[0], a.x); m[1] = umax(m[1], a.y); m[2] = umax(m[2], a.z); m[3] = umax(m[3], a.w);
-        m[4] = umax(m[4], b.x); m[5] = umax(m[5], b.y); m[6] = umax(m[6], b.z); m[7] = umax(m[7], b.w);
+    for (int j = 0; j < 4; ++j) {
+        v[j] = __uint_as_float(a[j]);
+        v[4 + j] = __uint_as_float(b[j]);
     }
 }
 
-template <int V>
-__device__ __forceinline__ void note_absmax(const float (&t)[V], uint32_t (&m)[V])
+// m: the lane's max-abs over its chunks.  Returns the scale of position threadIdx.x; inv (and with kScales scale) are
+// those of the lane's 8 positions.
+template <bool kScales, typename S>
+__device__ __forceinline__ float slice_quotients(const float (&m)[8], SliceQuotients<S> &q, float (&inv)[8], float (&scale)[8])
+{
+    const int l = threadIdx.x % S::L;
+    const int g = threadIdx.x / S::L;
+    u32x4 *row = reinterpret_cast<u32x4 *>(&q.part[g][l * kLaneElems]);
+    row[0] = u32x4{__float_as_uint(m[0]), __float_as_uint(m[1]), __float_as_uint(m[2]), __float_as_uint(m[3])};
+    row[1] = u32x4{__float_as_uint(m[4]), __float_as_uint(m[5]), __float_as_uint(m[6]), __float_as_uint(m[7])};
+    __syncthreads();
+    const int mine = threadIdx.x % S::kPos;
+    float a = q.part[0][mine];
+#pragma unroll
+    for (int h = 1; h < S::kGroups; ++h) a = __builtin_fmaxf(a, q.part[h][mine]);
+    float own, own_inv;
+    block_quotients(a, own, own_inv);
+    q.inv[mine] = own_inv;
+    if (kScales) q.scale[mine] = own;
+    __syncthreads();
+    read_eight(&q.inv[l * kLaneElems], inv);
+    if (kScales) read_eight(&q.scale[l * kLaneElems], scale);
+    return own;
+}
+
+__device__ __forceinline__ void fold_absmax(const float (&t)[8], float (&m)[8])
 {
 #pragma unroll
-    for (int j = 0; j < V; ++j) m[j] = umax(m[j], __float_as_uint(t[j]) & 0x7FFFFFFFu);
+    for (int j = 0; j < 8; ++j) m[j] = __builtin_fmaxf(m[j], __builtin_fabsf(t[j]));
 }
 
 __device__ __forceinline__ u32x2 scale_and_pack(const float (&t)[8], const float (&inv)[8])
@@ -125,202 +219,149 @@ __device__ __forceinline__ u32x2 scale_and_pack(const float (&t)[8], const float
     return w;
 }
 
-// R = chunks / 8 chunks per thread.
-template <int R>
-__device__ __forceinline__ void quantize_strided_body(const uint16_t *__restrict__ x, int8_t *__restrict__ codes,
-                                                      float *__restrict__ scales, const StridedSpot &sp,
-                                                      uint32_t (*red)[kSlicePos])
+// The slice's values t to the wire.
+template <typename S>
+__device__ __forceinline__ void send_slice(const float (&t)[S::R][8], int8_t *codes, float *scales, const StridedSpot &sp, SliceQuotients<S> &q)
 {
-    u32x4 xv[R];
+    float m[8] = {};
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        xv[r] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(x + sp.elem + (int64_t)r * kChunkGroups * kChunk));
-    }
-    uint32_t m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int r = 0; r < S::R; ++r) fold_absmax(t[r], m);
+    float inv[8];
+    const float own = slice_quotients<false>(m, q, inv, inv);
+    if (threadIdx.x < S::kPos) scales[sp.scale + threadIdx.x] = own;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        float t[8];
-        widen_bf16x8(xv[r], t);
-        note_absmax(t, m);
-    }
-    across_chunks_max(m, red);
-
-    float scale[8], inv[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) block_quotients(__uint_as_float(m[j]), scale[j], inv[j]);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        float t[8];
-        widen_bf16x8(xv[r], t);
-        *reinterpret_cast<u32x2 *>(codes + sp.elem + (int64_t)r * kChunkGroups * kChunk) = scale_and_pack(t, inv);
-    }
-    if (sp.g == 0) {
-        float *s = scales + sp.scale;
-        *reinterpret_cast<u32x4 *>(s) = u32x4{__float_as_uint(scale[0]), __float_as_uint(scale[1]),
-                                              __float_as_uint(scale[2]), __float_as_uint(scale[3])};
-        *reinterpret_cast<u32x4 *>(s + 4) = u32x4{__float_as_uint(scale[4]), __float_as_uint(scale[5]),
-                                                  __float_as_uint(scale[6]), __float_as_uint(scale[7])};
+    for (int r = 0; r < S::R; ++r) {
+        store_row_i8x8<S::kRow>(codes + sp.elem, sp.at, r, scale_and_pack(t[r], inv));
     }
 }
 
-template <int R>
-__global__ __launch_bounds__(kThreads) void quantize_strided_kernel(Global<int8_t> codes,
-                                                                    Global<float> scales,
-                                                                    const StridedSource src)
+template <int V>
+__device__ __forceinline__ void note_absmax(const float (&t)[V], uint32_t (&m)[V])
 {
-    __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
-    const StridedSpot sp = strided_spot(R * kChunkGroups, blockIdx.x);
-    quantize_strided_body<R>(strided_source(src, sp.minishard), codes, scales, sp, red);
+#pragma unroll
+    for (int j = 0; j < V; ++j) m[j] = umax(m[j], __float_as_uint(t[j]) & 0x7FFFFFFFu);
+}
+
+template <typename S>
+__device__ __forceinline__ void quantize_strided_body(const uint16_t *__restrict__ x, int8_t *__restrict__ codes,
+                                                      float *__restrict__ scales, const StridedSpot &sp, SliceQuotients<S> &q)
+{
+    u32x4 xv[S::R];
+#pragma unroll
+    for (int r = 0; r < S::R; ++r) xv[r] = load_row_bf16x8<S::kRow>(x + sp.elem, sp.at, r);
+    float t[S::R][8];
+#pragma unroll
+    for (int r = 0; r < S::R; ++r) widen_bf16x8(xv[r], t[r]);
+    send_slice<S>(t, codes, scales, sp, q);
+}
+
+template <typename S, typename... Source>
+__global__ __launch_bounds__(kThreads) void quantize_strided_kernel(Global<int8_t> codes, Global<float> scales, unsigned owned,
+                                                                    const Source... src)
+{
+    __shared__ __align__(16) SliceQuotients<S> q;
+    const StridedSpot sp = strided_spot<S>(blockIdx.x, owned);
+    quantize_strided_body<S>(strided_source(sp.minishard, src...), codes, scales, sp, q);
 }
 
 // One hop in the strided geometry.  Output wire may be the input wire: a
 // workgroup holds all its inputs in registers before it stores anything.
-template <int R>
+template <typename S>
 __device__ __forceinline__ void hop_strided_body(const int8_t *cin, const float *sin, const uint16_t *__restrict__ x,
-                                                 int8_t *cout, float *sout, const StridedSpot &sp,
-                                                 uint32_t (*red)[kSlicePos])
+                                                 int8_t *cout, float *sout, const StridedSpot &sp, SliceQuotients<S> &q)
 {
-    u32x4 xv[R];
-    u32x2 cv[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t at = sp.elem + (int64_t)r * kChunkGroups * kChunk;
-        xv[r] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(x + at));
-        cv[r] = *reinterpret_cast<const u32x2 *>(cin + at);
-    }
+    u32x4 xv[S::R];
+    u32x2 cv[S::R];
     float s_in[8];
-    {
-        const u32x4 a = *reinterpret_cast<const u32x4 *>(sin + sp.scale);
-        const u32x4 b = *reinterpret_cast<const u32x4 *>(sin + sp.scale + 4);
-        s_in[0] = __uint_as_float(a.x); s_in[1] = __uint_as_float(a.y);
-        s_in[2] = __uint_as_float(a.z); s_in[3] = __uint_as_float(a.w);
-        s_in[4] = __uint_as_float(b.x); s_in[5] = __uint_as_float(b.y);
-        s_in[6] = __uint_as_float(b.z); s_in[7] = __uint_as_float(b.w);
-    }
-
-    uint32_t m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    read_eight(sin + sp.scale + sp.pos, s_in);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        float xf[8], qf[8], t[8];
+    for (int r = 0; r < S::R; ++r) {
+        xv[r] = load_row_bf16x8<S::kRow>(x + sp.elem, sp.at, r);
+        cv[r] = load_row_i8x8<S::kRow>(cin + sp.elem, sp.at, r);
+    }
+    loads_first();
+    float t[S::R][8];
+#pragma unroll
+    for (int r = 0; r < S::R; ++r) {
+        float xf[8], qf[8];
         widen_bf16x8(xv[r], xf);
         widen_i8x8(cv[r], qf);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) t[j] = __builtin_fmaf(qf[j], s_in[j], xf[j]);
-        note_absmax(t, m);
+        for (int j = 0; j < 8; ++j) t[r][j] = __builtin_fmaf(qf[j], s_in[j], xf[j]);
     }
-    across_chunks_max(m, red);
-
-    float scale[8], inv[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) block_quotients(__uint_as_float(m[j]), scale[j], inv[j]);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        float xf[8], qf[8], t[8];
-        widen_bf16x8(xv[r], xf);
-        widen_i8x8(cv[r], qf);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) t[j] = __builtin_fmaf(qf[j], s_in[j], xf[j]);      // same operands, same bits
-        *reinterpret_cast<u32x2 *>(cout + sp.elem + (int64_t)r * kChunkGroups * kChunk) = scale_and_pack(t, inv);
-    }
-    if (sp.g == 0) {
-        float *s = sout + sp.scale;
-        *reinterpret_cast<u32x4 *>(s) = u32x4{__float_as_uint(scale[0]), __float_as_uint(scale[1]),
-                                              __float_as_uint(scale[2]), __float_as_uint(scale[3])};
-        *reinterpret_cast<u32x4 *>(s + 4) = u32x4{__float_as_uint(scale[4]), __float_as_uint(scale[5]),
-                                                  __float_as_uint(scale[6]), __float_as_uint(scale[7])};
-    }
+    send_slice<S>(t, cout, sout, sp, q);
 }
 
-template <int R>
-__global__ __launch_bounds__(kThreads) void hop_strided_kernel(Global<const int8_t> cin, Global<const float> sin,
-                                                               Global<int8_t> cout, Global<float> sout, unsigned mirror,
-                                                               const StridedSource src)
+template <typename S, typename... Source>
+__global__ __launch_bounds__(kThreads) void hop_strided_kernel(Global<const int8_t> cin, Global<const float> sin, Global<int8_t> cout,
+                                                               Global<float> sout, unsigned mirror, unsigned owned, const Source... src)
 {
-    __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
-    const StridedSpot sp = strided_spot(R * kChunkGroups, mirrored_place(blockIdx.x, mirror));
-    hop_strided_body<R>(cin, sin, strided_source(src, sp.minishard), cout, sout, sp, red);
+    __shared__ __align__(16) SliceQuotients<S> q;
+    const StridedSpot sp = strided_spot<S>(mirrored_place(blockIdx.x, mirror), owned);
+    hop_strided_body<S>(cin, sin, strided_source(sp.minishard, src...), cout, sout, sp, q);
 }
 
 // One iteration of the semi-loop reduce-scatter (Sec. 3.3) on both of its chains at once: the first half of the grid
 // (`count` workgroups, in whole groups of eight) advances the chain that walks up from device h+1, the second the one that
-// walks down from device h, each by one device -- the first iteration quantizes the chain's first shard (no incoming wire: cin == nullptr), the later ones are hops on
-// the chain's own wire buffer in place.  The two halves share nothing.
-struct StridedDirection {
-    int offset;             // as StridedSource::offset
-    const int8_t *cin;      // nullptr: this is the chain's first device, it only quantizes its shard
-    const float *sin;
-    int8_t *cout;
-    float *sout;
-};
-
-struct StridedDirections {
-    StridedDirection d[2];
-};
-
-template <int R>
-__global__ __launch_bounds__(kThreads) void semi_step_strided_kernel(int P, int per_shard, unsigned count, int backward,
-                                                                     const StridedDirections dirs, const PartialTable tab)
+// walks down from device h, each by one device -- the first iteration quantizes the chain's first shard, the later ones are
+// hops on the chain's own wire buffer in place.  The two halves share nothing.  `ring`: as in strided_source, the second
+// direction's offset from bit 16 on.
+template <typename S>
+__global__ __launch_bounds__(kThreads) void semi_step_strided_kernel(Global<int8_t> codes0, Global<float> scales0, Global<int8_t> codes1,
+                                                                     Global<float> scales1, int per_shard, int ring, unsigned count,
+                                                                     unsigned owned, int backward, int first, const PartialTable tab)
 {
-    __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
+    __shared__ __align__(16) SliceQuotients<S> q;
     const unsigned half = whole_groups(count);
     const unsigned place = mirrored_place(blockIdx.x, backward ? 2 * half : 0);
-    const unsigned at = place < half ? place : place - half;
+    const bool second = place >= half;
+    const unsigned at = second ? place - half : place;
     if (at >= count) return;            // uniform over the workgroup
-    const StridedSpot sp = strided_spot(R * kChunkGroups, at);
-    const StridedDirection d = place < half ? dirs.d[0] : dirs.d[1];
-    const int j = (per_shard > 0 ? (int)(sp.minishard / per_shard) : 0) + d.offset;     // < 2P
-    const uint16_t *x = tab.x[j >= P ? j - P : j];
-    if (d.cin == nullptr) {             // uniform over the workgroup
-        quantize_strided_body<R>(x, d.cout, d.sout, sp, red);
+    const StridedSpot sp = strided_spot<S>(at, owned);
+    int8_t *codes = second ? codes1 : codes0;
+    float *scales = second ? scales1 : scales0;
+    const uint16_t *x = strided_source(sp.minishard, per_shard, second ? ring >> 8 & ~255 | (ring & 255) : ring, tab);
+    if (first) {                        // uniform over the workgroup
+        quantize_strided_body<S>(x, codes, scales, sp, q);
     } else {
-        hop_strided_body<R>(d.cin, d.sin, x, d.cout, d.sout, sp, red);
+        hop_strided_body<S>(codes, scales, x, codes, scales, sp, q);
     }
 }
 
 // The last launch of a hop-by-hop flavour in the strided geometry: the device that ends up with the sum adds what
 // it received to its own bf16 shard -- one wire at the end of the full loop, one or two at the owner of the
-// semi-loop (Sec. 3.3: the shorter chain's wire first), none when it is alone -- each with one fused multiply-add
+// semi-loop (Sec. 3.3: the shorter chain's wire first), none when it is alone (nullptr) -- each with one fused multiply-add
 // per element, and hands the sum to the all-gather: quantized once more and dequantized (kAG), or narrowed to
 // bf16 as it is (Sec. 3.4).  out may be `own`: a thread reads its elements before it writes them.
-struct StridedWires {
-    const int8_t *codes[2];
-    const float *scales[2];
-};
-
-template <int R, bool kAG>
-__global__ __launch_bounds__(kThreads) void owner_strided_kernel(int received, unsigned mirror, Global<uint16_t> out,
-                                                                 const StridedWires wires, const StridedSource src)
+template <typename S, bool kAG, typename... Source>
+__global__ __launch_bounds__(kThreads) void owner_strided_kernel(Global<uint16_t> out, Global<const int8_t> codes0, Global<const float> scales0,
+                                                                 Global<const int8_t> codes1, Global<const float> scales1,
+                                                                 unsigned mirror, unsigned owned, const Source... src)
 {
-    __shared__ __align__(16) uint32_t red[kChunkGroups][kSlicePos];
-    constexpr int chunks = R * kChunkGroups;
-    const StridedSpot sp = strided_spot(chunks, mirrored_place(blockIdx.x, mirror));
-    const uint16_t *own = strided_source(src, sp.minishard);
+    __shared__ __align__(16) SliceQuotients<S> q;
+    const StridedSpot sp = strided_spot<S>(mirrored_place(blockIdx.x, mirror), owned);
+    const uint16_t *own = strided_source(sp.minishard, src...);
 
-    float acc[R][8];
+    float acc[S::R][8];
     {
-        u32x4 xv[R];
+        u32x4 xv[S::R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            xv[r] = __builtin_nontemporal_load(
-                reinterpret_cast<const u32x4 *>(own + sp.elem + (int64_t)r * kChunkGroups * kChunk));
-        }
+        for (int r = 0; r < S::R; ++r) xv[r] = load_row_bf16x8<S::kRow>(own + sp.elem, sp.at, r);
 #pragma unroll
-        for (int r = 0; r < R; ++r) widen_bf16x8(xv[r], acc[r]);
+        for (int r = 0; r < S::R; ++r) widen_bf16x8(xv[r], acc[r]);
     }
-    for (int k = 0; k < received; ++k) {
-        const int8_t *codes = wires.codes[k];
-        const float *scales = wires.scales[k];
-        u32x2 cv[R];
+#pragma unroll 1
+    for (int k = 0; k < 2; ++k) {
+        const int8_t *codes = k ? codes1 : codes0;
+        const float *scales = k ? scales1 : scales0;
+        if (!codes) break;              // uniform
+        u32x2 cv[S::R];
+        float s_in[8];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            cv[r] = *reinterpret_cast<const u32x2 *>(codes + sp.elem + (int64_t)r * kChunkGroups * kChunk);
-        }
-        const u32x4 a = *reinterpret_cast<const u32x4 *>(scales + sp.scale);
-        const u32x4 b = *reinterpret_cast<const u32x4 *>(scales + sp.scale + 4);
-        const float s_in[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
-                               __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
+        for (int r = 0; r < S::R; ++r) cv[r] = load_row_i8x8<S::kRow>(codes + sp.elem, sp.at, r);
+        read_eight(scales + sp.scale + sp.pos, s_in);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
+        for (int r = 0; r < S::R; ++r) {
             float qf[8];
             widen_i8x8(cv[r], qf);
 #pragma unroll
@@ -330,26 +371,19 @@ __global__ __launch_bounds__(kThreads) void owner_strided_kernel(int received, u
 
     float scale[8], inv[8];
     if (kAG) {
-        uint32_t m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        float m[8] = {};
 #pragma unroll
-        for (int r = 0; r < R; ++r) note_absmax(acc[r], m);
-        across_chunks_max(m, red);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) block_quotients(__uint_as_float(m[j]), scale[j], inv[j]);
+        for (int r = 0; r < S::R; ++r) fold_absmax(acc[r], m);
+        slice_quotients<true>(m, q, inv, scale);
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
+    for (int r = 0; r < S::R; ++r) {
         float d[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             d[j] = kAG ? (__builtin_rintf(acc[r][j] * inv[j]) + 0.0f) * scale[j] : acc[r][j];     // +0.0: the code as an integer
         }
-        u32x4 w;
-        w.x = narrow_bf16x2(d[0], d[1]);
-        w.y = narrow_bf16x2(d[2], d[3]);
-        w.z = narrow_bf16x2(d[4], d[5]);
-        w.w = narrow_bf16x2(d[6], d[7]);
-        __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(out + sp.elem + (int64_t)r * kChunkGroups * kChunk));
+        store_row_bf16x8<S::kRow>(out + sp.elem, sp.at, r, d);
     }
 }
 
@@ -381,10 +415,10 @@ __global__ __launch_bounds__(kThreads) void owner_strided_kernel(int received, u
 // 10.6 -> 5.6 us on MI355X).
 
 struct WaveSpot {
-    int64_t minishard;  // which minishard the workgroup works on
-    int64_t elem;       // first element of the lane in the first of its chunks
-    int64_t scale;      // index of the lane's first scale
-    int64_t row_step;   // elements between two consecutive chunks of the lane
+    unsigned minishard; // which minishard the workgroup works on
+    int64_t elem;       // first element of the workgroup's positions in the first chunk of its minishard
+    int64_t scale;      // index of their first scale
+    int at, pos;        // the lane's first element, from there, in the first of its chunks; its first position
     bool first_group;   // the lane stores the scales of its positions
 };
 
@@ -400,13 +434,14 @@ __device__ __forceinline__ WaveSpot wave_spot(int chunks)
     constexpr int kPerChunk = wave_layout_wgs<W, V>;
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const int g = (wave % W) * 8 + lane / 8;                    // chunk group, 0 .. 8W-1
-    const int64_t ms = blockIdx.x / kPerChunk;
-    const int pos = (blockIdx.x % kPerChunk) * (kPieces * 8 * V) + (wave / W) * (8 * V) + (lane % 8) * V;
+    const int part = blockIdx.x % kPerChunk;
+    constexpr int kPositions = kPieces * 8 * V;
     WaveSpot sp;
-    sp.minishard = ms;
-    sp.elem = ms * ((int64_t)kChunk * chunks) + (int64_t)g * kChunk + pos;
-    sp.scale = ms * kChunk + pos;
-    sp.row_step = (int64_t)8 * W * kChunk;
+    sp.minishard = blockIdx.x / kPerChunk;
+    sp.elem = (int64_t)sp.minishard * (kChunk * chunks) + part * kPositions;
+    sp.scale = (int64_t)sp.minishard * kChunk + part * kPositions;
+    sp.pos = (wave / W) * (8 * V) + (lane % 8) * V;
+    sp.at = g * kChunk + sp.pos;
     sp.first_group = g == 0;
     return sp;
 }
@@ -477,12 +512,16 @@ struct PieceOf<4> {
 template <int V>
 using Piece = typename PieceOf<V>::type;
 
-template <int R, int V>
+// Elements from a lane's chunk to its next.
+template <int W>
+constexpr int kWaveRow = 8 * W * kChunk;
+
+template <int R, int W, int V>
 __device__ __forceinline__ void load_strided(const uint16_t *x, const WaveSpot &sp, Piece<V> (&xv)[R])
 {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        xv[r] = __builtin_nontemporal_load(reinterpret_cast<const Piece<V> *>(x + sp.elem + r * sp.row_step));
+        xv[r] = __builtin_nontemporal_load(reinterpret_cast<const Piece<V> *>(x + sp.elem + r * kWaveRow<W> + sp.at));
     }
 }
 
@@ -586,7 +625,7 @@ void chain_strided_kernel(int P, int per_shard, Global<uint16_t> out, const Part
     constexpr int chunks = 8 * W * R;
     const WaveSpot sp = wave_spot<W, V>(chunks);
     // position i of the chain -> partial; `first` <= P and i < P, so one conditional subtraction wraps
-    const int first = per_shard > 0 ? (int)(sp.minishard / per_shard) + (kSemi ? 0 : 1) : 0;
+    const int first = per_shard > 0 ? (int)(sp.minishard / (unsigned)per_shard) + (kSemi ? 0 : 1) : 0;
     const auto part = [&](int i) {
         const int j = first + i;
         return tab.x[j >= P ? j - P : j];
@@ -594,25 +633,25 @@ void chain_strided_kernel(int P, int per_shard, Global<uint16_t> out, const Part
 
     float sum[R][V];
     Piece<V> xv[R];
-    load_strided<R, V>(part(0), sp, xv);
+    load_strided<R, W, V>(part(0), sp, xv);
     widen_strided<R, V>(xv, sum);
     if (kSemi) {
         const int h = P / 2;
         float t[R][V];
         if (h + 1 <= P - 1) {                       // h+1 -> h+2 -> ... -> P-1 -> owner: the shorter chain arrives first
-            load_strided<R, V>(part(h + 1), sp, xv);
+            load_strided<R, W, V>(part(h + 1), sp, xv);
             widen_strided<R, V>(xv, t);
             for (int i = h + 2; i <= P - 1; ++i) {
-                load_strided<R, V>(part(i), sp, xv);
+                load_strided<R, W, V>(part(i), sp, xv);
                 strided_hop<R, W, V, !kAG>(t, xv, st);
             }
             strided_send_into<R, W, V, !kAG>(t, sum, st);
         }
         if (h >= 1) {                               // h -> h-1 -> ... -> 1 -> owner
-            load_strided<R, V>(part(h), sp, xv);
+            load_strided<R, W, V>(part(h), sp, xv);
             widen_strided<R, V>(xv, t);
             for (int i = h - 1; i >= 1; --i) {
-                load_strided<R, V>(part(i), sp, xv);
+                load_strided<R, W, V>(part(i), sp, xv);
                 strided_hop<R, W, V, !kAG>(t, xv, st);
             }
             strided_send_into<R, W, V, !kAG>(t, sum, st);
@@ -623,7 +662,7 @@ void chain_strided_kernel(int P, int per_shard, Global<uint16_t> out, const Part
             // boundaries: moved by 4 bytes by whatever stands before it, it takes up to 9 % longer (MI355X, 40 minishards of
             // 128 chunks, P = 16: 42.1 us; 38.7 like this; 154 minishards 122.8 and 119.5).
             if (kRS && W == 2 && V == 8) asm volatile(".p2align 3");
-            load_strided<R, V>(part(i), sp, xv);
+            load_strided<R, W, V>(part(i), sp, xv);
             if (kRS) {
                 strided_hop<R, W, V, !kAG>(sum, xv, st);
             } else {
@@ -645,140 +684,39 @@ void chain_strided_kernel(int P, int per_shard, Global<uint16_t> out, const Part
         float d[V];
 #pragma unroll
         for (int j = 0; j < V; ++j) d[j] = kAG ? code_of<true>(sum[r][j], inv[j]) * scale[j] : sum[r][j];
-        store_piece<V>(out + sp.elem + r * sp.row_step, d);
+        store_piece<V>(out + sp.elem + r * kWaveRow<W> + sp.at, d);
     }
 }
 
-// ---------------------------------------------------------------- the per-pass kernels for few minishards
-//
-// The same passes in the wave layout: W = 4 waves share a piece of 64 positions, R = chunks / 32 rows per thread
-// instead of chunks / 8, 16 workgroups per minishard instead of 4.  Code pieces are 64 bytes, half a line, which is
-// why the per-pass kernels above have another layout; a message of few minishards is not bound by that but by the
-// time one wave takes (MI355X, hop-by-hop chain of four, five passes, 8 minishards: 64 chunks 17.9 -> 15.0 us, 128
-// chunks 24.4 -> 17.6).
-
-template <int R>
-struct WavePass {
-    static constexpr int W = 4, V = 8, kChunks = 8 * W * R;
-    WaveSpot sp;
-    ChunkMaxState<W, V> st;
-
-    __device__ __forceinline__ explicit WavePass(ChunkMaxRows<W, V> &red) : sp(wave_spot<W, V>(kChunks)), st{red, 0} {}
-
-    __device__ __forceinline__ void load(const uint16_t *x, float (&t)[R][V]) const
-    {
-        Piece<V> xv[R];
-        load_strided<R, V>(x, sp, xv);
-        widen_strided<R, V>(xv, t);
-    }
-
-    // t += codes * scales, one fused multiply-add per element
-    __device__ __forceinline__ void add_wire(const int8_t *codes, const float *scales, float (&t)[R][V]) const
-    {
-        u32x2 cv[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) cv[r] = *reinterpret_cast<const u32x2 *>(codes + sp.elem + r * sp.row_step);
-        const u32x4 a = *reinterpret_cast<const u32x4 *>(scales + sp.scale);
-        const u32x4 b = *reinterpret_cast<const u32x4 *>(scales + sp.scale + 4);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            float qf[V];
-            widen_i8x8(cv[r], qf);
-#pragma unroll
-            for (int j = 0; j < V; ++j) t[r][j] = __builtin_fmaf(qf[j], __uint_as_float(j < 4 ? a[j & 3] : b[j & 3]), t[r][j]);
-        }
-    }
-
-    __device__ __forceinline__ void send(const float (&t)[R][V], int8_t *codes, float *scales)
-    {
-        float scale[V], inv[V];
-        strided_quotients<R, W, V>(t, st, scale, inv);
-#pragma unroll
-        for (int r = 0; r < R; ++r) *reinterpret_cast<u32x2 *>(codes + sp.elem + r * sp.row_step) = scale_and_pack(t[r], inv);
-        if (sp.first_group) {
-            u32x4 *s = reinterpret_cast<u32x4 *>(scales + sp.scale);
-            s[0] = u32x4{__float_as_uint(scale[0]), __float_as_uint(scale[1]), __float_as_uint(scale[2]), __float_as_uint(scale[3])};
-            s[1] = u32x4{__float_as_uint(scale[4]), __float_as_uint(scale[5]), __float_as_uint(scale[6]), __float_as_uint(scale[7])};
-        }
-    }
-};
-
-// kWire: a hop; otherwise the chain's first shard is quantized.  The output wire may be the input wire: the waves of a
-// piece meet at a barrier between their last load and their first store.
-template <int R, bool kWire>
-__global__ __launch_bounds__(kThreads) void pass_strided_small_kernel(Global<const int8_t> cin, Global<const float> sin, Global<int8_t> cout,
-                                                                      Global<float> sout, const StridedSource src)
+// Dequantize in the strided geometry: element e uses scale (e / (1024*chunks)) * 1024 + e % 1024, so the 8 elements of a
+// lane use 8 consecutive scales, the same ones in each of its K tiles.  A workgroup takes T*K*8 consecutive elements of a
+// minishard, on the XCD that has it in the passes.
+template <int kChunks, int T, int K>
+__global__ __launch_bounds__(T) void dequantize_strided_kernel(Global<const int8_t> codes, Global<const float> scales,
+                                                               Global<uint16_t> out, unsigned mirror, unsigned owned)
 {
-    __shared__ __align__(16) ChunkMaxRows<4, 8> red;
-    WavePass<R> pass(red);
-    float t[R][8];
-    pass.load(strided_source(src, pass.sp.minishard), t);
-    if (kWire) pass.add_wire(cin, sin, t);
-    pass.send(t, cout, sout);
-}
-
-template <int R>
-__global__ __launch_bounds__(kThreads) void semi_step_strided_small_kernel(int P, int per_shard,
-                                                                           const StridedDirections dirs,
-                                                                           const PartialTable tab)
-{
-    __shared__ __align__(16) ChunkMaxRows<4, 8> red;
-    WavePass<R> pass(red);
-    const StridedDirection d = blockIdx.y == 0 ? dirs.d[0] : dirs.d[1];
-    const int j = (per_shard > 0 ? (int)(pass.sp.minishard / per_shard) : 0) + d.offset;     // < 2P
-    float t[R][8];
-    pass.load(tab.x[j >= P ? j - P : j], t);
-    if (d.cin != nullptr) pass.add_wire(d.cin, d.sin, t);       // uniform over the workgroup
-    pass.send(t, d.cout, d.sout);
-}
-
-template <int R, bool kAG>
-__global__ __launch_bounds__(kThreads) void owner_strided_small_kernel(int received, Global<uint16_t> out,
-                                                                       const StridedWires wires, const StridedSource src)
-{
-    __shared__ __align__(16) ChunkMaxRows<4, 8> red;
-    WavePass<R> pass(red);
-    float t[R][8];
-    pass.load(strided_source(src, pass.sp.minishard), t);
-    for (int k = 0; k < received; ++k) pass.add_wire(wires.codes[k], wires.scales[k], t);
-    float scale[8], inv[8];
-    if (kAG) strided_quotients<R, 4, 8>(t, pass.st, scale, inv);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        float d[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) d[j] = kAG ? code_of<true>(t[r][j], inv[j]) * scale[j] : t[r][j];
-        store_piece<8>(out + pass.sp.elem + r * pass.sp.row_step, d);
-    }
-}
-
-// Dequantize in the strided geometry: element e uses scale (e / (1024*chunks)) * 1024 + e % 1024, so the 8
-// elements of a lane use 8 consecutive scales.  n is a multiple of 1024: 8 elements are inside or outside as a whole.
-template <int K>
-__global__ __launch_bounds__(pass_threads(K)) void dequantize_strided_kernel(Global<const int8_t> codes,
-                                                                      Global<const float> scales, int64_t n,
-                                                                      int chunks, Global<uint16_t> out, int64_t mirror)
-{
-    constexpr int T = pass_threads(K);
-    const int64_t wg_at = first_element<T, K>(mirror);
+    static_assert(tile_elems<T> % kChunk == 0 && kChunk * kChunks % (tile_elems<T> * K) == 0, "whole chunks");
+    constexpr int kParts = kChunk * kChunks / (tile_elems<T> * K);
+    const MinishardPart place = minishard_part<kParts>(mirrored_place(blockIdx.x, mirror), owned);
     const int lane_at = threadIdx.x * kLaneElems;
-    const int64_t minishard = (int64_t)kChunk * chunks;
+    const int64_t at = (int64_t)place.minishard * (kChunk * kChunks) + place.part * (tile_elems<T> * K);
+    u32x2 cv[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) cv[k] = *reinterpret_cast<const u32x2 *>(codes + at + k * tile_elems<T> + lane_at);
+    const float *s = scales + (int64_t)place.minishard * kChunk + lane_at % kChunk;
+    const u32x4 a = *reinterpret_cast<const u32x4 *>(s);
+    const u32x4 b = *reinterpret_cast<const u32x4 *>(s + 4);
+    loads_first();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int64_t at = wg_at + k * tile_elems<T> + lane_at;
-        if (at >= n) continue;                       // n % 8 == 0: a lane is inside or outside as a whole
-        const u32x2 cv = *reinterpret_cast<const u32x2 *>(codes + at);
-        const float *s = scales + (at / minishard) * kChunk + at % kChunk;
-        const u32x4 a = *reinterpret_cast<const u32x4 *>(s);
-        const u32x4 b = *reinterpret_cast<const u32x4 *>(s + 4);
         float qf[8];
-        widen_i8x8(cv, qf);
+        widen_i8x8(cv[k], qf);
         u32x4 w;
         w.x = narrow_bf16x2(qf[0] * __uint_as_float(a.x), qf[1] * __uint_as_float(a.y));
         w.y = narrow_bf16x2(qf[2] * __uint_as_float(a.z), qf[3] * __uint_as_float(a.w));
         w.z = narrow_bf16x2(qf[4] * __uint_as_float(b.x), qf[5] * __uint_as_float(b.y));
         w.w = narrow_bf16x2(qf[6] * __uint_as_float(b.z), qf[7] * __uint_as_float(b.w));
-        __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(out + at));
+        __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(out + at + k * tile_elems<T> + lane_at));
     }
 }
 

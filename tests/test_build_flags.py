@@ -96,3 +96,11 @@ def test_a_wire_that_leaves_is_stored_with_its_hint(device_asm):
     for name, body in bodies:
         stores = [line for line in body.splitlines() if re.search(r"(global|buffer)_store_dwordx2", line)]
         assert len(stores) >= 2 and all(line.split(";")[0].rstrip().endswith(" nt") for line in stores), name
+
+
+def test_no_store_of_16_bytes_takes_an_offset_from_a_scalar_register(device_asm):
+    """The next instructions may overwrite what such a store is still reading: its row belongs in the descriptor."""
+    for name, asm in device_asm.items():
+        stores = re.findall(r"buffer_store_dwordx[34] [^;\n]*", asm)
+        assert name != "equarx_api.hip" or stores
+        assert not [line for line in stores if re.search(r"\], s\d+ ", line)], name

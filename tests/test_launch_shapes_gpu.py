@@ -385,6 +385,29 @@ def test_strided_layouts_above_the_small_ones_with_extreme_values(gpu, oracle, c
         assert (gpu.host_u16(dev[2]) == want).all(), flags
 
 
+@pytest.mark.parametrize("chunks,minishards", ((32, 8), (32, 65), (32, 191), (32, 192), (32, 203), (64, 9), (64, 47), (64, 127),
+                                               (64, 128), (64, 161), (128, 16), (128, 18), (128, 39)))
+def test_strided_passes_by_lanes_and_owners(gpu, oracle, long_values, chunks, minishards):  # noqa: F811
+    """Both sides of the lines between the layouts, with minishards left over behind whole runs on every XCD."""
+    n, P = 1024 * chunks * minishards, 3
+    x = [np.resize(long_values[i], n + i)[i:].copy() for i in range(P)]
+    dev = [gpu.dev_bf16(p) for p in x]
+    c, s = torch.empty(n, dtype=torch.int8, device="cuda"), torch.empty(n // chunks, device="cuda")
+    eq.equarx_quantize_strided(dev[0], chunks, c, s)
+    wc, ws = oracle.quantize_bf16_strided(x[0], chunks)
+    assert (c.cpu().numpy() == wc).all() and (_bits(s) == ws.view(np.uint32)).all()
+    eq.equarx_reduce_stage_strided(c, s, dev[1], chunks, c, s)
+    wc, ws = oracle.hop_strided(wc, ws, x[1], chunks)
+    assert (c.cpu().numpy() == wc).all() and (_bits(s) == ws.view(np.uint32)).all()
+    out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    for flags in (0, eq.SEMI_LOOP | eq.RING_ORDER, eq.RING_ORDER | eq.AG_UNQUANTIZED):
+        work = eq.alloc_variant_workspace(flags & ~eq.RING_ORDER, P, n, chunks)
+        eq.equarx_reduce_variant_hops_strided(dev, chunks, flags, out.fill_(5.0), work)
+        assert (gpu.host_u16(out) == _oracle_variant_strided(oracle, x, chunks, flags)).all(), flags
+    eq.equarx_reduce_quantized_strided(dev, chunks, out.fill_(5.0), eq.alloc_workspace(P, n, chunks))
+    assert (gpu.host_u16(out) == _oracle_variant_strided(oracle, x, chunks, 0)).all()
+
+
 SMALL = 768 * 2048              # single-launch calls of few partials: up to here the batched kernel
 ALL_SINGLE = SINGLE + (eq.SEMI_LOOP | eq.RING_ORDER, eq.AG_UNQUANTIZED | eq.RING_ORDER, eq.RS_UNQUANTIZED)
 
