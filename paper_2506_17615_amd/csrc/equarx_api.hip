@@ -592,13 +592,6 @@ inline int check_strided(int64_t n, int32_t chunks)
 
 inline int64_t minishards_of(int64_t n, int32_t chunks) { return n / ((int64_t)kChunk * chunks); }
 
-// Messages of up to this many minishards have layouts whose waves have a quarter or an eighth of the work: with more than
-// that every CU is busy, and the larger layouts do less work in all.  Single-launch chain, P = 8, 64 chunks, MI355X, us,
-// larger -> small layout: 1 minishard 10.6 -> 5.6, 4 12.1 -> 7.3, 16 12.9 -> 8.7, 32 13.5 -> 14.4; 16 of 32 chunks 10.0 -> 7.1.
-constexpr int64_t kStridedSmall = 16;
-// Between the two, for 64 chunks: half the work per wave (chain, 24 minishards 13.3 -> 10.1, 32 13.5 -> 10.9, 48 14.7 -> 15.3).
-constexpr int64_t kStridedMedium = 32;
-
 // f(layout) with the layout of the per-pass kernels: 16 lanes across a slice, where a code piece is a whole line and a thread
 // has 2, 4 or 8 rows.  8 lanes for few minishards of 64 and 128 chunks, which otherwise leave CUs idle.  32 for many of 32
 // chunks, and of 64 if the workgroups that gives are a whole number per CU (256), or over half of the next: every workgroup
@@ -631,12 +624,12 @@ inline void with_slices(int64_t n, int32_t chunks, F f)
             else f(Slices<32, 32>{});
             break;
         case 64:
-            if (ms <= kStridedSmall) f(Slices<64, 8>{});
+            if (ms <= 16) f(Slices<64, 8>{});
             else if (ms < 128 || (4 * ms - 1) % 256 < 128) f(Slices<64, 16>{});
             else f(Slices<64, 32>{});
             break;
         case 128:
-            if (ms <= kStridedSmall) f(Slices<128, 8>{});
+            if (ms <= 16) f(Slices<128, 8>{});
             else f(Slices<128, 16>{});
             break;
         default: break;
@@ -736,41 +729,71 @@ void do_owner_strided(const StridedWires &in, int64_t n, int32_t chunks, uint16_
 }
 
 // The single-launch chain and its flavours: chunks = 8 * W * R (see chain_strided_kernel).
-template <int R, int W, int V>
+template <int R, int W, int V, int kWaves>
 void launch_chain_strided_as(const PartialTable &tab, int P, int64_t minishards, int per_shard, bool semi, bool rs, bool ag,
                              uint16_t *out, LaunchCtx &ctx)
 {
     const unsigned grid = (unsigned)(minishards * wave_layout_wgs<W, V>);
-    if (semi && ag) ctx.launch(chain_strided_kernel<R, W, V, true, true, true>, grid, kThreads, P, per_shard, out, tab);
-    else if (semi) ctx.launch(chain_strided_kernel<R, W, V, true, true, false>, grid, kThreads, P, per_shard, out, tab);
-    else if (rs && ag) ctx.launch(chain_strided_kernel<R, W, V, false, true, true>, grid, kThreads, P, per_shard, out, tab);
-    else if (rs) ctx.launch(chain_strided_kernel<R, W, V, false, true, false>, grid, kThreads, P, per_shard, out, tab);
-    else ctx.launch(chain_strided_kernel<R, W, V, false, false, true>, grid, kThreads, P, per_shard, out, tab);
+    // Runs of minishards to an XCD (minishard_part), though nothing is read twice here, where the partials stream better so.
+    // MI355X, us, parts of a minishard on all XCDs -> runs, P = 8 and 16: 32 chunks, 672 minishards 62.6 -> 60.8, 113.7 -> 112.9, 1000 90.1
+    // -> 88.9 (400, without the cap, 37.3 -> 38.0, 68.4 -> 70.7); 64 chunks, 128 23.1 -> 24.4, 41.0 -> 44.1, 336 61.0 -> 62.9, 111.5 ->
+    // 117.9; 128 chunks, 64 25.2 -> 25.8, 45.5 -> 47.3, 100 42.5 -> 42.4, 78.5 -> 77.0, 160 63.5 -> 62.8, 122.5 -> 117.9, 256 102.6 -> 99.2.
+    constexpr int kChunks = 8 * W * R;
+    const bool own = V == 8 && ((kChunks == 32 && kWaves == 2) || (kChunks == 128 && minishards >= 96));
+    const unsigned owned = own ? owned_places<kChunks, wave_layout_wgs<W, V>>(minishards) : 0u;
+#define EQUARX_CHAIN(SEMI, RS, AG) \
+    ctx.launch(chain_strided_kernel<R, W, V, SEMI, RS, AG, kWaves>, grid, kThreads, P, per_shard, out, owned, tab)
+    if (semi && ag) EQUARX_CHAIN(true, true, true);
+    else if (semi) EQUARX_CHAIN(true, true, false);
+    else if (rs && ag) EQUARX_CHAIN(false, true, true);
+    else if (rs) EQUARX_CHAIN(false, true, false);
+    else EQUARX_CHAIN(false, false, true);
+#undef EQUARX_CHAIN
 }
 
+// Few minishards take layouts whose waves have an eighth, a quarter or half of the work, so that every CU has some; where
+// those are a round of the chip, the largest, which does least in all, is faster.  Measured on MI355X, us (GPU time of
+// captured calls), full loop of P = 8, chunks = 8 W R as R x W x V:
+//     minishards of 32    1x4x4 / 4x1x8     of 64    2x4x4 / 2x4x8 / 8x1x8     of 128    4x4x4 / 4x4x8 / 8x2x8
+//     5                       6.6/                       7.6/7.5/                            8.6/8.7/
+//     8                       6.8/8.3                    7.9/7.9/                            9.9/9.1/
+//     12                      7.3/8.4                    9.0/8.1/                           13.2/9.4/12.8
+//     20                      8.2/8.6                   10.6/9.0/10.3                       20.8/13.0/14.4
+//     24                      8.8/8.7                   11.5/9.4/                           21.9/13.6/14.9
+//     32                      9.5/8.9                   15.5/10.5/                          29.6/15.1/16.0
+//     40                     10.1/9.0                   19.3/15.7/12.6                           19.4/20.0
+//     48                                                     16.8/14.1                           21.6/21.8
+//     64                                                     18.0/14.6                           28.8/25.0
 // ring: shards of ceil(minishards / P) whole minishards, shard k in the order a ring gives it.
 void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chunks, bool semi, bool rs, bool ag,
                           bool ring, uint16_t *out, LaunchCtx &ctx)
 {
-    const int64_t ms = n / ((int64_t)kChunk * chunks);
+    const int64_t ms = minishards_of(n, chunks);
     const int per_shard = ring ? (int)((ms + P - 1) / P) : 0;
-    const bool small = ms <= kStridedSmall;
+    const int64_t wgs = ms * wave_layout_wgs<1, 8>;
+    // see chain_strided_kernel's kWaves
+    const bool short_round = wgs > 512 && wgs < 2048 && (wgs - 1) % 512 < 256, half_round = !rs && wgs > 640 && wgs <= 768;
+#define EQUARX_LAYOUT(...) launch_chain_strided_as<__VA_ARGS__>(tab, P, ms, per_shard, semi, rs, ag, out, ctx)
     switch (chunks) {
         case 32:
-            if (small) launch_chain_strided_as<1, 4, 4>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
-            else launch_chain_strided_as<4, 1, 8>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
+            if (ms <= 20) EQUARX_LAYOUT(1, 4, 4, 8);
+            else if (short_round) EQUARX_LAYOUT(4, 1, 8, 8);
+            else EQUARX_LAYOUT(4, 1, 8, 2);
             break;
         case 64:
-            if (small) launch_chain_strided_as<2, 4, 4>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
-            else if (ms <= kStridedMedium) launch_chain_strided_as<4, 2, 4>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
-            else launch_chain_strided_as<8, 1, 8>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
+            if (ms <= 8) EQUARX_LAYOUT(2, 4, 4, 8);
+            else if (ms <= 32) EQUARX_LAYOUT(2, 4, 8, 2);
+            else if (half_round) EQUARX_LAYOUT(8, 1, 8, 8);
+            else EQUARX_LAYOUT(8, 1, 8, 2);
             break;
         case 128:
-            if (small) launch_chain_strided_as<4, 4, 4>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
-            else launch_chain_strided_as<8, 2, 8>(tab, P, ms, per_shard, semi, rs, ag, out, ctx);
+            if (ms <= 6) EQUARX_LAYOUT(4, 4, 4, 8);
+            else if (ms <= 48) EQUARX_LAYOUT(4, 4, 8, 4);
+            else EQUARX_LAYOUT(8, 2, 8, 2);
             break;
         default: break;
     }
+#undef EQUARX_LAYOUT
 }
 
 template <int kChunks, int T, int K>

@@ -202,10 +202,11 @@ __device__ __forceinline__ float slice_quotients(const float (&m)[8], SliceQuoti
     return own;
 }
 
-__device__ __forceinline__ void fold_absmax(const float (&t)[8], float (&m)[8])
+template <int V>
+__device__ __forceinline__ void fold_absmax(const float (&t)[V], float (&m)[V])
 {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) m[j] = __builtin_fmaxf(m[j], __builtin_fabsf(t[j]));
+    for (int j = 0; j < V; ++j) m[j] = __builtin_fmaxf(m[j], __builtin_fabsf(t[j]));
 }
 
 __device__ __forceinline__ u32x2 scale_and_pack(const float (&t)[8], const float (&inv)[8])
@@ -233,13 +234,6 @@ __device__ __forceinline__ void send_slice(const float (&t)[S::R][8], int8_t *co
     for (int r = 0; r < S::R; ++r) {
         store_row_i8x8<S::kRow>(codes + sp.elem, sp.at, r, scale_and_pack(t[r], inv));
     }
-}
-
-template <int V>
-__device__ __forceinline__ void note_absmax(const float (&t)[V], uint32_t (&m)[V])
-{
-#pragma unroll
-    for (int j = 0; j < V; ++j) m[j] = umax(m[j], __float_as_uint(t[j]) & 0x7FFFFFFFu);
 }
 
 template <typename S>
@@ -408,11 +402,16 @@ __global__ __launch_bounds__(kThreads) void owner_strided_kernel(Global<uint16_t
 // Same operations in the same order as the hop-by-hop strided chain, hence
 // the same bits.
 //
+// A send does not compute anything twice either: the 8 lanes of a position end their exchange with one of its 8 positions'
+// maxima each (scatter_max), work out that one pair of quotients and hand it round (gather_lanes).  With every lane deriving
+// all 8 pairs, and 64-bit addresses per row, the full loop had 773, 1197 and 1290 vector instructions at 32, 64 and 128 chunks,
+// now 497, 857 and 881.  Measured on MI355X, us, P = 8, before -> after: 22 M elements of 32 chunks 66.9 -> 60.8, of 64 61.7 -> 60.5,
+// of 128 69.9 -> 68.5; 17 minishards of 32 chunks 10.3 -> 8.5, one 5.4 -> 4.2.
+//
 // A message of few minishards is bound by the time one wave takes per send,
 // not by memory: W = 4 waves share a piece and a lane has V = 4 positions
-// instead of 8, so a wave has an eighth of the rows and quotients and a
-// minishard 32 workgroups instead of 4 (one minishard of 64 chunks, P = 8:
-// 10.6 -> 5.6 us on MI355X).
+// instead of 8, so a wave has an eighth of the rows and a
+// minishard 32 workgroups instead of 4.
 
 struct WaveSpot {
     unsigned minishard; // which minishard the workgroup works on
@@ -427,17 +426,18 @@ template <int W, int V>
 constexpr int wave_layout_wgs = kChunk / ((kThreads / 64) / W * 8 * V);      // workgroups per minishard
 
 template <int W, int V>
-__device__ __forceinline__ WaveSpot wave_spot(int chunks)
+__device__ __forceinline__ WaveSpot wave_spot(int chunks, unsigned owned)
 {
     static_assert((W == 1 || W == 2 || W == 4) && (V == 4 || V == 8), "waves per position piece, positions per lane");
     constexpr int kPieces = (kThreads / 64) / W;                // position pieces per workgroup
     constexpr int kPerChunk = wave_layout_wgs<W, V>;
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const int g = (wave % W) * 8 + lane / 8;                    // chunk group, 0 .. 8W-1
-    const int part = blockIdx.x % kPerChunk;
+    const MinishardPart place = minishard_part<kPerChunk>(blockIdx.x, owned);
+    const int part = place.part;
     constexpr int kPositions = kPieces * 8 * V;
     WaveSpot sp;
-    sp.minishard = blockIdx.x / kPerChunk;
+    sp.minishard = place.minishard;
     sp.elem = (int64_t)sp.minishard * (kChunk * chunks) + part * kPositions;
     sp.scale = (int64_t)sp.minishard * kChunk + part * kPositions;
     sp.pos = (wave / W) * (8 * V) + (lane % 8) * V;
@@ -447,10 +447,10 @@ __device__ __forceinline__ WaveSpot wave_spot(int chunks)
 }
 
 
-// A maximum that waves exchange: one row per wave, two buffers in turn.
+// Maxima that waves exchange: one row per wave, two buffers in turn.
 template <int W, int V>
 struct ChunkMaxRows {
-    uint32_t row[W > 1 ? 2 : 1][kThreads / 64][8 * V];
+    float row[W > 1 ? 2 : 1][kThreads / 64][8 * V];
 };
 
 template <int W, int V>
@@ -459,42 +459,47 @@ struct ChunkMaxState {
     int parity;
 };
 
-// Max over all chunk groups for each of the lane's V positions.  Every thread of the workgroup calls this; the state
-// matters for W > 1 only.
-template <int W, int V>
-__device__ __forceinline__ void across_chunks_max_wave(uint32_t (&m)[V], ChunkMaxState<W, V> &st)
+// m: the lane's max-abs at each of its V positions.  Returns the max over the 8 chunk groups of the wave at ONE of them,
+// position g = lane / 8 for V = 8 and g / 2 for V = 4: at every step a lane hands on half of what it has and takes the other
+// half of what its partner has (a permlane swap does both for two values).
+template <int V>
+__device__ __forceinline__ float scatter_max(const float (&m)[V])
 {
+    uint32_t a[V / 2], b[V / 4];
 #pragma unroll
-    for (int j = 0; j < V; ++j) {
-        uint32_t v = m[j];
-        v = umax(v, dpp_read<0x128>(v));                                    // row_ror:8: lane ^ 8 within a row of 16
-        auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);      // lane ^ 16
-        v = umax(a[0], a[1]);
-        auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);      // lane ^ 32
-        m[j] = umax(b[0], b[1]);
+    for (int j = 0; j < V / 2; ++j) {
+        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(m[j]), __float_as_uint(m[j + V / 2]), false, false);
+        a[j] = umax(r[0], r[1]);
     }
-    if (W > 1) {
-        const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-        const int at = (lane % 8) * V;
-        if (lane < 8) {
-            u32x4 *row = reinterpret_cast<u32x4 *>(&st.red.row[st.parity][wave][at]);
 #pragma unroll
-            for (int q = 0; q < V / 4; ++q) row[q] = u32x4{m[4 * q], m[4 * q + 1], m[4 * q + 2], m[4 * q + 3]};
+    for (int j = 0; j < V / 4; ++j) {
+        auto r = __builtin_amdgcn_permlane16_swap(a[j], a[j + V / 4], false, false);
+        b[j] = umax(r[0], r[1]);
+    }
+    if constexpr (V == 4) return __uint_as_float(umax(b[0], dpp_read<0x128>(b[0])));      // row_ror:8: lane ^ 8
+    const bool odd = (threadIdx.x & 8) != 0;
+    const uint32_t keep = odd ? b[V / 4 - 1] : b[0], give = odd ? b[0] : b[V / 4 - 1];
+    return __uint_as_float(umax(keep, dpp_read<0x128>(give)));
+}
+
+// The way back: every lane gets the values of its V positions from the lanes that have them.
+template <int V>
+__device__ __forceinline__ void gather_lanes(float v, float (&all)[V])
+{
+    const uint32_t own = __float_as_uint(v), other = dpp_read<0x128>(own);
+    const bool odd = (threadIdx.x & 8) != 0;
+    const uint32_t two[2] = {odd ? other : own, odd ? own : other};
+    constexpr int kEach = V / 4;        // 2, or 1: both lanes of a pair have the same position
+#pragma unroll
+    for (int i = 0; i < kEach; ++i) {
+        const uint32_t x = kEach == 2 ? two[i] : own;
+        auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            auto q = __builtin_amdgcn_permlane32_swap(r[k], r[k], false, false);
+            all[kEach * k + i] = __uint_as_float(q[0]);
+            all[kEach * k + i + V / 2] = __uint_as_float(q[1]);
         }
-        __syncthreads();
-#pragma unroll
-        for (int w = 1; w < W; ++w) {
-            const u32x4 *other = reinterpret_cast<const u32x4 *>(&st.red.row[st.parity][wave ^ w][at]);
-#pragma unroll
-            for (int q = 0; q < V / 4; ++q) {
-                const u32x4 a = other[q];
-                m[4 * q] = umax(m[4 * q], a.x);
-                m[4 * q + 1] = umax(m[4 * q + 1], a.y);
-                m[4 * q + 2] = umax(m[4 * q + 2], a.z);
-                m[4 * q + 3] = umax(m[4 * q + 3], a.w);
-            }
-        }
-        st.parity ^= 1;
     }
 }
 
@@ -521,7 +526,12 @@ __device__ __forceinline__ void load_strided(const uint16_t *x, const WaveSpot &
 {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        xv[r] = __builtin_nontemporal_load(reinterpret_cast<const Piece<V> *>(x + sp.elem + r * kWaveRow<W> + sp.at));
+        if constexpr (V == 8) {
+            xv[r] = load_row_bf16x8<kWaveRow<W>>(x + sp.elem, sp.at, r);
+        } else {
+            xv[r] = __builtin_bit_cast(Piece<V>, __builtin_amdgcn_raw_buffer_load_b64(bounded(x + sp.elem, kMinishardEnd), sp.at * 2,
+                                                                                      r * kWaveRow<W> * 2, kNonTemporal));
+        }
     }
 }
 
@@ -551,17 +561,28 @@ __device__ __forceinline__ void widen_strided(const Piece<V> (&xv)[R], float (&t
     for (int r = 0; r < R; ++r) widen_piece<V>(xv[r], t[r]);
 }
 
-// scale and inverse scale of the lane's V blocks for the sums t.
+// scale and inverse scale of the lane's V blocks for the sums t.  A lane works one pair out and gets the others.  Every
+// thread of the workgroup calls this; the state matters for W > 1 only.
 template <int R, int W, int V>
 __device__ __forceinline__ void strided_quotients(const float (&t)[R][V], ChunkMaxState<W, V> &st, float (&scale)[V],
                                                   float (&inv)[V])
 {
-    uint32_t m[V] = {};
+    float m[V] = {};
 #pragma unroll
-    for (int r = 0; r < R; ++r) note_absmax(t[r], m);
-    across_chunks_max_wave<W, V>(m, st);
+    for (int r = 0; r < R; ++r) fold_absmax(t[r], m);
+    float a = scatter_max(m);
+    if (W > 1) {
+        const int wave = threadIdx.x / 64, at = threadIdx.x % 8 * V + threadIdx.x % 64 / 8 * V / 8;
+        st.red.row[st.parity][wave][at] = a;
+        __syncthreads();
 #pragma unroll
-    for (int j = 0; j < V; ++j) block_quotients(__uint_as_float(m[j]), scale[j], inv[j]);
+        for (int w = 1; w < W; ++w) a = __builtin_fmaxf(a, st.red.row[st.parity][wave ^ w][at]);
+        st.parity ^= 1;
+    }
+    float own_scale, own_inv;
+    block_quotients(a, own_scale, own_inv);
+    gather_lanes(own_scale, scale);
+    gather_lanes(own_inv, inv);
 }
 
 // The code of v as a float.  kPositiveZero: a value that rounds to zero from below gives +0.0, as the integer
@@ -602,28 +623,37 @@ __device__ __forceinline__ void strided_send_into(const float (&t)[R][V], float 
     }
 }
 
-// Waves per SIMD the compiler may plan for.  The full loop with a quantized reduce-scatter runs 3-4 us faster (of
-// 63-75 at the 27B-shaped size) held to two waves than at the four its ~120 registers would allow: the loads of one
-// partial per wave already fill the memory queues, and more waves only lengthen them.  The semi-loop (two dependent
-// half chains) and the unquantized reduce-scatter measured the other way round and keep the default.
-// The small-message layout keeps the default, too.
-constexpr int strided_chain_waves(bool semi, bool rs, int V) { return (!semi && rs && V == 8) ? 2 : 8; }
-
+// kWaves: waves per SIMD the compiler may plan for.  Two, where the registers would allow three to five: the loads of one
+// partial per wave fill the memory queues as it is, and the fewer places of memory are read at once the better they stream.
+// Eight, no cap, for the small layouts, and where two waves per SIMD, 512 workgroups at a time, would leave a last round of
+// less than half for itself (launch_chain_strided).  Measured on MI355X, us, P = 8, full loop | semi-loop | reduce-scatter in
+// fp32, capped / not:
+//     32 chunks, 128 minishards    13.2/13.5 | 13.9/14.0 | 12.8/12.9
+//                160 (1.3 rounds)  18.9/16.6 | 19.6/17.0 | 18.3/16.6
+//                200 (1.6)         20.9/21.3 | 22.1/21.7 | 20.0/21.0
+//                256 (2)           24.1/23.8 | 25.0/24.0 | 23.7/23.7
+//                336 (2.6)         31.8/32.9 | 33.5/32.5 | 31.1/31.8
+//                400 (3.1)         38.8/37.2 | 40.1/37.2 | 38.8/37.0
+//                1000              88.5/91.6 | 90.4/92.8 | 88.4/94.5
+//     64 chunks, 144 (1.1)         29.6/31.3 |           | 28.9/29.7
+//                192 (1.5)         36.8/35.5 |           | 36.9/34.5
+//                336               60.5/65.8 |           | 60.6/62.7
+//     128 chunks, 170              68.5/73.6 |           | 68.1/72.2
 // chunks = 8 * W * R.  kSemi: the semi-loop with partials[0] as the owner (always a quantized reduce-scatter);
 // otherwise the full loop in array order with the reduce-scatter quantized (kRS) or added in plain fp32.  kAG: the
 // finished sum is quantized once more and dequantized; otherwise narrowed to bf16 directly.
 // Ring layout (Sec. 3): with per_shard > 0 the tensor is cut into shards of per_shard minishards and shard k ends
 // on device k: the full loop takes the partials in the order k+1, k+2, ..., k (mod P), the semi-loop has device k
 // as its owner and the devices k+1, k+2, ... around it.  per_shard == 0: array order everywhere.
-template <int R, int W, int V, bool kSemi, bool kRS, bool kAG>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, strided_chain_waves(kSemi, kRS, V))))
-void chain_strided_kernel(int P, int per_shard, Global<uint16_t> out, const PartialTable tab)
+template <int R, int W, int V, bool kSemi, bool kRS, bool kAG, int kWaves>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, kWaves)))
+void chain_strided_kernel(int P, int per_shard, Global<uint16_t> out, unsigned owned, const PartialTable tab)
 {
     static_assert(kRS || !kSemi, "the semi-loop is a quantized reduce-scatter");
     __shared__ __align__(16) ChunkMaxRows<W, V> red;
     ChunkMaxState<W, V> st{red, 0};
     constexpr int chunks = 8 * W * R;
-    const WaveSpot sp = wave_spot<W, V>(chunks);
+    const WaveSpot sp = wave_spot<W, V>(chunks, owned);
     // position i of the chain -> partial; `first` <= P and i < P, so one conditional subtraction wraps
     const int first = per_shard > 0 ? (int)(sp.minishard / (unsigned)per_shard) + (kSemi ? 0 : 1) : 0;
     const auto part = [&](int i) {
@@ -658,11 +688,13 @@ void chain_strided_kernel(int P, int per_shard, Global<uint16_t> out, const Part
         }
     } else {
         for (int i = 1; i < P; ++i) {
-            // With two waves per SIMD and two waves per piece the loop's time hangs on how its instructions lie on 8-byte
-            // boundaries: moved by 4 bytes by whatever stands before it, it takes up to 9 % longer (MI355X, 40 minishards of
-            // 128 chunks, P = 16: 42.1 us; 38.7 like this; 154 minishards 122.8 and 119.5).
-            if (kRS && W == 2 && V == 8) asm volatile(".p2align 3");
+            // With two waves per piece the partial is requested before anything else of the hop: left to the compiler, 160
+            // minishards of 128 chunks take 66.3 us instead of 64.7, P = 16 120.4 instead of 117.4 (176: 71.6 and 72.2, 128.6 and
+            // 129.2).  An earlier body of this loop took up to 9 % longer off 8-byte boundaries; this one does not care.
+            constexpr bool kRequestFirst = W == 2 && V == 8;
+            if (kRS && kRequestFirst) asm volatile(".p2align 3");
             load_strided<R, W, V>(part(i), sp, xv);
+            if (kRequestFirst) loads_first();
             if (kRS) {
                 strided_hop<R, W, V, !kAG>(sum, xv, st);
             } else {

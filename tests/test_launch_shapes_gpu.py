@@ -408,6 +408,19 @@ def test_strided_passes_by_lanes_and_owners(gpu, oracle, long_values, chunks, mi
     assert (gpu.host_u16(out) == _oracle_variant_strided(oracle, x, chunks, 0)).all()
 
 
+@pytest.mark.parametrize("chunks,minishards", ((32, 20), (32, 21), (32, 128), (32, 129), (32, 192), (32, 193), (64, 8), (64, 9),
+                                               (64, 41), (128, 6), (128, 7), (128, 48), (128, 49)))
+def test_strided_single_launch_layouts(gpu, oracle, long_values, chunks, minishards):  # noqa: F811
+    """Both sides of the lines between the layouts of the strided chain and its flavours."""
+    n, P = 1024 * chunks * minishards, 4
+    x = [np.resize(long_values[i % 3], n + i)[i:].copy() for i in range(P)]
+    dev = [gpu.dev_bf16(p) for p in x]
+    out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    for flags in (0, eq.AG_UNQUANTIZED, eq.RS_UNQUANTIZED, eq.SEMI_LOOP | eq.RING_ORDER):
+        eq.equarx_reduce_variant_strided(dev, chunks, flags, out.fill_(5.0))
+        assert (gpu.host_u16(out) == _oracle_variant_strided(oracle, x, chunks, flags)).all(), flags
+
+
 SMALL = 768 * 2048              # single-launch calls of few partials: up to here the batched kernel
 ALL_SINGLE = SINGLE + (eq.SEMI_LOOP | eq.RING_ORDER, eq.AG_UNQUANTIZED | eq.RING_ORDER, eq.RS_UNQUANTIZED)
 
