@@ -343,15 +343,18 @@ void launch_chain_as(const PartialTable &tab, int P, int64_t n, bool rs, bool ag
     ctx.launch2d(chain_kernel<B, S::T, S::K, RS, AG, WIRE>, g.x, g.y, S::T, P, n, g.shard_elems, out, wire_codes,        \
                  wire_scales, c_step, s_step, tab)
     if (rs && ag) {
-        if (wire_codes) {
-            EQUARX_CHAIN(true, true, true);
+        constexpr KeptWire kLong = wire_through_l2(S::T, S::K) ? kWireThroughL2 : kCachedWire;
+        if (!wire_codes) {
+            EQUARX_CHAIN(true, true, kNoWire);
+        } else if ((reinterpret_cast<uintptr_t>(wire_codes) | (uintptr_t)c_step) % 64 == 0) {
+            EQUARX_CHAIN(true, true, kLong);
         } else {
-            EQUARX_CHAIN(true, true, false);
+            EQUARX_CHAIN(true, true, kCachedWire);
         }
     } else if (rs) {
-        EQUARX_CHAIN(true, false, false);
+        EQUARX_CHAIN(true, false, kNoWire);
     } else {
-        EQUARX_CHAIN(false, true, false);
+        EQUARX_CHAIN(false, true, kNoWire);
     }
 #undef EQUARX_CHAIN
 }

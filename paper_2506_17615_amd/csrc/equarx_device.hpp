@@ -848,15 +848,38 @@ __device__ __forceinline__ void load_tiles_together(const uint16_t *p, int64_t w
     for (int k = 0; k < K; ++k) v[k] = whole_end(e[k], lane_at);
 }
 
+// What becomes of the wire in a single launch: it stays in registers, or the caller keeps it (cached stores, or through L2).
+enum KeptWire { kNoWire, kCachedWire, kWireThroughL2 };
+
+// From the shapes of 1024 threads or 4 tiles on, a kept wire is written through L2, as the output is (store_bf16x8): P rows of
+// codes pushed out of the L2s as they fall cost the partials' reads more than stores that go straight on.  Not if its rows
+// do not begin on 64-byte lines: then every wave's stores begin and end within one, and written through those are two writes.
+// Non-temporal stores would be better still while no buffer is found again, and worse where the caller's are.  Measured on
+// MI355X, us, cached -> through L2 -> non-temporal, with buffers in turn and with one wire for all calls:
+//     P = 2, 20 M elements, block 256     28.8 -> 29.1 -> 28.4     27.9 -> 27.0 -> 28.5
+//     5, 10 M, 64                         32.5 -> 31.7 -> 30.4     29.1 -> 28.4 -> 30.2
+//     8, 5.8 M, 256                       28.6 -> 28.8 -> 27.7     26.0 -> 26.0 -> 27.7
+//     8, 12 M, 32                         61.4 -> 58.4 -> 54.4     51.9 -> 50.4 -> 54.2
+//     8, 22 M, 256                       105.1 -> 99.6 -> 97.6     91.4 -> 88.9 -> 97.5
+//     8, 12,000,001, 256                  60.5 -> 66.5             51.2 -> 51.0       (rows 16 bytes off)
+//     16, 16 M, 128                        161 -> 151 -> 139        125 -> 121 -> 138
+// Shorter messages' shapes keep cached stores: P = 12, 4.7 M 36.9 -> 40.0 -> 34.7, P = 3, 3 M 7.9 -> 8.2 -> 8.0.
+constexpr bool wire_through_l2(int T, int K) { return T == 1024 || K == 4; }
+
 // Writes what the wire carries after a quantization of one tile (8 codes per
 // lane starting at element base + off): row `row` of the kept wire.
-template <int B, bool kFull>
+template <int B, bool kFull, KeptWire kWire>
 __device__ __forceinline__ void store_wire_tile(int8_t *__restrict__ wire_codes, float *__restrict__ wire_scales,
                                                 int64_t c_step, int64_t s_step, int row, int64_t base, int off,
                                                 int64_t n, const float (&r)[8], float s)
 {
     constexpr int G = B / kLaneElems;
-    store_i8x8(wire_codes + (int64_t)row * c_step, base, off, n, kFull, pack_codes(r));
+    int8_t *codes = wire_codes + (int64_t)row * c_step;
+    if (kWire == kWireThroughL2 && kFull) {
+        __builtin_amdgcn_raw_buffer_store_b64(pack_codes(r), bounded(codes + base, 0x7fffffff), off, 0, kThroughL2);
+    } else {
+        store_i8x8(codes, base, off, n, kFull, pack_codes(r));
+    }
     if ((threadIdx.x % G) == 0 && (kFull || base + off < n)) wire_scales[(int64_t)row * s_step + (base + off) / B] = s;
 }
 
@@ -875,7 +898,7 @@ __device__ __forceinline__ void store_narrowed_tile(uint16_t *out, int64_t base,
 
 // The last step of a chain for one tile: quantize the finished fp32 sum once
 // more and dequantize it (quantized all-gather, Sec. 3.4), or narrow it directly.
-template <int B, bool kAG, bool kWire, bool kFull>
+template <int B, bool kAG, KeptWire kWire, bool kFull>
 __device__ __forceinline__ void finish_tile(const float (&t)[8], uint16_t *out,
                                             int8_t *__restrict__ wire_codes, float *__restrict__ wire_scales,
                                             int64_t c_step, int64_t s_step, int row, int64_t base, int off, int64_t n,
@@ -885,13 +908,13 @@ __device__ __forceinline__ void finish_tile(const float (&t)[8], uint16_t *out,
     if (kAG) {
         float r[8], s;
         quantize_lane_f<G, true>(t, r, s);      // +0.0 codes: the product below shows the sign of a zero
-        if (kWire) store_wire_tile<B, kFull>(wire_codes, wire_scales, c_step, s_step, row, base, off, n, r, s);
+        if (kWire) store_wire_tile<B, kFull, kWire>(wire_codes, wire_scales, c_step, s_step, row, base, off, n, r, s);
         float d[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) d[j] = r[j] * s;
-        store_narrowed_tile<kFull, kWire>(out, base, off, n, d, cached);
+        store_narrowed_tile<kFull, kWire != kNoWire>(out, base, off, n, d, cached);
     } else {
-        store_narrowed_tile<kFull, kWire>(out, base, off, n, t, cached);
+        store_narrowed_tile<kFull, kWire != kNoWire>(out, base, off, n, t, cached);
     }
 }
 
@@ -973,7 +996,7 @@ __device__ __forceinline__ void tail_body(const int8_t *__restrict__ cin, const 
         widen_i8x8(cv[k], qf);
 #pragma unroll
         for (int j = 0; j < 8; ++j) t[j] = __builtin_fmaf(qf[j], sv[k], xf[j]);
-        finish_tile<B, kAG, false, kFull>(t, out, nullptr, nullptr, 0, 0, 0, wg_at + k * tile_elems<T>, lane_at, n);
+        finish_tile<B, kAG, kNoWire, kFull>(t, out, nullptr, nullptr, 0, 0, 0, wg_at + k * tile_elems<T>, lane_at, n);
     }
 }
 
@@ -1006,7 +1029,7 @@ __device__ __forceinline__ int ring_prev(int j, int P) { return j == 0 ? P - 1 :
 // quantized all-gather a -0.0 code can only flip the sign of zero sums along
 // the chain, which no max-abs, scale or integer code sees, and the last
 // quantization hands out +0.0 codes.
-template <int B, int T, int K, bool kRS, bool kWire, bool kPositiveZero, bool kFull>
+template <int B, int T, int K, bool kRS, KeptWire kWire, bool kPositiveZero, bool kFull>
 __device__ __forceinline__ void hop_tiles(float (&t)[K][8], const u32x4 (&x)[K], int8_t *__restrict__ wire_codes,
                                           float *__restrict__ wire_scales, int64_t c_step, int64_t s_step, int row,
                                           int64_t wg_at, int64_t n)
@@ -1019,7 +1042,7 @@ __device__ __forceinline__ void hop_tiles(float (&t)[K][8], const u32x4 (&x)[K],
             float r[8], s;
             quantize_lane_f<G, kPositiveZero>(t[k], r, s);
             if (kWire) {
-                store_wire_tile<B, kFull>(wire_codes, wire_scales, c_step, s_step, row,
+                store_wire_tile<B, kFull, kWire>(wire_codes, wire_scales, c_step, s_step, row,
                                           wg_at + k * tile_elems<T>, lane_at, n, r, s);
             }
             float xf[8];
@@ -1042,7 +1065,7 @@ __device__ __forceinline__ void hop_tiles(float (&t)[K][8], const u32x4 (&x)[K],
 // hop (or several) ahead was measured with four tiles per thread and is SLOWER
 // on MI355X (63 -> 67..72 us at the 27B-shaped size): the memory system is
 // saturated as it is, and more outstanding requests only lengthen its queues.
-template <int B, int T, int K, bool kRS, bool kAG, bool kWire, bool kFull>
+template <int B, int T, int K, bool kRS, bool kAG, KeptWire kWire, bool kFull>
 __device__ __forceinline__ void chain_body(const PartialTable &tab, int P, int rot, int64_t n,
                                            uint16_t *out, int8_t *__restrict__ wire_codes,
                                            float *__restrict__ wire_scales, int64_t c_step, int64_t s_step,
@@ -1219,7 +1242,7 @@ __device__ __forceinline__ Span workgroup_span(int64_t n, int64_t shard_elems, i
 //     block 256, AG in bf16   62.1 -> 61.1 (61.4)     93.9 ->  89.6 (91.5)    261.5 -> 244.3 (257.4)
 constexpr int chain_waves(int K) { return K == 4 ? 2 : 8; }
 
-template <int B, int T, int K, bool kRS, bool kAG, bool kWire>
+template <int B, int T, int K, bool kRS, bool kAG, KeptWire kWire>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(1, chain_waves(K))))
 void chain_kernel(int P, int64_t n, int64_t shard_elems, Global<uint16_t> out,
                   Global<int8_t> wire_codes,
@@ -1584,7 +1607,7 @@ __device__ __forceinline__ void semi_body(const PartialTable &tab, int P, int ro
         for (int c = 1; c < count; ++c) {
             j = dir == 0 ? ring_next(j, P) : ring_prev(j, P);
             load_tiles_together<T, K, kFull>(tab.x[j], wg_at, n, xv);
-            hop_tiles<B, T, K, true, false, !kAG, kFull>(t, xv, nullptr, nullptr, 0, 0, 0, wg_at, n);
+            hop_tiles<B, T, K, true, kNoWire, !kAG, kFull>(t, xv, nullptr, nullptr, 0, 0, 0, wg_at, n);
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -1598,7 +1621,7 @@ __device__ __forceinline__ void semi_body(const PartialTable &tab, int P, int ro
 
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        finish_tile<B, kAG, false, kFull>(own[k], out, nullptr, nullptr, 0, 0, 0, wg_at + k * tile_elems<T>, lane_at, n,
+        finish_tile<B, kAG, kNoWire, kFull>(own[k], out, nullptr, nullptr, 0, 0, 0, wg_at + k * tile_elems<T>, lane_at, n,
                                           cached);
     }
 }

@@ -421,6 +421,15 @@ def test_strided_single_launch_layouts(gpu, oracle, long_values, chunks, minisha
         assert (gpu.host_u16(out) == _oracle_variant_strided(oracle, x, chunks, flags)).all(), flags
 
 
+@pytest.mark.parametrize("n,P", ((6_300_032, 3), (6_300_033, 7), (20 * 2 ** 20 + 64, 4), (20 * 2 ** 20 + 80, 4)))
+def test_long_kept_wires(gpu, oracle, long_values, n, P):  # noqa: F811
+    """Rows of the kept wire on 64-byte lines and off them, in both of the shapes that write them through the L2s."""
+    x = [np.resize(long_values[i % 3], n + i)[i:].copy() for i in range(P)]
+    want, wc, ws = oracle.reduce_chain(x, 64, keep_wire=True)
+    got, c, s = gpu.gpu_chain_fused(x, 64)
+    assert (got == want).all() and (c == wc).all() and (s.view(np.uint32) == ws.view(np.uint32)).all()
+
+
 SMALL = 768 * 2048              # single-launch calls of few partials: up to here the batched kernel
 ALL_SINGLE = SINGLE + (eq.SEMI_LOOP | eq.RING_ORDER, eq.AG_UNQUANTIZED | eq.RING_ORDER, eq.RS_UNQUANTIZED)
 
