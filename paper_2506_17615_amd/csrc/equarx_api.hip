@@ -639,12 +639,15 @@ inline void with_slices(int64_t n, int32_t chunks, F f)
     }
 }
 
+// The places of a launch that go to the XCDs by whole minishards (minishard_part), for the wire that it writes or reads.
 template <typename S>
-inline unsigned strided_grid(int64_t n) { return (unsigned)(minishards_of(n, S::kChunks) * S::kParts); }
+inline unsigned strided_owned(int64_t n, const void *wire) { return owned_places<S::kChunks, S::kParts>(minishards_of(n, S::kChunks), wire); }
 
-// The places of a launch that go to the XCDs by whole minishards (minishard_part).
 template <typename S>
-inline unsigned strided_owned(int64_t n) { return owned_places<S::kChunks, S::kParts>(minishards_of(n, S::kChunks)); }
+inline unsigned strided_count(int64_t n) { return (unsigned)(minishards_of(n, S::kChunks) * S::kParts); }
+
+template <typename S>
+inline unsigned strided_grid(int64_t n, unsigned owned) { return strided_count<S>(n) + missing_minishards(owned) * S::kParts; }
 
 // The first workgroups of a grid, in whole groups of eight, that a launch takes in the opposite order (mirrored_place).
 inline unsigned strided_mirror(unsigned grid, bool backward) { return backward ? grid & ~7u : 0; }
@@ -686,7 +689,8 @@ void do_quantize_strided(int64_t n, int32_t chunks, int8_t *codes, float *scales
 {
     with_slices(n, chunks, [&](auto slices) {
         using S = decltype(slices);
-        ctx.launch(quantize_strided_kernel<S, Source...>, strided_grid<S>(n), kThreads, codes, scales, strided_owned<S>(n), src...);
+        const unsigned owned = strided_owned<S>(n, codes);
+        ctx.launch(quantize_strided_kernel<S, Source...>, strided_grid<S>(n, owned), kThreads, codes, scales, owned, src...);
     });
 }
 
@@ -696,9 +700,8 @@ void do_hop_strided(const int8_t *cin, const float *sin, int64_t n, int32_t chun
 {
     with_slices(n, chunks, [&](auto slices) {
         using S = decltype(slices);
-        const unsigned grid = strided_grid<S>(n);
-        ctx.launch(hop_strided_kernel<S, Source...>, grid, kThreads, cin, sin, cout, sout, strided_mirror(grid, backward),
-                   strided_owned<S>(n), src...);
+        const unsigned owned = strided_owned<S>(n, cout), grid = strided_grid<S>(n, owned);
+        ctx.launch(hop_strided_kernel<S, Source...>, grid, kThreads, cin, sin, cout, sout, strided_mirror(grid, backward), owned, src...);
     });
 }
 
@@ -708,9 +711,9 @@ void do_semi_step_strided(const WireBuffers &w, const PartialTable &tab, int P, 
 {
     with_slices(n, chunks, [&](auto slices) {
         using S = decltype(slices);
-        const unsigned count = strided_grid<S>(n);
-        ctx.launch(semi_step_strided_kernel<S>, 2 * whole_groups(count), kThreads, w.c[0], w.s[0], w.c[1], w.s[1], per_shard,
-                   ring_word(P, up, down), count, strided_owned<S>(n), backward, first, tab);
+        const unsigned count = strided_count<S>(n), owned0 = strided_owned<S>(n, w.c[0]), owned1 = strided_owned<S>(n, w.c[1]);
+        ctx.launch(semi_step_strided_kernel<S>, 2 * semi_step_half<S>(count, owned0, owned1), kThreads, w.c[0], w.s[0], w.c[1], w.s[1],
+                   per_shard, ring_word(P, up, down), count, owned0, owned1, (backward ? 1 : 0) | (first ? 2 : 0), tab);
     });
 }
 
@@ -725,9 +728,9 @@ void do_owner_strided(const StridedWires &in, int64_t n, int32_t chunks, uint16_
 {
     with_slices(n, chunks, [&](auto slices) {
         using S = decltype(slices);
-        const unsigned grid = strided_grid<S>(n);
+        const unsigned owned = strided_owned<S>(n, in.codes[1] ? in.codes[1] : in.codes[0]), grid = strided_grid<S>(n, owned);
         ctx.launch(owner_strided_kernel<S, kAG, Source...>, grid, kThreads, out, in.codes[0], in.scales[0], in.codes[1],
-                   in.scales[1], strided_mirror(grid, backward), strided_owned<S>(n), src...);
+                   in.scales[1], strided_mirror(grid, backward), owned, src...);
     });
 }
 
@@ -743,7 +746,7 @@ void launch_chain_strided_as(const PartialTable &tab, int P, int64_t minishards,
     // 117.9; 128 chunks, 64 25.2 -> 25.8, 45.5 -> 47.3, 100 42.5 -> 42.4, 78.5 -> 77.0, 160 63.5 -> 62.8, 122.5 -> 117.9, 256 102.6 -> 99.2.
     constexpr int kChunks = 8 * W * R;
     const bool own = V == 8 && ((kChunks == 32 && kWaves == 2) || (kChunks == 128 && minishards >= 96));
-    const unsigned owned = own ? owned_places<kChunks, wave_layout_wgs<W, V>>(minishards) : 0u;
+    const unsigned owned = own ? owned_places<kChunks, wave_layout_wgs<W, V>>(minishards, nullptr) : 0u;
 #define EQUARX_CHAIN(SEMI, RS, AG) \
     ctx.launch(chain_strided_kernel<R, W, V, SEMI, RS, AG, kWaves>, grid, kThreads, P, per_shard, out, owned, tab)
     if (semi && ag) EQUARX_CHAIN(true, true, true);
@@ -804,9 +807,9 @@ void launch_dequantize_strided(const int8_t *codes, const float *scales, int64_t
                                LaunchCtx &ctx, bool backward)
 {
     constexpr int kParts = kChunk * kChunks / (tile_elems<T> * K);
-    const unsigned grid = (unsigned)(minishards * kParts);
-    ctx.launch(dequantize_strided_kernel<kChunks, T, K>, grid, T, codes, scales, out, strided_mirror(grid, backward),
-               owned_places<kChunks, kParts>(minishards));
+    const unsigned owned = owned_places<kChunks, kParts>(minishards, codes);
+    const unsigned grid = (unsigned)(minishards * kParts) + missing_minishards(owned) * kParts;
+    ctx.launch(dequantize_strided_kernel<kChunks, T, K>, grid, T, codes, scales, out, strided_mirror(grid, backward), owned);
 }
 
 // 256 threads x 4 tiles, where a lane reads its scales once for 32 elements; 2 while that leaves CUs without work.  Measured on

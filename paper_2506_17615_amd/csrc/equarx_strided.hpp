@@ -53,7 +53,9 @@ __host__ __device__ inline unsigned whole_groups(unsigned count) { return (count
 // Which minishard, and which of its kParts equal parts, the workgroup at place `at` of a launch takes.  The first places
 // go to the XCDs in runs of 2^18 elements, whole minishards, the parts of each one after the other; those that follow,
 // fewer than 8 runs, count the parts of one minishard after another.  `owned`: the number of the first, a multiple of 8
-// kParts runs, and the logarithm of the run's minishards in its low two bits.
+// kParts runs; in its low two bits the logarithm of the run's minishards, and in the three above by how many minishards the
+// first run is shorter, so that runs begin where the wire's address is a multiple of 2^18 (as nearly as minishards allow).
+// The places of what is missing there are for minishards below 0 (strided_spot's `outside`).
 //
 // So a minishard is on one XCD in every launch, also in the dequantization, which takes consecutive elements: each finds
 // the wire in the L2 that holds it.  With the parts of a minishard on four XCDs the dequantization did not.  Runs, because
@@ -64,30 +66,35 @@ __host__ __device__ inline unsigned whole_groups(unsigned count) { return (count
 // 2^17 101.7, of 2^18 91.1.  A contiguous eighth of the tensor to an XCD is as good in the hops and worse without any (P = 2,
 // 35.7 M: 51.3, runs 50.9, four XCDs 49.2).
 struct MinishardPart {
-    unsigned minishard;
+    int minishard;
     int part;
 };
+
+__host__ __device__ inline unsigned missing_minishards(unsigned owned) { return owned >> 2 & 7u; }
 
 template <int kParts>
 __device__ __forceinline__ MinishardPart minishard_part(unsigned at, unsigned owned)
 {
-    static_assert(kParts >= 4, "two bits to spare");
-    const unsigned run = owned & 3u;
-    if (at >= (owned & ~3u)) return MinishardPart{at / kParts, (int)(at % kParts)};
+    static_assert(kParts % 4 == 0, "five bits to spare");
+    const unsigned run = owned & 3u, missing = missing_minishards(owned);
+    if (at >= (owned & ~31u)) return MinishardPart{(int)(at / kParts - missing), (int)(at % kParts)};
     const unsigned in_xcd = at / 8, in_run = in_xcd & ((kParts << run) - 1), group = in_xcd / kParts >> run;
-    return MinishardPart{(group * 8 + at % 8 << run) + in_run / kParts, (int)(in_run % kParts)};
+    return MinishardPart{(int)((group * 8 + at % 8 << run) + in_run / kParts - missing), (int)(in_run % kParts)};
 }
 
 template <int kChunks, int kParts>
-inline unsigned owned_places(int64_t minishards)
+inline unsigned owned_places(int64_t minishards, const void *wire)
 {
+    constexpr int kLen = kChunk * kChunks;
     int run = kChunks == 32 ? 3 : kChunks == 64 ? 2 : 1;
     while (run > 0 && minishards < (int64_t)8 << run) --run;
-    return ((unsigned)(minishards >> (3 + run) << (3 + run)) * kParts) | run;
+    const unsigned missing = (unsigned)((reinterpret_cast<uintptr_t>(wire) + kLen / 2) / kLen) & ((1u << run) - 1);
+    return ((unsigned)((minishards + missing) >> (3 + run) << (3 + run)) * kParts) | missing << 2 | run;
 }
 
 struct StridedSpot {
-    unsigned minishard; // which minishard the workgroup works on
+    bool outside;       // nothing to do here
+    int minishard;      // which minishard the workgroup works on
     int64_t elem;       // first element of the slice in the first chunk of its minishard
     int64_t scale;      // index of the slice's first scale
     int at, pos;        // the lane's first element, from there, in the first of its chunks; its first position
@@ -99,6 +106,7 @@ __device__ __forceinline__ StridedSpot strided_spot(unsigned at, unsigned owned)
 {
     StridedSpot sp;
     const MinishardPart slice = minishard_part<S::kParts>(at, owned);
+    sp.outside = slice.minishard < 0;
     sp.minishard = slice.minishard;
     sp.elem = (int64_t)slice.minishard * (kChunk * S::kChunks) + slice.part * S::kPos;
     sp.scale = (int64_t)slice.minishard * kChunk + slice.part * S::kPos;
@@ -148,12 +156,12 @@ __device__ __forceinline__ void store_row_bf16x8(uint16_t *base, int at, int r, 
 // ring step on every shard at once, the partial of device (k + offset) mod P for the workgroups of shard k, 0 <= offset < P.
 // `ring`: P, and the offset from bit 8 on.  One tensor's address is in scalar registers when a wave starts; a table has to
 // be asked first.
-__device__ __forceinline__ const uint16_t *strided_source(unsigned, Global<const uint16_t> x) { return x; }
+__device__ __forceinline__ const uint16_t *strided_source(int, Global<const uint16_t> x) { return x; }
 
-__device__ __forceinline__ const uint16_t *strided_source(unsigned minishard, int per_shard, int ring, const PartialTable &tab)
+__device__ __forceinline__ const uint16_t *strided_source(int minishard, int per_shard, int ring, const PartialTable &tab)
 {
     const int P = ring & 255;
-    const int j = (per_shard > 0 ? (int)(minishard / (unsigned)per_shard) : 0) + (ring >> 8 & 255);     // < 2P
+    const int j = (per_shard > 0 ? (int)((unsigned)minishard / (unsigned)per_shard) : 0) + (ring >> 8 & 255);     // < 2P
     return tab.x[j >= P ? j - P : j];
 }
 
@@ -255,6 +263,7 @@ __global__ __launch_bounds__(kThreads) void quantize_strided_kernel(Global<int8_
 {
     __shared__ __align__(16) SliceQuotients<S> q;
     const StridedSpot sp = strided_spot<S>(blockIdx.x, owned);
+    if (sp.outside) return;             // uniform over the workgroup
     quantize_strided_body<S>(strided_source(sp.minishard, src...), codes, scales, sp, q);
 }
 
@@ -292,30 +301,39 @@ __global__ __launch_bounds__(kThreads) void hop_strided_kernel(Global<const int8
 {
     __shared__ __align__(16) SliceQuotients<S> q;
     const StridedSpot sp = strided_spot<S>(mirrored_place(blockIdx.x, mirror), owned);
+    if (sp.outside) return;             // uniform over the workgroup
     hop_strided_body<S>(cin, sin, strided_source(sp.minishard, src...), cout, sout, sp, q);
 }
 
 // One iteration of the semi-loop reduce-scatter (Sec. 3.3) on both of its chains at once: the first half of the grid
-// (`count` workgroups, in whole groups of eight) advances the chain that walks up from device h+1, the second the one that
+// (`count` workgroups and those of missing minishards, in whole groups of eight) advances the chain that walks up from device h+1, the second the one that
 // walks down from device h, each by one device -- the first iteration quantizes the chain's first shard, the later ones are
 // hops on the chain's own wire buffer in place.  The two halves share nothing.  `ring`: as in strided_source, the second
 // direction's offset from bit 16 on.
 template <typename S>
+__host__ __device__ inline unsigned semi_step_half(unsigned count, unsigned owned0, unsigned owned1)
+{
+    const unsigned a = missing_minishards(owned0), b = missing_minishards(owned1);
+    return whole_groups(count + (a > b ? a : b) * S::kParts);
+}
+
+// backward_first: bit 0, the launch walks back; bit 1, it is the first iteration.
+template <typename S>
 __global__ __launch_bounds__(kThreads) void semi_step_strided_kernel(Global<int8_t> codes0, Global<float> scales0, Global<int8_t> codes1,
                                                                      Global<float> scales1, int per_shard, int ring, unsigned count,
-                                                                     unsigned owned, int backward, int first, const PartialTable tab)
+                                                                     unsigned owned0, unsigned owned1, int backward_first, const PartialTable tab)
 {
     __shared__ __align__(16) SliceQuotients<S> q;
-    const unsigned half = whole_groups(count);
-    const unsigned place = mirrored_place(blockIdx.x, backward ? 2 * half : 0);
+    const unsigned half = semi_step_half<S>(count, owned0, owned1);
+    const unsigned place = mirrored_place(blockIdx.x, backward_first & 1 ? 2 * half : 0);
     const bool second = place >= half;
-    const unsigned at = second ? place - half : place;
-    if (at >= count) return;            // uniform over the workgroup
+    const unsigned at = second ? place - half : place, owned = second ? owned1 : owned0;
     const StridedSpot sp = strided_spot<S>(at, owned);
+    if (sp.outside || at >= count + missing_minishards(owned) * S::kParts) return;      // uniform over the workgroup
     int8_t *codes = second ? codes1 : codes0;
     float *scales = second ? scales1 : scales0;
     const uint16_t *x = strided_source(sp.minishard, per_shard, second ? ring >> 8 & ~255 | (ring & 255) : ring, tab);
-    if (first) {                        // uniform over the workgroup
+    if (backward_first & 2) {           // uniform over the workgroup
         quantize_strided_body<S>(x, codes, scales, sp, q);
     } else {
         hop_strided_body<S>(codes, scales, x, codes, scales, sp, q);
@@ -334,6 +352,7 @@ __global__ __launch_bounds__(kThreads) void owner_strided_kernel(Global<uint16_t
 {
     __shared__ __align__(16) SliceQuotients<S> q;
     const StridedSpot sp = strided_spot<S>(mirrored_place(blockIdx.x, mirror), owned);
+    if (sp.outside) return;             // uniform over the workgroup
     const uint16_t *own = strided_source(sp.minishard, src...);
 
     float acc[S::R][8];
@@ -730,6 +749,7 @@ __global__ __launch_bounds__(T) void dequantize_strided_kernel(Global<const int8
     static_assert(tile_elems<T> % kChunk == 0 && kChunk * kChunks % (tile_elems<T> * K) == 0, "whole chunks");
     constexpr int kParts = kChunk * kChunks / (tile_elems<T> * K);
     const MinishardPart place = minishard_part<kParts>(mirrored_place(blockIdx.x, mirror), owned);
+    if (place.minishard < 0) return;    // uniform over the workgroup
     const int lane_at = threadIdx.x * kLaneElems;
     const int64_t at = (int64_t)place.minishard * (kChunk * kChunks) + place.part * (tile_elems<T> * K);
     u32x2 cv[K];

@@ -400,8 +400,10 @@ def test_strided_passes_by_lanes_and_owners(gpu, oracle, long_values, chunks, mi
     wc, ws = oracle.hop_strided(wc, ws, x[1], chunks)
     assert (c.cpu().numpy() == wc).all() and (_bits(s) == ws.view(np.uint32)).all()
     out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
-    for flags in (0, eq.SEMI_LOOP | eq.RING_ORDER, eq.RING_ORDER | eq.AG_UNQUANTIZED):
-        work = eq.alloc_variant_workspace(flags & ~eq.RING_ORDER, P, n, chunks)
+    for flags, moved in ((0, 0), (0, 5 << 16), (eq.SEMI_LOOP, 3 << 16 | 256), (eq.SEMI_LOOP | eq.RING_ORDER, 0),
+                         (eq.RING_ORDER | eq.AG_UNQUANTIZED, 7 << 15)):      # where in memory the wires begin
+        work = torch.empty(2 ** 20 + 4 * n, dtype=torch.uint8, device="cuda")
+        work = work[-work.data_ptr() % 2 ** 18 + moved:][:eq.alloc_variant_workspace(flags & ~eq.RING_ORDER, P, n, chunks).numel()]
         eq.equarx_reduce_variant_hops_strided(dev, chunks, flags, out.fill_(5.0), work)
         assert (gpu.host_u16(out) == _oracle_variant_strided(oracle, x, chunks, flags)).all(), flags
     eq.equarx_reduce_quantized_strided(dev, chunks, out.fill_(5.0), eq.alloc_workspace(P, n, chunks))
