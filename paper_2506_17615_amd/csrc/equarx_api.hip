@@ -671,7 +671,26 @@ struct StridedSource {
 
 inline Global<const uint16_t> one_tensor(const void *x) { return static_cast<const uint16_t *>(x); }
 
-inline int ring_word(int P, int offset, int second = 0) { return P | offset << 8 | second << 16; }
+// floor(m / d) = umulhi(2 m, magic) >> shift for all m < 2^30: magic = ceil(2^(32 + shift) / (2 d)) with 2^shift <= 2 d <
+// 2^(shift + 1) is off by less than a part in 2^31.  (2 d a power of two would need 2^32: half of that, and one bit less.)
+struct RingDivision {
+    unsigned magic, shift;
+};
+
+inline RingDivision ring_division(int d)
+{
+    if (d <= 0) return {0, 0};      // array order: every minishard in shard 0
+    const uint64_t twice = 2 * (uint64_t)d;
+    unsigned shift = 0;
+    while (twice >> (shift + 1)) ++shift;
+    if ((twice & (twice - 1)) == 0) return {1u << 31, shift - 1};
+    return {(unsigned)(((((uint64_t)1 << (32 + shift)) + twice - 1)) / twice), shift};
+}
+
+inline unsigned ring_word(int P, unsigned shift, int offset, int second = 0)
+{
+    return (unsigned)P | (unsigned)offset << 8 | (unsigned)second << 16 | shift << 24;
+}
 
 // f(the source as a kernel takes it): see strided_source.
 template <typename F>
@@ -680,7 +699,8 @@ inline void with_source(const StridedSource &src, F f)
     if (src.per_shard == 0) {
         f(Global<const uint16_t>(src.tab.x[src.offset]));
     } else {
-        f(src.per_shard, ring_word(src.P, src.offset), src.tab);
+        const RingDivision by = ring_division(src.per_shard);
+        f(by.magic, ring_word(src.P, by.shift, src.offset), src.tab);
     }
 }
 
@@ -709,11 +729,12 @@ void do_hop_strided(const int8_t *cin, const float *sin, int64_t n, int32_t chun
 void do_semi_step_strided(const WireBuffers &w, const PartialTable &tab, int P, int per_shard, int up, int down, bool first, int64_t n,
                           int32_t chunks, LaunchCtx &ctx, bool backward)
 {
+    const RingDivision by = ring_division(per_shard);
     with_slices(n, chunks, [&](auto slices) {
         using S = decltype(slices);
         const unsigned count = strided_count<S>(n), owned0 = strided_owned<S>(n, w.c[0]), owned1 = strided_owned<S>(n, w.c[1]);
         ctx.launch(semi_step_strided_kernel<S>, 2 * semi_step_half<S>(count, owned0, owned1), kThreads, w.c[0], w.s[0], w.c[1], w.s[1],
-                   per_shard, ring_word(P, up, down), count, owned0, owned1, (backward ? 1 : 0) | (first ? 2 : 0), tab);
+                   by.magic, ring_word(P, by.shift, up, down), count, owned0, owned1, (backward ? 1 : 0) | (first ? 2 : 0), tab);
     });
 }
 
