@@ -426,7 +426,7 @@ __device__ __forceinline__ void store_i8x8(int8_t *p, int64_t base, int off, int
 // The output of chain_kernel and semi_kernel is, for full workgroups, either streamed (non-temporal, straight to memory)
 // or cached: written through L2 (sc0 sc1) so that it stays in the 256 MB Infinity Cache, where the next kernel that reads
 // it, or the next call that writes the same buffer, finds it; worth it while the output is a modest part of that cache.
-// small_kernel, the strided chain (cached 64.6 us instead of 63.9 at the 27B shape) and the end of a message stream.
+// small_kernel, the strided chain (cached 1 % slower at the 27B shape) and the end of a message stream.
 // Measured on MI355X, P = 8, us streamed -> cached: three output buffers in turn 23.0 -> 22.6 (7.9 M elements), 61.8 -> 60.1
 // (22 M), 96.4 -> 92.3 (33.5 M), 131.4 -> 125.8 (44 M), 176.9 -> 182.4 (60 M); nine in turn, so that none is found
 // again, 23.4 -> 23.0, 62.5 -> 62.5, 97.0 -> 96.2, 132.0 -> 132.3, 179.0 -> 181.4.
