@@ -268,6 +268,48 @@ def test_non_finite_inputs_do_not_fault_and_stay_in_their_block(gpu, oracle):
     assert (out[keep] == oo[keep]).all() and (wc[:, keep] == owc[:, keep]).all() and (ws[:, clean] == ows[:, clean]).all()
 
 
+@pytest.mark.parametrize("chunks,minishards", ((32, 9), (32, 24), (32, 192), (64, 8), (64, 20), (64, 128), (128, 6), (128, 18),
+                                               (128, 49)))
+def test_a_nan_fills_its_block_of_the_strided_geometry(gpu, oracle, chunks, minishards):
+    """In every layout, hop by hop and in one launch: no element of the block is finite, every other block matches."""
+    n, P = 1024 * chunks * minishards, 3
+    rng = np.random.default_rng(chunks + minishards)
+    x = [gpu.bf16_of(rng.standard_normal(n, dtype=np.float32)) for _ in range(P)]
+    filled = np.zeros((P, minishards, 1024), bool)
+    for k, e in enumerate(rng.choice(n, 48 * P, replace=False)):
+        x[k % P][e] = (0x7FC0, 0xFFC0, 0x7F81)[k % 7 % 3]
+        filled[k % P, e // (1024 * chunks), e % 1024] = True
+    dev = [gpu.dev_bf16(p) for p in x]
+
+    def holds(got, want, blocks):
+        """got, want: an element, or a scale, per position of a minishard."""
+        blocks = np.broadcast_to(blocks[:, None], (minishards, got.size // blocks.size, 1024)).reshape(-1)
+        assert np.isnan(got[blocks]).all() and (got[~blocks].view(np.uint32) == want[~blocks].view(np.uint32)).all()
+
+    c, s = torch.empty(n, dtype=torch.int8, device="cuda"), torch.empty(n // chunks, device="cuda")
+    eq.equarx_quantize_strided(dev[0], chunks, c, s)
+    wc, ws = oracle.quantize_bf16_strided(x[0], chunks)
+    holds(s.cpu().numpy(), ws, filled[0])
+    eq.equarx_reduce_stage_strided(c, s, dev[1], chunks, c, s)
+    wc, ws = oracle.hop_strided(wc, ws, x[1], chunks)
+    holds(s.cpu().numpy(), ws, filled[0] | filled[1])
+
+    def widened(u16):
+        return (u16.astype(np.uint32) << 16).view(np.float32)
+
+    out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    for flags in (0, eq.RING_ORDER, eq.SEMI_LOOP, eq.SEMI_LOOP | eq.RING_ORDER, eq.RS_UNQUANTIZED):
+        want = widened(_oracle_variant_strided(oracle, x, chunks, flags))
+        eq.equarx_reduce_variant_strided(dev, chunks, flags, out.fill_(5.0))
+        holds(widened(gpu.host_u16(out)), want, filled.any(axis=0))
+        if flags != eq.RS_UNQUANTIZED:
+            work = eq.alloc_variant_workspace(flags & ~eq.RING_ORDER, P, n, chunks)
+            eq.equarx_reduce_variant_hops_strided(dev, chunks, flags, out.fill_(5.0), work)
+            holds(widened(gpu.host_u16(out)), want, filled.any(axis=0))
+    eq.equarx_reduce_quantized_strided(dev, chunks, out.fill_(5.0), eq.alloc_workspace(P, n, chunks))
+    holds(widened(gpu.host_u16(out)), widened(_oracle_variant_strided(oracle, x, chunks, 0)), filled.any(axis=0))
+
+
 def test_bad_arguments_raise(gpu):
     x = torch.zeros(4096, dtype=torch.bfloat16, device="cuda")
     c = torch.zeros(4096, dtype=torch.int8, device="cuda")
