@@ -616,7 +616,10 @@ inline int64_t minishards_of(int64_t n, int32_t chunks) { return n / ((int64_t)k
 //     544           97.3/97.2        91.7/93.7         176.7/177.8      178.3/176.6
 // What they replace (32 lanes, every value computed twice, and up to 16 minishards the chain's layout, which is 8 lanes) took
 // 22.8, 27.5, 30.6 | 37.5, 44.7, 65.3 | 81.7, 98.2, 117.7 us for 1, 8, 16 | 24, 64, 128 | 192, 256, 320 minishards of 64 chunks.
-// f(layout) with the layout of the per-pass kernels.
+// From 2^35 elements on a minishard of 64 chunks takes 32 lanes whatever the rounds: half as many workgroups, because a launch
+// holds fewer than 2^32 threads, and with 16 lanes a step of the semi-loop had that many at 2^36 elements, which the card's
+// memory holds if the partials are one tensor.  (128 chunks reach it at 2^37, where the wires alone take 2^38 bytes and a
+// partial as much again: no card of 288 GiB holds them.)
 template <typename F>
 inline void with_slices(int64_t n, int32_t chunks, F f)
 {
@@ -628,7 +631,7 @@ inline void with_slices(int64_t n, int32_t chunks, F f)
             break;
         case 64:
             if (ms <= 16) f(Slices<64, 8>{});
-            else if (ms < 128 || (4 * ms - 1) % 256 < 128) f(Slices<64, 16>{});
+            else if (ms < 128 || ((4 * ms - 1) % 256 < 128 && n < (int64_t)1 << 35)) f(Slices<64, 16>{});
             else f(Slices<64, 32>{});
             break;
         case 128:
