@@ -781,6 +781,40 @@ void launch_chain_strided_as(const PartialTable &tab, int P, int64_t minishards,
 #undef EQUARX_CHAIN
 }
 
+// Which reduce-scatters in fp32 of `wgs` workgroups are sum_strided_kernel's: between one and one and a half rounds of the chip
+// at two workgroups per CU, where the chain's kernel is left with a round that is half empty, and for two partials, where there
+// is one addition in all, up to two.  Measured on MI355X, us, chain's kernel / this one:
+//     chunks, minishards (rounds)   P = 2          3             4             6             8             16
+//     32, 128 (1)                 5.50/4.46
+//         160 (1.25)              5.90/5.68    7.88/7.89    9.47/9.97    13.0/13.3      16.6/16.7     28.9/29.1
+//         192 (1.5)               6.68/7.05
+//         200 (1.6)               8.30/7.28   10.32/9.83   12.30/12.35   16.25/16.21     20.1/20.7     35.5/36.7
+//         224 (1.75)              9.03/8.95                13.03/13.98
+//         256 (2)                 9.94/8.70   12.33/11.45  14.75/14.45   19.31/18.67     24.0/24.6     42.5/42.2
+//         336 (2.6)               12.5/12.2    15.7/15.8    19.0/19.3     25.4/26.5      31.6/32.5     56.7/63.7
+//     64, 112 (0.9)               8.18/8.02    10.3/10.2    12.8/12.7     17.1/16.9      21.1/21.5     39.2/37.7
+//         132 (1.03)              10.4/10.2    13.6/        17.3/         23.5/21.7      29.9/27.6     52.9/49.3
+//         144 (1.1)               10.5/11.0    13.9/13.9    17.0/17.0     23.6/22.8      30.2/28.6     57.7/53.3
+//         160 (1.25)              11.4/11.3    14.6/15.1    17.9/18.1     24.4/24.1      31.6/30.5     60.2/55.1
+//         176 (1.4)               12.6/11.9    15.7/16.1    19.1/19.6     26.4/26.7      32.8/32.6     64.0/61.6
+//         192 (1.5)               13.3/12.4    16.7/15.8    20.5/21.0     28.3/28.0      36.1/35.6     64.0/61.6
+//         200 (1.6)               14.5/14.7    19.3/19.9    23.6/24.9     30.8/31.9      40.8/42.8     76.1/79.0
+//     128, 56 (0.9)               8.41/7.90                                                            41.4/39.4
+//         64 (1)                  9.24/8.48    11.6/11.6    14.0/14.8     18.9/19.7      24.0/24.4     43.3/43.3
+//         72 (1.1)                11.4/11.4    15.0/14.8    18.1/18.0     24.9/24.5      32.0/31.1     59.4/56.9
+//         96 (1.5)                14.6/13.0    18.0/17.4    22.0/21.7     30.6/29.2      38.0/35.8     68.6/67.7
+//         112 (1.75)              17.2/16.9    21.6/22.2    26.5/27.6     36.8/36.6      46.3/47.8     84.9/88.9
+//         128 (2)                 19.1/18.2    23.4/24.2    29.5/28.9     40.1/40.6      50.5/49.5     93.2/89.8
+inline bool sums_apart(int32_t chunks, int64_t wgs, int P)
+{
+    switch (chunks) {
+        case 32: return wgs <= 1024 && ((P <= 3 && wgs > 768) || (P == 2 && wgs >= 512 && wgs <= 640));
+        case 64: return wgs <= 768 && (P == 2 ? wgs > 640 : P >= 6 ? wgs > 512 : P >= 4 && wgs > 512 && wgs <= 544);
+        case 128: return wgs > (P == 2 || P > 8 ? 384 : 512) && wgs <= (P == 2 ? 1024 : 768);
+        default: return false;
+    }
+}
+
 // Few minishards take layouts whose waves have an eighth, a quarter or half of the work, so that every CU has some; where
 // those are a round of the chip, the largest, which does least in all, is faster.  Measured on MI355X, us (GPU time of
 // captured calls), full loop of P = 8, chunks = 8 W R as R x W x V:
@@ -803,6 +837,14 @@ void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chu
     const int64_t wgs = ms * wave_layout_wgs<1, 8>;
     // see chain_strided_kernel's kWaves
     const bool short_round = wgs > 512 && wgs < 2048 && (wgs - 1) % 512 < 256, half_round = !rs && wgs > 640 && wgs <= 768;
+    if (!rs && sums_apart(chunks, chunks == 128 ? 2 * wgs : wgs, P)) {
+#define EQUARX_SUM(R, W) ctx.launch(sum_strided_kernel<R, W>, (unsigned)(ms * wave_layout_wgs<W, 8>), kThreads, P, per_shard, out, tab)
+        if (chunks == 32) EQUARX_SUM(4, 1);
+        else if (chunks == 64) EQUARX_SUM(8, 1);
+        else EQUARX_SUM(8, 2);
+#undef EQUARX_SUM
+        return;
+    }
 #define EQUARX_LAYOUT(...) launch_chain_strided_as<__VA_ARGS__>(tab, P, ms, per_shard, semi, rs, ag, out, ctx)
     switch (chunks) {
         case 32:

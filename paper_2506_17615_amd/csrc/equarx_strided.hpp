@@ -756,6 +756,104 @@ void chain_strided_kernel(int P, int per_shard, Global<uint16_t> out, unsigned o
     }
 }
 
+// The quotients of the lane's V blocks with every lane working out all of them, in exchanges that do not wait for one another:
+// more instructions than strided_quotients and, for one send in all, less time.
+template <int R, int W, int V>
+__device__ __forceinline__ void quotients_in_every_lane(const float (&t)[R][V], ChunkMaxRows<W, V> &red, float (&scale)[V], float (&inv)[V])
+{
+    float m[V];
+    absmax_of_rows(t, m);
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        uint32_t v = __float_as_uint(m[j]);
+        v = umax(v, dpp_read<0x128>(v));                                    // row_ror:8: lane ^ 8
+        auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        v = umax(a[0], a[1]);
+        auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        m[j] = __uint_as_float(umax(b[0], b[1]));
+    }
+    if (W > 1) {
+        const int wave = threadIdx.x / 64, at = threadIdx.x % 8 * V;
+        if (threadIdx.x % 64 < 8) {
+#pragma unroll
+            for (int j = 0; j < V; ++j) red.row[0][wave][at + j] = m[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 1; w < W; ++w) {
+#pragma unroll
+            for (int j = 0; j < V; ++j) m[j] = larger(m[j], red.row[0][wave ^ w][at + j]);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < V; ++j) block_quotients(m[j], scale[j], inv[j]);
+}
+
+// chain_strided_kernel's reduce-scatter in fp32 for the sizes at which that kernel is slower (sums_apart): the partials are
+// added and the sum is quantized once.  What bounds it is how the partials stream.  With eight rows a wave asks for two,
+// waits for the first and then asks for the other six, so that less of a partial is requested at once; addresses are 64 bits
+// per row, which spreads the requests; nothing limits the waves per SIMD.  Measured on MI355X, us, chain_strided_kernel -> this,
+// P = 2, 8 and 16: 64 chunks, 192 minishards 13.3, 36.1, 64.0 -> 12.4, 35.6, 61.6; 128 chunks, 96 14.6, 38.0, 68.6 -> 13.0, 35.8,
+// 67.7; P = 8 and 16, 64 chunks, 132 29.9, 52.9 -> 27.6, 49.3; P = 2, 32 chunks, 256 9.9 -> 8.7, 128 chunks, 64 9.2 -> 8.5.  With buffer
+// loads, all rows at once or the quotients handed round, at most half of that.
+template <int R, int W>
+__global__ __launch_bounds__(kThreads) void sum_strided_kernel(int P, int per_shard, Global<uint16_t> out, const PartialTable tab)
+{
+    constexpr int V = 8;
+    __shared__ __align__(16) ChunkMaxRows<W, V> red;
+    const WaveSpot sp = wave_spot<W, V>(8 * W * R, 0u);
+    const int first = per_shard > 0 ? (int)(sp.minishard / (unsigned)per_shard) + 1 : 0;       // as in chain_strided_kernel
+    const auto part = [&](int i) {
+        const int j = first + i;
+        return tab.x[j >= P ? j - P : j];
+    };
+    const int64_t at = sp.elem + sp.at;
+
+    float sum[R][V];
+    Piece<V> xv[R];
+    const auto request = [&](const uint16_t *x, int r) {
+        xv[r] = __builtin_nontemporal_load(reinterpret_cast<const Piece<V> *>(x + at + r * kWaveRow<W>));
+    };
+    const auto add = [&](int r) {
+        float xf[V];
+        widen_piece<V>(xv[r], xf);
+#pragma unroll
+        for (int j = 0; j < V; ++j) sum[r][j] = sum[r][j] + xf[j];
+    };
+    {
+        const uint16_t *x = part(0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) request(x, r);
+        widen_strided<R, V>(xv, sum);
+    }
+    for (int i = 1; i < P; ++i) {
+        constexpr int kAhead = R == 8 ? 2 : R;
+        const uint16_t *x = part(i);
+#pragma unroll
+        for (int r = 0; r < kAhead; ++r) request(x, r);
+        if (kAhead < R) {
+            __builtin_amdgcn_sched_barrier(0);
+            add(0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int r = kAhead; r < R; ++r) request(x, r);
+        if (kAhead < R) loads_first();
+#pragma unroll
+        for (int r = kAhead < R ? 1 : 0; r < R; ++r) add(r);
+    }
+
+    float scale[V], inv[V];
+    quotients_in_every_lane<R, W, V>(sum, red, scale, inv);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        float d[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) d[j] = code_of<true>(sum[r][j], inv[j]) * scale[j];
+        store_piece<V>(out + at + r * kWaveRow<W>, d);
+    }
+}
+
 // Dequantize in the strided geometry: element e uses scale (e / (1024*chunks)) * 1024 + e % 1024, so the 8 elements of a
 // lane use 8 consecutive scales, the same ones in each of its K tiles.  A workgroup takes T*K*8 consecutive elements of a
 // minishard, on the XCD that has it in the passes.

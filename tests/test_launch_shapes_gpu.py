@@ -423,6 +423,29 @@ def test_strided_single_launch_layouts(gpu, oracle, long_values, chunks, minisha
         assert (gpu.host_u16(out) == _oracle_variant_strided(oracle, x, chunks, flags)).all(), flags
 
 
+@pytest.mark.parametrize("chunks,minishards,P", ((32, 127, 2), (32, 128, 2), (32, 160, 2), (32, 161, 2), (32, 192, 3), (32, 193, 3),
+                                                 (32, 193, 4), (32, 256, 2), (32, 257, 2), (64, 160, 2), (64, 161, 2), (64, 128, 4),
+                                                 (64, 129, 4), (64, 136, 4), (64, 137, 4), (64, 192, 6), (64, 193, 6), (128, 48, 2),
+                                                 (128, 49, 2), (128, 48, 9), (128, 49, 9), (128, 64, 3), (128, 65, 3), (128, 96, 4),
+                                                 (128, 97, 3), (128, 128, 2), (128, 129, 2)))
+def test_strided_sums_in_fp32(gpu, oracle, long_values, chunks, minishards, P):  # noqa: F811
+    """Both sides of the lines of the reduce-scatter in fp32 that has a kernel of its own; a NaN, which fills its block, and an
+    output that is one of the partials."""
+    n = 1024 * chunks * minishards
+    x = [np.resize(long_values[i % 3], n + i)[i:].copy() for i in range(P)]
+    spoilt = np.zeros((minishards, 1, 1024), bool)
+    for k, e in enumerate(np.random.default_rng(n + P).choice(n, 48, replace=False)):
+        x[k % P][e] = (0x7FC0, 0xFFC0, 0x7F81)[k % 3]
+        spoilt[e // (1024 * chunks), 0, e % 1024] = True
+    spoilt = np.broadcast_to(spoilt, (minishards, chunks, 1024)).reshape(-1)
+    for flags in (eq.RS_UNQUANTIZED, eq.RS_UNQUANTIZED | eq.RING_ORDER):
+        dev = [gpu.dev_bf16(p) for p in x]
+        eq.equarx_reduce_variant_strided(dev, chunks, flags, dev[P // 2])
+        got = gpu.host_u16(dev[P // 2])
+        assert (got[~spoilt] == _oracle_variant_strided(oracle, x, chunks, flags)[~spoilt]).all(), flags
+        assert ((got[spoilt] & 0x7FFF) > 0x7F80).all(), flags
+
+
 @pytest.mark.parametrize("n,P", ((6_300_032, 3), (6_300_033, 7), (20 * 2 ** 20 + 64, 4), (20 * 2 ** 20 + 80, 4)))
 def test_long_kept_wires(gpu, oracle, long_values, n, P):  # noqa: F811
     """Rows of the kept wire on 64-byte lines and off them, in both of the shapes that write them through the L2s."""
