@@ -773,8 +773,9 @@ void launch_chain_strided_as(const PartialTable &tab, int P, int64_t minishards,
     const unsigned owned = own ? owned_places<kChunks, wave_layout_wgs<W, V>>(minishards, nullptr) : 0u;
 #define EQUARX_CHAIN(SEMI, RS, AG) \
     ctx.launch(chain_strided_kernel<R, W, V, SEMI, RS, AG, kWaves>, grid, kThreads, P, per_shard, out, owned, tab)
-    if (semi && ag) EQUARX_CHAIN(true, true, true);
-    else if (semi) EQUARX_CHAIN(true, true, false);
+    constexpr bool kSemi = kChunks != 64 || V != 8 || W != 1 || kWaves == 2;        // the semi-loop comes here too
+    if (kSemi && semi && ag) EQUARX_CHAIN(kSemi, true, true);
+    else if (kSemi && semi) EQUARX_CHAIN(kSemi, true, false);
     else if (rs && ag) EQUARX_CHAIN(false, true, true);
     else if (rs) EQUARX_CHAIN(false, true, false);
     else EQUARX_CHAIN(false, false, true);
@@ -836,7 +837,9 @@ void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chu
     const int per_shard = ring ? (int)((ms + P - 1) / P) : 0;
     const int64_t wgs = ms * wave_layout_wgs<1, 8>;
     // see chain_strided_kernel's kWaves
-    const bool short_round = wgs > 512 && wgs < 2048 && (wgs - 1) % 512 < 256, half_round = !rs && wgs > 640 && wgs <= 768;
+    const int64_t last = (wgs - 1) % 512 + 1;       // workgroups of the last round
+    const bool short_round = wgs > 512 && wgs < 2048 && last <= (wgs < 1024 || !rs || P <= 4 ? 256 : 128);
+    const bool half_round = !semi && wgs > (rs ? 720 : 640) && wgs <= 768;
     if (!rs && sums_apart(chunks, chunks == 128 ? 2 * wgs : wgs, P)) {
 #define EQUARX_SUM(R, W) ctx.launch(sum_strided_kernel<R, W>, (unsigned)(ms * wave_layout_wgs<W, 8>), kThreads, P, per_shard, out, tab)
         if (chunks == 32) EQUARX_SUM(4, 1);
@@ -849,7 +852,7 @@ void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chu
     switch (chunks) {
         case 32:
             if (ms <= 20) EQUARX_LAYOUT(1, 4, 4, 8);
-            else if (short_round) EQUARX_LAYOUT(4, 1, 8, 8);
+            else if (short_round || (semi && P <= 4 && wgs > 512)) EQUARX_LAYOUT(4, 1, 8, 8);
             else EQUARX_LAYOUT(4, 1, 8, 2);
             break;
         case 64:

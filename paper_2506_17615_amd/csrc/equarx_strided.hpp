@@ -661,20 +661,32 @@ __device__ __forceinline__ void strided_send_into(const float (&t)[R][V], float 
 
 // kWaves: waves per SIMD the compiler may plan for.  Two, where the registers would allow three to five: the loads of one
 // partial per wave fill the memory queues as it is, and the fewer places of memory are read at once the better they stream.
-// Eight, no cap, for the small layouts, and where two waves per SIMD, 512 workgroups at a time, would leave a last round of
-// less than half for itself (launch_chain_strided).  Measured on MI355X, us, P = 8, full loop | semi-loop | reduce-scatter in
-// fp32, capped / not:
-//     32 chunks, 128 minishards    13.2/13.5 | 13.9/14.0 | 12.8/12.9
-//                160 (1.3 rounds)  18.9/16.6 | 19.6/17.0 | 18.3/16.6
-//                200 (1.6)         20.9/21.3 | 22.1/21.7 | 20.0/21.0
-//                256 (2)           24.1/23.8 | 25.0/24.0 | 23.7/23.7
-//                336 (2.6)         31.8/32.9 | 33.5/32.5 | 31.1/31.8
-//                400 (3.1)         38.8/37.2 | 40.1/37.2 | 38.8/37.0
-//                1000              88.5/91.6 | 90.4/92.8 | 88.4/94.5
-//     64 chunks, 144 (1.1)         29.6/31.3 |           | 28.9/29.7
-//                192 (1.5)         36.8/35.5 |           | 36.9/34.5
-//                336               60.5/65.8 |           | 60.6/62.7
-//     128 chunks, 170              68.5/73.6 |           | 68.1/72.2
+// Eight, no cap, where two waves per SIMD, 512 workgroups at a time, would leave a last round to a few: at 32 chunks one of up
+// to half of the chip's workgroups, from two rounds on and with more than four partials one of up to a quarter, because there
+// the others gain more; at 64 chunks the half round after the first, unless it is nearly empty (the semi-loop's registers
+// allow two waves either way).  Eight for the semi-loop of 32 chunks of up to four partials too, whose chains are one or two
+// sends long and do not fill the queues.  The layouts of one row have eight and no use for a cap; of 64 chunks, 2 x 4 x 8 has
+// registers for as many as its workgroups need under either; 4 x 4 x 8 has four: 128 chunks, P = 8, 16 and 32 minishards
+// 9.3 and 13.8 us, with two the same but 40 minishards 20.2 instead of 18.9, without one 10.8 and 14.5.  Measured on MI355X, us,
+// capped / not, P = 2, 4, 8, 16:
+//     32 chunks, minishards (rounds)   full loop                                   semi-loop
+//         144 (1.1)      6.8/6.0  10.8/8.9   18.4/15.1  33.3/26.9     7.4/6.0  11.7/9.4   19.3/16.2  34.3/28.9
+//         192 (1.5)      7.8/6.7  11.9/10.7  20.1/18.7  36.5/34.0     7.9/7.2  12.7/11.1  21.5/19.6  38.2/35.5
+//         200 (1.6)      8.4/7.7  12.6/12.5  21.0/21.9  37.4/38.0     9.1/7.7  14.2/13.2  22.2/22.9  38.2/42.2
+//         256 (2)        9.9/9.4  15.2/14.5  24.4/24.9  42.8/45.9    10.6/9.3  16.1/14.8  25.0/26.3  43.5/46.9
+//         288 (2.25)    11.0/11.0 17.4/17.2  29.5/29.9  53.8/56.1    11.7/11.2 18.5/17.5  30.6/30.0  54.8/57.0
+//         336 (2.6)     12.4/12.2 19.3/19.6  32.3/34.0  57.8/63.5    13.4/12.8 20.9/19.7  33.9/34.1  59.1/64.2
+//         400 (3.1)     14.7/14.2 23.1/22.0  39.4/37.6  72.4/69.4    15.6/15.0 24.9/22.2  41.0/38.6  73.4/70.6
+//         448 (3.5)     15.9/15.9 24.8/25.3  42.1/45.0  76.4/85.9    16.7/16.2 26.4/25.6  43.6/43.2  77.3/87.1
+//         512 (4)       17.6/17.4 28.0/26.8  46.5/46.0  84.3/86.0    18.8/17.6 29.4/27.1  47.9/50.0  85.0/88.8
+//         1000 (7.8)    31.7/31.7 51.5/51.7  89.1/92.3   166/175     33.8/32.3 54.5/51.8  91.5/93.3   165/176
+//     64 chunks                        full loop                                   reduce-scatter in fp32
+//         144 (1.1)     10.6/11.1 17.4/18.6  30.8/32.3  59.3/62.0    10.5/11.2 16.9/17.4  30.4/30.9  57.6/58.2
+//         176 (1.4)     12.8/12.8 20.1/19.9  35.5/35.4  65.9/67.8    12.9/12.6 20.3/19.1  34.6/34.2  62.7/60.0
+//         184 (1.44)    13.4/13.1 21.3/20.4  37.3/36.8  68.4/67.8
+//         192 (1.5)     14.3/13.6 22.5/20.8  37.3/36.2  67.3/67.3    14.2/13.4 22.6/20.6  39.0/36.5  73.6/69.5
+//         220 (1.7)     15.9/15.8 24.8/24.9  42.9/44.1  80.4/84.2    15.6/15.5 24.8/24.0  42.8/43.2  79.8/81.1
+//         336 (2.6)     23.1/23.2 36.9/38.0  66.5/69.2   113/125     23.3/23.6 37.1/38.0  64.8/65.3   125/130
 // chunks = 8 * W * R.  kSemi: the semi-loop with partials[0] as the owner (always a quantized reduce-scatter);
 // otherwise the full loop in array order with the reduce-scatter quantized (kRS) or added in plain fp32.  kAG: the
 // finished sum is quantized once more and dequantized; otherwise narrowed to bf16 directly.

@@ -446,6 +446,20 @@ def test_strided_sums_in_fp32(gpu, oracle, long_values, chunks, minishards, P): 
         assert ((got[spoilt] & 0x7FFF) > 0x7F80).all(), flags
 
 
+@pytest.mark.parametrize("chunks,minishards,P", ((32, 129, 4), (32, 192, 5), (32, 193, 4), (32, 193, 5), (32, 288, 5), (32, 289, 5), (32, 400, 5), (32, 448, 4), (32, 448, 5),
+                                                 (32, 511, 5), (32, 512, 5), (64, 129, 4), (64, 160, 4), (64, 161, 4), (64, 180, 4), (64, 181, 4), (64, 192, 4), (64, 193, 4),
+                                                 (128, 95, 4), (128, 96, 5), (128, 97, 4)))
+def test_strided_single_launch_rules(gpu, oracle, long_values, chunks, minishards, P):  # noqa: F811
+    """Both sides of the lines that hang on rounds of workgroups and on partials: caps, layouts and runs of minishards."""
+    n = 1024 * chunks * minishards
+    x = [np.resize(long_values[i % 3], n + i)[i:].copy() for i in range(P)]
+    dev = [gpu.dev_bf16(p) for p in x]
+    out = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    for flags in (0, eq.AG_UNQUANTIZED, eq.RS_UNQUANTIZED, eq.SEMI_LOOP, eq.SEMI_LOOP | eq.RING_ORDER | eq.AG_UNQUANTIZED):
+        eq.equarx_reduce_variant_strided(dev, chunks, flags, out.fill_(5.0))
+        assert (gpu.host_u16(out) == _oracle_variant_strided(oracle, x, chunks, flags)).all(), flags
+
+
 @pytest.mark.parametrize("n,P", ((6_300_032, 3), (6_300_033, 7), (20 * 2 ** 20 + 64, 4), (20 * 2 ** 20 + 80, 4)))
 def test_long_kept_wires(gpu, oracle, long_values, n, P):  # noqa: F811
     """Rows of the kept wire on 64-byte lines and off them, in both of the shapes that write them through the L2s."""
