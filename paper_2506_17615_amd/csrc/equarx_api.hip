@@ -764,12 +764,31 @@ void launch_chain_strided_as(const PartialTable &tab, int P, int64_t minishards,
                              uint16_t *out, LaunchCtx &ctx)
 {
     const unsigned grid = (unsigned)(minishards * wave_layout_wgs<W, V>);
-    // Runs of minishards to an XCD (minishard_part), though nothing is read twice here, where the partials stream better so.
-    // MI355X, us, parts of a minishard on all XCDs -> runs, P = 8 and 16: 32 chunks, 672 minishards 62.6 -> 60.8, 113.7 -> 112.9, 1000 90.1
-    // -> 88.9 (400, without the cap, 37.3 -> 38.0, 68.4 -> 70.7); 64 chunks, 128 23.1 -> 24.4, 41.0 -> 44.1, 336 61.0 -> 62.9, 111.5 ->
-    // 117.9; 128 chunks, 64 25.2 -> 25.8, 45.5 -> 47.3, 100 42.5 -> 42.4, 78.5 -> 77.0, 160 63.5 -> 62.8, 122.5 -> 117.9, 256 102.6 -> 99.2.
+    // Runs of minishards to an XCD (minishard_part), though nothing is read twice here, where the partials stream better so: at
+    // 32 chunks with the cap beyond the first round, and for sums in fp32 in the middle of its second half; at 128 chunks from 96
+    // minishards on, except that where they are just two rounds more than four partials, and sums in fp32, do not.  MI355X, us, parts
+    // of a minishard on all XCDs -> runs; P = 8 and 16: 64 chunks, 128 minishards 23.1 -> 24.4, 41.0 -> 44.1, 336 61.0 -> 62.9, 111.5 ->
+    // 117.9; 32 chunks, 672 62.6 -> 60.8, 113.7 -> 112.9, 1000 90.1 -> 88.9 (400, without the cap, 37.3 -> 38.0, 68.4 -> 70.7).
+    // 32 chunks, P = 2, 3, 4 and 8:
+    //     minishards   full loop                                               sums in fp32
+    //     64       3.31 -> 3.62, 4.25 -> 4.66, 5.34 -> 5.51, 9.16 -> 9.12     3.36 -> 3.32, 4.10 -> 4.41, 5.21 -> 5.58, 8.57 -> 8.73
+    //     96       5.04 -> 4.80, 5.76 -> 5.79, 6.92 -> 7.00, 10.9 -> 10.7     4.72 -> 4.29, 5.33 -> 5.20, 6.74 -> 6.65, 10.4 -> 10.2
+    //     128      5.25 -> 5.75, 6.44 -> 6.85, 7.70 -> 7.97, 12.7 -> 12.7     4.79 -> 5.53, 6.29 -> 6.82, 7.51 -> 7.92, 12.5 -> 12.4
+    // 128 chunks, means over four places in memory, P = 2, 4, 8 and 16 (semi-loop and sums: P = 8):
+    //     minishards   full loop                                               semi-loop        sums in fp32
+    //     64                                   25.2 -> 25.8, 45.5 -> 47.3
+    //     97       15.7 -> 15.1, 24.5 -> 23.5, 41.8 -> 40.1, 77.0 -> 74.3     43.0 -> 40.8     42.2 -> 38.8
+    //     104      16.8 -> 16.6, 25.9 -> 25.7, 44.0 -> 43.9, 81.4 -> 79.3     44.6 -> 45.4     43.8 -> 44.2
+    //     112      17.5 -> 17.2, 27.0 -> 26.8, 45.9 -> 46.0, 84.9 -> 84.7     46.3 -> 47.4     45.7 -> 46.3
+    //     128      18.8 -> 19.0, 29.0 -> 29.2, 49.8 -> 51.2, 93.6 -> 95.5     50.0 -> 51.9     49.3 -> 50.9
+    //     136      20.9 -> 20.4, 33.2 -> 33.0, 59.3 -> 59.5,  113 -> 114      59.1 -> 59.9     56.5 -> 57.1
+    //     160      23.0 -> 23.0, 36.2 -> 36.0, 63.6 -> 63.9,  124 -> 122      64.5 -> 65.2     64.6 -> 62.9
+    //     256      35.5 -> 34.5, 58.1 -> 55.4,  103 -> 101,   195 -> 186       103 -> 101       103 -> 100
     constexpr int kChunks = 8 * W * R;
-    const bool own = V == 8 && ((kChunks == 32 && kWaves == 2) || (kChunks == 128 && minishards >= 96));
+    const bool two_rounds = minishards >= 112 && minishards <= 128;
+    const bool between = !rs && minishards > 72 && minishards < 120;
+    const bool own = V == 8 && ((kChunks == 32 && kWaves == 2 && (minishards > 128 || between)) ||
+                                (kChunks == 128 && minishards >= 96 && !(two_rounds && (P > 4 || !rs))));
     const unsigned owned = own ? owned_places<kChunks, wave_layout_wgs<W, V>>(minishards, nullptr) : 0u;
 #define EQUARX_CHAIN(SEMI, RS, AG) \
     ctx.launch(chain_strided_kernel<R, W, V, SEMI, RS, AG, kWaves>, grid, kThreads, P, per_shard, out, owned, tab)

@@ -424,7 +424,7 @@ def test_strided_single_launch_layouts(gpu, oracle, long_values, chunks, minisha
 
 
 @pytest.mark.parametrize("chunks,minishards,P", ((32, 127, 2), (32, 128, 2), (32, 160, 2), (32, 161, 2), (32, 192, 3), (32, 193, 3),
-                                                 (32, 193, 4), (32, 256, 2), (32, 257, 2), (64, 160, 2), (64, 161, 2), (64, 128, 4),
+                                                 (32, 193, 4), (32, 200, 1), (32, 256, 2), (32, 257, 2), (64, 160, 2), (64, 161, 2), (64, 128, 4),
                                                  (64, 129, 4), (64, 136, 4), (64, 137, 4), (64, 192, 6), (64, 193, 6), (128, 48, 2),
                                                  (128, 49, 2), (128, 48, 9), (128, 49, 9), (128, 64, 3), (128, 65, 3), (128, 96, 4),
                                                  (128, 97, 3), (128, 128, 2), (128, 129, 2)))
@@ -446,9 +446,10 @@ def test_strided_sums_in_fp32(gpu, oracle, long_values, chunks, minishards, P): 
         assert ((got[spoilt] & 0x7FFF) > 0x7F80).all(), flags
 
 
-@pytest.mark.parametrize("chunks,minishards,P", ((32, 129, 4), (32, 192, 5), (32, 193, 4), (32, 193, 5), (32, 288, 5), (32, 289, 5), (32, 400, 5), (32, 448, 4), (32, 448, 5),
+@pytest.mark.parametrize("chunks,minishards,P", ((32, 72, 4), (32, 73, 4), (32, 120, 4), (32, 129, 4), (32, 192, 5), (32, 193, 4), (32, 193, 5), (32, 288, 5), (32, 289, 5), (32, 400, 5), (32, 448, 4), (32, 448, 5),
                                                  (32, 511, 5), (32, 512, 5), (64, 129, 4), (64, 160, 4), (64, 161, 4), (64, 180, 4), (64, 181, 4), (64, 192, 4), (64, 193, 4),
-                                                 (128, 95, 4), (128, 96, 5), (128, 97, 4)))
+                                                 (128, 95, 4), (128, 96, 5), (128, 97, 4),
+                                                 (128, 111, 5), (128, 112, 4), (128, 112, 5), (128, 128, 5), (128, 129, 5)))
 def test_strided_single_launch_rules(gpu, oracle, long_values, chunks, minishards, P):  # noqa: F811
     """Both sides of the lines that hang on rounds of workgroups and on partials: caps, layouts and runs of minishards."""
     n = 1024 * chunks * minishards
