@@ -848,6 +848,12 @@ inline bool sums_apart(int32_t chunks, int64_t wgs, int P)
 //     40                     10.1/9.0                   19.3/15.7/12.6                           19.4/20.0
 //     48                                                     16.8/14.1                           21.6/21.8
 //     64                                                     18.0/14.6                           28.8/25.0
+// 128 chunks by the partials (P = 2, 3, 4, 8, 16): 8 minishards, 4x4x4 / 4x4x8 2.6/2.9, 4.0/4.5, 4.7/5.3, 8.0/8.5, 14.6/15.1 (and
+// 15.7/15.1 another time), reduce-scatter in fp32 3.2/3.5, 3.9/4.3, 4.7/5.1, 8.7/8.0, 14.9/13.7, 9 full loop 3.1/3.3, 4.9/4.6, 6.3/5.4,
+// 10.6/8.6, 19.5/15.2.  Up to 32 minishards 8x2x8, a workgroup per CU at most, is the faster for the
+// reduce-scatter in fp32, where one send is all, and for two partials from 25: 4x4x8 / 8x2x8, fp32, 18 minishards 4.5/4.2, 5.9/5.1,
+// 6.7/6.1, 11.6/9.8, 20.0/17.0, 32 5.9/4.9, 7.6/6.2, 8.9/7.3, 13.7/12.9, 24.1/22.4 (16: P = 4 5.5/6.3); full loop, 24 4.9/5.0, 6.2/6.4,
+// 7.6/8.0, 32 6.1/5.7, 7.5/7.1, 8.7/8.7, 13.4/15.8; semi-loop, 32 5.8/5.4, 7.3/7.7.
 // ring: shards of ceil(minishards / P) whole minishards, shard k in the order a ring gives it.
 void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chunks, bool semi, bool rs, bool ag,
                           bool ring, uint16_t *out, LaunchCtx &ctx)
@@ -881,7 +887,8 @@ void launch_chain_strided(const PartialTable &tab, int P, int64_t n, int32_t chu
             else EQUARX_LAYOUT(8, 1, 8, 2);
             break;
         case 128:
-            if (ms <= 6) EQUARX_LAYOUT(4, 4, 4, 8);
+            if (ms <= 6 || (ms <= 8 && P <= (rs ? 8 : 4))) EQUARX_LAYOUT(4, 4, 4, 8);
+            else if (ms <= 32 && (rs ? P == 2 && ms > 24 : ms > 16)) EQUARX_LAYOUT(8, 2, 8, 2);
             else if (ms <= 48) EQUARX_LAYOUT(4, 4, 8, 4);
             else EQUARX_LAYOUT(8, 2, 8, 2);
             break;

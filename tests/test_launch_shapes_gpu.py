@@ -449,7 +449,8 @@ def test_strided_sums_in_fp32(gpu, oracle, long_values, chunks, minishards, P): 
 @pytest.mark.parametrize("chunks,minishards,P", ((32, 72, 4), (32, 73, 4), (32, 120, 4), (32, 129, 4), (32, 192, 5), (32, 193, 4), (32, 193, 5), (32, 288, 5), (32, 289, 5), (32, 400, 5), (32, 448, 4), (32, 448, 5),
                                                  (32, 511, 5), (32, 512, 5), (64, 129, 4), (64, 160, 4), (64, 161, 4), (64, 180, 4), (64, 181, 4), (64, 192, 4), (64, 193, 4),
                                                  (128, 95, 4), (128, 96, 5), (128, 97, 4),
-                                                 (128, 111, 5), (128, 112, 4), (128, 112, 5), (128, 128, 5), (128, 129, 5)))
+                                                 (128, 111, 5), (128, 112, 4), (128, 112, 5), (128, 128, 5), (128, 129, 5),
+                                                 (128, 8, 8), (128, 8, 9), (128, 9, 3), (128, 16, 2), (128, 17, 2), (128, 24, 2), (128, 25, 2), (128, 32, 2), (128, 33, 2)))
 def test_strided_single_launch_rules(gpu, oracle, long_values, chunks, minishards, P):  # noqa: F811
     """Both sides of the lines that hang on rounds of workgroups and on partials: caps, layouts and runs of minishards."""
     n = 1024 * chunks * minishards
