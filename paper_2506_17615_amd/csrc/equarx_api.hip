@@ -642,9 +642,33 @@ inline void with_slices(int64_t n, int32_t chunks, F f)
     }
 }
 
-// The places of a launch that go to the XCDs by whole minishards (minishard_part), for the wire that it writes or reads.
+// The places of a launch that go to the XCDs by whole minishards (minishard_part), for the wire that it writes or reads.  `spread`
+// (short_and_long): none.
 template <typename S>
-inline unsigned strided_owned(int64_t n, const void *wire) { return owned_places<S::kChunks, S::kParts>(minishards_of(n, S::kChunks), wire); }
+inline unsigned strided_owned(int64_t n, const void *wire, bool spread)
+{
+    return spread ? 0u : owned_places<S::kChunks, S::kParts>(minishards_of(n, S::kChunks), wire);
+}
+
+// The flavours hop by hop of few partials, where the wire is rewritten twice at most and runs gain the least, keep the parts of
+// a minishard on all XCDs from 10 Mi elements on: two partials of 64 and up to four of 128 chunks.  Measured on MI355X, us, runs
+// -> all XCDs, semi-loop and full loop in ring order, means over four places in memory:
+//     chunks, elements     P = 2                          3                              4
+//     128, 10.5 M      17.8 -> 16.5, 16.4 -> 16.2     25.2 -> 24.4, 24.6 -> 24.2     32.0 -> 31.3, 32.6 -> 32.2
+//          12.6 M      20.0 -> 18.6, 18.9 -> 18.5     29.1 -> 27.5, 27.7 -> 26.6     37.1 -> 35.7, 36.5 -> 35.5
+//          14.7 M      23.8 -> 23.6, 23.9 -> 23.4     33.5 -> 33.6, 33.9 -> 33.1     43.3 -> 42.8, 44.3 -> 43.5
+//          16.8 M      25.9 -> 25.2, 25.7 -> 25.0     36.4 -> 36.1, 36.8 -> 35.5     47.1 -> 46.2, 47.9 -> 45.7
+//          25.2 M      38.1 -> 37.4, 38.0 -> 37.3     53.3 -> 52.0, 54.1 -> 53.4     69.5 -> 68.6, 69.2 -> 69.2
+//          33.6 M      48.3 -> 47.7, 48.0 -> 47.2     68.0 -> 65.8, 69.0 -> 69.0     89.7 -> 88.3, 89.4 -> 90.7
+//     64,  10.5 M      17.1 -> 15.6, 15.9 -> 15.4     24.9 -> 24.6, 23.5 -> 23.0     32.0 -> 31.3, 31.4 -> 30.5
+//          13.1 M      21.5 -> 20.9, 21.1 -> 20.6     29.8 -> 30.5, 30.3 -> 29.6     38.6 -> 39.0, 39.7 -> 38.9
+//          16.8 M      25.4 -> 25.3, 25.1 -> 25.1     35.9 -> 36.3, 35.2 -> 34.7     45.9 -> 46.5, 45.5 -> 45.6
+//          19.7 M      29.9 -> 29.5, 29.6 -> 29.3     41.9 -> 43.1, 42.0 -> 41.8     54.8 -> 55.7, 54.3 -> 54.0
+// (32 chunks, P = 2, 8.4 M 12.2 -> 12.8, 12.2 -> 12.7; 64 chunks, P = 2, 4.2 and 8.4 M 8.0 -> 9.3, 12.5 -> 12.7.)
+inline bool short_and_long(int32_t chunks, int64_t n, int P)
+{
+    return n >= (int64_t)10 << 20 && ((chunks == 64 && P == 2) || (chunks == 128 && P <= 4));
+}
 
 template <typename S>
 inline unsigned strided_count(int64_t n) { return (unsigned)(minishards_of(n, S::kChunks) * S::kParts); }
@@ -708,34 +732,35 @@ inline void with_source(const StridedSource &src, F f)
 }
 
 template <typename... Source>
-void do_quantize_strided(int64_t n, int32_t chunks, int8_t *codes, float *scales, LaunchCtx &ctx, Source... src)
+void do_quantize_strided(int64_t n, int32_t chunks, int8_t *codes, float *scales, LaunchCtx &ctx, bool spread, Source... src)
 {
     with_slices(n, chunks, [&](auto slices) {
         using S = decltype(slices);
-        const unsigned owned = strided_owned<S>(n, codes);
+        const unsigned owned = strided_owned<S>(n, codes, spread);
         ctx.launch(quantize_strided_kernel<S, Source...>, strided_grid<S>(n, owned), kThreads, codes, scales, owned, src...);
     });
 }
 
 template <typename... Source>
 void do_hop_strided(const int8_t *cin, const float *sin, int64_t n, int32_t chunks, int8_t *cout, float *sout, LaunchCtx &ctx,
-                    bool backward, Source... src)
+                    bool backward, bool spread, Source... src)
 {
     with_slices(n, chunks, [&](auto slices) {
         using S = decltype(slices);
-        const unsigned owned = strided_owned<S>(n, cout), grid = strided_grid<S>(n, owned);
+        const unsigned owned = strided_owned<S>(n, cout, spread), grid = strided_grid<S>(n, owned);
         ctx.launch(hop_strided_kernel<S, Source...>, grid, kThreads, cin, sin, cout, sout, strided_mirror(grid, backward), owned, src...);
     });
 }
 
 // Step t of the semi-loop's two chains, the first device of one at `up` and of the other at `down` from the owner.
 void do_semi_step_strided(const WireBuffers &w, const PartialTable &tab, int P, int per_shard, int up, int down, bool first, int64_t n,
-                          int32_t chunks, LaunchCtx &ctx, bool backward)
+                          int32_t chunks, LaunchCtx &ctx, bool backward, bool spread)
 {
     const RingDivision by = ring_division(per_shard);
     with_slices(n, chunks, [&](auto slices) {
         using S = decltype(slices);
-        const unsigned count = strided_count<S>(n), owned0 = strided_owned<S>(n, w.c[0]), owned1 = strided_owned<S>(n, w.c[1]);
+        const unsigned count = strided_count<S>(n);
+        const unsigned owned0 = strided_owned<S>(n, w.c[0], spread), owned1 = strided_owned<S>(n, w.c[1], spread);
         ctx.launch(semi_step_strided_kernel<S>, 2 * semi_step_half<S>(count, owned0, owned1), kThreads, w.c[0], w.s[0], w.c[1], w.s[1],
                    by.magic, ring_word(P, by.shift, up, down), count, owned0, owned1, (backward ? 1 : 0) | (first ? 2 : 0), tab);
     });
@@ -748,11 +773,12 @@ struct StridedWires {
 };
 
 template <bool kAG, typename... Source>
-void do_owner_strided(const StridedWires &in, int64_t n, int32_t chunks, uint16_t *out, LaunchCtx &ctx, bool backward, Source... src)
+void do_owner_strided(const StridedWires &in, int64_t n, int32_t chunks, uint16_t *out, LaunchCtx &ctx, bool backward, bool spread,
+                      Source... src)
 {
     with_slices(n, chunks, [&](auto slices) {
         using S = decltype(slices);
-        const unsigned owned = strided_owned<S>(n, in.codes[1] ? in.codes[1] : in.codes[0]), grid = strided_grid<S>(n, owned);
+        const unsigned owned = strided_owned<S>(n, in.codes[1] ? in.codes[1] : in.codes[0], spread), grid = strided_grid<S>(n, owned);
         ctx.launch(owner_strided_kernel<S, kAG, Source...>, grid, kThreads, out, in.codes[0], in.scales[0], in.codes[1],
                    in.scales[1], strided_mirror(grid, backward), owned, src...);
     });
@@ -1412,7 +1438,7 @@ int equarx_quantize_strided(const void *x_bf16, int64_t n, int32_t chunks, int8_
     mem.writes(codes, (size_t)n);
     mem.writes(scales, (size_t)(n / chunks) * sizeof(float));
     if (int st = mem.check()) return st;
-    do_quantize_strided(n, chunks, codes, scales, ctx, one_tensor(x_bf16));
+    do_quantize_strided(n, chunks, codes, scales, ctx, false, one_tensor(x_bf16));
     return ctx.status();
 }
 
@@ -1444,7 +1470,7 @@ int equarx_reduce_stage_strided(const int8_t *codes_in, const float *scales_in, 
         misaligned(codes_out, kAlign) || misaligned(scales_out, kAlign))
         return EQUARX_MISALIGNED;
     if (int st = check_hop_memory(codes_in, scales_in, local_bf16, n, n / chunks, codes_out, scales_out)) return st;
-    do_hop_strided(codes_in, scales_in, n, chunks, codes_out, scales_out, ctx, false, one_tensor(local_bf16));
+    do_hop_strided(codes_in, scales_in, n, chunks, codes_out, scales_out, ctx, false, false, one_tensor(local_bf16));
     return ctx.status();
 }
 
@@ -1470,9 +1496,9 @@ int equarx_reduce_quantized_strided(const void *const *partials_bf16, int32_t P,
     const int at = strided_chain_buffer(n, P);
     int8_t *const c = w.c[at];
     float *const sc = w.s[at];
-    do_quantize_strided(n, chunks, c, sc, ctx, one_tensor(partials_bf16[0]));
+    do_quantize_strided(n, chunks, c, sc, ctx, false, one_tensor(partials_bf16[0]));
     for (int32_t i = 1; i < P; ++i) {
-        do_hop_strided(c, sc, n, chunks, c, sc, ctx, walks_back(n, i), one_tensor(partials_bf16[i]));
+        do_hop_strided(c, sc, n, chunks, c, sc, ctx, walks_back(n, i), false, one_tensor(partials_bf16[i]));
     }
     do_dequantize_strided(c, sc, n, chunks, out_bf16, ctx, walks_back(n, P));
     return ctx.status();
@@ -1548,6 +1574,7 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
     const WireBuffers w = carve_workspace(workspace, n, n / chunks);
     uint16_t *out = static_cast<uint16_t *>(out_bf16);
     StridedWires wires = {{nullptr, nullptr}, {nullptr, nullptr}};
+    const bool spread = short_and_long(chunks, n, P);
     // Ring layout: shards of ceil(M / P) whole minishards; every launch is one ring step on all P shards at once,
     // the workgroups of shard k reading the partial of device (k + offset) mod P.  Array order: offset = partial.
     const int64_t minishards = n / ((int64_t)kChunk * chunks);
@@ -1557,15 +1584,15 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
     // position i of the semi-loop counts from its owner: device k in a ring, partial 0 otherwise
     const auto around = [&](int i) { return StridedSource{tab, P, per_shard, i}; };
     const auto quantize = [&](const StridedSource &from, int to) {
-        with_source(from, [&](auto... src) { do_quantize_strided(n, chunks, w.c[to], w.s[to], ctx, src...); });
+        with_source(from, [&](auto... src) { do_quantize_strided(n, chunks, w.c[to], w.s[to], ctx, spread, src...); });
     };
     const auto hop = [&](const StridedSource &from, int on, bool backward) {
-        with_source(from, [&](auto... src) { do_hop_strided(w.c[on], w.s[on], n, chunks, w.c[on], w.s[on], ctx, backward, src...); });
+        with_source(from, [&](auto... src) { do_hop_strided(w.c[on], w.s[on], n, chunks, w.c[on], w.s[on], ctx, backward, spread, src...); });
     };
     const auto finish = [&](const StridedSource &own, bool backward) {
         with_source(own, [&](auto... src) {
-            if (ag) do_owner_strided<true>(wires, n, chunks, out, ctx, backward, src...);
-            else do_owner_strided<false>(wires, n, chunks, out, ctx, backward, src...);
+            if (ag) do_owner_strided<true>(wires, n, chunks, out, ctx, backward, spread, src...);
+            else do_owner_strided<false>(wires, n, chunks, out, ctx, backward, spread, src...);
         });
     };
 
@@ -1588,7 +1615,7 @@ int equarx_reduce_variant_hops_strided(const void *const *partials_bf16, int32_t
     for (int32_t t = 0; t < nb; ++t) {
         const bool backward = walks_back(2 * n, t);
         if (t < na) {
-            do_semi_step_strided(w, tab, P, per_shard, h + 1 + t, h - t, t == 0, n, chunks, ctx, backward);
+            do_semi_step_strided(w, tab, P, per_shard, h + 1 + t, h - t, t == 0, n, chunks, ctx, backward, spread);
         } else if (t == 0) {
             quantize(around(h), 1);
         } else {

@@ -462,6 +462,20 @@ def test_strided_single_launch_rules(gpu, oracle, long_values, chunks, minishard
         assert (gpu.host_u16(out) == _oracle_variant_strided(oracle, x, chunks, flags)).all(), flags
 
 
+@pytest.mark.parametrize("chunks,minishards,P", ((64, 159, 2), (64, 160, 2), (64, 203, 2), (64, 160, 3), (128, 79, 3), (128, 80, 4),
+                                                 (128, 101, 2), (128, 96, 5)))
+def test_strided_hops_of_few_partials(gpu, oracle, long_values, chunks, minishards, P):  # noqa: F811
+    """Around 10 Mi elements, from which few partials keep the parts of a minishard on all XCDs."""
+    n = 1024 * chunks * minishards
+    x = [np.resize(long_values[i % 3], n + i)[i:].copy() for i in range(P)]
+    for flags in (0, eq.RING_ORDER | eq.AG_UNQUANTIZED, eq.SEMI_LOOP, eq.SEMI_LOOP | eq.RING_ORDER):
+        dev = [gpu.dev_bf16(p) for p in x]
+        work = eq.alloc_variant_workspace(flags & ~eq.RING_ORDER, P, n, chunks)
+        work = torch.empty(work.numel() + (5 << 16), dtype=torch.uint8, device="cuda")[5 << 16:]
+        eq.equarx_reduce_variant_hops_strided(dev, chunks, flags, dev[0], work)
+        assert (gpu.host_u16(dev[0]) == _oracle_variant_strided(oracle, x, chunks, flags)).all(), flags
+
+
 @pytest.mark.parametrize("n,P", ((6_300_032, 3), (6_300_033, 7), (20 * 2 ** 20 + 64, 4), (20 * 2 ** 20 + 80, 4)))
 def test_long_kept_wires(gpu, oracle, long_values, n, P):  # noqa: F811
     """Rows of the kept wire on 64-byte lines and off them, in both of the shapes that write them through the L2s."""
