@@ -934,20 +934,25 @@ void launch_dequantize_strided(const int8_t *codes, const float *scales, int64_t
 }
 
 // 256 threads x 4 tiles, where a lane reads its scales once for 32 elements; 2 while that leaves CUs without work.  Measured on
-// MI355X, us, wires and outputs in turn, 256 x 1 / 256 x 2 / 256 x 4 / 512 x 2 (one instance for every number of chunks, which
-// divided by it per lane, and each load behind a condition: 256 x 1 up to 4 Mi, 512 x 2 above):
+// MI355X, us, 256 x 1 / 256 x 2 / 256 x 4, three wires and outputs in turn, and one:
 //     elements, chunks
-//     1.0 M, 64      2.35/2.48/2.45/2.45   (2.41)
-//     3.1 M, 64      2.95/2.78/2.91/2.90   (3.09)
-//     5.2 M, 32      4.27/3.71/3.54/3.76   (4.18)
-//     5.2 M, 64      4.42/3.56/3.52/3.61   (4.61)
-//     6.3 M, 64      5.33/4.90/4.18/4.71   (5.50)
-//     8.4 M, 64      6.76/6.32/5.19/6.15   (7.35)
-//     14.7 M, 64     11.0/9.77/9.32/9.89   (11.4)
-//     22 M, 64       14.7/13.5/13.0/13.4   (15.2)
-//     22 M, 128      13.2/13.6/13.1/13.4   (14.2)
-//     62.9 M, 32     36.9/32.6/32.3/33.0   (37.5)
-constexpr int64_t kTwoTileDequantize = (int64_t)5 << 20;
+//     0.5 M, 64       1.97/1.98/1.99     1.98/1.96/1.98
+//     1.0 M, 64       2.04/2.08/2.04     2.05/2.08/2.07
+//     2.1 M, 64       2.20/2.14/2.31     2.31/2.26/2.34
+//     3.1 M, 64       2.44/2.37/2.44     2.55/2.44/2.46
+//     4.2 M, 32       2.62/2.46/2.69     2.69/2.51/2.70
+//     5.2 M, 64       3.00/2.70/2.96     2.93/2.73/2.99
+//     5.8 M, 32       3.14/2.84/3.02     3.07/2.80/3.08
+//     6.3 M, 32       3.24/3.01/3.24     3.18/2.99/3.31
+//     6.3 M, 128      3.21/3.03/3.27     3.21/2.99/3.31
+//     7.3 M, 32       4.06/3.84/3.50     3.53/3.34/3.53
+//     8.4 M, 64       3.83/3.70/3.82     3.62/3.59/3.73
+//     14.7 M, 64      11.0/9.77/9.32
+//     22 M, 64        14.7/13.5/13.0
+//     62.9 M, 32      36.9/32.6/32.3
+// (512 x 2 is between the last two, and 256 x 1 or 512 x 2 took 3.1, 3.6 and 4.8 us at 5.2, 6.3 and 7.3 M with one instance for
+// every number of chunks, which divided by it per lane, and each load behind a condition.)
+constexpr int64_t kTwoTileDequantize = (int64_t)6 << 20;
 
 void do_dequantize_strided(const int8_t *codes, const float *scales, int64_t n, int32_t chunks, void *out,
                            LaunchCtx &ctx, bool backward = false)

@@ -476,6 +476,18 @@ def test_strided_hops_of_few_partials(gpu, oracle, long_values, chunks, minishar
         assert (gpu.host_u16(dev[0]) == _oracle_variant_strided(oracle, x, chunks, flags)).all(), flags
 
 
+@pytest.mark.parametrize("chunks,minishards", ((32, 191), (32, 192), (32, 193), (64, 97), (128, 48), (128, 49)))
+def test_strided_dequantization_around_six_mi_elements(gpu, oracle, long_values, chunks, minishards):  # noqa: F811
+    """Two tiles a lane and four, with a wire that begins between two runs."""
+    n = 1024 * chunks * minishards
+    codes, scales = oracle.quantize_bf16_strided(np.resize(long_values[0], n), chunks)
+    c = torch.empty(n + (3 << 16), dtype=torch.int8, device="cuda")[3 << 16:]
+    c.copy_(torch.from_numpy(codes))
+    out = torch.full((n,), 5.0, dtype=torch.bfloat16, device="cuda")
+    eq.equarx_dequantize_strided(c, torch.from_numpy(scales).cuda(), chunks, out)
+    assert (gpu.host_u16(out) == oracle.dequantize_bf16_strided(codes, scales, chunks)).all()
+
+
 @pytest.mark.parametrize("n,P", ((6_300_032, 3), (6_300_033, 7), (20 * 2 ** 20 + 64, 4), (20 * 2 ** 20 + 80, 4)))
 def test_long_kept_wires(gpu, oracle, long_values, n, P):  # noqa: F811
     """Rows of the kept wire on 64-byte lines and off them, in both of the shapes that write them through the L2s."""
