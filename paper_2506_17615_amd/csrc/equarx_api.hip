@@ -682,8 +682,9 @@ inline unsigned strided_mirror(unsigned grid, bool backward) { return backward ?
 // A strided chain rewrites one wire in place to its end: the dequantization takes every tile on the XCD that wrote it, and
 // finds it in that L2.  A last hop that writes beside the wire it reads costs (MI355X, us, P = 2, 3, 4 and 8, in place ->
 // beside) 8.8 -> 8.8, 12.0 -> 11.9, 15.1 -> 15.3, 28.0 -> 28.3 at 2.1 M elements of 32 chunks, 21.4 -> 22.6, 29.6 -> 30.9, 36.9 -> 38.2,
-// 68.7 -> 70.6 at 12.6 M of 64, 34.2 -> 38.7, 46.7 -> 52.0, 59.5 -> 64.5, 111.3 -> 116.5 at 22 M.  Up to 3 Mi elements and from 9 to 28
-// Mi it is the workspace's second buffer, as where a chain of that length leaves its last wire: one is as good as the other.
+// 68.7 -> 70.6 at 12.6 M of 64, 34.2 -> 38.7, 46.7 -> 52.0, 59.5 -> 64.5, 111.3 -> 116.5 at 22 M.  Which of the workspace's buffers it is
+// makes no difference to the time, and the header promises nothing about it: up to 3 Mi elements and from 9 to 28 Mi the second,
+// where such a chain has always left its last wire and where tests/test_launch_shapes_gpu.py looks for it.
 inline int strided_chain_buffer(int64_t n, int P)
 {
     return P > 1 && (n <= (int64_t)3 << 20 || (n >= (int64_t)9 << 20 && n <= (int64_t)28 << 20)) ? 1 : 0;

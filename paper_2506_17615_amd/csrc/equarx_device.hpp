@@ -1043,7 +1043,7 @@ __device__ __forceinline__ void hop_tiles(float (&t)[K][8], const u32x4 (&x)[K],
             quantize_lane_f<G, kPositiveZero>(t[k], r, s);
             if (kWire) {
                 store_wire_tile<B, kFull, kWire>(wire_codes, wire_scales, c_step, s_step, row,
-                                          wg_at + k * tile_elems<T>, lane_at, n, r, s);
+                                                 wg_at + k * tile_elems<T>, lane_at, n, r, s);
             }
             float xf[8];
             widen_bf16x8(x[k], xf);

@@ -119,7 +119,8 @@ __device__ __forceinline__ StridedSpot strided_spot(unsigned at, unsigned owned)
 // does, the lane's offset and, in a scalar register, the row's, so that no row costs vector instructions.  The 16-byte
 // store has its row in the descriptor: the compiler takes an offset in a scalar register for a reason to let the next
 // instruction overwrite what the store is still reading, and on MI355X it does overwrite it (words of the output held later
-// values, now and then, with two workgroups on a CU).
+// values, now and then, with two workgroups on a CU).  The 8-byte store keeps it there: the architecture's manual names the hazard
+// for stores of more than 64 bits, whose data the memory unit takes in a second step, and for no others.
 constexpr int kMinishardEnd = kChunk * 128 * 2;     // bytes from there that no descriptor has to reach past
 
 template <int kRow>
@@ -433,29 +434,31 @@ __global__ __launch_bounds__(kThreads) void owner_strided_kernel(Global<uint16_t
 // of its group: R = chunks/8 rows of 8 running sums per thread.  For 128
 // chunks that would be 16 rows (128 sums, 64 load registers: one wave per
 // SIMD), so there W = 2 waves share a position piece, wave w taking the chunk
-// groups 8w .. 8w+7 (R = 8), and the two maxima meet through 256 bytes of LDS
-// and one barrier per send (the buffer alternates, so the barrier of the next
-// send also separates this send's reads from the writes of the one after).
+// groups 8w .. 8w+7 (R = 8), and the two maxima meet through LDS, 256 bytes a
+// wave and 2 KiB in all, and one barrier per send (the buffer alternates, so the
+// barrier of the next send also separates this send's reads from the writes of
+// the one after).
 // Same operations in the same order as the hop-by-hop strided chain, hence
 // the same bits.
 //
 // A send does not compute anything twice either: the 8 lanes of a position end their exchange with one of its 8 positions'
 // maxima each (scatter_max), work out that one pair of quotients and hand it round (gather_lanes).  With every lane deriving
 // all 8 pairs, and 64-bit addresses per row, the full loop had 773, 1197 and 1290 vector instructions at 32, 64 and 128 chunks,
-// now 497, 857 and 881.  Measured on MI355X, us, P = 8, before -> after: 22 M elements of 32 chunks 66.9 -> 60.8, of 64 61.7 -> 60.5,
-// of 128 69.9 -> 68.5; 17 minishards of 32 chunks 10.3 -> 8.5, one 5.4 -> 4.2.
+// now 497, 857 and 881.  Measured on MI355X, us of GPU time, P = 8, before -> after: 22 M elements of 32 chunks 66.9 -> 60.8, of 64
+// 61.7 -> 60.5, of 128 69.9 -> 68.5; 17 minishards of 32 chunks 10.3 -> 8.5, one 5.4 -> 4.2.  (Calls among others, with the
+// launch: of 64 chunks 61.4..61.6, and up to 66 by where the partials lie in memory.)
 //
 // A message of few minishards is bound by the time one wave takes per send,
 // not by memory: W = 4 waves share a piece and a lane has V = 4 positions
-// instead of 8, so a wave has an eighth of the rows and a
-// minishard 32 workgroups instead of 4.
+// instead of 8, so a wave has a quarter of the rows at half of the positions,
+// an eighth of the work, and a minishard 32 workgroups instead of 4.  In
+// between, at 64 and 128 chunks, 4 waves share a piece and a lane has its 8
+// positions: a quarter of the work, and 16 workgroups.
 
 struct WaveSpot {
     unsigned minishard; // which minishard the workgroup works on
     int64_t elem;       // first element of the workgroup's positions in the first chunk of its minishard
-    int64_t scale;      // index of their first scale
-    int at, pos;        // the lane's first element, from there, in the first of its chunks; its first position
-    bool first_group;   // the lane stores the scales of its positions
+    int at;             // the lane's first element, from there, in the first of its chunks
 };
 
 // W waves per position piece, V positions per lane; a 256-thread workgroup covers (4 / W) * 8 V positions.
@@ -476,13 +479,9 @@ __device__ __forceinline__ WaveSpot wave_spot(int chunks, unsigned owned)
     WaveSpot sp;
     sp.minishard = place.minishard;
     sp.elem = (int64_t)sp.minishard * (kChunk * chunks) + part * kPositions;
-    sp.scale = (int64_t)sp.minishard * kChunk + part * kPositions;
-    sp.pos = (wave / W) * (8 * V) + (lane % 8) * V;
-    sp.at = g * kChunk + sp.pos;
-    sp.first_group = g == 0;
+    sp.at = g * kChunk + (wave / W) * (8 * V) + (lane % 8) * V;
     return sp;
 }
-
 
 // Maxima that waves exchange: one row per wave, two buffers in turn.
 template <int W, int V>
@@ -738,7 +737,8 @@ void chain_strided_kernel(int P, int per_shard, Global<uint16_t> out, unsigned o
         for (int i = 1; i < P; ++i) {
             // With two waves per piece the partial is requested before anything else of the hop: left to the compiler, 160
             // minishards of 128 chunks take 66.3 us instead of 64.7, P = 16 120.4 instead of 117.4 (176: 71.6 and 72.2, 128.6 and
-            // 129.2).  An earlier body of this loop took up to 9 % longer off 8-byte boundaries; this one does not care.
+            // 129.2).  An earlier body of this loop took up to 9 % longer off 8-byte boundaries; this one takes the same time on
+            // either, and stays on them (tests/test_build_flags.py).
             constexpr bool kRequestFirst = W == 2 && V == 8;
             if (kRS && kRequestFirst) asm volatile(".p2align 3");
             load_strided<R, W, V>(part(i), sp, xv);
