@@ -104,3 +104,21 @@ def test_no_store_of_16_bytes_takes_an_offset_from_a_scalar_register(device_asm)
         stores = re.findall(r"buffer_store_dwordx[34] [^;\n]*", asm)
         assert name != "equarx_api.hip" or stores
         assert not [line for line in stores if re.search(r"\], s\d+ ", line)], name
+
+
+def _row_is_a_constant(store):
+    """Whether the operand behind the descriptor of a buffer store is a constant; anything else is a scalar register."""
+    return re.search(r"\bs\[\d+:\d+\],\s*(?:-?\d+|0x[0-9a-f]+)(?=\s|$)", store) is not None
+
+
+def test_every_wide_store_has_a_constant_behind_its_descriptor(device_asm):
+    """As above, with every form that the operand can take: without modifiers behind it, and in m0, vcc or a trap register."""
+    for good in ("v[0:3], v4, s[8:11], 0 offen nt", "v[0:3], off, s[8:11], 0", "v[0:3], v4, s[8:11], -1 offen", "v[0:2], off, s[0:3], 64 offset:16"):
+        assert _row_is_a_constant("buffer_store_dwordx4 " + good), good
+    for bad in ("s20", "m0", "vcc_lo", "ttmp4"):
+        for form in ("v[0:3], off, s[8:11], %s", "v[0:3], v4, s[8:11], %s offen nt", "v[0:3], off, s[8:11], %s offset:16"):
+            assert not _row_is_a_constant("buffer_store_dwordx4 " + form % bad), (form, bad)
+    for name, asm in device_asm.items():
+        stores = re.findall(r"buffer_store_(?:dwordx[34]|format_xyzw?|b96|b128)\s[^;\n]*", asm)
+        assert name != "equarx_api.hip" or len(stores) > 100
+        assert not [line for line in stores if not _row_is_a_constant(line)], name
