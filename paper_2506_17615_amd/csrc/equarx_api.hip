@@ -840,7 +840,7 @@ void launch_chain_strided_as(const PartialTable &tab, int P, int64_t minishards,
 //         256 (2)                 9.94/8.70   12.33/11.45  14.75/14.45   19.31/18.67     24.0/24.6     42.5/42.2
 //         336 (2.6)               12.5/12.2    15.7/15.8    19.0/19.3     25.4/26.5      31.6/32.5     56.7/63.7
 //     64, 112 (0.9)               8.18/8.02    10.3/10.2    12.8/12.7     17.1/16.9      21.1/21.5     39.2/37.7
-//         132 (1.03)              10.4/10.2    13.6/        17.3/         23.5/21.7      29.9/27.6     52.9/49.3
+//         132 (1.03)              10.4/10.2                              23.5/21.7      29.9/27.6     52.9/49.3
 //         144 (1.1)               10.5/11.0    13.9/13.9    17.0/17.0     23.6/22.8      30.2/28.6     57.7/53.3
 //         160 (1.25)              11.4/11.3    14.6/15.1    17.9/18.1     24.4/24.1      31.6/30.5     60.2/55.1
 //         176 (1.4)               12.6/11.9    15.7/16.1    19.1/19.6     26.4/26.7      32.8/32.6     64.0/61.6

@@ -863,6 +863,9 @@ enum KeptWire { kNoWire, kCachedWire, kWireThroughL2 };
 //     8, 22 M, 256                       105.1 -> 99.6 -> 97.6     91.4 -> 88.9 -> 97.5
 //     8, 12,000,001, 256                  60.5 -> 66.5             51.2 -> 51.0       (rows 16 bytes off)
 //     16, 16 M, 128                        161 -> 151 -> 139        125 -> 121 -> 138
+// Nine sets of buffers, three and one for all calls, another time: P = 2, 20 M 29.2 -> 29.0, 28.2 -> 26.9, 27.8 -> 26.7; P = 8, 5.8 M
+// 28.9 -> 29.0, 26.1 -> 25.9, 26.1 -> 25.8; 22 M 105.1 -> 99.9, 105.4 -> 99.7, 90.5 -> 87.7; and of 160 calls (P = 2 to 16, 4.8 to 33.6 M,
+// blocks 64 and 256) with three sets and one none is slower by more than 0.6 %.
 // Shorter messages' shapes keep cached stores: P = 12, 4.7 M 36.9 -> 40.0 -> 34.7, P = 3, 3 M 7.9 -> 8.2 -> 8.0.
 constexpr bool wire_through_l2(int T, int K) { return T == 1024 || K == 4; }
 
