@@ -642,6 +642,20 @@ inline void with_slices(int64_t n, int32_t chunks, F f)
     }
 }
 
+// f(layout) with the layout of the owner's kernel: that of the other passes, but of 128 chunks 32 lanes where 16 would give more
+// than three and at most four workgroups per CU.  A workgroup there reads its own values first and then the wires, and the
+// fourth of a CU does so after the others.  Measured on MI355X, us per call, 16 -> 32 lanes in this launch, semi-loop and full loop in
+// ring order, P = 2 and 3: 96 minishards 18.7 -> 19.7, 18.5 -> 19.5, 27.5 -> 28.1, 26.5 -> 28.9; 97 21.7 -> 20.2, 21.2 -> 20.0, 30.2 -> 28.0, 30.6 ->
+// 30.7; 112 23.5 -> 21.6, 23.2 -> 21.7, 33.2 -> 30.7, 32.7 -> 32.9; 128 25.1 -> 24.1, 24.9 -> 23.9, 35.7 -> 34.7, 35.3 -> 35.6; 140 28.7 -> 28.9, 28.4 ->
+// 28.9, 40.3 -> 41.3, 40.5 -> 42.3.
+template <typename F>
+inline void with_owner_slices(int64_t n, int32_t chunks, F f)
+{
+    const int64_t ms = minishards_of(n, chunks);
+    if (chunks == 128 && ms > 96 && ms <= 128) f(Slices<128, 32>{});
+    else with_slices(n, chunks, f);
+}
+
 // The places of a launch that go to the XCDs by whole minishards (minishard_part), for the wire that it writes or reads.  `spread`
 // (short_and_long): none.
 template <typename S>
@@ -651,13 +665,14 @@ inline unsigned strided_owned(int64_t n, const void *wire, bool spread)
 }
 
 // The flavours hop by hop of few partials, where the wire is rewritten twice at most and runs gain the least, keep the parts of
-// a minishard on all XCDs from 10 Mi elements on: two partials of 64 and up to four of 128 chunks.  Measured on MI355X, us, runs
+// a minishard on all XCDs from 10 Mi elements on: two partials of 64 and up to four of 128 chunks, but three and four not where
+// the owner has 32 lanes (with_owner_slices; semi-loop, 104 minishards, 29.6 -> 28.7 and 40.3 -> 38.4 with runs).  Measured on MI355X, us, runs
 // -> all XCDs, semi-loop and full loop in ring order, means over four places in memory:
 //     chunks, elements     P = 2                          3                              4
 //     128, 10.5 M      17.8 -> 16.5, 16.4 -> 16.2     25.2 -> 24.4, 24.6 -> 24.2     32.0 -> 31.3, 32.6 -> 32.2
 //          12.6 M      20.0 -> 18.6, 18.9 -> 18.5     29.1 -> 27.5, 27.7 -> 26.6     37.1 -> 35.7, 36.5 -> 35.5
-//          14.7 M      23.8 -> 23.6, 23.9 -> 23.4     33.5 -> 33.6, 33.9 -> 33.1     43.3 -> 42.8, 44.3 -> 43.5
-//          16.8 M      25.9 -> 25.2, 25.7 -> 25.0     36.4 -> 36.1, 36.8 -> 35.5     47.1 -> 46.2, 47.9 -> 45.7
+//          14.7 M      21.9 -> 21.6, 22.2 -> 21.7     30.4 -> 30.7, 32.2 -> 32.9     40.6 -> 41.8, 42.6 -> 42.5
+//          16.8 M      24.8 -> 24.1, 24.5 -> 23.9     34.5 -> 34.7, 34.7 -> 35.6     45.7 -> 46.3, 45.3 -> 46.0
 //          25.2 M      38.1 -> 37.4, 38.0 -> 37.3     53.3 -> 52.0, 54.1 -> 53.4     69.5 -> 68.6, 69.2 -> 69.2
 //          33.6 M      48.3 -> 47.7, 48.0 -> 47.2     68.0 -> 65.8, 69.0 -> 69.0     89.7 -> 88.3, 89.4 -> 90.7
 //     64,  10.5 M      17.1 -> 15.6, 15.9 -> 15.4     24.9 -> 24.6, 23.5 -> 23.0     32.0 -> 31.3, 31.4 -> 30.5
@@ -667,7 +682,8 @@ inline unsigned strided_owned(int64_t n, const void *wire, bool spread)
 // (32 chunks, P = 2, 8.4 M 12.2 -> 12.8, 12.2 -> 12.7; 64 chunks, P = 2, 4.2 and 8.4 M 8.0 -> 9.3, 12.5 -> 12.7.)
 inline bool short_and_long(int32_t chunks, int64_t n, int P)
 {
-    return n >= (int64_t)10 << 20 && ((chunks == 64 && P == 2) || (chunks == 128 && P <= 4));
+    const int64_t ms = minishards_of(n, chunks);
+    return n >= (int64_t)10 << 20 && ((chunks == 64 && P == 2) || (chunks == 128 && (P <= 2 || (P <= 4 && (ms <= 96 || ms > 128)))));
 }
 
 template <typename S>
@@ -777,7 +793,7 @@ template <bool kAG, typename... Source>
 void do_owner_strided(const StridedWires &in, int64_t n, int32_t chunks, uint16_t *out, LaunchCtx &ctx, bool backward, bool spread,
                       Source... src)
 {
-    with_slices(n, chunks, [&](auto slices) {
+    with_owner_slices(n, chunks, [&](auto slices) {
         using S = decltype(slices);
         const unsigned owned = strided_owned<S>(n, in.codes[1] ? in.codes[1] : in.codes[0], spread), grid = strided_grid<S>(n, owned);
         ctx.launch(owner_strided_kernel<S, kAG, Source...>, grid, kThreads, out, in.codes[0], in.scales[0], in.codes[1],

@@ -463,9 +463,11 @@ def test_strided_single_launch_rules(gpu, oracle, long_values, chunks, minishard
 
 
 @pytest.mark.parametrize("chunks,minishards,P", ((64, 159, 2), (64, 160, 2), (64, 203, 2), (64, 160, 3), (128, 79, 3), (128, 80, 4),
-                                                 (128, 101, 2), (128, 96, 5)))
+                                                 (128, 96, 3), (128, 96, 5), (128, 97, 2), (128, 101, 3), (128, 128, 1),
+                                                 (128, 128, 5), (128, 129, 3)))
 def test_strided_hops_of_few_partials(gpu, oracle, long_values, chunks, minishards, P):  # noqa: F811
-    """Around 10 Mi elements, from which few partials keep the parts of a minishard on all XCDs."""
+    """Around 10 Mi elements, from which few partials keep the parts of a minishard on all XCDs, and where the owner has lanes of
+    its own."""
     n = 1024 * chunks * minishards
     x = [np.resize(long_values[i % 3], n + i)[i:].copy() for i in range(P)]
     for flags in (0, eq.RING_ORDER | eq.AG_UNQUANTIZED, eq.SEMI_LOOP, eq.SEMI_LOOP | eq.RING_ORDER):
