@@ -647,12 +647,15 @@ inline void with_slices(int64_t n, int32_t chunks, F f)
 // fourth of a CU does so after the others.  Measured on MI355X, us per call, 16 -> 32 lanes in this launch, semi-loop and full loop in
 // ring order, P = 2 and 3: 96 minishards 18.7 -> 19.7, 18.5 -> 19.5, 27.5 -> 28.1, 26.5 -> 28.9; 97 21.7 -> 20.2, 21.2 -> 20.0, 30.2 -> 28.0, 30.6 ->
 // 30.7; 112 23.5 -> 21.6, 23.2 -> 21.7, 33.2 -> 30.7, 32.7 -> 32.9; 128 25.1 -> 24.1, 24.9 -> 23.9, 35.7 -> 34.7, 35.3 -> 35.6; 140 28.7 -> 28.9, 28.4 ->
-// 28.9, 40.3 -> 41.3, 40.5 -> 42.3.
+// 28.9, 40.3 -> 41.3, 40.5 -> 42.3.  An owner that is `alone`, with no wire to wait for, has 32 lanes from 96 minishards of 64 chunks and
+// 80 of 128 on: 64 chunks, 64 minishards 4.13 -> 4.14, 96 5.27 -> 4.72, 120 5.87 -> 5.47, 160 8.5 -> 7.4, 128 chunks, 64 6.04 -> 5.87, 80 8.68 ->
+// 8.18, 112 12.2 -> 9.2, 170 18.0 -> 16.8, 192 19.4 -> 19.0, 256 25.1 -> 24.7.
 template <typename F>
-inline void with_owner_slices(int64_t n, int32_t chunks, F f)
+inline void with_owner_slices(int64_t n, int32_t chunks, bool alone, F f)
 {
     const int64_t ms = minishards_of(n, chunks);
-    if (chunks == 128 && ms > 96 && ms <= 128) f(Slices<128, 32>{});
+    if (chunks == 128 && ((ms > 96 && ms <= 128) || (alone && ms >= 80))) f(Slices<128, 32>{});
+    else if (chunks == 64 && alone && ms >= 96) f(Slices<64, 32>{});
     else with_slices(n, chunks, f);
 }
 
@@ -679,11 +682,14 @@ inline unsigned strided_owned(int64_t n, const void *wire, bool spread)
 //          13.1 M      21.5 -> 20.9, 21.1 -> 20.6     29.8 -> 30.5, 30.3 -> 29.6     38.6 -> 39.0, 39.7 -> 38.9
 //          16.8 M      25.4 -> 25.3, 25.1 -> 25.1     35.9 -> 36.3, 35.2 -> 34.7     45.9 -> 46.5, 45.5 -> 45.6
 //          19.7 M      29.9 -> 29.5, 29.6 -> 29.3     41.9 -> 43.1, 42.0 -> 41.8     54.8 -> 55.7, 54.3 -> 54.0
-// (32 chunks, P = 2, 8.4 M 12.2 -> 12.8, 12.2 -> 12.7; 64 chunks, P = 2, 4.2 and 8.4 M 8.0 -> 9.3, 12.5 -> 12.7.)
+// (32 chunks, P = 2, 8.4 M 12.2 -> 12.8, 12.2 -> 12.7; 64 chunks, P = 2, 4.2 and 8.4 M 8.0 -> 9.3, 12.5 -> 12.7.)  One partial has no wire
+// that an XCD could keep: spread from 7 Mi elements on, 32 chunks, 5.2 M 4.3 -> 4.7, 6.3 M 4.9 -> 4.9, 8.4 M 6.0 -> 5.7, 10.5 M 7.8 -> 7.5, 13.1 M
+// 10.3 -> 10.0, 64 chunks, 16.8 M 12.8 -> 12.0, 128 chunks, 21 M 16.3 -> 16.1.
 inline bool short_and_long(int32_t chunks, int64_t n, int P)
 {
+    if (P == 1) return n >= (int64_t)7 << 20;
     const int64_t ms = minishards_of(n, chunks);
-    return n >= (int64_t)10 << 20 && ((chunks == 64 && P == 2) || (chunks == 128 && (P <= 2 || (P <= 4 && (ms <= 96 || ms > 128)))));
+    return n >= (int64_t)10 << 20 && ((chunks == 64 && P == 2) || (chunks == 128 && (P == 2 || (P <= 4 && (ms <= 96 || ms > 128)))));
 }
 
 template <typename S>
@@ -793,7 +799,7 @@ template <bool kAG, typename... Source>
 void do_owner_strided(const StridedWires &in, int64_t n, int32_t chunks, uint16_t *out, LaunchCtx &ctx, bool backward, bool spread,
                       Source... src)
 {
-    with_owner_slices(n, chunks, [&](auto slices) {
+    with_owner_slices(n, chunks, !in.codes[0], [&](auto slices) {
         using S = decltype(slices);
         const unsigned owned = strided_owned<S>(n, in.codes[1] ? in.codes[1] : in.codes[0], spread), grid = strided_grid<S>(n, owned);
         ctx.launch(owner_strided_kernel<S, kAG, Source...>, grid, kThreads, out, in.codes[0], in.scales[0], in.codes[1],

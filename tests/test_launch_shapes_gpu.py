@@ -463,8 +463,9 @@ def test_strided_single_launch_rules(gpu, oracle, long_values, chunks, minishard
 
 
 @pytest.mark.parametrize("chunks,minishards,P", ((64, 159, 2), (64, 160, 2), (64, 203, 2), (64, 160, 3), (128, 79, 3), (128, 80, 4),
-                                                 (128, 96, 3), (128, 96, 5), (128, 97, 2), (128, 101, 3), (128, 128, 1),
-                                                 (128, 128, 5), (128, 129, 3)))
+                                                 (128, 96, 3), (128, 96, 5), (128, 97, 2), (128, 101, 3), (128, 128, 5),
+                                                 (128, 129, 3), (32, 223, 1), (32, 224, 1), (64, 95, 1), (64, 96, 1), (64, 129, 1),
+                                                 (128, 79, 1), (128, 80, 1), (128, 128, 1), (128, 129, 1)))
 def test_strided_hops_of_few_partials(gpu, oracle, long_values, chunks, minishards, P):  # noqa: F811
     """Around 10 Mi elements, from which few partials keep the parts of a minishard on all XCDs, and where the owner has lanes of
     its own."""
